@@ -39,7 +39,14 @@ namespace svg2 {
 // (half the L2 -> LDS traffic, but 8 wavefronts behind one barrier) 8.17 / 25.7.
 static constexpr int ATT_NSTG = 2;         // K and V tile buffers in LDS (each); the schedule is written for two
 static constexpr int ATT_RUN_LDS = 1920;     // runs of a work item kept in LDS (15 KB: two workgroups of 80 KB still fit a CU)
-static constexpr int ATT_OPS_B = 0;        // vector operations of a block's probabilities done early (see phase B)
+static constexpr int ATT_OPS_B = 16;       // vector operations of a block's probabilities done early (see phase B)
+// Largest sum of a block's probabilities before the reference level is moved: 2^40.  The level is the maximum of a
+// query's FIRST score block and no maximum is taken after that: fp32 and bf16 carry a probability of 2^40 with the
+// same relative precision as one of 1, and 2^40 times any sequence length stays far inside the fp32 range of the
+// accumulators.  (Taking every block's maximum and letting it lead the level by at most 2^8 cost 8 v_max3 and a chain of
+// eight dependent instructions per 32 keys: 3.22 against 3.09 ms for dense attention of 24 heads of 16,384 tokens,
+// 31.6 against 30.65 ms for a layer of 40 heads of 75,600 with 2 k-means iterations.)
+static constexpr float ATT_LEVEL_MAX = 1099511627776.0f;
 
 // ---------------------------------------------------------------- plan
 // grid (H), block 256.
@@ -433,22 +440,20 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
     __syncthreads();
 
     // ---- schedule.  The key sequence is consumed in blocks of 32 keys (two per 64-key
-    // tile).  Per block j the work is S_j = K_j Q^T (KS matrix instructions), the running
-    // maximum, P_j = exp2(S_j - m) (vector ALU, 6 operations per pair of scores: two fma,
+    // tile).  Per block j the work is S_j = K_j Q^T (KS matrix instructions),
+    // P_j = exp2(S_j - m) (vector ALU, 6 operations per pair of scores: two fma,
     // two exp2, one pack to bf16, one row-sum dot) and O^T += V_j^T P_j^T (NPV matrix
     // instructions).  The blocks are software-pipelined so that every matrix instruction
     // has about the same amount of independent vector work in its shadow:
     //
     //   phase A(j):  S_{j+1} = K_{j+1} Q^T   ||  last two thirds of P_j, LDS reads of V_j^T
-    //   phase B(j):  O^T += V_j^T P_j^T      ||  maximum of S_{j+1} and the decision about the
-    //                                            running maximum (first half), first third of
-    //                                            P_{j+1} (second half), LDS reads of K_{j+2}
+    //   phase B(j):  O^T += V_j^T P_j^T      ||  first third of P_{j+1}, LDS reads of K_{j+2}
     //
     // The instruction stream is laid out by hand (ATT_FENCE keeps the compiler from moving
-    // code across chunk boundaries).  The running maximum only moves when it would grow by
-    // more than 2^8 (probabilities stay below 256), so rescaling the output accumulators is
-    // rare; it is applied at the end of phase B, when block j has been accumulated under the
-    // old maximum.  Accumulator i of a block is key 8 (i/4) + 4 half + i%4.
+    // code across chunk boundaries).  The reference level m of a query is the maximum of its
+    // first score block; it only moves when a block's sum leaves the range (ATT_LEVEL_MAX),
+    // which is checked at the end of phase A, before the block is accumulated.
+    // Accumulator i of a block is key 8 (i/4) + 4 half + i%4.
     //
     // Tile t lives in K buffer t % 2 and V buffer t % 2.  One barrier per tile: at the top of
     // tile t every wavefront has finished tile t - 1 and all fetches issued during tile t - 1
@@ -472,8 +477,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
     f32x16 s0, s1;                              // scores of block 0 / block 1 of a tile
     unsigned pw0[8], pw1[8];                    // probabilities of block 0 / block 1, two bf16 per word
     bf16x8 ka[KS], va[NPV];                     // K operands of the next score block, V^T operands of this one
-    float psum = 0.f, m_acc = 0.f, t0 = 0.f, t1 = 0.f;    // m_acc: the maximum the accumulators are expressed under
-    bool any_upd = false;
+    float psum = 0.f, t0 = 0.f, t1 = 0.f;
 
     // operation `op` (0..47) of the probabilities of one block: S -> pw
     auto exp_op = [&](const f32x16 &S, unsigned *pw, int op) {
@@ -490,14 +494,29 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
         for (int i = 0; i < 16; ++i)
             if (base + 8 * (i >> 2) + 4 * half + (i & 3) >= rem) S[i] = -INFINITY;
     };
-    // the decision about the running maximum, given the maximum mx of a new score block
-    auto decide = [&](float mx) {
+    // Sum of a block's probabilities out of range (above ATT_LEVEL_MAX, infinite or not a number): take the level of
+    // every query whose block maximum is more than 2^8 above it up to that maximum, bring the accumulators along and
+    // form the block's probabilities again.  S still holds the scores, and the block has not been accumulated yet.
+    auto relevel = [&](const f32x16 &S, unsigned *pw) {
+        float mx = fmaxf(S[0], S[1]);
+#pragma unroll
+        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, S[i]);
         const float mx_s = max_xor32(mx) * scale_log2;
-        const bool upd = mx_s > m_run + 8.0f;
-        any_upd = __any(upd);
-        m_run = upd ? mx_s : m_run;
-        ATT_PIN(m_run)
+        const float m_new = mx_s > m_run + 8.0f ? mx_s : m_run;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int b = 0; b < DVB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
         psum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pw[e] = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(S[2 * e], scale_log2, -m_run)),
+                                __builtin_amdgcn_exp2f(fmaf(S[2 * e + 1], scale_log2, -m_run)));
+            psum = add_bf16x2(pw[e], psum);
+        }
     };
     // K operands of a score block: KBYTE = byte offset of the block's first row in LDS
     auto load_k = [&](auto kbyte_tag, int s) {
@@ -514,11 +533,13 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
         __builtin_memcpy(&va[idx], &lo, 8);
         __builtin_memcpy(reinterpret_cast<char *>(&va[idx]) + 8, &hi, 8);
     };
-    // phase A: Sacc = K Q^T from ka[] (if DO_S)  ||  operations 16..47 of pw = exp2(Sexp - m), V^T operands from VBYTE
+    // phase A: Sacc = K Q^T from ka[] (if DO_S)  ||  operations OPS_B..47 of pw = exp2(Sexp - m), V^T operands from
+    // VBYTE, the check of the block's sum
     auto phase_a = [&](auto do_s_tag, auto vbyte_tag, auto vfetch_tag, f32x16 &Sacc, const f32x16 &Sexp, unsigned *pw) {
         constexpr bool DO_S = decltype(do_s_tag)::value;
         constexpr int VFETCH = decltype(vfetch_tag)::value;     // >= 0: LDS byte offset of the V buffer to fill
         constexpr int KPF = KS / NPASS;                         // k-steps per load instruction
+        bool out_of_range = false;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if (DO_S) {
@@ -533,26 +554,29 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
             for (int idx = (2 * NPV * s) / KS; idx < (2 * NPV * (s + 1)) / KS && idx < NPV; ++idx)
                 load_v(vbyte_tag, idx);         // all issued in the first half, so they have landed by phase B
 #pragma unroll
-            for (int op = OPS_B + ((NOPS - OPS_B) * s) / KS; op < OPS_B + ((NOPS - OPS_B) * (s + 1)) / KS; ++op)
+            for (int op = OPS_B + ((NOPS - OPS_B) * s) / (KS - 1);
+                 op < OPS_B + ((NOPS - OPS_B) * (s + 1)) / (KS - 1) && op < NOPS; ++op)
                 exp_op(Sexp, pw, op);
+            // compared in front of the last matrix instruction, branched on behind it
+            if (s == KS - 2) out_of_range = __any(!(psum <= ATT_LEVEL_MAX));
             if constexpr (VFETCH >= 0) {
                 if (s % KPF == KPF - 1) { ATT_FETCH1(s / KPF, off_nx, Vb, ld_voff, VFETCH) }
             }
             ATT_FENCE
         }
+        if (__builtin_expect(out_of_range, 0)) relevel(Sexp, pw);       // rare
         l_run += psum;
+        psum = 0.f;
     };
-    // phase B: O^T += V^T P^T from va[] and pr[]  ||  maximum of Snext and the decision, then operations
-    // 0..15 of pn = exp2(Snext - m) (if DO_MAX); K operands of the block after Snext from KBYTE (if DO_K)
-    auto phase_b = [&](auto do_max_tag, auto do_k_tag, auto kbyte_tag, auto kfetch_tag, auto slot_tag, bool do_kfetch,
+    // phase B: O^T += V^T P^T from va[] and pr[]  ||  operations 0..OPS_B-1 of pn = exp2(Snext - m) (if DO_P); K operands
+    // of the block after Snext from KBYTE (if DO_K)
+    auto phase_b = [&](auto do_p_tag, auto do_k_tag, auto kbyte_tag, auto kfetch_tag, auto slot_tag, bool do_kfetch,
                        const unsigned *pr, const f32x16 &Snext, unsigned *pn) {
-        constexpr bool DO_MAX = decltype(do_max_tag)::value;
+        constexpr bool DO_P = decltype(do_p_tag)::value;
         constexpr bool DO_K = decltype(do_k_tag)::value;
         constexpr int KFETCH = decltype(kfetch_tag)::value;     // >= 0: LDS byte offset of the K buffer to fill
         constexpr int SLOT = decltype(slot_tag)::value;         // which half of s_rows holds that tile's rows
         constexpr int KF0 = NPV / 4;                            // first matrix instruction followed by a load
-        constexpr int HB = NPV / 2;
-        float mx = -INFINITY;
 #pragma unroll
         for (int idx = 0; idx < NPV; ++idx) {
             bf16x8 pb;
@@ -563,22 +587,9 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
 #pragma unroll
                 for (int s = (KS * idx) / NPV; s < (KS * (idx + 1)) / NPV; ++s) load_k(kbyte_tag, s);
             }
-            if (DO_MAX && idx < HB) {
+            if (DO_P && idx > 0) {
 #pragma unroll
-                for (int c = (8 * idx) / HB; c < (8 * (idx + 1)) / HB; ++c) {
-                    // the first read of the new scores is an ordinary fmaxf, so that the compiler puts the wait
-                    // states between the matrix instructions and the vector read; the other reads come later
-                    if (c == 0) mx = max2_raw(fmaxf(Snext[0], Snext[1]), Snext[2]);
-                    else if (c < 7) mx = max3_raw(mx, Snext[2 * c + 1], Snext[2 * c + 2]);
-                    else mx = max2_raw(mx, Snext[15]);
-                    ATT_PIN(mx)
-                }
-                if (idx == HB - 1) decide(mx);
-            }
-            if (DO_MAX && idx >= HB) {
-#pragma unroll
-                for (int op = (OPS_B * (idx - HB)) / HB; op < (OPS_B * (idx - HB + 1)) / HB; ++op)
-                    exp_op(Snext, pn, op);
+                for (int op = OPS_B * (idx - 1) / (NPV - 1); op < OPS_B * idx / (NPV - 1); ++op) exp_op(Snext, pn, op);
             }
             if constexpr (KFETCH >= 0) {
                 if (do_kfetch) {
@@ -592,18 +603,8 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
             }
             ATT_FENCE
         }
-        if (DO_MAX && any_upd) {            // rare: the factor is only formed here
-            const float alpha = __builtin_amdgcn_exp2f(m_acc - m_run);
-            m_acc = m_run;
-            l_run *= alpha;
-#pragma unroll
-            for (int b = 0; b < DVB; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-        }
     };
     using T = std::true_type;
-    using F = std::false_type;
 
     // ---- prologue: S of block 0 of tile 0, its maximum, the first third of its probabilities,
     // K operands of block 1
@@ -617,11 +618,10 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
 #pragma unroll
         for (int s = 0; s < KS; ++s) load_k(std::integral_constant<int, 32 * RB>{}, s);
         if (L < 32) mask_block(s0, 0, L);
-        float mx = fmaxf(fmaxf(s0[0], s0[1]), s0[2]);
+        float mx = fmaxf(s0[0], s0[1]);
 #pragma unroll
-        for (int i = 3; i < 16; ++i) mx = fmaxf(mx, s0[i]);
-        decide(mx);                             // key 0 exists, so the maximum is finite; nothing to rescale yet
-        m_acc = m_run;
+        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, s0[i]);
+        m_run = max_xor32(mx) * scale_log2;     // key 0 exists, so the maximum is finite
 #pragma unroll
         for (int op = 0; op < OPS_B; ++op) exp_op(s0, pw0, op);
     }

@@ -393,6 +393,27 @@ def test_attention_scores_that_climb_by_hundreds_between_tiles(svg2, oracle, dty
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("at", [32, 63, 64, 300])
+def test_attention_one_block_of_scores_far_above_the_first(svg2, oracle, d, at):
+    """The bf16 kernel's reference level is the maximum of a query's first 32 scores and moves only when a block's sum
+    of probabilities leaves the fp32 range it is given: from key `at` on, half of the queries see scores that are
+    hundreds above the level (their probabilities under it are infinite), the other half scores as far below."""
+    r = np.random.default_rng(31 + at)
+    N = 420
+    u = r.standard_normal(d).astype(np.float32)
+    u /= np.linalg.norm(u)
+    sign = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)[:, None].astype(np.float32)
+    Q = wl.round_to_bf16((sign * u[None] + 0.03 * r.standard_normal((N, d))).astype(np.float32) * 64.0)
+    step = np.where(np.arange(N) < at, 0.0, 1.0)[:, None].astype(np.float32)
+    K = wl.round_to_bf16((step * u[None] + 0.03 * r.standard_normal((N, d))).astype(np.float32) * 64.0)
+    V = wl.round_to_bf16(r.standard_normal((N, d)).astype(np.float32))
+    lq = (np.arange(N) % 2).astype(np.int32)
+    lk = (np.arange(N) // 100).astype(np.int32)
+    sel = [np.arange(5), np.arange(5)]
+    _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "bf16", few_keys=True)
+
+
+@pytest.mark.parametrize("d", [128, 64])
 def test_attention_tile_loop_edges_random_small_shapes(svg2, oracle, d):
     """The matrix-core kernel's tile loop has a schedule with look-ahead (K two tiles ahead, V one, the row look-up
     three): walk it through every length from no key tile to a dozen, with query tiles that fill one to four
