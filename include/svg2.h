@@ -327,7 +327,8 @@ int svg2_attention_recall(const float *lse_selected, const float *lse_all, int H
  *   u         [H,C]   fp64              uniform numbers in [0,1)
  *   centroids [H,C,d] fp32 out          the drawn tokens (input of svg2_kmeans)
  *   picked    [H,C]   int32 out or NULL their token indices
- * All arithmetic is fp64; C passes over X.
+ * Every distance that decides a draw is fp64; tokens that a cheaper lower bound
+ * already rules out are not measured.
  * ------------------------------------------------------------------------- */
 size_t svg2_kmeans_pp_init_workspace_size(int H, int N, int C);
 int svg2_kmeans_pp_init(const void *X, int dtype, int H, int N, int d, int C,

@@ -17,7 +17,6 @@
 namespace svg2 {
 
 static constexpr int DG_BLOCK = 1024;       // tokens per workgroup in the recall kernel (256 threads x 4)
-static constexpr int KPP_BLOCK = 256;       // tokens per block sum in k-means++
 
 // ---------------------------------------------------------------- recall
 // grid (nblk, H), block 256
@@ -71,214 +70,483 @@ int recall_launch(const float *lse_sel, const float *lse_all, int H, int N, floa
 }
 
 // ---------------------------------------------------------------- k-means++
-// One draw.  grid (H), block 256.  k = 0: token floor(u * N).  Otherwise the first token whose running
-// sum of D2 exceeds u * sum(D2): the workgroup first finds the block of KPP_BLOCK tokens in which the running sum
-// crosses the threshold (block sums come from the update kernel), then the token inside it.
-template <typename T>
-__global__ __launch_bounds__(256) void kpp_pick_kernel(const T *__restrict__ X, const double *__restrict__ u,
-                                                       const double *__restrict__ d2,
-                                                       const double *__restrict__ bsum, int N, int d, int C, int k,
-                                                       int nblk, int32_t *__restrict__ picked,
-                                                       float *__restrict__ centroids)
+// A draw is a chain: find the token (from the sums of D2 that the draw before it left), then measure the tokens against
+// it.  One launch does both: every workgroup finds the token by itself -- a few hundred block sums and one block of D2,
+// read by all of them -- and then updates its own block, so no second kernel waits for the first.  D2, the block
+// sums and the change flags alternate between two buffers, because a block that is being updated may still be read
+// by the workgroups that look for the token; a chunk of D2 is written only where it differs from what the buffer
+// holds (it changed in this draw or in the last one).
+//
+// Most tokens are not nearer to the new centre than to an older one, and a 4-bit copy of the tokens is enough to see
+// it: with x^ = s_x q_x the copy (q_x 4-bit integers, one scale per token), r_x >= ||x - x^||, and c^, r_c the
+// same for the centre in 8 bits, ||x - c|| >= ||x^ - c^|| - r_x - r_c, where ||x^ - c^||^2 takes one integer dot
+// product (v_dot8_i32_i4, twice for the two halves of c's digits).  Only the tokens whose bound is below D2 are
+// read and measured, in double precision; the others are exactly those that a measurement would have left as they are
+// (margins for the rounding of the bound are in the constants), so the draws do not depend on it.  A token costs D / 2
+// + 20 bytes per draw instead of its row.
+//
+// What bounds a draw now is the chain: launch, two round trips to find the token, one for its row, one or two for the
+// rows that are measured.  24 heads of 16,384 tokens (d = 128, bf16, 64 components, 500 draws): 13 us per draw against
+// 101 us with two kernels and every row read (6.46 / 50.6 ms in all).  Of the 13 us about 3 are the launch, 3 the
+// bound over all tokens (28 MB, which the L2s of the 8 XCDs keep between the draws; read from memory it would be 4), 3
+// the search, 4 the measuring.  The step kernel is held to 64 registers so that six workgroups of five wavefronts fit
+// a CU: with two more rows in flight per group it spills (11.3 ms), with fewer workgroups resident it takes 6.7 ms.
+static constexpr int KPP_CHUNK = 256;       // tokens a workgroup handles at a time, one per thread
+static constexpr int KPP_TARGET_WGS = 1536; // workgroups of a launch: six per CU, all resident at once
+
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float v)
 {
-    __shared__ double s_scan[256];
-    __shared__ int s_pick;
-    const int h = blockIdx.x, tid = threadIdx.x;
-    const double uk = u[(size_t)h * C + k];
-    const double *dh = d2 + (size_t)h * N;
-    // The running sum is taken hierarchically (block sums, then groups of 4 tokens, then tokens), every level
-    // with a 256-wide inclusive scan in LDS; the first position whose inclusive sum exceeds the threshold wins.
-    __shared__ double s_base;
-    __shared__ int s_blk;
-    auto scan256 = [&](double v) {              // inclusive scan over the workgroup (Hillis-Steele in LDS)
-        s_scan[tid] = v;
-        __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {
-            const double t = (tid >= o) ? s_scan[tid - o] : 0.0;
-            __syncthreads();
-            s_scan[tid] += t;
-            __syncthreads();
-        }
-        return s_scan[tid];
-    };
-    if (tid == 0) { s_pick = -1; s_blk = 0x7FFFFFFF; s_base = 0.0; }
-    __syncthreads();
-    if (k > 0) {
-        double total = 0.0;
-        for (int b0 = 0; b0 < nblk; b0 += 256) {
-            const double incl = scan256(b0 + tid < nblk ? bsum[(size_t)h * nblk + b0 + tid] : 0.0);
-            total += s_scan[255];
-            (void)incl;
-            __syncthreads();
-        }
-        const double target = uk * total;
-        if (total > 0.0) {
-            double base = 0.0;                  // running sum before the current chunk of 256 blocks
-            for (int b0 = 0; b0 < nblk; b0 += 256) {
-                const double v = b0 + tid < nblk ? bsum[(size_t)h * nblk + b0 + tid] : 0.0;
-                const double incl = base + scan256(v);
-                if (b0 + tid < nblk && incl > target) atomicMin(&s_blk, b0 + tid);
-                __syncthreads();
-                if (s_blk != 0x7FFFFFFF) {
-                    if (tid == s_blk - b0) s_base = incl - v;      // running sum before the crossing block
-                    __syncthreads();
-                    break;
-                }
-                base += s_scan[255];
-                __syncthreads();
-            }
-            // inside the block: one token per thread
-            for (int blk = s_blk; blk < nblk; ++blk) {
-                const int n = blk * KPP_BLOCK + tid;
-                const double v = (n < N) ? dh[n] : 0.0;
-                const double incl = s_base + scan256(v);
-                __shared__ int s_tok;
-                if (tid == 0) s_tok = 0x7FFFFFFF;
-                __syncthreads();
-                if (n < N && incl > target) atomicMin(&s_tok, n);
-                __syncthreads();
-                if (s_tok != 0x7FFFFFFF) {
-                    if (tid == 0) s_pick = s_tok;
-                    __syncthreads();
-                    break;
-                }
-                __syncthreads();
-                if (tid == 255) s_base = incl;  // rounding pushed the crossing into the next block
-                __syncthreads();
-            }
-            if (tid == 0 && s_pick < 0) {       // rounding left the running sum at the threshold
-                for (int n = N - 1; n >= 0; --n)
-                    if (dh[n] > 0.0) { s_pick = n; break; }
-            }
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int pick = s_pick;
-        if (pick < 0) pick = (int)floor(uk * (double)N);
-        pick = max(0, min(N - 1, pick));
-        s_pick = pick;
-        picked[(size_t)h * C + k] = pick;
-    }
-    __syncthreads();
-    const int pick = s_pick;
-    for (int j = tid; j < d; j += 256)
-        centroids[((size_t)h * C + k) * d + j] = Elem<T>::load(X + ((size_t)h * N + pick) * d + j);
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
+{
+    const unsigned long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+// over groups of LPT = 8 or 16 lanes, result in every lane: quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_mirror
+template <int LPT> __device__ __forceinline__ double group_sum(double v)
+{
+    v += dpp_f64<0xB1>(v);
+    v += dpp_f64<0x4E>(v);
+    v += dpp_f64<0x141>(v);
+    if (LPT == 16) v += dpp_f64<0x140>(v);
+    return v;
+}
+template <int LPT> __device__ __forceinline__ float group_sum(float v)
+{
+    v += dpp_f32<0xB1>(v);
+    v += dpp_f32<0x4E>(v);
+    v += dpp_f32<0x141>(v);
+    if (LPT == 16) v += dpp_f32<0x140>(v);
+    return v;
+}
+template <int LPT> __device__ __forceinline__ float group_max(float v)
+{
+    v = fmaxf(v, dpp_f32<0xB1>(v));
+    v = fmaxf(v, dpp_f32<0x4E>(v));
+    v = fmaxf(v, dpp_f32<0x141>(v));
+    if (LPT == 16) v = fmaxf(v, dpp_f32<0x140>(v));
+    return v;
 }
 
-// `per` (4 or 8) consecutive elements as doubles, with 8- or 16-byte loads
-__device__ __forceinline__ void load_elems(const bf16_t *p, int per, double *out)
+// 8 consecutive elements: as loaded (16-byte loads), and as floats
+template <typename T> struct Raw8 { uint4 w[sizeof(T) / 2]; };
+template <typename T> __device__ __forceinline__ Raw8<T> load_raw(const T *p)
 {
-    if (per == 8) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(p);
-        const unsigned w[4] = {v.x, v.y, v.z, v.w};
-        for (int q = 0; q < 4; ++q) {
-            out[2 * q] = (double)__uint_as_float(w[q] << 16);
-            out[2 * q + 1] = (double)__uint_as_float(w[q] & 0xFFFF0000u);
-        }
-    } else {
-        const uint2 v = *reinterpret_cast<const uint2 *>(p);
-        const unsigned w[2] = {v.x, v.y};
-        for (int q = 0; q < 2; ++q) {
-            out[2 * q] = (double)__uint_as_float(w[q] << 16);
-            out[2 * q + 1] = (double)__uint_as_float(w[q] & 0xFFFF0000u);
-        }
-    }
-}
-__device__ __forceinline__ void load_elems(const float *p, int per, double *out)
-{
-    for (int q = 0; q < per; q += 4) {
-        const float4 v = *reinterpret_cast<const float4 *>(p + q);
-        out[q] = v.x; out[q + 1] = v.y; out[q + 2] = v.z; out[q + 3] = v.w;
-    }
-}
-
-// D2[n] = min(D2[n], ||x_n - c||^2) against the centre drawn last, and the sum of D2 per KPP_BLOCK tokens.
-// grid (nblk, H), block 256; 16 lanes share a token (d / 16 elements each), 16 tokens per pass, 4 passes in flight.
-template <typename T>
-__global__ __launch_bounds__(256) void kpp_update_kernel(const T *__restrict__ X,
-                                                         const int32_t *__restrict__ picked, int N, int d, int C,
-                                                         int k, int nblk, double *__restrict__ d2,
-                                                         double *__restrict__ bsum)
-{
-    __shared__ double s_red[256];
-    const int h = blockIdx.y, tid = threadIdx.x;
-    const int sub = tid >> 4, part = tid & 15;
-    const int per = d / 16;                    // 4 or 8 elements per lane
-    const T *Xh = X + (size_t)h * N * d;
-    const T *c = Xh + (size_t)picked[(size_t)h * C + k] * d + part * per;
-    double cv[8], xv[8];
-    load_elems(c, per, cv);
-    double acc = 0.0;
-    for (int r = 0; r < KPP_BLOCK; r += 64) {
-        double a[4], old[4];
+    Raw8<T> r;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int n = blockIdx.x * KPP_BLOCK + r + 16 * q + sub;
-            a[q] = 0.0;
-            old[q] = INFINITY;
-            if (n < N) {
-                load_elems(Xh + (size_t)n * d + part * per, per, xv);
-                for (int j = 0; j < per; ++j) {
-                    const double t = xv[j] - cv[j];
-                    a[q] += t * t;
-                }
-                if (k > 0 && part == 0) old[q] = d2[(size_t)h * N + n];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            for (int o = 1; o < 16; o <<= 1) a[q] += __shfl_xor(a[q], o);
-            const int n = blockIdx.x * KPP_BLOCK + r + 16 * q + sub;
-            if (n < N && part == 0) {
-                const double nv = a[q] < old[q] ? a[q] : old[q];
-                d2[(size_t)h * N + n] = nv;
-                acc += nv;
-            }
-        }
-    }
-    s_red[tid] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) s_red[tid] += s_red[tid + o];
-        __syncthreads();
-    }
-    if (tid == 0) bsum[(size_t)h * nblk + blockIdx.x] = s_red[0];
+    for (int i = 0; i < (int)sizeof(T) / 2; ++i) r.w[i] = reinterpret_cast<const uint4 *>(p)[i];
+    return r;
 }
+__device__ __forceinline__ void to_floats(const Raw8<bf16_t> &r, float (&out)[8])
+{
+    const unsigned w[4] = {r.w[0].x, r.w[0].y, r.w[0].z, r.w[0].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        out[2 * q] = __uint_as_float(w[q] << 16);
+        out[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u);
+    }
+}
+__device__ __forceinline__ void to_floats(const Raw8<float> &r, float (&out)[8])
+{
+    __builtin_memcpy(out, r.w, 32);
+}
+template <typename T> __device__ __forceinline__ void load_8(const T *p, float (&out)[8]) { to_floats(load_raw(p), out); }
 
-struct KppWs {
-    double *d2, *bsum;
-    int32_t *picked;
-    size_t total;
+// smallest bf16 number that is not below v (v >= 0)
+__device__ __forceinline__ unsigned bf16_up(float v) { return (__float_as_uint(v) + 0xFFFFu) >> 16; }
+__device__ __forceinline__ float bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// A row v ~ scale * q, q integers in -MAXQ .. MAXQ: what the bound needs besides the digits.
+struct KppRow {
+    float scale, r;     // r >= ||v - scale q||; both are bf16 numbers
+    int q2;             // sum of q^2
 };
 
-static KppWs kpp_carve(void *ws, int H, int N, int C)
+// Digits of the 8 elements of a lane and the row's KppRow (in every lane of the group)
+template <int LPT, int MAXQ> __device__ __forceinline__ KppRow kpp_digits(const float (&x)[8], int (&q)[8])
 {
-    KppWs k;
+    float m = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(x[j]));
+    KppRow row;
+    row.scale = bf16_lo(bf16_up(group_max<LPT>(m) * (1.0f / MAXQ)));
+    const float inv = row.scale > 0.f ? 1.0f / row.scale : 0.f;
+    float e2 = 0.f, q2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        q[j] = max(-MAXQ, min(MAXQ, (int)rintf(x[j] * inv)));
+        const float e = fmaf(-row.scale, (float)q[j], x[j]);
+        e2 = fmaf(e, e, e2);
+        q2 += (float)(q[j] * q[j]);
+    }
+    q2 = group_sum<LPT>(q2);                    // at most 128 * 119^2: exact
+    e2 = group_sum<LPT>(e2);
+    row.q2 = (int)q2;
+    // the error of e (2^-24 |x| per element) and of the sums is far inside these margins
+    row.r = bf16_lo(bf16_up(1.0001f * sqrtf(e2) + 1e-6f * sqrtf(row.scale * row.scale * q2 + e2)));
+    return row;
+}
+__device__ __forceinline__ unsigned pack_nibbles(const int (&q)[8])
+{
+    unsigned w = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w |= (unsigned)(q[j] & 15) << (4 * j);
+    return w;
+}
+
+struct KppBufs {
+    double *d2[2], *csum[2];    // [H,N]; [H,nch] sums of D2 over the chunks
+    int32_t *chg[2];            // [H,nch] the chunk's D2 changed in the draw that wrote the flag
+    uint4 *dig;                 // [H,D/32,N] 4-bit digits: 16-byte piece p of consecutive tokens is contiguous
+    uint2 *row;                 // [H,N] scale and r (bf16), sum of q^2 (16 bits) and D2 rounded up (bf16)
+    int32_t *picked;            // [H,C]
+    int nch, cpw;               // chunks per head, chunks per workgroup
+};
+
+// sum over the first 256 threads, in every thread (fixed order)
+__device__ __forceinline__ double block_sum_256(double v, double *s_w)
+{
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) s_w[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+}
+
+// First draw: token floor(u N); every token's D2 against it and its digits.  grid (workgroups, H), block 256.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void kpp_first_kernel(const T *__restrict__ X, const double *__restrict__ u, KppBufs w,
+                                                        int N, int C, float *__restrict__ centroids)
+{
+    constexpr int LPT = D / 8, G = 256 / LPT, UB = 4;       // lanes per token, tokens per pass, passes in flight
+    __shared__ double s_w[4];
+    const int h = blockIdx.y, tid = threadIdx.x, grp = tid / LPT, part = tid % LPT;
+    const T *Xh = X + (size_t)h * N * D;
+    const int pick = max(0, min(N - 1, (int)floor(u[(size_t)h * C] * (double)N)));
+    float c[8];
+    load_8(Xh + (size_t)pick * D + part * 8, c);
+    if (blockIdx.x == 0 && grp == 0) {
+        if (part == 0) w.picked[(size_t)h * C] = pick;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) centroids[(size_t)h * C * D + part * 8 + j] = c[j];
+    }
+    if (C == 1) return;
+    for (int ch = (int)blockIdx.x * w.cpw; ch < min(w.nch, ((int)blockIdx.x + 1) * w.cpw); ++ch) {
+        const int n_lo = ch * KPP_CHUNK, n_hi = min(N, n_lo + KPP_CHUNK);
+        double acc = 0.0;
+        for (int n0 = n_lo; n0 < n_hi; n0 += G * UB) {
+            float x[UB][8];
+#pragma unroll
+            for (int b = 0; b < UB; ++b) load_8(Xh + (size_t)min(n_hi - 1, n0 + b * G + grp) * D + part * 8, x[b]);
+#pragma unroll
+            for (int b = 0; b < UB; ++b) {
+                const int n = n0 + b * G + grp;
+                double a = 0.0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const double t = (double)x[b][j] - (double)c[j];
+                    a = fma(t, t, a);
+                }
+                a = group_sum<LPT>(a);
+                int q[8];
+                const KppRow row = kpp_digits<LPT, 7>(x[b], q);
+                if (n < n_hi) {
+                    if (!(a < INFINITY)) a = INFINITY;      // (a distance that is not a number never lowers D2)
+                    reinterpret_cast<unsigned *>(w.dig + ((size_t)h * (D / 32) + part / 4) * N + n)[part % 4] = pack_nibbles(q);
+                    if (part == 0) {
+                        w.d2[0][(size_t)h * N + n] = a;
+                        w.row[(size_t)h * N + n] = make_uint2((__float_as_uint(row.scale) >> 16) | __float_as_uint(row.r),
+                                                              (unsigned)row.q2 | (bf16_up((float)a) << 16));
+                        acc += a;
+                    }
+                }
+            }
+        }
+        const double sum = block_sum_256(acc, s_w);
+        if (tid == 0) {
+            w.csum[0][(size_t)h * w.nch + ch] = sum;
+            w.chg[0][(size_t)h * w.nch + ch] = 1;
+        }
+    }
+}
+
+// Inclusive sums over the wavefront's lanes
+__device__ __forceinline__ double wave_scan(double v, int lane)
+{
+    for (int s = 1; s < 64; s <<= 1) {
+        const double t = __shfl_up(v, s);
+        if (lane >= s) v += t;
+    }
+    return v;
+}
+
+// The token of a draw, found by one wavefront: the first token whose running sum of D2 exceeds uk * sum(D2), from the
+// sums cs[nch] of the chunks and then the tokens dh[N] of the chunk in which the running sum crosses.
+__device__ __forceinline__ int kpp_pick(const double *dh, const double *cs, int N, int nch, double uk, int lane)
+{
+    constexpr int M = KPP_CHUNK / 64;
+    const int per = (nch + 63) / 64, b0 = min(nch, lane * per), b1 = min(nch, b0 + per);
+    double loc = 0.0;
+#pragma unroll 4
+    for (int b = b0; b < b1; ++b) loc += cs[b];
+    const double incl = wave_scan(loc, lane), total = __shfl(incl, 63);
+    const double target = uk * total;
+    int pick = -1;
+    if (total > 0.0) {
+        double run = incl - loc;
+        int mine = nch;
+        for (int b = b0; b < b1; ++b) {
+            const double v = cs[b];
+            if (run + v > target) { mine = b; break; }
+            run += v;
+        }
+        // the first lane that found a chunk has the first chunk, and the running sum in front of it
+        const unsigned long long found = __ballot(mine < nch);
+        const int src = found ? __ffsll((long long)found) - 1 : 0;
+        double base = __shfl(run, src);
+        for (int ch = __shfl(mine, src); ch < nch; ++ch) {      // a second pass only if rounding pushed the crossing on
+            double v[M], lb = 0.0;
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                const int n = ch * KPP_CHUNK + lane * M + i;
+                v[i] = n < N ? dh[n] : 0.0;
+                lb += v[i];
+            }
+            const double li = wave_scan(lb, lane);
+            double r = base + (li - lb);
+            int tok = -1;
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                r += v[i];
+                if (tok < 0 && r > target && v[i] > 0.0) tok = ch * KPP_CHUNK + lane * M + i;
+            }
+            const unsigned long long hit = __ballot(tok >= 0);
+            if (hit) {
+                pick = __shfl(tok, __ffsll((long long)hit) - 1);
+                break;
+            }
+            base += __shfl(li, 63);
+        }
+        if (pick < 0) {                         // rounding left the running sum at the threshold: last token with D2 > 0
+            for (int n = lane; n < N; n += 64)
+                if (dh[n] > 0.0) pick = n;
+            for (int s = 32; s > 0; s >>= 1) pick = max(pick, __shfl_xor(pick, s));
+        }
+    }
+    if (pick < 0) pick = (int)floor(uk * (double)N);        // every D2 is zero
+    return max(0, min(N - 1, pick));
+}
+
+// Draw k >= 1.  grid (workgroups, H), block 320: wavefront 4 finds the token and the digits of the centre while
+// wavefronts 0..3 wait for what the bound needs of their tokens (one wavefront that did both would wait for its bulk
+// loads first: a wavefront's loads return in order).  The last draw has nothing to update and is launched with one
+// workgroup per head.
+template <typename T, int D>
+__global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ X, const double *__restrict__ u, KppBufs w,
+                                                          int N, int C, int k, float *__restrict__ centroids)
+{
+    constexpr int LPT = D / 8, G = 256 / LPT, UB = 4 / sizeof(T);       // UB: rows in flight per group of lanes
+    constexpr int NW = D / 8, NQ = D / 32;      // digit words and 16-byte pieces per token
+    __shared__ __align__(16) int s_c[2 * NW];   // digits of the centre: high, then low halves
+    __shared__ double2 s_cd[D / 2];             // the centre: elements 8 p + 2 j, + 1 at j * LPT + p
+    __shared__ KppRow s_row;
+    __shared__ double s_new[KPP_CHUNK];         // lowered D2 of a token, or negative
+    __shared__ uint16_t s_left[KPP_CHUNK];
+    __shared__ double s_w[4];
+    __shared__ int s_nleft, s_chg;
+
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int grp = tid / LPT, part = tid % LPT;
+    const bool finder = tid >= 256;
+    const int o = k & 1, nch = w.nch;
+    const T *Xh = X + (size_t)h * N * D;
+    const double *dh = (o ? w.d2[0] : w.d2[1]) + (size_t)h * N;
+    const double *cs = (o ? w.csum[0] : w.csum[1]) + (size_t)h * nch;
+    const int32_t *fl = (o ? w.chg[0] : w.chg[1]) + (size_t)h * nch;
+    const uint4 *qh = w.dig + (size_t)h * NQ * N;
+    uint2 *rh = w.row + (size_t)h * N;
+    const bool last = k + 1 == C;
+    const int ch_lo = (int)blockIdx.x * w.cpw, ch_hi = last ? ch_lo : min(nch, ch_lo + w.cpw);
+
+    uint2 row = {};
+    uint4 dig[NQ] = {};
+    int chg_old = 0;
+    auto load_tok = [&](int ch) {               // one token per thread
+        const int n = min(N - 1, ch * KPP_CHUNK + tid);
+        row = rh[n];
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) dig[p] = qh[(size_t)p * N + n];
+        chg_old = fl[ch];
+    };
+    if (!finder) {
+        load_tok(ch_lo);
+    } else {
+        const int pick = kpp_pick(dh, cs, N, nch, u[(size_t)h * C + k], lane);
+        float c[8];
+        load_8(Xh + (size_t)pick * D + part * 8, c);
+        // digits q = 16 hi + lo with hi in -7 .. 7, lo in -8 .. 7
+        int q[8], hi[8], lo[8];
+        const KppRow r = kpp_digits<LPT, 119>(c, q);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            hi[j] = (q[j] + 8) >> 4;
+            lo[j] = q[j] - 16 * hi[j];
+        }
+        if (lane < LPT) {
+            s_c[part] = (int)pack_nibbles(hi);
+            s_c[NW + part] = (int)pack_nibbles(lo);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s_cd[j * LPT + part] = make_double2((double)c[2 * j], (double)c[2 * j + 1]);
+            if (part == 0) { s_row = r; s_nleft = 0; s_chg = 0; }
+            if (blockIdx.x == 0) {
+                if (part == 0) w.picked[(size_t)h * C + k] = pick;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) centroids[((size_t)h * C + k) * D + part * 8 + j] = c[j];
+            }
+        }
+    }
+    if (last) return;
+    __syncthreads();
+    const float c_scale = s_row.scale, c_r = s_row.r, c_n2 = c_scale * c_scale * (float)s_row.q2;
+
+    // ---- D2[n] = min(D2[n], ||x_n - c||^2) for the tokens of the workgroup's chunks, and the chunks' sums
+    for (int ch = ch_lo; ch < ch_hi; ++ch) {
+        if (ch > ch_lo && !finder) load_tok(ch);
+        const int c0 = ch * KPP_CHUNK;
+        const bool in = !finder && c0 + tid < N;
+        int dot = 0, dlo = 0;
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+            const int4 a = *reinterpret_cast<const int4 *>(&s_c[4 * p]);
+            dot = __builtin_amdgcn_sdot8((int)dig[p].x, a.x, dot, false);
+            dot = __builtin_amdgcn_sdot8((int)dig[p].y, a.y, dot, false);
+            dot = __builtin_amdgcn_sdot8((int)dig[p].z, a.z, dot, false);
+            dot = __builtin_amdgcn_sdot8((int)dig[p].w, a.w, dot, false);
+        }
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+            const int4 a = *reinterpret_cast<const int4 *>(&s_c[NW + 4 * p]);
+            dlo = __builtin_amdgcn_sdot8((int)dig[p].x, a.x, dlo, false);
+            dlo = __builtin_amdgcn_sdot8((int)dig[p].y, a.y, dlo, false);
+            dlo = __builtin_amdgcn_sdot8((int)dig[p].z, a.z, dlo, false);
+            dlo = __builtin_amdgcn_sdot8((int)dig[p].w, a.w, dlo, false);
+        }
+        dot = 16 * dot + dlo;
+        // ||x^ - c^||^2 from below (its three terms are each within 3 units in the last place of n2)
+        const float scale = bf16_lo(row.x), r = bf16_hi(row.x), d2_up = bf16_hi(row.y);
+        const float n2 = fmaf(scale * scale, (float)(row.y & 0xFFFFu), c_n2);
+        const float t = fmaf(-2.0f * scale * c_scale, (float)dot, n2) - 1e-6f * n2;
+        const float lb = sqrtf(fmaxf(t, 0.f)) - (r + c_r);
+        // leave the token out only if the bound is an ordinary number and says so (inputs that are no numbers are measured)
+        const bool left = in && !(t < 1e37f && lb > 0.f && lb * lb > 1.00001f * d2_up);
+        const unsigned long long m = __ballot(left);
+        int pos = 0;
+        if (lane == 0 && m) pos = atomicAdd(&s_nleft, __popcll(m));
+        pos = __builtin_amdgcn_readfirstlane(pos) + __popcll(m & ((1ull << lane) - 1ull));
+        if (left) s_left[pos] = (uint16_t)tid;
+        if (!finder) s_new[tid] = -1.0;
+        __syncthreads();
+        const int nleft = s_nleft;
+        if (!finder && nleft > 0) {
+            for (int i0 = 0; i0 < nleft; i0 += G * UB) {
+                Raw8<T> raw[UB];
+                double old[UB];
+                int at[UB];
+#pragma unroll
+                for (int b = 0; b < UB; ++b) {
+                    at[b] = s_left[min(nleft - 1, i0 + b * G + grp)];
+                    raw[b] = load_raw(Xh + (size_t)(c0 + at[b]) * D + part * 8);
+                    old[b] = dh[c0 + at[b]];
+                }
+#pragma unroll
+                for (int b = 0; b < UB; ++b) {
+                    if (i0 + b * G >= nleft) break;
+                    asm volatile("" ::: "memory");      // the centre is read from LDS as it is used: 16 registers less
+                    float x[8];
+                    to_floats(raw[b], x);
+                    double a = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double2 c = s_cd[j * LPT + part];
+                        const double e0 = (double)x[2 * j] - c.x, e1 = (double)x[2 * j + 1] - c.y;
+                        a = fma(e0, e0, a);
+                        a = fma(e1, e1, a);
+                    }
+                    a = group_sum<LPT>(a);
+                    if (part == 0 && i0 + b * G + grp < nleft && a < old[b]) {
+                        s_new[at[b]] = a;
+                        s_chg = 1;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const bool chg = s_chg != 0;
+        double v = 0.0;
+        if (in && (chg || chg_old)) {           // the buffer that is written holds D2 of two draws ago
+            v = s_new[tid];
+            if (v < 0.0) v = dh[c0 + tid];
+            else rh[c0 + tid].y = (row.y & 0xFFFFu) | (bf16_up((float)v) << 16);
+            (o ? w.d2[1] : w.d2[0])[(size_t)h * N + c0 + tid] = v;
+        }
+        double sum = cs[ch];
+        if (chg) sum = block_sum_256(v, s_w);   // (chg is the same in every thread)
+        if (tid == 0) {
+            (o ? w.csum[1] : w.csum[0])[(size_t)h * nch + ch] = sum;
+            (o ? w.chg[1] : w.chg[0])[(size_t)h * nch + ch] = chg;
+            s_nleft = 0;                        // (read behind the next chunk's first barrier only)
+        }
+        if (ch + 1 < ch_hi) {
+            __syncthreads();
+            if (tid == 0) s_chg = 0;
+        }
+    }
+}
+
+// Chunks per workgroup: as many as it takes to have at most KPP_TARGET_WGS workgroups (each of them repeats the search
+// for the token of the draw).
+static KppBufs kpp_carve(void *ws, int H, int N, int d, int C, size_t *total)
+{
+    KppBufs k;
+    k.nch = (int)(((long long)N + KPP_CHUNK - 1) / KPP_CHUNK);
+    k.cpw = (int)(((long long)H * k.nch + KPP_TARGET_WGS - 1) / KPP_TARGET_WGS);
     Carver c(ws);
-    k.d2 = c.take<double>((size_t)H * N);
-    k.bsum = c.take<double>((size_t)H * cdiv(N, KPP_BLOCK));
+    for (int i = 0; i < 2; ++i) {
+        k.d2[i] = c.take<double>((size_t)H * N);
+        k.csum[i] = c.take<double>((size_t)H * k.nch);
+        k.chg[i] = c.take<int32_t>((size_t)H * k.nch);
+    }
+    k.dig = c.take<uint4>((size_t)H * N * (d / 32));
+    k.row = c.take<uint2>((size_t)H * N);
     k.picked = c.take<int32_t>((size_t)H * C);
-    k.total = c.used;
+    *total = c.used;
     return k;
 }
 
-size_t kpp_ws_bytes(int H, int N, int C) { return kpp_carve(nullptr, H, N, C).total; }
-
-template <typename T>
-static int kpp_run(const T *X, int H, int N, int d, int C, const double *u, float *centroids, int32_t *picked,
-                   void *ws, hipStream_t st)
+// (the size query does not name d: the larger of the two head dimensions)
+size_t kpp_ws_bytes(int H, int N, int C)
 {
-    const KppWs w = kpp_carve(ws, H, N, C);
-    int32_t *pk = picked ? picked : w.picked;
-    const int nblk = cdiv(N, KPP_BLOCK);
-    for (int k = 0; k < C; ++k) {
-        hipLaunchKernelGGL(kpp_pick_kernel<T>, dim3(H), dim3(256), 0, st, X, u, w.d2, w.bsum, N, d, C, k, nblk, pk,
+    size_t total;
+    (void)kpp_carve(nullptr, H, N, 128, C, &total);
+    return total;
+}
+
+template <typename T, int D>
+static int kpp_run(const T *X, int H, int N, int C, const double *u, float *centroids, int32_t *picked, void *ws,
+                   hipStream_t st)
+{
+    size_t total;
+    KppBufs w = kpp_carve(ws, H, N, D, C, &total);
+    if (picked) w.picked = picked;
+    const int nwg = cdiv(w.nch, w.cpw);
+    hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(C > 1 ? nwg : 1, H), dim3(256), 0, st, X, u, w, N, C, centroids);
+    for (int k = 1; k < C; ++k)
+        hipLaunchKernelGGL((kpp_step_kernel<T, D>), dim3(k + 1 < C ? nwg : 1, H), dim3(320), 0, st, X, u, w, N, C, k,
                            centroids);
-        if (k + 1 < C)
-            hipLaunchKernelGGL(kpp_update_kernel<T>, dim3(nblk, H), dim3(256), 0, st, X, pk, N, d, C, k, nblk, w.d2,
-                               w.bsum);
-    }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
 }
@@ -286,9 +554,14 @@ static int kpp_run(const T *X, int H, int N, int d, int C, const double *u, floa
 int kpp_launch(const void *X, int dtype, int H, int N, int d, int C, const double *u, float *centroids,
                int32_t *picked, void *ws, hipStream_t st)
 {
-    if (dtype == SVG2_BF16)
-        return kpp_run<bf16_t>(static_cast<const bf16_t *>(X), H, N, d, C, u, centroids, picked, ws, st);
-    return kpp_run<float>(static_cast<const float *>(X), H, N, d, C, u, centroids, picked, ws, st);
+    if (dtype == SVG2_BF16) {
+        const bf16_t *x = static_cast<const bf16_t *>(X);
+        return d == 128 ? kpp_run<bf16_t, 128>(x, H, N, C, u, centroids, picked, ws, st)
+                        : kpp_run<bf16_t, 64>(x, H, N, C, u, centroids, picked, ws, st);
+    }
+    const float *x = static_cast<const float *>(X);
+    return d == 128 ? kpp_run<float, 128>(x, H, N, C, u, centroids, picked, ws, st)
+                    : kpp_run<float, 64>(x, H, N, C, u, centroids, picked, ws, st);
 }
 
 }  // namespace svg2

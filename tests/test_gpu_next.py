@@ -85,6 +85,26 @@ def test_kmeans_pp_degenerate_inputs(svg2, oracle):
     np.testing.assert_array_equal(to_np(res.picked[0]), oracle.kmeans_pp(X[0], 3, u[0])[0])
 
 
+@pytest.mark.parametrize("H,N,d,C,dtype,comps", [
+    (1, 1, 64, 1, "bf16", 1), (1, 255, 128, 40, "f32", 5), (2, 257, 64, 257, "bf16", 30),
+    (3, 2000, 128, 300, "bf16", 2000),        # no structure: more distinct nearest centres per block than are looked at
+    (5, 6001, 64, 90, "f32", 12), (2, 400001, 64, 9, "bf16", 3), (1, 1700000, 64, 3, "bf16", 2)])
+def test_kmeans_pp_block_edges_and_skipped_tokens(svg2, oracle, H, N, d, C, dtype, comps):
+    """Lengths around a block, blocks of several chunks, more centres than the table of a block's nearest centres holds,
+    components far enough apart that most tokens are left out of a draw."""
+    r = np.random.default_rng(700 + N)
+    centres = (4.0 * r.standard_normal((comps, d))).astype(np.float32)
+    X = centres[np.sort(r.integers(0, comps, size=(H, N)), axis=1)] + r.standard_normal((H, N, d), dtype=np.float32)
+    X = wl.round_to_bf16(X) if dtype == "bf16" else X
+    u = r.random((H, C))
+    res = svg2.svg2_kmeans_pp_init(to_dev(X, dtype), C, torch.from_numpy(u).cuda())
+    torch.cuda.synchronize()
+    for i in range(H):
+        picked, rows = oracle.kmeans_pp(X[i], C, u[i])
+        np.testing.assert_array_equal(to_np(res.picked[i]), picked)
+        np.testing.assert_array_equal(to_np(res.centroids[i]), rows)
+
+
 def test_kmeans_pp_then_lloyd_lowers_the_objective(svg2):
     # seeding feeds svg2_kmeans: the objective after the first assign step is the k-means++ potential and it
     # does not grow over the iterations (Section 4.1 / 4.3)
