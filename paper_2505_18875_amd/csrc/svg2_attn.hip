@@ -18,7 +18,7 @@
 //                      already laid out as the B operand of O^T += V^T P^T.
 //                      V^T comes out of LDS through the transposing 64-bit
 //                      read (ds_read_b64_tr_b16).
-//   attn_f32_kernel    fp32 storage: plain FMA kernel, one query per thread.
+//   attn_f32_kernel    fp32 storage: MFMA 32x32x2 fp32, the keys of a work item split over the wavefronts.
 //
 // The result of sorted row r is stored at row perm_q[r] (Section 4.1: the
 // inverse query permutation restores the original order).
@@ -732,96 +732,216 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
 }
 
 // ---------------------------------------------------------------- fp32 kernel
-// grid (max_tiles, H), block 64: one query row per thread, 32 keys per LDS tile.
+// grid (max_tiles, H), block 64 * F32_NW.  A work item is 32 consecutive rows of one query cluster; its key sequence is
+// cut into blocks of 32 keys which the wavefronts take in turn (wavefront w: blocks w, w + F32_NW, ..), each with its own
+// running softmax over its share of the keys; the shares are put together through LDS at the end.  So a short layer
+// (one head of 4096 tokens is 128 work items) still puts work on 512 SIMDs, and no wavefront waits for another
+// before the end.
+//
+// Matrix instruction 32x32x2 (fp32 in, fp32 out: the products and sums of the definition, at twice the rate of the
+// vector ALU; 64 cycles each).  S^T = K Q^T: a lane supplies key `col`, and its half of d is the half of the row the
+// lane half names (the contraction index may be taken in any order), so K goes from memory to the operand registers
+// in 16-byte loads.  Accumulator i is key 8 (i / 4) + 4 half + i % 4 of query `col` -- which is what O^T += V^T P^T wants
+// as its other operand, step i contracting the keys of accumulator i of the two lane halves.  Row m of output block b
+// is column DVB m + b, so that one load of DVB consecutive floats is the operand of all DVB blocks, and the DVB
+// accumulators of a row are consecutive floats of the result.
+//
+// Nothing is staged in LDS: a 32-key block is 128 matrix instructions (8192 cycles, d = 128) and 32 loads of 1 KB per
+// wavefront, so the loads hide behind the arithmetic with two register buffers that take turns (A: first halves of K
+// and of V, B: second halves).  One query per thread with K and V in LDS (64 queries per wavefront, one wavefront per
+// workgroup) took 13.8 instead of 0.80 ms for 4 heads of 9601 tokens at d = 128 (31 % selected: 58 GFLOP, so 72 of the
+// 154 TFLOP/s a large fp32 product reaches), and 760 instead of 37 us for one head of 4096 tokens at d = 64.
+static constexpr int F32_NW = 4;
+static constexpr int F32_BM = 32;
+
 template <int D>
-__global__ __launch_bounds__(64) void attn_f32_kernel(
+__global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int N, int Cq, int Ck,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ n_tiles, int max_tiles,
-    const int2 *__restrict__ runs, const int32_t *__restrict__ row_keys, float scale, float *__restrict__ O,
-    float *__restrict__ lse)
+    const int2 *__restrict__ runs, const int32_t *__restrict__ row_keys, const int32_t *__restrict__ tile_run,
+    int key_tiles, float scale_log2, float *__restrict__ O, float *__restrict__ lse)
 {
-    constexpr int TN = 32;
-    __shared__ __align__(16) float sK[TN * D];
-    __shared__ __align__(16) float sV[TN * D];
+    constexpr int DVB = D / 32;                 // output blocks of 32 columns
+    constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's share of K or V
+    constexpr int ROW = D + 4;                  // LDS row of the final sum, padded
+    constexpr int RB = D * 4;                   // bytes per row
+    typedef float fvec __attribute__((ext_vector_type(DVB)));
+    extern __shared__ __align__(16) float s_o[];        // [F32_NW][32][ROW]
+    __shared__ float s_m[F32_NW][32], s_l[F32_NW][32];
     const int h = blockIdx.y, t = blockIdx.x, tid = threadIdx.x;
     if (t >= n_tiles[h]) return;
     const int4 desc = tiles[(size_t)h * max_tiles + t];
     const int ci = desc.x, row0 = desc.y, nrows = desc.z;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
     const int e0 = row_ptr[(size_t)h * (Cq + 1) + ci];
     const int nnz = row_ptr[(size_t)h * (Cq + 1) + ci + 1] - e0;
     const int L = row_keys[(size_t)h * Cq + ci];
     const int2 *rn = runs + (size_t)h * Cq * Ck + e0;
-    const float *Kh = K + (size_t)h * N * D, *Vh = V + (size_t)h * N * D;
+    const int32_t *trh = tile_run + ((size_t)h * Cq + ci) * key_tiles;
+    const int32_t *pkh = perm_k ? perm_k + (size_t)h * N : nullptr;
+    const char *Kb = reinterpret_cast<const char *>(K + (size_t)h * N * D);
+    const char *Vb = reinterpret_cast<const char *>(V + (size_t)h * N * D);
+    const int nblk = (L + 31) / 32;
 
-    const int r = row0 + min(tid, nrows - 1);
-    const int qr = perm_k ? perm_q[(size_t)h * N + r] : r;      // gather-free: Q is in token order
-    float q[D], o[D];
+    float q[D / 2];
+    {
+        int r = row0 + min(nrows - 1, col);
+        if (perm_k) r = perm_q[(size_t)h * N + r];      // gather-free: Q is in token order
+        const float4 *src = reinterpret_cast<const float4 *>(Q + ((size_t)h * N + r) * D + half * (D / 2));
 #pragma unroll
-    for (int k = 0; k < D / 4; ++k) {
-        const float4 w = reinterpret_cast<const float4 *>(Q + ((size_t)h * N + qr) * D)[k];
-        q[4 * k] = w.x; q[4 * k + 1] = w.y; q[4 * k + 2] = w.z; q[4 * k + 3] = w.w;
+        for (int k = 0; k < D / 8; ++k) {
+            const float4 w = src[k];
+            q[4 * k] = w.x; q[4 * k + 1] = w.y; q[4 * k + 2] = w.z; q[4 * k + 3] = w.w;
+        }
     }
+    f32x16 oacc[DVB];
 #pragma unroll
-    for (int k = 0; k < D; ++k) o[k] = 0.f;
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[b][i] = 0.f;
     float m = -INFINITY, l = 0.f;
 
-    // loader: lanes 0..31 own key slot tid, lanes 32..63 the same slots (second half of the row)
-    const int slot = tid & 31, hpart = tid >> 5;
-    int cur = 0;
-    for (int k0 = 0; k0 < L; k0 += TN) {
-        __syncthreads();
-        const int kk = k0 + slot;
-        if (kk < L) {
-            while (cur + 1 < nnz && kk >= rn[cur + 1].y) ++cur;
-            const int2 rs = rn[cur];
-            size_t src = (size_t)(rs.x + kk - rs.y);
-            if (perm_k) src = (size_t)perm_k[(size_t)h * N + src];  // gather-free: sorted row -> token
-            const float4 *kp = reinterpret_cast<const float4 *>(Kh + src * D + hpart * (D / 2));
-            const float4 *vp = reinterpret_cast<const float4 *>(Vh + src * D + hpart * (D / 2));
-            float4 *dk = reinterpret_cast<float4 *>(sK + slot * D + hpart * (D / 2));
-            float4 *dv = reinterpret_cast<float4 *>(sV + slot * D + hpart * (D / 2));
-            for (int c = 0; c < D / 8; ++c) { dk[c] = kp[c]; dv[c] = vp[c]; }
+    // byte offset of the row of key 32 j + col (past the end: the last key's row, so that nothing but selected rows is
+    // ever read; its score is masked)
+    auto row_off = [&](int j) -> unsigned {
+        const int kk = min(32 * j + col, L - 1);
+        int c = trh[j >> 1];                    // run in which the 64-key tile starts
+        while (c + 1 < nnz && kk >= rn[c + 1].y) ++c;
+        const int2 rs = rn[c];
+        int r = rs.x + kk - rs.y;
+        if (perm_k) r = pkh[r];                 // gather-free: sorted row -> token
+        return (unsigned)r * RB;
+    };
+    float4 bufA[NB], bufB[NB];
+    auto load_k = [&](float4 (&buf)[NB], unsigned off, int hf) {
+        const float4 *src = reinterpret_cast<const float4 *>(Kb + (off + (unsigned)(half * (RB / 2) + hf * (RB / 4))));
+#pragma unroll
+        for (int i = 0; i < NB; ++i) buf[i] = src[i];
+    };
+    // V of contraction steps 8 hf .. 8 hf + 7: step i takes key 8 (i / 4) + 4 half + i % 4, columns DVB col ..
+    auto load_v = [&](float4 (&buf)[NB], unsigned off, int hf) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int st = 8 * hf + i;
+            const unsigned r = (unsigned)__shfl((int)off, 8 * (st / 4) + 4 * half + st % 4);
+            const fvec v = *reinterpret_cast<const fvec *>(Vb + (r + (unsigned)(col * (4 * DVB))));
+            __builtin_memcpy(reinterpret_cast<char *>(buf) + i * (4 * DVB), &v, 4 * DVB);
         }
-        __syncthreads();
-        const int nk = min(TN, L - k0);
-        float s[TN];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            float acc = 0.f;
-            if (j < nk) {
-#pragma unroll
-                for (int k = 0; k < D; ++k) acc = fmaf(q[k], sK[j * D + k], acc);
-                acc *= scale;
-                mx = fmaxf(mx, acc);
-            }
-            s[j] = acc;
-        }
-        const float m_new = fmaxf(m, mx);
-        const float alpha = expf(m - m_new);
-        m = m_new;
-        l *= alpha;
-#pragma unroll
-        for (int k = 0; k < D; ++k) o[k] *= alpha;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            if (j < nk) {
-                const float p = expf(s[j] - m_new);
-                l += p;
-#pragma unroll
-                for (int k = 0; k < D; ++k) o[k] = fmaf(p, sV[j * D + k], o[k]);
-            }
-        }
+    };
+#define F32_FENCE __builtin_amdgcn_sched_barrier(0);
+
+    unsigned off = 0;
+    if (wave < nblk) {
+        off = row_off(wave);
+        load_k(bufA, off, 0);
     }
-    if (tid < nrows) {
-        const size_t dst = (size_t)h * N + (perm_q ? perm_q[(size_t)h * N + r] : r);
-        const float inv = (l > 0.f) ? 1.0f / l : 0.f;
+    for (int j = wave; j < nblk; j += F32_NW) {
+        load_k(bufB, off, 1);
+        const int jn = j + F32_NW;
+        const unsigned off_n = row_off(min(jn, nblk - 1));
+        F32_FENCE
+        f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < D / 4; ++k)
-            reinterpret_cast<float4 *>(O + dst * D)[k] =
-                make_float4(o[4 * k] * inv, o[4 * k + 1] * inv, o[4 * k + 2] * inv, o[4 * k + 3] * inv);
-        if (lse) lse[dst] = (l > 0.f) ? m + logf(l) : -INFINITY;
+        for (int i = 0; i < NB; ++i) {
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, q[4 * i], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, q[4 * i + 1], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, q[4 * i + 2], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, q[4 * i + 3], S, 0, 0, 0);
+        }
+        F32_FENCE
+        load_v(bufA, off, 0);
+        F32_FENCE
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, q[4 * (NB + i)], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, q[4 * (NB + i) + 1], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, q[4 * (NB + i) + 2], S, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, q[4 * (NB + i) + 3], S, 0, 0, 0);
+        }
+        F32_FENCE
+        load_v(bufB, off, 1);
+        F32_FENCE
+        if (j == nblk - 1) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (32 * j + 8 * (i >> 2) + 4 * half + (i & 3) >= L) S[i] = -INFINITY;
+        }
+        float mx = fmaxf(S[0], S[1]);
+#pragma unroll
+        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, S[i]);
+        mx = fmaxf(m, max_xor32(mx) * scale_log2);
+        if (__any(mx > m)) {
+            const float alpha = __builtin_amdgcn_exp2f(m - mx);
+            m = mx;
+            l *= alpha;
+#pragma unroll
+            for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], scale_log2, -m));
+            l += S[i];
+        }
+        F32_FENCE
+        auto pv = [&](const float4 (&buf)[NB], int hf) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                fvec v;
+                __builtin_memcpy(&v, reinterpret_cast<const char *>(buf) + i * (4 * DVB), 4 * DVB);
+#pragma unroll
+                for (int b = 0; b < DVB; ++b)
+                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[b], S[8 * hf + i], oacc[b], 0, 0, 0);
+            }
+        };
+        pv(bufA, 0);
+        F32_FENCE
+        load_k(bufA, off_n, 0);                 // (after the last block: a valid row, not used)
+        F32_FENCE
+        pv(bufB, 1);
+        F32_FENCE
+        off = off_n;
+    }
+#undef F32_FENCE
+
+    // ---- the shares of the wavefronts: common level, scaled accumulators to LDS, sum, store
+    l = sum_xor32(l);
+    if (half == 0) { s_m[wave][col] = m; s_l[wave][col] = l; }
+    __syncthreads();
+    float m_all = s_m[0][col];
+#pragma unroll
+    for (int w = 1; w < F32_NW; ++w) m_all = fmaxf(m_all, s_m[w][col]);
+    const float f = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_all);
+    float *so = s_o + (size_t)(wave * 32 + col) * ROW;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = 8 * (i >> 2) + 4 * half + (i & 3);
+        fvec v;
+#pragma unroll
+        for (int b = 0; b < DVB; ++b) v[b] = oacc[b][i] * f;
+        *reinterpret_cast<fvec *>(so + DVB * row) = v;
+    }
+    __syncthreads();
+    constexpr int LPR = D / 4;                  // lanes per row of the result
+    for (int r = tid / LPR; r < nrows; r += 64 * F32_NW / LPR) {
+        const int c4 = (tid % LPR) * 4;
+        float mm = s_m[0][r], lt = 0.f;
+#pragma unroll
+        for (int w = 1; w < F32_NW; ++w) mm = fmaxf(mm, s_m[w][r]);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < F32_NW; ++w) {
+            if (s_m[w][r] != -INFINITY) lt += s_l[w][r] * __builtin_amdgcn_exp2f(s_m[w][r] - mm);
+            const float4 v = *reinterpret_cast<const float4 *>(s_o + (size_t)(w * 32 + r) * ROW + c4);
+            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+        }
+        const size_t dst = (size_t)h * N + (perm_q ? perm_q[(size_t)h * N + row0 + r] : row0 + r);
+        const float inv = (lt > 0.f) ? 1.0f / lt : 0.f;
+        *reinterpret_cast<float4 *>(O + dst * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+        if (lse && c4 == 0) lse[dst] = (lt > 0.f) ? (mm + log2f(lt)) * 0.6931471805599453f : -INFINITY;
     }
 }
 
@@ -839,9 +959,14 @@ static size_t attn_lds_bytes(int d, int Ck)
            (size_t)std::min(Ck + 1, ATT_RUN_LDS) * sizeof(int2);
 }
 
+static size_t attn_f32_lds_bytes(int d) { return (size_t)F32_NW * F32_BM * (d + 4) * sizeof(float); }
+
 int attn_prepare(int dtype, int d)
 {
-    if (dtype != SVG2_BF16) return SVG2_OK;
+    if (dtype != SVG2_BF16) {
+        if (d == 128) return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128>), attn_f32_lds_bytes(d));
+        return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<64>), attn_f32_lds_bytes(d));
+    }
     const size_t lds = attn_lds_bytes(d, SVG2_MAX_CLUSTERS);
     if (d == 128) {
         SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(attn_bf16_kernel<128, true>), lds));
@@ -898,12 +1023,11 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
         const float *q = static_cast<const float *>(Qp), *k = static_cast<const float *>(Kp),
                     *v = static_cast<const float *>(Vp);
         float *o = static_cast<float *>(O);
-        if (d == 128)
-            hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(max_tiles, H), dim3(64), 0, st, q, k, v, N, Cq, Ck, row_ptr,
-                               perm_q, perm_k, tiles, n_tiles, max_tiles, runs, row_keys, scale, o, lse);
-        else
-            hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(max_tiles, H), dim3(64), 0, st, q, k, v, N, Cq, Ck, row_ptr,
-                               perm_q, perm_k, tiles, n_tiles, max_tiles, runs, row_keys, scale, o, lse);
+        static_assert(F32_BM == attn_bm(SVG2_F32), "the plan cuts query clusters into the tiles of this kernel");
+        auto kern = d == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>;
+        hipLaunchKernelGGL(kern, dim3(max_tiles, H), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, N, Cq, Ck,
+                           row_ptr, perm_q, perm_k, tiles, n_tiles, max_tiles, runs, row_keys, a.tile_run, a.key_tiles,
+                           scale * 1.4426950408889634f, o, lse);
     }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;

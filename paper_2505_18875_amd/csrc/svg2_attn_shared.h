@@ -86,7 +86,7 @@ __device__ __forceinline__ float sum_xor32(float x)
 }
 
 // ---- plan workspace (host)
-inline int attn_bm(int dtype) { return dtype == SVG2_BF16 ? 32 * ATT_NW : 64; }   // rows per tile
+constexpr int attn_bm(int dtype) { return dtype == SVG2_BF16 ? 32 * ATT_NW : 32; }   // rows per tile
 
 struct AttnWs {
     int4 *tiles;

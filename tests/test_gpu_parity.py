@@ -432,6 +432,23 @@ def test_attention_tile_loop_edges_random_small_shapes(svg2, oracle, d):
         _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "bf16", few_keys=True)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_attention_f32_key_blocks_shared_by_the_wavefronts(svg2, oracle, d):
+    """The fp32 kernel deals the 32-key blocks of a work item out to four wavefronts and adds their shares at the end:
+    key counts on both sides of every count of blocks from none to nine (some wavefronts then have nothing), query
+    clusters of 1 to 70 rows, key clusters of a few rows, permuted and gather-free."""
+    r = np.random.default_rng(9100 + d)
+    for L in [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 160, 161, 255, 257, 288]:
+        N = L + int(r.integers(0, 40))
+        Ck = max(1, N // int(r.integers(1, 20)))
+        Q, K, V = (r.standard_normal((N, d)).astype(np.float32) for _ in range(3))
+        lk = np.concatenate([np.arange(L) % max(1, Ck - 1), np.full(N - L, max(0, Ck - 1))]).astype(np.int32)
+        r.shuffle(lk)
+        lq = r.integers(0, 3, size=N).astype(np.int32)
+        sel = [np.arange(max(1, Ck - 1)), np.arange(Ck), np.zeros(0, np.int64)]
+        _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "f32", tol=(1e-4, 1e-5))
+
+
 def test_attention_more_selected_key_clusters_than_the_run_table_in_lds_holds(svg2, oracle):
     """The matrix-core kernel keeps the (first row, keys before) table of a query cluster's selected key clusters in LDS
     up to 1919 entries and reads it from global memory beyond: one row of this case selects 2600 of 2700 key clusters
