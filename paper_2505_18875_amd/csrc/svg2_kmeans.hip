@@ -9,7 +9,7 @@
 //             Each accumulator gets its position written into its 4 lowest mantissa bits; the largest and the
 //             second largest of these keys are tracked per token (max3 / med3 trees, no compare-and-select
 //             chains), which gives the label and the gap to the runner-up.
-//             fp32 input: a plain FMA kernel (one token per thread).
+//             fp32 input: MFMA 32x32x2 fp32, the centroids of a token dealt out to several wavefronts.
 //   settle    (bf16) every token whose gap is within the error bound of the fp32 contraction is assigned
 //             again in double precision, over all centroids, lowest index winning an exact tie.  Products of
 //             two bf16 numbers are exact and their sums fit a double, so these labels are THE argmin of the
@@ -70,6 +70,7 @@ struct KmSide {
     // workspace
     bf16_t *cb;                 // [H,C,d] centroids rounded to bf16 (bf16 input)
     bf16_t *cbT;                // [H,d/8,C,8] the same, 16-byte chunk-major: chunk q of consecutive centroids is contiguous
+    float *ct;                  // [H,d/4,C,4] the fp32 centroids, chunk-major (fp32 input; in the place of cb and cbT)
     float *hcn;                 // [H,C] -||c||^2 / 2 of the rounded centroids (bf16 input), ||c||^2 (fp32 input)
     double *cn64;               // [H,C] ||c||^2 of the rounded centroids
     double *cd;                 // [H,C,d] centroids in double (what an empty cluster keeps)
@@ -203,6 +204,8 @@ __global__ void kmeans_finalize_kernel(KmArgs a, int mode, int set)
         S.cb[idx] = b;
         S.cbT[(((size_t)h * (d / 8) + (k >> 3)) * C + j) * 8 + (k & 7)] = b;
         cr = (double)bf16_to_f32(b);
+    } else {
+        S.ct[(((size_t)h * (d / 4) + (k >> 2)) * C + j) * 4 + (k & 3)] = (float)c;
     }
     double sq = cr * cr;
     for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
@@ -664,56 +667,117 @@ __global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
     }
 }
 
-// ---------------------------------------------------------------- assign, fp32 FMA
+// ---------------------------------------------------------------- assign, fp32
+// grid (token blocks, H, sides), block 64 * KF_NW; the side with more work (the last one: the K tokens of a layer) comes
+// first.  Matrix instruction 32x32x2 fp32 (fp32 products and sums, 64 cycles): the centroid tile is the A operand, 32
+// tokens are the B operand, a lane's 16 accumulators are 16 centroids of ONE token.  The contraction index may be taken
+// in any order: lane half h contributes its own half of the row, so a lane's share of a token is D/2 consecutive floats.
+// The two halves of the contraction have an accumulator each (shorter chains of roundings than one sum over D).
+//
+// The instruction is slow enough (a row block of 32 centroids is D/2 of them, 4096 cycles at D = 128) that the
+// centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
+// register buffers that take turns.  What decides is how many SIMDs have work, so the row blocks of a token block are
+// dealt out to up to four wavefronts (KF_NW / nc token blocks per workgroup, nc wavefronts each, nc as many as there are
+// row blocks) and the shares compared through LDS.  One token per thread with the centroids in LDS (300 workgroups
+// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 104 us per iteration for 4 heads of
+// 9601 tokens against 100 and 500 centroids at D = 128 (5.9 GFLOP), and 28 instead of 5.4 us for one head of 4096 against
+// 16 and 32 at D = 64.
+static constexpr int KF_NW = 4;
+
 template <int D, bool OBJ>
-__global__ __launch_bounds__(128) void kmeans_assign_f32_kernel(const float *__restrict__ X,
-                                                                const float *__restrict__ cent,
-                                                                const float *__restrict__ cn, int N, int C,
-                                                                int32_t *__restrict__ labels,
-                                                                float *__restrict__ objective, int obj_stride)
+__global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs a, KmIter it)
 {
-    constexpr int CT = 32;
-    __shared__ __align__(16) float s_c[CT * D];
-    __shared__ float s_cn[CT];
-    const int h = blockIdx.y, tid = threadIdx.x;
-    const int n = blockIdx.x * 128 + tid;
-    const float *xr = X + ((size_t)h * N + min(n, N - 1)) * D;
-    float x[D];
+    constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's half row
+    __shared__ float s_cn[SVG2_MAX_CLUSTERS];
+    __shared__ float s_best[KF_NW][32];
+    __shared__ int s_idx[KF_NW][32];
+    const int side = (int)(gridDim.z - 1 - blockIdx.z);
+    const KmSide S = side ? a.s[1] : a.s[0];
+    int32_t *labels = side ? it.lab[1] : it.lab[0];
+    const int N = a.N, C = S.C, h = blockIdx.y, tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    const int nrb = (C + 31) / 32;
+    const int nc = nrb >= 3 ? 4 : nrb;          // wavefronts that share a token block
+    const int wc = wave % nc, wt = wave / nc;
+    const int wg_tok0 = (int)blockIdx.x * (KF_NW / nc) * 32;
+    if (wg_tok0 >= N) return;                   // the grid is sized for nc = 4
+    const int n0 = wg_tok0 + wt * 32, n = n0 + col;
+
+    float x[D / 2];
+    {
+        const float4 *src = reinterpret_cast<const float4 *>(static_cast<const float *>(S.X) +
+                                                             ((size_t)h * N + min(n, N - 1)) * D + half * (D / 2));
 #pragma unroll
-    for (int k = 0; k < D / 4; ++k) {
-        const float4 v = reinterpret_cast<const float4 *>(xr)[k];
-        x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+        for (int k = 0; k < D / 8; ++k) {
+            const float4 v = src[k];
+            x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+        }
     }
+    const float4 *ct = reinterpret_cast<const float4 *>(S.ct) + ((size_t)h * (D / 4) + half * (D / 8)) * C;
+    float4 bufA[NB], bufB[NB];
+    auto load_c = [&](float4 (&buf)[NB], int rb, int hf) {
+        const int j = min(rb * 32 + col, C - 1);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) buf[i] = ct[(size_t)(hf * NB + i) * C + j];
+    };
+    load_c(bufA, min(wc, nrb - 1), 0);
+    for (int c = tid; c < 32 * nrb; c += 64 * KF_NW) s_cn[c] = c < C ? S.hcn[(size_t)h * C + c] : INFINITY;
+    __syncthreads();
+
     float best = INFINITY;
     int bidx = 0;
-    for (int c0 = 0; c0 < C; c0 += CT) {
-        __syncthreads();
-        for (int e = tid; e < CT * D; e += 128) {
-            const int r = e / D;
-            s_c[e] = (c0 + r < C) ? cent[((size_t)h * C + c0 + r) * D + (e % D)] : 0.f;
-        }
-        if (tid < CT) s_cn[tid] = (c0 + tid < C) ? cn[(size_t)h * C + c0 + tid] : INFINITY;
-        __syncthreads();
-        const int nr = min(CT, C - c0);
-        for (int r = 0; r < nr; ++r) {
-            float dot = 0.f;
+    for (int rb = wc; rb < nrb; rb += nc) {
+        load_c(bufB, rb, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 acc0 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
 #pragma unroll
-            for (int k = 0; k < D; ++k) dot = fmaf(x[k], s_c[r * D + k], dot);
-            const float dist = fmaf(-2.f, dot, s_cn[r]);
-            if (dist < best) { best = dist; bidx = c0 + r; }
+        for (int i = 0; i < NB; ++i) {
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc0, 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc0, 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc0, 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc0, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_c(bufA, min(rb + nc, nrb - 1), 0);         // (past the last row block: a valid one, not used)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc1, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // accumulator i is centroid 8 (i / 4) + 4 half + i % 4 of the row block: ascending in a lane, so strict <
+        // keeps the lowest index; the padding rows of the last block are at infinity
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int j = rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+            const float dist = fmaf(-2.f, acc0[i] + acc1[i], s_cn[j]);
+            if (dist < best) { best = dist; bidx = j; }
         }
     }
-    if (n < N) labels[(size_t)h * N + n] = bidx;
-    if (OBJ) {
-        float v = 0.f;
-        if (n < N) {
-            float x2 = 0.f;
+    // the two lane halves, then the wavefronts of a token block, hold disjoint centroids of the same token
+    auto merge = [&](float ob, int oj) {
+        if (ob < best || (ob == best && oj < bidx)) { best = ob; bidx = oj; }
+    };
+    merge(__shfl_xor(best, 32), __shfl_xor(bidx, 32));
+    if (nc > 1) {
+        if (half == 0) { s_best[wave][col] = best; s_idx[wave][col] = bidx; }
+        __syncthreads();
+        if (wc != 0) return;
+        for (int w = 1; w < nc; ++w) merge(s_best[wave + w][col], s_idx[wave + w][col]);
+    }
+    if (half == 0 && n < N) labels[(size_t)h * N + n] = bidx;
+    if (OBJ && S.objective) {
+        float x2 = 0.f;
 #pragma unroll
-            for (int k = 0; k < D; ++k) x2 = fmaf(x[k], x[k], x2);
-            v = x2 + best;
-        }
+        for (int k = 0; k < D / 2; ++k) x2 = fmaf(x[k], x[k], x2);
+        x2 += __shfl_xor(x2, 32);
+        float v = (half == 0 && n < N) ? x2 + best : 0.f;
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if ((tid & 63) == 0) atomicAdd(objective + (size_t)h * obj_stride, v);
+        if (lane == 0) atomicAdd(S.objective + (size_t)h * a.iters + it.t, v);
     }
 }
 
@@ -824,7 +888,8 @@ static void kmeans_carve_side(Carver &c, KmSide &k, int H, int N, int d, int C)
     k.C = C;
     k.max_pieces = cdiv(N, KM_SEG) + C;
     k.cb = c.take<bf16_t>((size_t)H * C * d);
-    k.cbT = c.take<bf16_t>((size_t)H * C * d);
+    k.cbT = c.take<bf16_t>((size_t)H * C * d);          // right behind cb, so the two hold H C d floats
+    k.ct = reinterpret_cast<float *>(k.cb);
     k.hcn = c.take<float>((size_t)H * C);
     k.cn64 = c.take<double>((size_t)H * C);
     k.cd = c.take<double>((size_t)H * C * d);
@@ -942,18 +1007,9 @@ static int kmeans_run(KmArgs a, hipStream_t st)
                 hipLaunchKernelGGL((kmeans_settle_kernel<D>), dim3(KM_SETTLE_BLOCKS, H * ns), dim3(256), 0, st, a, it);
             }
         } else {
-            const dim3 grid(cdiv(N, 128), H);
             ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);
-            for (int s = 0; s < ns; ++s) {
-                const float *Xf = reinterpret_cast<const float *>(a.s[s].X);
-                float *obj = a.s[s].objective ? a.s[s].objective + t : nullptr;
-                if (obj)
-                    hipLaunchKernelGGL((kmeans_assign_f32_kernel<D, true>), grid, dim3(128), 0, st, Xf, a.s[s].centroids,
-                                       a.s[s].hcn, N, a.s[s].C, it.lab[s], obj, iters);
-                else
-                    hipLaunchKernelGGL((kmeans_assign_f32_kernel<D, false>), grid, dim3(128), 0, st, Xf, a.s[s].centroids,
-                                       a.s[s].hcn, N, a.s[s].C, it.lab[s], obj, iters);
-            }
+            auto kern = any_obj ? kmeans_assign_f32_kernel<D, true> : kmeans_assign_f32_kernel<D, false>;
+            hipLaunchKernelGGL(kern, dim3(cdiv(N, 32), H, ns), dim3(64 * KF_NW), 0, st, a, it);
         }
         // label-sorted order of the tokens and its pieces, then the segmented sum over it
         SortArgs sa = {};

@@ -181,6 +181,23 @@ def test_kmeans_ragged_shapes(svg2, oracle, dtype, d, N, C):
     _check_kmeans(oracle, res, X, init, 3, dtype == "bf16", 2, C)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("N,C", [(31, 31), (33, 32), (130, 33), (129, 64), (65, 65), (97, 96), (160, 97), (1000, 128),
+                                 (4200, 4096)])
+def test_kmeans_f32_row_blocks_shared_by_the_wavefronts(svg2, oracle, d, N, C):
+    """The fp32 assign kernel deals the 32-centroid row blocks of a token block out to one, two or four wavefronts:
+    counts of centroids and tokens on both sides of these limits.  The second half of the centroids repeats the first,
+    so every token has an exact tie between row blocks, which the lowest index wins."""
+    r = np.random.default_rng(7100 + N + d)
+    X = r.standard_normal((2, N, d)).astype(np.float32) + 2.0 * r.standard_normal((2, 1, d)).astype(np.float32)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(2)]).astype(np.float32)
+    init[:, (C + 1) // 2:] = init[:, :C // 2]
+    res = svg2.svg2_kmeans(to_dev(X), to_dev(init), 1, want_objective=True)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, 1, False, 2, C)
+    assert to_np(res.labels).max() < (C + 1) // 2
+
+
 @pytest.mark.parametrize("H,N,C", [(300, 700, 40), (77, 1300, 520)])
 def test_kmeans_many_heads_a_workgroups_share_crosses_head_boundaries(svg2, oracle, H, N, C):
     # The bf16 assign kernel gives every CU an equal share of the 512-token blocks of ALL heads: with a few blocks per
