@@ -103,6 +103,28 @@ def test_select_topp_csr(svg2, oracle, H, Cq, Ck, d, p):
     _check_select(oracle, res2, cq, ck, None, counts_k, p, H)
 
 
+@pytest.mark.parametrize("H,Cq,Ck,d", [(1, 1, 2, 128), (2, 31, 63, 64), (1, 32, 64, 128), (2, 33, 65, 128), (1, 9, 127, 64),
+                                       (1, 8, 129, 128), (1, 7, 255, 64), (2, 65, 257, 128), (1, 17, 1025, 64),
+                                       (1, 5, 2049, 128)])
+def test_select_edges_of_the_score_tiles_and_of_the_sort(svg2, oracle, H, Cq, Ck, d):
+    """Cluster counts on both sides of a 32 x 128 score tile, of a wavefront's and of a workgroup's share of the sort, and
+    of the rows of a list-copying workgroup; a third of the key clusters share their centroid and size with another one
+    (exact ties, which the lower index wins)."""
+    r = np.random.default_rng(1200 + Cq + Ck)
+    cq = (1.3 * r.standard_normal((H, Cq, d))).astype(np.float32)
+    ck = (1.3 * r.standard_normal((H, Ck, d))).astype(np.float32)
+    counts_k = r.integers(0, 300, size=(H, Ck)).astype(np.int32)
+    counts_k[:, 0] = 7
+    t = Ck // 3
+    ck[:, Ck - t:], counts_k[:, Ck - t:] = ck[:, :t], counts_k[:, :t]
+    counts_q = r.integers(0, 3, size=(H, Cq)).astype(np.int32)
+    counts_q[:, 0] = 1
+    for p in (0.37, 0.9):
+        res = svg2.svg2_select_topp(to_dev(cq), to_dev(ck), to_dev(counts_q), to_dev(counts_k), p, want_p_est=True)
+        torch.cuda.synchronize()
+        assert _check_select(oracle, res, cq, ck, counts_q, counts_k, p, H) <= max(2, Cq // 20) * H
+
+
 def test_select_ties_and_equal_sizes(svg2, oracle):
     # identical centroids: all P' equal, ties resolved towards the lower index on both sides
     cq = np.zeros((1, 3, 64), dtype=np.float32)
