@@ -70,7 +70,8 @@ struct KmSide {
     // workspace
     bf16_t *cb;                 // [H,C,d] centroids rounded to bf16 (bf16 input)
     bf16_t *cbT;                // [H,d/8,C,8] the same, 16-byte chunk-major: chunk q of consecutive centroids is contiguous
-    float *ct;                  // [H,d/4,C,4] the fp32 centroids, chunk-major (fp32 input; in the place of cb and cbT)
+    float *ct;                  // [H,2,d/8,C,4] the fp32 centroids, even then odd elements, chunk-major (fp32 input; in
+                                // the place of cb and cbT)
     float *hcn;                 // [H,C] -||c||^2 / 2 of the rounded centroids (bf16 input), ||c||^2 (fp32 input)
     double *cn64;               // [H,C] ||c||^2 of the rounded centroids
     double *cd;                 // [H,C,d] centroids in double (what an empty cluster keeps)
@@ -205,7 +206,7 @@ __global__ void kmeans_finalize_kernel(KmArgs a, int mode, int set)
         S.cbT[(((size_t)h * (d / 8) + (k >> 3)) * C + j) * 8 + (k & 7)] = b;
         cr = (double)bf16_to_f32(b);
     } else {
-        S.ct[(((size_t)h * (d / 4) + (k >> 2)) * C + j) * 4 + (k & 3)] = (float)c;
+        S.ct[((((size_t)h * 2 + (k & 1)) * (d / 8) + (k >> 3)) * C + j) * 4 + ((k >> 1) & 3)] = (float)c;
     }
     double sq = cr * cr;
     for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
@@ -670,16 +671,16 @@ __global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
 // ---------------------------------------------------------------- assign, fp32
 // grid (token blocks, H, sides), block 64 * KF_NW; the side with more work (the last one: the K tokens of a layer) comes
 // first.  Matrix instruction 32x32x2 fp32 (fp32 products and sums, 64 cycles): the centroid tile is the A operand, 32
-// tokens are the B operand, a lane's 16 accumulators are 16 centroids of ONE token.  The contraction index may be taken
-// in any order: lane half h contributes its own half of the row, so a lane's share of a token is D/2 consecutive floats.
-// The two halves of the contraction have an accumulator each (shorter chains of roundings than one sum over D).
+// tokens are the B operand, a lane's 16 accumulators are 16 centroids of ONE token.  The contraction index runs in its
+// natural order (lane half h supplies the elements of parity h): the instruction adds its two products one after the
+// other with a rounding behind each, so an accumulator is bit for bit the chain of fmaf over k = 0 .. D - 1.
 //
 // The instruction is slow enough (a row block of 32 centroids is D/2 of them, 4096 cycles at D = 128) that the
 // centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
 // register buffers that take turns.  What decides is how many SIMDs have work, so the row blocks of a token block are
 // dealt out to up to four wavefronts (KF_NW / nc token blocks per workgroup, nc wavefronts each, nc as many as there are
 // row blocks) and the shares compared through LDS.  One token per thread with the centroids in LDS (300 workgroups
-// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 104 us per iteration for 4 heads of
+// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 100 us per iteration for 4 heads of
 // 9601 tokens against 100 and 500 centroids at D = 128 (5.9 GFLOP), and 28 instead of 5.4 us for one head of 4096 against
 // 16 and 32 at D = 64.
 static constexpr int KF_NW = 4;
@@ -704,17 +705,21 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     if (wg_tok0 >= N) return;                   // the grid is sized for nc = 4
     const int n0 = wg_tok0 + wt * 32, n = n0 + col;
 
-    float x[D / 2];
+    float x[D / 2];                             // x[s]: element 2 s + half of the token
     {
         const float4 *src = reinterpret_cast<const float4 *>(static_cast<const float *>(S.X) +
                                                              ((size_t)h * N + min(n, N - 1)) * D + half * (D / 2));
 #pragma unroll
         for (int k = 0; k < D / 8; ++k) {
+            // the lane halves load half a row each and trade its odd elements for the other half's even ones
             const float4 v = src[k];
-            x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+            const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.x), __float_as_uint(v.y), false, false);
+            const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.z), __float_as_uint(v.w), false, false);
+            x[2 * k] = __uint_as_float(p[0]); x[D / 4 + 2 * k] = __uint_as_float(p[1]);
+            x[2 * k + 1] = __uint_as_float(q[0]); x[D / 4 + 2 * k + 1] = __uint_as_float(q[1]);
         }
     }
-    const float4 *ct = reinterpret_cast<const float4 *>(S.ct) + ((size_t)h * (D / 4) + half * (D / 8)) * C;
+    const float4 *ct = reinterpret_cast<const float4 *>(S.ct) + ((size_t)h * 2 + half) * (D / 8) * C;
     float4 bufA[NB], bufB[NB];
     auto load_c = [&](float4 (&buf)[NB], int rb, int hf) {
         const int j = min(rb * 32 + col, C - 1);
@@ -730,23 +735,23 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     for (int rb = wc; rb < nrb; rb += nc) {
         load_c(bufB, rb, 1);
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 acc0 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+        f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc0, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc0, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc0, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc0, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc, 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         load_c(bufA, min(rb + nc, nrb - 1), 0);         // (past the last row block: a valid one, not used)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc1, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc1, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc1, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc1, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         // accumulator i is centroid 8 (i / 4) + 4 half + i % 4 of the row block: ascending in a lane, so strict <
@@ -754,7 +759,7 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int j = rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-            const float dist = fmaf(-2.f, acc0[i] + acc1[i], s_cn[j]);
+            const float dist = fmaf(-2.f, acc[i], s_cn[j]);
             if (dist < best) { best = dist; bidx = j; }
         }
     }
