@@ -49,7 +49,13 @@ static constexpr int ATT_OPS_B = 16;       // vector operations of a block's pro
 static constexpr float ATT_LEVEL_MAX = 1099511627776.0f;
 
 // ---------------------------------------------------------------- plan
-// grid (H), block 256.
+// grid (1 + ceil(Cq / 4), H), block 256.  Workgroup 0 of a head writes its tiles, the others take four CSR rows each, one
+// per wavefront.  A cluster with many tiles and a run with many key tiles have their entries written by the whole
+// wavefront.  (One workgroup per head for all rows took 45 to 60 us whatever the number of heads, each wavefront a
+// quarter of the rows with three dependent round trips to memory each: 24 heads of 9601 tokens, 100 x 500 clusters: 51 us,
+// 6 us now; dense attention of 24 heads of 9601 tokens: 13 us, 5 us now.)
+static constexpr int PLAN_OWN = 4;              // up to this many entries are written by the lane that holds the cluster
+
 __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t *__restrict__ offsets_q,
                                                         const int32_t *__restrict__ offsets_k,
                                                         const int32_t *__restrict__ row_ptr,
@@ -61,100 +67,87 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t *__restric
                                                         int32_t *__restrict__ tile_run)
 {
     __shared__ int32_t s_wave[4];
-    __shared__ int32_t s_carry;
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t *oq = offsets_q + (size_t)h * (Cq + 1);
-    const int32_t *ok = offsets_k + (size_t)h * (Ck + 1);
-    const int32_t *rp = row_ptr + (size_t)h * (Cq + 1);
-    const int32_t *ci = col_idx + (size_t)h * Cq * Ck;
-    int2 *rn = runs + (size_t)h * Cq * Ck;
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    // tiles: running count over clusters, 256 clusters per pass
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int c0 = 0; c0 < Cq; c0 += 256) {
-        const int c = c0 + tid;
-        const int start = (c < Cq) ? oq[c] : 0;
-        const int size = (c < Cq) ? oq[c + 1] - start : 0;
-        const int nt = (size + BM - 1) / BM;
-        int incl = nt;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
-        }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        int base = s_carry;
-        for (int w = 0; w < wave; ++w) base += s_wave[w];
-        const int first = base + incl - nt;
-        if (c < Cq) cl_first[(size_t)h * Cq + c] = first;
-        for (int t = 0; t < nt; ++t)
-            tiles[(size_t)h * max_tiles + first + t] = make_int4(c, start + t * BM, min(BM, size - t * BM), 0);
-        __syncthreads();
-        if (tid == 255) s_carry = base + incl;
-        __syncthreads();
-    }
-    if (tid == 0) n_tiles[h] = s_carry;
-
-    // runs: one wavefront per CSR row, 64 entries per pass
-    for (int i = wave; i < Cq; i += 4) {
-        const int e0 = rp[i], e1 = rp[i + 1];
+    if (blockIdx.x == 0) {
+        // tiles: running count over clusters, 256 clusters per pass
+        const int32_t *oq = offsets_q + (size_t)h * (Cq + 1);
+        int4 *tl = tiles + (size_t)h * max_tiles;
         int carry = 0;
-        for (int e = e0; e < e1; e += 64) {
-            const int idx = e + lane;
-            int start = 0, len = 0;
-            if (idx < e1) {
-                const int j = ci[idx];
-                start = ok[j];
-                len = ok[j + 1] - start;
-            }
-            int incl = len;
+        for (int c0 = 0; c0 < Cq; c0 += 256) {
+            const int c = c0 + tid;
+            const int start = (c < Cq) ? oq[c] : 0;
+            const int size = (c < Cq) ? oq[c + 1] - start : 0;
+            const int nt = (size + BM - 1) / BM;
+            int incl = nt;
             for (int o = 1; o < 64; o <<= 1) {
                 const int v = __shfl_up(incl, o);
                 if (lane >= o) incl += v;
             }
-            if (idx < e1) {
-                const int before = carry + incl - len;          // keys of the row in front of this run
-                rn[idx] = make_int2(start, before);
-                // the 64-key tiles whose first key lies in this run start their row look-up here
-                int32_t *tr = tile_run + ((size_t)h * Cq + i) * key_tiles;
-                for (int t = (before + ATT_BN - 1) / ATT_BN; t * ATT_BN < before + len && t < key_tiles; ++t) tr[t] = idx - e0;
+            __syncthreads();                            // the pass before has read s_wave
+            if (lane == 63) s_wave[wave] = incl;
+            __syncthreads();
+            int base = carry;
+            for (int w = 0; w < 4; ++w) {
+                if (w < wave) base += s_wave[w];
+                carry += s_wave[w];
             }
-            carry += __shfl(incl, 63);
+            const int first = base + incl - nt;
+            if (c < Cq) cl_first[(size_t)h * Cq + c] = first;
+            if (nt <= PLAN_OWN)
+                for (int t = 0; t < nt; ++t) tl[first + t] = make_int4(c, start + t * BM, min(BM, size - t * BM), 0);
+            for (unsigned long long big = __ballot(nt > PLAN_OWN); big; big &= big - 1) {
+                const int src = __builtin_ctzll(big);
+                const int bn = __shfl(nt, src), bf = __shfl(first, src), bs = __shfl(start, src), bz = __shfl(size, src);
+                for (int t = lane; t < bn; t += 64)
+                    tl[bf + t] = make_int4(c - lane + src, bs + t * BM, min(BM, bz - t * BM), 0);
+            }
         }
-        if (lane == 0) row_keys[(size_t)h * Cq + i] = carry;
+        if (tid == 0) n_tiles[h] = carry;
+        return;
     }
-}
 
-// tile_base[h] = number of tiles of heads < h; tile_base[H] = all tiles.  One workgroup.
-__global__ __launch_bounds__(256) void attn_tile_base_kernel(const int32_t *__restrict__ n_tiles, int H,
-                                                             int32_t *__restrict__ tile_base)
-{
-    __shared__ int32_t s_wave[4];
-    __shared__ int32_t s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int h0 = 0; h0 < H; h0 += 256) {
-        const int h = h0 + tid;
-        const int n = (h < H) ? n_tiles[h] : 0;
-        int incl = n;
+    // runs: one wavefront per CSR row, 64 entries per pass
+    const int i = ((int)blockIdx.x - 1) * 4 + wave;
+    if (i >= Cq) return;
+    const int32_t *ok = offsets_k + (size_t)h * (Ck + 1);
+    const int32_t *rp = row_ptr + (size_t)h * (Cq + 1);
+    const int32_t *ci = col_idx + (size_t)h * Cq * Ck;
+    int2 *rn = runs + (size_t)h * Cq * Ck;
+    int32_t *tr = tile_run + ((size_t)h * Cq + i) * key_tiles;
+    const int e0 = rp[i], e1 = rp[i + 1];
+    int carry = 0;
+    for (int e = e0; e < e1; e += 64) {
+        const int idx = e + lane;
+        int start = 0, len = 0;
+        if (idx < e1) {
+            const int j = ci[idx];
+            start = ok[j];
+            len = ok[j + 1] - start;
+        }
+        int incl = len;
         for (int o = 1; o < 64; o <<= 1) {
             const int v = __shfl_up(incl, o);
             if (lane >= o) incl += v;
         }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        int base = s_carry;
-        for (int w = 0; w < wave; ++w) base += s_wave[w];
-        if (h < H) tile_base[h] = base + incl - n;
-        __syncthreads();
-        if (tid == 255) s_carry = base + incl;
-        __syncthreads();
+        const int before = carry + incl - len;          // keys of the row in front of this run
+        if (idx < e1) rn[idx] = make_int2(start, before);
+        // the 64-key tiles whose first key lies in this run start their row look-up here
+        const int t0 = (before + ATT_BN - 1) / ATT_BN;
+        const int t1 = min((before + len + ATT_BN - 1) / ATT_BN, key_tiles);
+        if (t1 - t0 <= PLAN_OWN)
+            for (int t = t0; t < t1; ++t) tr[t] = idx - e0;
+        for (unsigned long long big = __ballot(t1 - t0 > PLAN_OWN); big; big &= big - 1) {
+            const int src = __builtin_ctzll(big);
+            const int b0 = __shfl(t0, src), b1 = __shfl(t1, src);
+            for (int t = b0 + lane; t < b1; t += 64) tr[t] = e - e0 + src;
+        }
+        carry += __shfl(incl, 63);
     }
-    if (tid == 0) tile_base[H] = s_carry;
+    if (lane == 0) row_keys[(size_t)h * Cq + i] = carry;
 }
 
+// tile_base[h] = number of tiles of heads < h, tile_base[H] = all tiles; and
 // order[0 .. all tiles): the work items sorted by decreasing number of key tiles (longest first), so that the
 // last workgroups of a launch are short ones.  The tiles of one query cluster stay together (they read the
 // same keys); among clusters of equal length the order is whatever the atomics give -- it only decides when a
@@ -164,18 +157,39 @@ static constexpr int ORD_BUCKETS = 2048;
 static constexpr int ORD_MAX_CLUSTERS = 1 << 20;
 
 __global__ __launch_bounds__(1024) void attn_order_kernel(const int32_t *__restrict__ offsets_q,
-                                                          const int32_t *__restrict__ tile_base,
+                                                          const int32_t *__restrict__ n_tiles, int32_t *tile_base,
                                                           const int32_t *__restrict__ row_keys,
                                                           const int32_t *__restrict__ cl_first, int H, int Cq, int BM,
                                                           int32_t *__restrict__ order)
 {
     __shared__ int32_t s_cnt[ORD_BUCKETS];
     __shared__ int32_t s_part[1024];
-    const int tid = threadIdx.x;
+    __shared__ int32_t s_wave[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int all = 0;
+    for (int h0 = 0; h0 < H; h0 += 1024) {
+        const int h = h0 + tid;
+        const int n = (h < H) ? n_tiles[h] : 0;
+        int incl = n;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o);
+            if (lane >= o) incl += v;
+        }
+        __syncthreads();                        // the pass before has read s_wave
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int base = all;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) base += s_wave[w];
+            all += s_wave[w];
+        }
+        if (h < H) tile_base[h] = base + incl - n;
+    }
+    if (tid == 0) tile_base[H] = all;
+    __syncthreads();                            // tile_base is read by other threads of this workgroup below
     const long long ncl = (long long)H * Cq;
     if (ncl > ORD_MAX_CLUSTERS) {
-        const int total = tile_base[H];
-        for (int v = tid; v < total; v += 1024) order[v] = v;
+        for (int v = tid; v < all; v += 1024) order[v] = v;
         return;
     }
     for (int b = tid; b < ORD_BUCKETS; b += 1024) s_cnt[b] = 0;
@@ -982,12 +996,11 @@ int attn_plan_launch(int dtype, int H, int N, int Cq, int Ck, const int32_t *off
                      const int32_t *row_ptr, const int32_t *col_idx, void *ws, hipStream_t st)
 {
     const AttnWs a = attn_carve(ws, dtype, H, N, Cq, Ck);
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(H), dim3(256), 0, st, offsets_q, offsets_k, row_ptr, col_idx, Cq, Ck,
-                       attn_bm(dtype), a.max_tiles, a.tiles, a.n_tiles, a.runs, a.row_keys, a.cl_first, a.key_tiles,
-                       a.tile_run);
-    hipLaunchKernelGGL(attn_tile_base_kernel, dim3(1), dim3(256), 0, st, a.n_tiles, H, a.tile_base);
+    hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + cdiv(Cq, 4), H), dim3(256), 0, st, offsets_q, offsets_k, row_ptr, col_idx,
+                       Cq, Ck, attn_bm(dtype), a.max_tiles, a.tiles, a.n_tiles, a.runs, a.row_keys, a.cl_first,
+                       a.key_tiles, a.tile_run);
     if (dtype == SVG2_BF16)                     // the fp32 kernel is launched on a (tile, head) grid and needs no list
-        hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(1024), 0, st, offsets_q, a.tile_base, a.row_keys,
+        hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(1024), 0, st, offsets_q, a.n_tiles, a.tile_base, a.row_keys,
                            a.cl_first, H, Cq, attn_bm(dtype), a.order);
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
