@@ -74,7 +74,7 @@ struct KmSide {
                                 // the place of cb and cbT)
     float *hcn;                 // [H,C] -||c||^2 / 2 of the rounded centroids (bf16 input), ||c||^2 (fp32 input)
     double *cn64;               // [H,C] ||c||^2 of the rounded centroids
-    double *cd;                 // [H,C,d] centroids in double (what an empty cluster keeps)
+    double *cd;                 // [H,C,d] centroids in double of the clusters that are empty (what they keep)
     double *csum;               // [H,C,d] cluster sums, kept between iterations
     float *best, *second;       // [H,N] running best / runner-up between centroid chunks (C > KM_CMAX only)
     int32_t *flag_cnt;          // [H] tokens to settle
@@ -86,6 +86,7 @@ struct KmSide {
     int32_t *offsets[2], *perm[2], *first_piece[2], *n_pieces[2];
     int4 *pieces[2];
     double *psum[2];            // [H,max_pieces,d]
+    int32_t *moved[2];          // [H,max_pieces] whether the delta update found a token in the piece (else no psum)
     int max_pieces;
 };
 
@@ -154,66 +155,118 @@ __device__ __forceinline__ bf16_t f64_to_bf16(double m)
 }
 
 // ---------------------------------------------------------------- finalize
-// grid (max C, H, sides), block d.  mode 0: centroids <- init (first call).  mode 1: cluster sum = sum of the
-// cluster's pieces of set `set`.  mode 2 (delta update): cluster sum = previous cluster sum + the pieces of the
-// tokens that joined the cluster (set `set`) - the pieces of the tokens that left it (the other set).  All sums
-// are doubles of bf16 / fp32 values: exact, whatever the order.
-template <bool BF16>
-__global__ void kmeans_finalize_kernel(KmArgs a, int mode, int set)
+// grid (ceil(clusters of both sides / KM_FIN_NW), H), block 64 * KM_FIN_NW: one wavefront per cluster, lane l holds
+// elements l (and l + 64).  mode 0: what the first assign step reads, from the caller's centroids.  mode 1: cluster sum
+// = sum of the cluster's pieces of set `it.set`.  mode 2 (delta update): cluster sum = previous cluster sum + the pieces
+// of the tokens that joined the cluster (set `it.set`) - the pieces of the tokens that left it (the other set), as far
+// as a piece has any (`moved`).  All sums are doubles of bf16 / fp32 values, in the order of the pieces.
+//
+// What bounds it is the bytes it touches (a cluster's double sums in and out, its pieces), so it touches what the next
+// step reads and no more: the fp32 centroids go out in the last iteration, and the mean in double is kept only of a
+// cluster that has just run empty (it is the previous sum over the previous count).  One workgroup of D threads per
+// cluster, all of these written in every iteration and every piece read whether anything moved in it or not, took 24
+// instead of 14 us per iteration at 24 heads of 16,384 tokens (100 and 500 clusters, d = 128) and 45 instead of 31 us at
+// 40 heads of 75,600.  Only loads that are needed are issued: eight pieces always requested together (the missing ones as
+// duplicates of the first) took 25 and 53 us.
+static constexpr int KM_FIN_NW = 4;
+static constexpr int KM_FIN_UB = 8;             // pieces requested together
+
+template <bool BF16, int D>
+__global__ __launch_bounds__(64 * KM_FIN_NW) void kmeans_finalize_kernel(KmArgs a, KmIter it, int mode)
 {
-    __shared__ double s_red[2];
-    const KmSide S = blockIdx.z ? a.s[1] : a.s[0];
-    const int j = blockIdx.x, h = blockIdx.y, k = threadIdx.x, C = S.C, d = blockDim.x;
-    if (j >= C) return;
-    if (j == 0 && k == 0) S.flag_cnt[h] = 0;           // the next assign step starts an empty list
-    const size_t idx = ((size_t)h * C + j) * d + k;
-    double c;
+    constexpr int EL = D / 64;
+    const int lane = threadIdx.x & 63, h = blockIdx.y, set = it.set;
+    const int jj = blockIdx.x * KM_FIN_NW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int side = jj >= a.s[0].C ? 1 : 0;
+    const KmSide S = side ? a.s[1] : a.s[0];
+    const int C = S.C, j = side ? jj - a.s[0].C : jj;
+    if (side >= a.nsides || j >= C) return;
+    if (j == 0 && lane == 0) S.flag_cnt[h] = 0;         // the next assign step starts an empty list
+    const size_t idx = ((size_t)h * C + j) * D + lane;
+    double c[EL];
     if (mode != 0) {
         const int32_t *off = KM_SEL(S.offsets, set) + (size_t)h * (C + 1);
         const int cnt = off[j + 1] - off[j];
-        const int32_t *fp = KM_SEL(S.first_piece, set) + (size_t)h * (C + 1);
-        const int p0 = fp[j], p1 = fp[j + 1];
-        const double *ps = KM_SEL(S.psum, set) + (size_t)h * S.max_pieces * d;
-        double s = (mode == 2) ? S.csum[idx] : 0.0;
-        // unrolled so that the loads of 8 pieces are in flight together: the largest cluster of a head has dozens
-        // of pieces and its block decides how long the launch takes
-#pragma unroll 8
-        for (int q = p0; q < p1; ++q) s += ps[(size_t)q * d + k];
-        if (mode == 2) {
-            const int32_t *fo = KM_SEL(S.first_piece, 1 - set) + (size_t)h * (C + 1);
-            const int o0 = fo[j], o1 = fo[j + 1];
-            const double *po = KM_SEL(S.psum, 1 - set) + (size_t)h * S.max_pieces * d;
-#pragma unroll 8
-            for (int q = o0; q < o1; ++q) s -= po[(size_t)q * d + k];
+        double s[EL], s_prev[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            s_prev[e] = (mode == 2 || (cnt == 0 && it.t > 0)) ? S.csum[idx + 64 * e] : 0.0;
+            s[e] = mode == 2 ? s_prev[e] : 0.0;
         }
+        auto add_pieces = [&](int st, double sign) {
+            const int32_t *fp = KM_SEL(S.first_piece, st) + (size_t)h * (C + 1);
+            const int p0 = fp[j], np = fp[j + 1] - p0;
+            const double *ps = KM_SEL(S.psum, st) + ((size_t)h * S.max_pieces + p0) * D + lane;
+            const int32_t *mv = KM_SEL(S.moved, st) + (size_t)h * S.max_pieces + p0;
+            // KM_FIN_UB pieces in flight together: the largest cluster of a head has dozens and its wavefront decides
+            // how long the launch takes
+            for (int p = 0; p < np; p += 64) {
+                unsigned long long m = __ballot(p + lane < np && (mode == 1 || mv[min(p + lane, np - 1)] != 0));
+                while (m) {
+                    double v[KM_FIN_UB][EL];
+                    int n = 0;
+#pragma unroll
+                    for (int u = 0; u < KM_FIN_UB; ++u)
+                        if (m) {
+                            const int q = p + (int)__builtin_ctzll(m);
+                            m &= m - 1;
+                            n = u + 1;
+#pragma unroll
+                            for (int e = 0; e < EL; ++e) v[u][e] = ps[(size_t)q * D + 64 * e];
+                        }
+#pragma unroll
+                    for (int u = 0; u < KM_FIN_UB; ++u)
+                        if (u < n) {
+#pragma unroll
+                            for (int e = 0; e < EL; ++e) s[e] += sign * v[u][e];
+                        }
+                }
+            }
+        };
+        add_pieces(set, 1.0);
+        if (mode == 2) add_pieces(1 - set, -1.0);
         if (cnt > 0) {
-            c = s / (double)cnt;
-        } else {
-            s = 0.0;
-            c = S.cd[idx];                              // an empty cluster keeps its centroid
+#pragma unroll
+            for (int e = 0; e < EL; ++e) c[e] = s[e] / (double)cnt;
+        } else {                                        // an empty cluster keeps its centroid
+            const int prev = it.t > 0 ? S.counts[(size_t)h * C + j] : 0;
+#pragma unroll
+            for (int e = 0; e < EL; ++e) {
+                c[e] = it.t == 0 ? (double)S.init[idx + 64 * e]
+                       : prev > 0 ? s_prev[e] / (double)prev
+                                  : S.cd[idx + 64 * e];
+                S.cd[idx + 64 * e] = c[e];
+                s[e] = 0.0;
+            }
         }
-        S.csum[idx] = s;
-        if (k == 0) S.counts[(size_t)h * C + j] = cnt;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            S.csum[idx + 64 * e] = s[e];
+            if (it.t + 1 == a.iters) S.centroids[idx + 64 * e] = (float)c[e];
+        }
+        if (lane == 0) S.counts[(size_t)h * C + j] = cnt;
     } else {
-        c = (double)S.init[idx];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) c[e] = (double)S.init[idx + 64 * e];
     }
-    S.cd[idx] = c;
-    S.centroids[idx] = (float)c;
-    double cr = (double)(float)c;
-    if (BF16) {
-        const bf16_t b = f64_to_bf16(c);
-        S.cb[idx] = b;
-        S.cbT[(((size_t)h * (d / 8) + (k >> 3)) * C + j) * 8 + (k & 7)] = b;
-        cr = (double)bf16_to_f32(b);
-    } else {
-        S.ct[((((size_t)h * 2 + (k & 1)) * (d / 8) + (k >> 3)) * C + j) * 4 + ((k >> 1) & 3)] = (float)c;
+    double n2 = 0.0;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+        const int k = lane + 64 * e;
+        double cr = (double)(float)c[e];
+        if (BF16) {
+            const bf16_t b = f64_to_bf16(c[e]);
+            S.cb[idx + 64 * e] = b;
+            S.cbT[(((size_t)h * (D / 8) + (k >> 3)) * C + j) * 8 + (k & 7)] = b;
+            cr = (double)bf16_to_f32(b);
+        } else {
+            S.ct[((((size_t)h * 2 + (k & 1)) * (D / 8) + (k >> 3)) * C + j) * 4 + ((k >> 1) & 3)] = (float)c[e];
+        }
+        double sq = cr * cr;
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        n2 = e == 0 ? sq : n2 + sq;
     }
-    double sq = cr * cr;
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
-    if ((k & 63) == 0) s_red[k >> 6] = sq;
-    __syncthreads();
-    if (k == 0) {
-        const double n2 = (d > 64) ? s_red[0] + s_red[1] : s_red[0];
+    if (lane == 0) {
         S.cn64[(size_t)h * C + j] = n2;
         S.hcn[(size_t)h * C + j] = BF16 ? (float)(-0.5 * n2) : (float)n2;
     }
@@ -839,6 +892,8 @@ __global__ __launch_bounds__(256) void kmeans_segsum_kernel(KmArgs a, KmIter it)
             if (take) list[cnt + __popcll(m & lt_mask)] = srcs[i];
             cnt += __popcll(m);
         }
+        if (lane == 0) KM_SEL(S.moved, set)[(size_t)h * S.max_pieces + piece] = cnt;
+        if (cnt == 0) return;
     }
     double acc[EPL];
 #pragma unroll
@@ -906,6 +961,7 @@ static void kmeans_carve_side(Carver &c, KmSide &k, int H, int N, int d, int C)
         k.n_pieces[s] = c.take<int32_t>((size_t)H);
         k.pieces[s] = c.take<int4>((size_t)H * k.max_pieces);
         k.psum[s] = c.take<double>((size_t)H * k.max_pieces * d);
+        k.moved[s] = c.take<int32_t>((size_t)H * k.max_pieces);
     }
     k.labels_alt = c.take<int32_t>((size_t)H * N);
     k.flag_cnt = c.take<int32_t>((size_t)H);
@@ -970,19 +1026,20 @@ static int kmeans_run(KmArgs a, hipStream_t st)
     const int H = a.H, N = a.N, iters = a.iters, ns = a.nsides;
     int ncu = 0;
     if (BF16) SVG2_TRY(device_cu_count(&ncu));
-    int cmax = 0, pmax = 0;
+    int call = 0, pmax = 0;
     bool any_obj = false;
     for (int s = 0; s < ns; ++s) {
-        cmax = std::max(cmax, a.s[s].C);
+        call += a.s[s].C;
         pmax = std::max(pmax, a.s[s].max_pieces);
         if (a.s[s].objective) {
             any_obj = true;
             hipLaunchKernelGGL(kmeans_zero_kernel, dim3(cdiv(H * iters, 256)), dim3(256), 0, st, a.s[s].objective, H * iters);
         }
     }
+    const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);
     {
         ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
-        hipLaunchKernelGGL((kmeans_finalize_kernel<BF16>), dim3(cmax, H, ns), dim3(D), 0, st, a, 0, 0);
+        hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, KmIter{}, 0);
     }
     for (int t = 0; t < iters; ++t) {
         // Update step: the first iteration, and every KM_FULL_EVERY-th after that, sums every cluster afresh; the
@@ -1045,7 +1102,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
         {
             ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
-            hipLaunchKernelGGL((kmeans_finalize_kernel<BF16>), dim3(cmax, H, ns), dim3(D), 0, st, a, full ? 1 : 2, it.set);
+            hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, it,
+                               full ? 1 : 2);
         }
     }
     return SVG2_OK;

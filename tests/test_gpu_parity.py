@@ -301,6 +301,28 @@ def test_kmeans_empty_cluster_keeps_centroid_and_warm_start(svg2, oracle):
     assert np.mean(to_np(res2.labels[0]) == ref2.labels) >= 0.999
 
 
+@pytest.mark.parametrize("dtype,d,N,C,iters", [
+    ("bf16", 128, 60, 50, 2), ("bf16", 64, 90, 80, 3), ("f32", 128, 90, 80, 5), ("bf16", 128, 120, 90, 18),
+    # clusters of 8, 9, 64 and more pieces of 256 tokens
+    ("bf16", 128, 2300, 1, 3), ("bf16", 64, 20000, 2, 4), ("f32", 128, 40000, 2, 3)])
+def test_kmeans_clusters_that_run_empty_and_clusters_of_many_pieces(svg2, oracle, dtype, d, N, C, iters):
+    """A cluster keeps its centroid from the moment it runs empty (in the first iteration: the initial one; later: the
+    mean of its last members), stays at it while it is empty, and starts from nothing when tokens come back."""
+    r = np.random.default_rng(5200 + N + iters)
+    X = r.standard_normal((2, N, d)).astype(np.float32)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(2)]).astype(np.float32)
+    if C > 4:                   # a few centroids that nothing is near, and a few that share their tokens
+        init[:, 3] += 50.0
+        init[:, C // 2] = init[:, C // 2 - 1] + 0.01
+    if dtype == "bf16":
+        X = wl.round_to_bf16(X)
+    res = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), iters)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, iters, dtype == "bf16", 2, C)
+    if C > 4:
+        assert (to_np(res.counts) == 0).any()
+
+
 @pytest.mark.parametrize("dtype,N,C,iters", [("bf16", 16384, 200, 26), ("f32", 3000, 400, 19)])
 def test_kmeans_many_iterations_centroids_are_means_of_the_labels(svg2, dtype, N, C, iters):
     # From the second iteration on the update step only moves the tokens whose label changed between the cluster
