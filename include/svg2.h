@@ -361,11 +361,12 @@ int svg2_kmeans_pp_init(const void *X, int dtype, int H, int N, int d, int C,
 enum {
     SVG2_K_KMEANS_ASSIGN = 0,      /* assign step, Q and K side in one launch (Section 4.1) */
     SVG2_K_KMEANS_SETTLE = 1,      /* near-ties again in double precision                   */
-    SVG2_K_KMEANS_SORT = 2,        /* counting sort of the labels (3 kernels)               */
+    SVG2_K_KMEANS_SORT = 2,        /* counting sort of the labels                           */
     SVG2_K_KMEANS_SEGSUM_FULL = 3, /* segmented sum over all tokens                         */
     SVG2_K_KMEANS_SEGSUM_DELTA = 4,/* segmented sum over the tokens whose label changed     */
     SVG2_K_KMEANS_FINALIZE = 5,    /* means, bf16 copy, norms                               */
-    SVG2_K_PERMUTE_SORT = 6,       /* permutation index vectors of Q and K (3 kernels)      */
+    SVG2_K_PERMUTE_SORT = 6,       /* index vectors of svg2_permute; in svg2_forward* the last
+                                    * sort of k-means is the permutation                    */
     SVG2_K_PERMUTE_GATHER = 7,     /* permuted copies of Q, K, V                            */
     SVG2_N_KERNEL_CLASSES = 8
 };

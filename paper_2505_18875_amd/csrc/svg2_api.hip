@@ -132,9 +132,7 @@ static ForwardLayout forward_layout(void *ws, int dtype, int H, int N, int d, in
     L.sv = c.take<float>(fp8 ? (size_t)H : 0);
     // the stages run one after another on one stream and share one scratch area
     size_t s = kmeans_pair_ws_bytes(dtype, H, N, d, Cq, Ck);     // both sides run in the same launches
-    size_t t = permute_ws_bytes(H, N, Cq) + permute_ws_bytes(H, N, Ck);
-    if (t > s) s = t;
-    t = select_ws_bytes(H, Cq, Ck);
+    size_t t = select_ws_bytes(H, Cq, Ck);
     if (t > s) s = t;
     t = attn_ws_bytes(dtype, H, N, d, Cq, Ck);
     if (t > s) s = t;
@@ -428,12 +426,12 @@ static int forward_impl(const void *Q, const void *K, const void *V, int dtype, 
     profile_mark(pb, 0, st);
     // Section 4.1: cluster Q and K independently (both sides share every launch)
     SVG2_TRY(kmeans_pair_launch(Q, K, dtype, H, N, d, Cq, Ck, iters, cq_inout, ck_inout, L.labels_q, L.labels_k,
-                                L.counts_q, L.counts_k, L.stage_ws, st));
+                                L.counts_q, L.counts_k, L.offsets_q, L.offsets_k, L.perm_q, L.perm_k, L.stage_ws, st));
     profile_mark(pb, 1, st);
-    // Section 4.1: permutations; K and V share pi_k
-    // (gather-free: only the index vectors; the rows are fetched through them in the attention kernel)
-    SVG2_TRY(permute_pair_launch(L.labels_q, L.labels_k, H, N, Cq, Ck, L.offsets_q, L.offsets_k, L.perm_q, L.perm_k,
-                                 !gather_free, Q, K, V, L.Qp, L.Kp, L.Vp, dtype, d, L.stage_ws, st));
+    // Section 4.1: permutations, with the order that k-means leaves; K and V share pi_k
+    // (gather-free: the rows are fetched through it in the attention kernel)
+    if (!gather_free)
+        SVG2_TRY(gather_pair_launch(L.perm_q, L.perm_k, H, N, Q, K, V, L.Qp, L.Kp, L.Vp, dtype, d, st));
     if (mode == FWD_FP8) {              // E4M3 copies in token order, one scale per head and tensor
         SVG2_TRY(fp8_quant_launch(Q, dtype, H, N, d, L.Q8, L.sq, L.stage_ws, st));
         SVG2_TRY(fp8_quant_launch(K, dtype, H, N, d, L.K8, L.sk, L.stage_ws, st));

@@ -119,11 +119,13 @@ int kmeans_launch(const void *X, int dtype, int H, int N, int d, int C, int iter
                   const float *init, float *centroids, int32_t *labels, int32_t *counts,
                   float *objective, void *ws, hipStream_t st);
 // k-means of the Q tokens and of the K tokens of a layer together (one launch per step for both sides); the
-// workspace holds both sides' scratch (kmeans_pair_ws_bytes)
+// workspace holds both sides' scratch (kmeans_pair_ws_bytes).  The update step of the last iteration sorts the tokens by
+// the labels that are handed back, so its order is the layer's permutation (Section 4.1) and goes out as well.
 size_t kmeans_pair_ws_bytes(int dtype, int H, int N, int d, int Cq, int Ck);
 int kmeans_pair_launch(const void *Q, const void *K, int dtype, int H, int N, int d, int Cq, int Ck, int iters,
                        float *cq_inout, float *ck_inout, int32_t *labels_q, int32_t *labels_k, int32_t *counts_q,
-                       int32_t *counts_k, void *ws, hipStream_t st);
+                       int32_t *counts_k, int32_t *offsets_q, int32_t *offsets_k, int32_t *perm_q, int32_t *perm_k,
+                       void *ws, hipStream_t st);
 
 // One problem of the counting sort (all heads of one side: the Q tokens or the K tokens of a layer).
 struct SortSide {
@@ -145,10 +147,8 @@ struct SortArgs {
 int sort_launch(SortArgs a, int nsides, int H, int N, hipStream_t st);
 
 size_t permute_ws_bytes(int H, int N, int C);
-int permute_pair_launch(const int32_t *labels_q, const int32_t *labels_k, int H, int N, int Cq, int Ck,
-                        int32_t *offsets_q, int32_t *offsets_k, int32_t *perm_q, int32_t *perm_k, bool copy,
-                        const void *Q, const void *K, const void *V, void *Qp, void *Kp, void *Vp, int dtype, int d,
-                        void *ws, hipStream_t st);
+int gather_pair_launch(const int32_t *perm_q, const int32_t *perm_k, int H, int N, const void *Q, const void *K,
+                       const void *V, void *Qp, void *Kp, void *Vp, int dtype, int d, hipStream_t st);
 int permute_launch(const int32_t *labels, int H, int N, int C, int32_t *offsets, int32_t *perm,
                    int32_t *inv_perm, int n_tensors, const void *const *src, void *const *dst,
                    int dtype, int d, void *ws, hipStream_t st);

@@ -1144,7 +1144,8 @@ int kmeans_launch(const void *X, int dtype, int H, int N, int d, int C, int iter
 
 int kmeans_pair_launch(const void *Q, const void *K, int dtype, int H, int N, int d, int Cq, int Ck, int iters,
                        float *cq_inout, float *ck_inout, int32_t *labels_q, int32_t *labels_k, int32_t *counts_q,
-                       int32_t *counts_k, void *ws, hipStream_t st)
+                       int32_t *counts_k, int32_t *offsets_q, int32_t *offsets_k, int32_t *perm_q, int32_t *perm_k,
+                       void *ws, hipStream_t st)
 {
     KmArgs a = {};
     a.nsides = 2; a.H = H; a.N = N; a.iters = iters;
@@ -1153,6 +1154,12 @@ int kmeans_pair_launch(const void *Q, const void *K, int dtype, int H, int N, in
     kmeans_carve_side(c, a.s[1], H, N, d, Ck);
     kmeans_fill_side(a.s[0], Q, cq_inout, cq_inout, labels_q, counts_q, nullptr);
     kmeans_fill_side(a.s[1], K, ck_inout, ck_inout, labels_k, counts_k, nullptr);
+    // the set of the last iteration is the caller's
+    const int last = (iters - 1) & 1;
+    a.s[0].offsets[last] = offsets_q;
+    a.s[0].perm[last] = perm_q;
+    a.s[1].offsets[last] = offsets_k;
+    a.s[1].perm[last] = perm_k;
     return kmeans_dispatch(a, dtype, d, st);
 }
 

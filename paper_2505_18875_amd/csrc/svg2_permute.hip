@@ -276,37 +276,17 @@ int permute_launch(const int32_t *labels, int H, int N, int C, int32_t *offsets,
     return SVG2_OK;
 }
 
-// Both permutations of a layer (Section 4.1: pi_q for Q, pi_k shared by K and V) with one launch per sort step.
-// ws holds the histograms of both sides (permute_ws_bytes for each, Q first).  copy = false: index vectors only.
-int permute_pair_launch(const int32_t *labels_q, const int32_t *labels_k, int H, int N, int Cq, int Ck,
-                        int32_t *offsets_q, int32_t *offsets_k, int32_t *perm_q, int32_t *perm_k, bool copy,
-                        const void *Q, const void *K, const void *V, void *Qp, void *Kp, void *Vp, int dtype, int d,
-                        void *ws, hipStream_t st)
+// The permuted copies of a layer (Section 4.1: pi_q for Q, pi_k shared by K and V).
+int gather_pair_launch(const int32_t *perm_q, const int32_t *perm_k, int H, int N, const void *Q, const void *K,
+                       const void *V, void *Qp, void *Kp, void *Vp, int dtype, int d, hipStream_t st)
 {
-    SortArgs a = {};
-    a.s[0].labels = labels_q;
-    a.s[0].C = Cq;
-    a.s[0].hist = static_cast<int32_t *>(ws);
-    a.s[0].offsets = offsets_q;
-    a.s[0].perm = perm_q;
-    a.s[1].labels = labels_k;
-    a.s[1].C = Ck;
-    a.s[1].hist = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + permute_ws_bytes(H, N, Cq));
-    a.s[1].offsets = offsets_k;
-    a.s[1].perm = perm_k;
-    {
-        ProfileSpan sp(SVG2_K_PERMUTE_SORT, st);
-        SVG2_TRY(sort_launch(a, 2, H, N, st));
-    }
-    if (copy) {
-        ProfileSpan sp(SVG2_K_PERMUTE_GATHER, st);
-        const void *src_q[1] = {Q};
-        void *dst_q[1] = {Qp};
-        gather_launch(perm_q, H, N, 1, src_q, dst_q, dtype, d, st);
-        const void *src_k[2] = {K, V};
-        void *dst_k[2] = {Kp, Vp};
-        gather_launch(perm_k, H, N, 2, src_k, dst_k, dtype, d, st);
-    }
+    ProfileSpan sp(SVG2_K_PERMUTE_GATHER, st);
+    const void *src_q[1] = {Q};
+    void *dst_q[1] = {Qp};
+    gather_launch(perm_q, H, N, 1, src_q, dst_q, dtype, d, st);
+    const void *src_k[2] = {K, V};
+    void *dst_k[2] = {Kp, Vp};
+    gather_launch(perm_k, H, N, 2, src_k, dst_k, dtype, d, st);
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
 }
