@@ -7,6 +7,7 @@
 //   scatter  per (head, chunk): one wavefront walks its chunk in token order,
 //            ranking equal labels inside each group of 64 with ballots, so the
 //            order inside a cluster stays the original token order
+//   (short heads: all three in one workgroup per head, permute_sort_head_kernel)
 //   gather   dst[r,:] = src[perm[r],:], 16 bytes per lane, rows coalesced on
 //            the write side
 //
@@ -45,97 +46,171 @@ __global__ __launch_bounds__(256) void permute_hist_kernel(SortArgs a, int N, in
     for (int c = threadIdx.x; c < C; c += blockDim.x) out[c] = s_hist[c];
 }
 
-// One workgroup per head and side.  hist[h][k][c] becomes the first sorted row that
-// chunk k writes for cluster c.  The loads of a cluster's column are issued SCAN_UB at a time before they are
-// used, so the kernel waits for a few round trips to memory instead of one per chunk.
-// If the side asks for it (S.pieces), the kernel also cuts every cluster into pieces of at most S.seg sorted rows
-// (never crossing a cluster boundary) for the segmented sum of the k-means update step: pieces[h][first_piece[c] + t]
-// = (cluster, first row, rows, 0), first_piece[h][C] = n_pieces[h] = number of pieces of the head.
+static constexpr int SCAN_THREADS = 1024;
 static constexpr int SCAN_UB = 16;
 
-__global__ __launch_bounds__(256) void permute_scan_kernel(SortArgs a, int N, int nchunks)
+// Exclusive prefix sum over the workgroup's threads; *total = sum of all.
+__device__ __forceinline__ int scan_threads(int v, int32_t *s_wave, int *total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+    }
+    __syncthreads();                                    // s_wave of an earlier call has been read
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+        const int u = s_wave[w];
+        before += w < wave ? u : 0;
+        all += u;
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// s_tot[0 .. C): sizes of the clusters -> first sorted row of each; offsets[h] is written.  If the side asks for it
+// (S.pieces), every cluster is also cut into pieces of at most S.seg sorted rows (never crossing a cluster boundary) for
+// the segmented sum of the k-means update step: pieces[h][first_piece[c] + t] = (cluster, first row, rows, 0),
+// first_piece[h][C] = n_pieces[h] = number of pieces of the head.
+__device__ __forceinline__ void scan_clusters(const SortSide &S, int h, int N, int32_t *s_tot, int32_t *s_wave)
+{
+    const int tid = threadIdx.x, C = S.C, seg = S.seg;
+    int32_t *off = S.offsets + (size_t)h * (C + 1);
+    int carry = 0, carry_p = 0;
+    for (int cb = 0; cb < C; cb += SCAN_THREADS) {
+        const int c = cb + tid;
+        const int size = c < C ? s_tot[c] : 0;
+        int all;
+        const int start = carry + scan_threads(size, s_wave, &all);
+        carry += all;
+        if (c < C) {
+            s_tot[c] = start;
+            off[c] = start;
+        }
+        if (S.pieces == nullptr) continue;
+        const int np = (size + seg - 1) / seg;
+        const int first = carry_p + scan_threads(np, s_wave, &all);
+        carry_p += all;
+        if (c < C) S.first_piece[(size_t)h * (C + 1) + c] = first;
+        for (int t = 0; t < np; ++t)
+            S.pieces[(size_t)h * S.max_pieces + first + t] = make_int4(c, start + t * seg, min(seg, size - t * seg), 0);
+    }
+    if (tid == 0) {
+        off[C] = N;
+        if (S.pieces) {
+            S.first_piece[(size_t)h * (C + 1) + C] = carry_p;
+            S.n_pieces[h] = carry_p;
+        }
+    }
+    __syncthreads();
+}
+
+// One workgroup per head and side.  hist[h][k][c] becomes the first sorted row that chunk k writes for cluster c.  What
+// bounds it is the chain of round trips to memory: the chunks of a cluster are dealt out to as many threads as there
+// are (1024 over the clusters), SCAN_UB loads of a thread are issued before they are used.  (256 threads, each with all
+// chunks of its clusters: 22 instead of 13 us at 40 heads of 75,600 tokens in 100 and 500 clusters, 24 instead of 12 us on
+// average over 8 heads of 37,800 in 100 and in 2000.)
+__global__ __launch_bounds__(SCAN_THREADS) void permute_scan_kernel(SortArgs a, int N, int nchunks)
 {
     extern __shared__ int32_t s_tot[];                 // [C] totals, then exclusive offsets
-    __shared__ int32_t s_part[256];
-    __shared__ int32_t s_wave[4];
-    __shared__ int32_t s_carry;
+    __shared__ int32_t s_part[SCAN_THREADS];
+    __shared__ int32_t s_wave[SCAN_THREADS / 64];
     const SortSide S = blockIdx.z ? a.s[1] : a.s[0];      // (a select of scalars, not an indexed copy)
     const int h = blockIdx.x, tid = threadIdx.x, C = S.C;
     int32_t *hh = S.hist + (size_t)h * nchunks * C;
-    for (int c = tid; c < C; c += 256) {
+    int cw = SCAN_THREADS;                              // clusters side by side; the threads form SCAN_THREADS / cw parts
+    while (cw > 64 && cw / 2 >= C) cw >>= 1;
+    const int parts = SCAN_THREADS / cw, part = tid / cw, cl = tid & (cw - 1);
+    const int per = (nchunks + parts - 1) / parts, k_lo = min(nchunks, part * per), k_hi = min(nchunks, k_lo + per);
+    for (int cb = 0; cb < C; cb += cw) {                // (more than one pass only with parts = 1)
+        const int c = cb + cl;
         int run = 0;
-        for (int k0 = 0; k0 < nchunks; k0 += SCAN_UB) {
-            int v[SCAN_UB];
+        if (c < C)
+            for (int k0 = k_lo; k0 < k_hi; k0 += SCAN_UB) {
+                int v[SCAN_UB];
 #pragma unroll
-            for (int u = 0; u < SCAN_UB; ++u) v[u] = (k0 + u < nchunks) ? hh[(size_t)(k0 + u) * C + c] : 0;
+                for (int u = 0; u < SCAN_UB; ++u) v[u] = (k0 + u < k_hi) ? hh[(size_t)(k0 + u) * C + c] : 0;
 #pragma unroll
-            for (int u = 0; u < SCAN_UB; ++u) run += v[u];
+                for (int u = 0; u < SCAN_UB; ++u) run += v[u];
+            }
+        s_part[tid] = run;
+        __syncthreads();
+        if (part == 0 && c < C) {
+            for (int q = 1; q < parts; ++q) run += s_part[q * cw + cl];
+            s_tot[c] = run;
         }
-        s_tot[c] = run;
+        if (cb + cw < C) __syncthreads();
     }
     __syncthreads();
-    // exclusive scan of s_tot over c: each thread owns a contiguous slice
-    const int per = (C + 255) / 256;
-    const int c0 = min(C, tid * per), c1 = min(C, c0 + per);
-    int sum = 0;
-    for (int c = c0; c < c1; ++c) sum += s_tot[c];
-    s_part[tid] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) { int v = s_part[t]; s_part[t] = run; run += v; }
-    }
-    __syncthreads();
-    int run = s_part[tid];
-    for (int c = c0; c < c1; ++c) { int v = s_tot[c]; s_tot[c] = run; run += v; }
-    __syncthreads();
-    int32_t *off = S.offsets + (size_t)h * (C + 1);
-    for (int c = tid; c < C; c += 256) {
+    scan_clusters(S, h, N, s_tot, s_wave);
+    for (int cb = 0; cb < C; cb += cw) {
+        const int c = cb + cl;
+        if (c >= C) break;
         int pos = s_tot[c];
-        off[c] = pos;
-        for (int k0 = 0; k0 < nchunks; k0 += SCAN_UB) {
+        for (int q = 0; q < part; ++q) pos += s_part[q * cw + cl];
+        for (int k0 = k_lo; k0 < k_hi; k0 += SCAN_UB) {
             int v[SCAN_UB];
 #pragma unroll
-            for (int u = 0; u < SCAN_UB; ++u) v[u] = (k0 + u < nchunks) ? hh[(size_t)(k0 + u) * C + c] : 0;
+            for (int u = 0; u < SCAN_UB; ++u) v[u] = (k0 + u < k_hi) ? hh[(size_t)(k0 + u) * C + c] : 0;
 #pragma unroll
             for (int u = 0; u < SCAN_UB; ++u) {
-                if (k0 + u < nchunks) hh[(size_t)(k0 + u) * C + c] = pos;
+                if (k0 + u < k_hi) hh[(size_t)(k0 + u) * C + c] = pos;
                 pos += v[u];
             }
         }
     }
-    if (tid == 0) off[C] = N;
-    if (S.pieces == nullptr) return;
+}
 
-    // pieces of the segmented sum: running count over the clusters, 256 clusters per pass
-    const int seg = S.seg, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int cb = 0; cb < C; cb += 256) {
-        const int c = cb + tid;
-        const int start = (c < C) ? s_tot[c] : 0;
-        const int size = (c < C) ? ((c + 1 < C) ? s_tot[c + 1] : N) - start : 0;
-        const int np = (size + seg - 1) / seg;
-        int incl = np;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
+// Stable ranks of one chunk: a wavefront walks it in token order, 64 tokens at a time; lr[] holds the labels of the
+// chunk, s_cur[c] the next free sorted row of cluster c (of this chunk alone).
+__device__ __forceinline__ void scatter_chunk(const int (&lr)[PERM_CHUNK / 64], int n0, int n1, int nbits, int32_t *s_cur,
+                                              int32_t *__restrict__ pm, int32_t *__restrict__ ip)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int i = 0; i < PERM_CHUNK / 64; ++i) {
+        const int g = n0 + i * 64;
+        if (g >= n1) break;
+        const int n = g + lane;
+        const bool valid = n < n1;
+        const int l = lr[i];
+        // lanes holding the same label as this one (what bounds the kernel: four vector instructions per bit and group)
+        const unsigned long long live = __ballot(valid);
+        unsigned lo = (unsigned)live, hi = (unsigned)(live >> 32);
+        for (int b = 0; b < nbits; ++b) {
+            const unsigned bit = (unsigned)__builtin_amdgcn_sbfe(l, b, 1);      // 0 or all ones
+            const unsigned long long m = __ballot(bit != 0);
+            lo &= ~((unsigned)m ^ bit);
+            hi &= ~((unsigned)(m >> 32) ^ bit);
         }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        int base = s_carry;
-        for (int w = 0; w < wave; ++w) base += s_wave[w];
-        const int first = base + incl - np;
-        if (c < C) S.first_piece[(size_t)h * (C + 1) + c] = first;
-        for (int t = 0; t < np; ++t)
-            S.pieces[(size_t)h * S.max_pieces + first + t] = make_int4(c, start + t * seg, min(seg, size - t * seg), 0);
-        __syncthreads();
-        if (tid == 255) s_carry = base + incl;
-        __syncthreads();
+        const unsigned long long peers = (unsigned long long)hi << 32 | lo;
+        if (valid) {
+            const int pos = s_cur[l] + __popcll(peers & lt_mask);
+            pm[pos] = n;
+            if (ip) ip[n] = pos;
+        }
+        // the first lane of every peer group advances that cluster's cursor; LDS operations of one wavefront complete in
+        // order, so it is enough that the compiler keeps theirs
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers & lt_mask) == 0) s_cur[l] += __popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
-    if (tid == 0) {
-        S.first_piece[(size_t)h * (C + 1) + C] = s_carry;
-        S.n_pieces[h] = s_carry;
+}
+
+__device__ __forceinline__ void load_chunk_labels(int (&lr)[PERM_CHUNK / 64], const int32_t *lab, int n0, int n1)
+{
+    // all labels of the chunk are requested up front (one memory round trip instead of one per group of 64)
+#pragma unroll
+    for (int i = 0; i < PERM_CHUNK / 64; ++i) {
+        const int n = n0 + i * 64 + (threadIdx.x & 63);
+        lr[i] = (n < n1) ? lab[n] : 0;
     }
 }
 
@@ -143,49 +218,56 @@ __global__ __launch_bounds__(64) void permute_scatter_kernel(SortArgs a, int N, 
 {
     extern __shared__ int32_t s_cur[];                 // [C] next free sorted row per cluster
     const SortSide S = blockIdx.z ? a.s[1] : a.s[0];      // (a select of scalars, not an indexed copy)
-    const int chunk = blockIdx.x, h = blockIdx.y, lane = threadIdx.x, C = S.C, nbits = S.nbits;
+    const int chunk = blockIdx.x, h = blockIdx.y, lane = threadIdx.x, C = S.C;
     const int32_t *base = S.hist + ((size_t)h * nchunks + chunk) * C;
+    const int n0 = chunk * PERM_CHUNK, n1 = min(N, n0 + PERM_CHUNK);
+    int lr[PERM_CHUNK / 64];
+    load_chunk_labels(lr, S.labels + (size_t)h * N, n0, n1);
     for (int c = lane; c < C; c += 64) s_cur[c] = base[c];
     __syncthreads();
-    const int32_t *lab = S.labels + (size_t)h * N;
-    int32_t *pm = S.perm + (size_t)h * N;
-    int32_t *ip = S.inv_perm ? S.inv_perm + (size_t)h * N : nullptr;
-    const int n0 = chunk * PERM_CHUNK;
-    const int n1 = min(N, n0 + PERM_CHUNK);
-    const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // all labels of the chunk are requested up front (one memory round trip instead of one per group of 64)
-    constexpr int NG = PERM_CHUNK / 64;
-    int lr[NG];
+    scatter_chunk(lr, n0, n1, S.nbits, s_cur, S.perm + (size_t)h * N, S.inv_perm ? S.inv_perm + (size_t)h * N : nullptr);
+}
+
+// The whole sort of a head in one workgroup, for heads of at most 16 wavefronts x 1024 tokens whose histograms fit
+// SORT1_LDS: wavefront w counts, ranks and scatters chunk w (`chunk` tokens, as few as give every wavefront one), the
+// histograms and their scan stay in LDS.  Three launches that each wait for a few round trips to memory become one:
+// 2 heads of 1024 tokens in 16 and 32 clusters 17 -> 5.4 us, 24 heads of 16,384 in 100 and 500 29 -> 19 us.
+// With more tokens the heads alone do not fill the chip and the three kernels spread better.
+static constexpr int SORT1_WAVES = SCAN_THREADS / 64;
+static constexpr size_t SORT1_LDS = 60 * 1024;
+
+__global__ __launch_bounds__(SCAN_THREADS) void permute_sort_head_kernel(SortArgs a, int N, int chunk, int nchunks)
+{
+    extern __shared__ int32_t s_hist[];                // [nchunks + 1][C], the last row the totals
+    __shared__ int32_t s_wave[SCAN_THREADS / 64];
+    const SortSide S = blockIdx.z ? a.s[1] : a.s[0];      // (a select of scalars, not an indexed copy)
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, C = S.C;
+    const int n0 = wave * chunk, n1 = min(N, n0 + chunk);       // (a wavefront past the last chunk: n1 <= n0)
+    int32_t *s_tot = s_hist + (size_t)nchunks * C, *s_own = s_hist + (size_t)wave * C;
+    int lr[PERM_CHUNK / 64];
+    load_chunk_labels(lr, S.labels + (size_t)h * N, n0, n1);
+    for (int e = tid; e < nchunks * C; e += SCAN_THREADS) s_hist[e] = 0;
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NG; ++i) {
-        const int n = n0 + i * 64 + lane;
-        lr[i] = (n < n1) ? lab[n] : 0;
-    }
-#pragma unroll
-    for (int i = 0; i < NG; ++i) {
-        const int g = n0 + i * 64;
-        if (g >= n1) break;
-        const int n = g + lane;
-        const bool valid = n < n1;
-        const int l = lr[i];
-        // lanes holding the same label as this one
-        unsigned long long peers = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            const bool bit = (l >> b) & 1;
-            const unsigned long long m = __ballot(bit);
-            peers &= bit ? m : ~m;
+    for (int i = 0; i < PERM_CHUNK / 64; ++i)
+        if (n0 + i * 64 + lane < n1) atomicAdd(&s_own[lr[i]], 1);
+    __syncthreads();
+    for (int c = tid; c < C; c += SCAN_THREADS) {
+        int run = 0;
+        for (int k = 0; k < nchunks; ++k) {
+            const int v = s_hist[k * C + c];
+            s_hist[k * C + c] = run;
+            run += v;
         }
-        int pos = 0;
-        if (valid) {
-            pos = s_cur[l] + __popcll(peers & lt_mask);
-            pm[pos] = n;
-            if (ip) ip[n] = pos;
-        }
-        __syncthreads();
-        // the first lane of every peer group advances that cluster's cursor
-        if (valid && (peers & lt_mask) == 0) s_cur[l] += __popcll(peers);
-        __syncthreads();
+        s_tot[c] = run;
     }
+    __syncthreads();
+    scan_clusters(S, h, N, s_tot, s_wave);
+    if (n0 >= n1) return;
+    for (int c = lane; c < C; c += 64) s_own[c] += s_tot[c];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    scatter_chunk(lr, n0, n1, S.nbits, s_own, S.perm + (size_t)h * N, S.inv_perm ? S.inv_perm + (size_t)h * N : nullptr);
 }
 
 // dst[h, r, :] = src[h, perm[h, r], :] for up to two tensors; a row is
@@ -218,7 +300,8 @@ size_t permute_ws_bytes(int H, int N, int C)
     return align256((size_t)H * nchunks * C * sizeof(int32_t));
 }
 
-// The counting sort of one or two sides (labels -> offsets, perm, inv_perm; pieces if asked for): three launches.
+// The counting sort of one or two sides (labels -> offsets, perm, inv_perm; pieces if asked for): one
+// launch or three.
 // The caller fills labels, C, hist, offsets, perm, inv_perm and the piece fields of every side; nbits is set here.
 int sort_launch(SortArgs a, int nsides, int H, int N, hipStream_t st)
 {
@@ -231,8 +314,17 @@ int sort_launch(SortArgs a, int nsides, int H, int N, hipStream_t st)
         cmax = std::max(cmax, a.s[s].C);
     }
     const size_t lds = (size_t)cmax * sizeof(int32_t);
+    // one workgroup per head, if the histograms of as many wavefronts as the tokens need fit its LDS
+    const int waves = std::min<int>(SORT1_WAVES, (int)(SORT1_LDS / lds) - 1), groups = cdiv(N, 64);
+    if (waves >= 1 && cdiv(groups, waves) * 64 <= PERM_CHUNK) {
+        const int chunk = cdiv(groups, waves) * 64, nch = cdiv(N, chunk);
+        hipLaunchKernelGGL(permute_sort_head_kernel, dim3(H, 1, nsides), dim3(SCAN_THREADS), (nch + 1) * lds, st, a, N, chunk,
+                           nch);
+        SVG2_HIP_CHECK(hipGetLastError());
+        return SVG2_OK;
+    }
     hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks, H, nsides), dim3(256), lds, st, a, N, nchunks);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(H, 1, nsides), dim3(256), lds, st, a, N, nchunks);
+    hipLaunchKernelGGL(permute_scan_kernel, dim3(H, 1, nsides), dim3(SCAN_THREADS), lds, st, a, N, nchunks);
     hipLaunchKernelGGL(permute_scatter_kernel, dim3(nchunks, H, nsides), dim3(64), lds, st, a, N, nchunks);
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;

@@ -64,6 +64,24 @@ def test_permute_bit_exact(svg2, oracle, H, N, C, dtype, d):
     assert torch.equal(res2.perm, res.perm) and torch.equal(res2.offsets, res.offsets)
 
 
+@pytest.mark.parametrize("H,N,C", [
+    # one workgroup per head: 1 to 16 wavefronts, the last one with 1 .. 64 tokens, up to what its LDS holds
+    (1, 63, 5), (3, 65, 7), (2, 1023, 100), (2, 1025, 33), (1, 16384, 900), (1, 15000, 959), (1, 2000, 4096 - 96),
+    # three kernels: too long, or too many clusters
+    (2, 16385, 500), (1, 16384, 1000), (1, 4096, 4096), (2, 33000, 4096), (1, 40000, 1025), (1, 70000, 64), (2, 20000, 1)])
+def test_permute_sort_routes(svg2, oracle, H, N, C):
+    r = np.random.default_rng(150 + N)
+    labels = r.integers(0, C, size=(H, N)).astype(np.int32)
+    labels[:, N // 3: N // 2] = C // 2          # a long stretch of one label
+    res = svg2.svg2_permute(to_dev(labels), C, [])
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = oracle.permute(labels[h], C)
+        np.testing.assert_array_equal(to_np(res.offsets[h]), ref.offsets)
+        np.testing.assert_array_equal(to_np(res.perm[h]), ref.perm)
+        np.testing.assert_array_equal(to_np(res.inv_perm[h]), ref.inv_perm)
+
+
 # ------------------------------------------------------------------ selection
 
 def _check_select(oracle, res, cq, ck, counts_q, counts_k, p, H):
