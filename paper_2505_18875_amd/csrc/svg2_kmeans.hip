@@ -317,13 +317,20 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
 #define KM_PIN(X)
     // this workgroup's part of the block sequence, the same for both sides
     const int part_q = nb_all / (int)gridDim.x, part_r = nb_all % (int)gridDim.x;
-    const int part_lo = (int)blockIdx.x * part_q + min((int)blockIdx.x, part_r);
-    const int part_hi = part_lo + part_q + ((int)blockIdx.x < part_r ? 1 : 0);
+    int part_lo = (int)blockIdx.x * part_q + min((int)blockIdx.x, part_r);
+    int part_hi = part_lo + part_q + ((int)blockIdx.x < part_r ? 1 : 0);
+    // at most as many blocks as CUs over both sides: one block of one side per workgroup (2 heads of 1024 tokens, D = 64:
+    // 13.4 us with both sides of a block one after the other in one workgroup and all 512 rows staged, 8.3 us now)
+    const bool one_block = (int)gridDim.x == a.nsides * nb_all;
+    if (one_block) {
+        part_lo = (int)blockIdx.x % nb_all;
+        part_hi = part_lo + 1;
+    }
 #pragma unroll 1
-    for (int sd = 0; sd < a.nsides; ++sd) {
+    for (int sd = one_block ? (int)blockIdx.x / nb_all : 0; sd < a.nsides; sd = one_block ? a.nsides : sd + 1) {
     // odd workgroups start with the first side, even ones with the second: while one half of the CUs is on the Q
     // tokens of a layer (few centroids, waits for memory) the other is on the K tokens (many, matrix cores)
-    const int side = (blockIdx.x & 1) ? sd : a.nsides - 1 - sd;
+    const int side = one_block || (blockIdx.x & 1) ? sd : a.nsides - 1 - sd;
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
     const int C = S.C;
@@ -378,32 +385,36 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
         // starts at another row, so that the workgroups of a head that run side by side do not ask the same L2
         // channel for the same line at the same moment.
         {
-            constexpr int PER = KM_CMAX * (D / 8) / (64 * KM_NW), HALF = PER;
-            static_assert((KM_CMAX & (KM_CMAX - 1)) == 0, "row rotation wraps with a mask");
-            const int rot = (int)(blockIdx.x * 37u) & (KM_CMAX - 1);
+            constexpr int PER = KM_CMAX * (D / 8) / (64 * KM_NW);
             // the addresses are formed here, in every chunk: formed once in front of the chunk loop (where the
             // compiler would move them) they would sit in scratch memory while the token blocks are computed
             int tid_o = tid;
             asm volatile("" : "+v"(tid_o));
+            auto stage = [&](auto nv_tag) {
+                constexpr int NV = decltype(nv_tag)::value, ROWS = NV * 64 * KM_NW / (D / 8);
+                static_assert((ROWS & (ROWS - 1)) == 0, "row rotation wraps with a mask");
+                const int rot = (int)(blockIdx.x * 37u);
+                uint4 v[NV];
 #pragma unroll
-            for (int i0 = 0; i0 < PER; i0 += HALF) {
-                uint4 v[HALF];
-#pragma unroll
-                for (int i = 0; i < HALF; ++i) {
-                    const int e = tid_o + (i0 + i) * 64 * KM_NW, r = ((e / (D / 8)) + rot) & (KM_CMAX - 1);
+                for (int i = 0; i < NV; ++i) {
+                    const int e = tid_o + i * 64 * KM_NW, r = ((e / (D / 8)) + rot) & (ROWS - 1);
                     v[i] = reinterpret_cast<const uint4 *>(cbh + (size_t)(c0 + min(r, cc - 1)) * D)[e % (D / 8)];
                 }
                 // in the same round trip: this thread's -||c||^2/2 and the wavefront's first block of tokens
                 const float hv = hcnh[c0 + min(tid_o, cc - 1)];
                 load_x(std::integral_constant<int, 0>{}, wave);
 #pragma unroll
-                for (int i = 0; i < HALF; ++i) {
-                    const int e = tid_o + (i0 + i) * 64 * KM_NW, r = ((e / (D / 8)) + rot) & (KM_CMAX - 1);
+                for (int i = 0; i < NV; ++i) {
+                    const int e = tid_o + i * 64 * KM_NW, r = ((e / (D / 8)) + rot) & (ROWS - 1);
                     if (r >= cc) v[i] = make_uint4(0, 0, 0, 0);
                     *reinterpret_cast<uint4 *>(&s_c[r * ROW + (e % (D / 8)) * 8]) = v[i];
                 }
                 s_hcn[tid] = tid < cc ? hv : KM_PAD_HCN;
-            }
+            };
+            // few centroids: a quarter of the rows is all there is to stage (at D = 128 a second form costs registers
+            // that the step loop does not have)
+            if (D == 64 && ccp <= KM_CMAX / 4) stage(std::integral_constant<int, PER / 4>{});
+            else stage(std::integral_constant<int, PER>{});
         }
         __syncthreads();
         {
@@ -1058,7 +1069,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
         if (BF16) {
             const long long nb_all = (long long)H * cdiv(N, KM_WG_TOKENS);
-            const dim3 grid((unsigned)std::min<long long>(ncu, nb_all));
+            // a block of one side per workgroup while there are CUs enough for that, else a share of both sides
+            const dim3 grid((unsigned)(ns * nb_all <= ncu ? ns * nb_all : std::min<long long>(ncu, nb_all)));
             auto kern = any_obj ? kmeans_assign_bf16_kernel<D, true> : kmeans_assign_bf16_kernel<D, false>;
             {
                 ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);
