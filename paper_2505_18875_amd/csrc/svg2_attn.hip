@@ -746,11 +746,14 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
 }
 
 // ---------------------------------------------------------------- fp32 kernel
-// grid (max_tiles, H), block 64 * F32_NW.  A work item is 32 consecutive rows of one query cluster; its key sequence is
+// grid (tile list), block 64 * F32_NW.  A work item is 32 consecutive rows of one query cluster; its key sequence is
 // cut into blocks of 32 keys which the wavefronts take in turn (wavefront w: blocks w, w + F32_NW, ..), each with its own
 // running softmax over its share of the keys; the shares are put together through LDS at the end.  So a short layer
 // (one head of 4096 tokens is 128 work items) still puts work on 512 SIMDs, and no wavefront waits for another
-// before the end.
+// before the end.  The list runs longest first: 1400 work items of very different lengths on 256 CUs in head-major order
+// left the last third of the launch half empty (4 heads of 9601 tokens, d = 128: 0.80 ms, 0.66 ms in this order).  Eight
+// wavefronts share a work item rather than four for the small layers, where a CU has one at most (one head of 4096 tokens,
+// d = 64: 31 instead of 35 us).
 //
 // Matrix instruction 32x32x2 (fp32 in, fp32 out: the products and sums of the definition, at twice the rate of the
 // vector ALU; 64 cycles each).  S^T = K Q^T: a lane supplies key `col`, and its half of d is the half of the row the
@@ -763,18 +766,20 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_bf16_kernel(
 // Nothing is staged in LDS: a 32-key block is 128 matrix instructions (8192 cycles, d = 128) and 32 loads of 1 KB per
 // wavefront, so the loads hide behind the arithmetic with two register buffers that take turns (A: first halves of K
 // and of V, B: second halves).  One query per thread with K and V in LDS (64 queries per wavefront, one wavefront per
-// workgroup) took 13.8 instead of 0.80 ms for 4 heads of 9601 tokens at d = 128 (31 % selected: 58 GFLOP, so 72 of the
-// 154 TFLOP/s a large fp32 product reaches), and 760 instead of 37 us for one head of 4096 tokens at d = 64.
-static constexpr int F32_NW = 4;
+// workgroup) took 13.8 instead of 0.66 ms for 4 heads of 9601 tokens at d = 128 (31 % selected: 58 GFLOP, so 88 of the
+// 154 TFLOP/s a large fp32 product reaches; a seventh of the rows of the 32-row tiles is padding), and 760 instead of
+// 31 us for one head of 4096 tokens at d = 64.  K rows through LDS (whole rows, direct loads, read back by row) instead of
+// 16 bytes of a row of its own per lane: 0.88 instead of 0.81 ms, so it is not these loads that bound it.
+static constexpr int F32_NW = 8;
 static constexpr int F32_BM = 32;
 
 template <int D>
 __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
-    const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int N, int Cq, int Ck,
+    const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int Cq, int Ck,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
-    const int4 *__restrict__ tiles, const int32_t *__restrict__ n_tiles, int max_tiles,
+    const int4 *__restrict__ tiles, const int32_t *__restrict__ tile_base, const int32_t *__restrict__ order, int max_tiles,
     const int2 *__restrict__ runs, const int32_t *__restrict__ row_keys, const int32_t *__restrict__ tile_run,
-    int key_tiles, float scale_log2, float *__restrict__ O, float *__restrict__ lse)
+    int key_tiles, float scale_log2, int group, float *__restrict__ O, float *__restrict__ lse)
 {
     constexpr int DVB = D / 32;                 // output blocks of 32 columns
     constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's share of K or V
@@ -783,9 +788,15 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     typedef float fvec __attribute__((ext_vector_type(DVB)));
     extern __shared__ __align__(16) float s_o[];        // [F32_NW][32][ROW]
     __shared__ float s_m[F32_NW][32], s_l[F32_NW][32];
-    const int h = blockIdx.y, t = blockIdx.x, tid = threadIdx.x;
-    if (t >= n_tiles[h]) return;
-    const int4 desc = tiles[(size_t)h * max_tiles + t];
+    // the list of all heads' tiles, longest first, handed out in groups of `group` per XCD (as in the bf16 kernel)
+    const int tid = threadIdx.x, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int pos = (slot / group) * (8 * group) + xcd * group + slot % group;
+    if (pos >= tile_base[H]) return;
+    const int v = order[pos];
+    int h = 0;
+    for (int step = 1 << 15; step > 0; step >>= 1)
+        if (h + step < H && tile_base[h + step] <= v) h += step;
+    const int4 desc = tiles[(size_t)h * max_tiles + (v - tile_base[h])];
     const int ci = desc.x, row0 = desc.y, nrows = desc.z;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
@@ -999,9 +1010,8 @@ int attn_plan_launch(int dtype, int H, int N, int Cq, int Ck, const int32_t *off
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + cdiv(Cq, 4), H), dim3(256), 0, st, offsets_q, offsets_k, row_ptr, col_idx,
                        Cq, Ck, attn_bm(dtype), a.max_tiles, a.tiles, a.n_tiles, a.runs, a.row_keys, a.cl_first,
                        a.key_tiles, a.tile_run);
-    if (dtype == SVG2_BF16)                     // the fp32 kernel is launched on a (tile, head) grid and needs no list
-        hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(1024), 0, st, offsets_q, a.n_tiles, a.tile_base, a.row_keys,
-                           a.cl_first, H, Cq, attn_bm(dtype), a.order);
+    hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(1024), 0, st, offsets_q, a.n_tiles, a.tile_base, a.row_keys,
+                       a.cl_first, H, Cq, attn_bm(dtype), a.order);
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
 }
@@ -1013,15 +1023,14 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
     const AttnWs a = attn_carve(ws, dtype, H, N, Cq, Ck);
     const int max_tiles = a.max_tiles;
     int4 *tiles = a.tiles;
-    int32_t *n_tiles = a.n_tiles;
     int32_t *tile_base = a.tile_base;
     int2 *runs = a.runs;
     int32_t *row_keys = a.row_keys;
     if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)d);
+    const int total = H * max_tiles;
+    const int group = ATT_GROUP;
+    const int nwg = cdiv(total, 8 * group) * 8 * group;
     if (dtype == SVG2_BF16) {
-        const int total = H * max_tiles;
-        const int group = ATT_GROUP;
-        const int nwg = cdiv(total, 8 * group) * 8 * group;
         const float scale_log2 = scale * 1.4426950408889634f;
         const bf16_t *q = static_cast<const bf16_t *>(Qp), *k = static_cast<const bf16_t *>(Kp),
                      *v = static_cast<const bf16_t *>(Vp);
@@ -1038,9 +1047,9 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
         float *o = static_cast<float *>(O);
         static_assert(F32_BM == attn_bm(SVG2_F32), "the plan cuts query clusters into the tiles of this kernel");
         auto kern = d == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>;
-        hipLaunchKernelGGL(kern, dim3(max_tiles, H), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, N, Cq, Ck,
-                           row_ptr, perm_q, perm_k, tiles, n_tiles, max_tiles, runs, row_keys, a.tile_run, a.key_tiles,
-                           scale * 1.4426950408889634f, o, lse);
+        hipLaunchKernelGGL(kern, dim3(nwg), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, H, N, Cq, Ck,
+                           row_ptr, perm_q, perm_k, tiles, tile_base, a.order, max_tiles, runs, row_keys, a.tile_run,
+                           a.key_tiles, scale * 1.4426950408889634f, group, o, lse);
     }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
