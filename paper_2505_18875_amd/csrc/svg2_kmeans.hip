@@ -93,6 +93,7 @@ struct KmSide {
 struct KmArgs {
     KmSide s[2];
     int nsides, H, N, iters;
+    int nc[2];                  // wavefronts that share a token block (fp32 assign)
 };
 
 // labels written / read by iteration t
@@ -742,9 +743,9 @@ __global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
 // The instruction is slow enough (a row block of 32 centroids is D/2 of them, 4096 cycles at D = 128) that the
 // centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
 // register buffers that take turns.  What decides is how many SIMDs have work, so the row blocks of a token block are
-// dealt out to up to four wavefronts (KF_NW / nc token blocks per workgroup, nc wavefronts each, nc as many as there are
-// row blocks) and the shares compared through LDS.  One token per thread with the centroids in LDS (300 workgroups
-// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 100 us per iteration for 4 heads of
+// dealt out to up to four wavefronts (KF_NW / nc token blocks per workgroup, nc wavefronts each, kmeans_f32_share) and the
+// shares compared through LDS.  One token per thread with the centroids in LDS (300 workgroups
+// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 96 us per iteration for 4 heads of
 // 9601 tokens against 100 and 500 centroids at D = 128 (5.9 GFLOP), and 28 instead of 5.4 us for one head of 4096 against
 // 16 and 32 at D = 64.
 static constexpr int KF_NW = 4;
@@ -763,10 +764,10 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
     const int nrb = (C + 31) / 32;
-    const int nc = nrb >= 3 ? 4 : nrb;          // wavefronts that share a token block
+    const int nc = KM_SEL(a.nc, side);
     const int wc = wave % nc, wt = wave / nc;
     const int wg_tok0 = (int)blockIdx.x * (KF_NW / nc) * 32;
-    if (wg_tok0 >= N) return;                   // the grid is sized for nc = 4
+    if (wg_tok0 >= N) return;                   // the grid is sized for the larger nc
     const int n0 = wg_tok0 + wt * 32, n = n0 + col;
 
     float x[D / 2];                             // x[s]: element 2 s + half of the token
@@ -1031,16 +1032,31 @@ static int device_cu_count(int *ncu)
     return SVG2_OK;
 }
 
+// Wavefronts that share a token block of the fp32 assign step: every one of them loads the tokens, so a share has at
+// least four row blocks where the token blocks alone are enough for two wavefronts per SIMD, and as few as one otherwise.
+// (One share per row block, up to four, whatever the number of token blocks:
+// 100 instead of 96 us per iteration for 4 heads of 9601 tokens against 100 and 500 centroids at D = 128.)
+static int kmeans_f32_share(int H, int N, int C)
+{
+    const int nrb = cdiv(C, 32);
+    const long long blocks = (long long)H * cdiv(N, 32);
+    int nc = 1;
+    while (nc < KF_NW && 2 * nc <= nrb && (nrb > 4 * nc || blocks * nc < 2048)) nc *= 2;
+    return nc;
+}
+
 template <typename T, int D, bool BF16>
 static int kmeans_run(KmArgs a, hipStream_t st)
 {
     const int H = a.H, N = a.N, iters = a.iters, ns = a.nsides;
     int ncu = 0;
     if (BF16) SVG2_TRY(device_cu_count(&ncu));
-    int call = 0, pmax = 0;
+    int call = 0, pmax = 0, ncmax = 1;
     bool any_obj = false;
     for (int s = 0; s < ns; ++s) {
         call += a.s[s].C;
+        a.nc[s] = kmeans_f32_share(H, N, a.s[s].C);
+        ncmax = std::max(ncmax, a.nc[s]);
         pmax = std::max(pmax, a.s[s].max_pieces);
         if (a.s[s].objective) {
             any_obj = true;
@@ -1083,7 +1099,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         } else {
             ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);
             auto kern = any_obj ? kmeans_assign_f32_kernel<D, true> : kmeans_assign_f32_kernel<D, false>;
-            hipLaunchKernelGGL(kern, dim3(cdiv(N, 32), H, ns), dim3(64 * KF_NW), 0, st, a, it);
+            hipLaunchKernelGGL(kern, dim3(cdiv(N, 32 * (KF_NW / ncmax)), H, ns), dim3(64 * KF_NW), 0, st, a, it);
         }
         // label-sorted order of the tokens and its pieces, then the segmented sum over it
         SortArgs sa = {};
