@@ -44,7 +44,9 @@ static constexpr int KM_WG_TOKENS = KM_NW * KM_TB * 32;
 static constexpr int KM_UB = 4;        // load instructions in flight per wavefront in the segmented sum
 static constexpr int KM_SEG = 256;     // rows per piece of the segmented sum
 static constexpr int KM_FULL_EVERY = 16; // iterations between updates that sum every cluster afresh (the others move the changed tokens)
-static constexpr int KM_SETTLE_BLOCKS = 64;  // workgroups per head and side that walk the list of near-ties
+// Workgroups per head and side that walk the list of near-ties: about as many as run at once (5 per CU) in the launch,
+// within these limits (24 heads of 16,384 tokens: 12.5 us with 64, 8.9 with 26; 40 of 75,600: 23 with 64, 26 with 16).
+static constexpr int KM_SETTLE_BLOCKS = 64, KM_SETTLE_MIN = 32, KM_SETTLE_WG = 1280;
 // A token is settled in double precision when the gap between its two best keys is at most
 //     KM_TIE_KEY * |best key|  +  KM_TIE_ACC * (||x||^2 / 2 + max_j ||c_j||^2).
 // First term: the 4 mantissa bits given to the position move a key by less than 16 units in its last place,
@@ -665,19 +667,33 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
 }
 
 // ---------------------------------------------------------------- settle near-ties, bf16 input
-// grid (KM_SETTLE_BLOCKS, H * sides), block 256: one workgroup per listed token at a time.  The token's distance
-// ||c_j||^2 - 2 x.c_j to EVERY centroid in double precision: wavefront w takes the centroid groups
-// 64 (w + 4 i) .. + 64, lane l of it centroid l of the group (read from the chunk-major copy, so the 64 lanes of a
-// load read 1 KB of consecutive memory); smallest distance wins, lowest index on an exact tie.  x and c are bf16
-// numbers: every product is exact and the sums of 128 of them fit a double, so this is the argmin of the
-// definition.  A token costs a wavefront a few thousand double-precision instructions, which is why the four
-// wavefronts share it: what the launch takes is the time of ONE token (a head lists a few dozen).
+// grid (workgroups per head and side, H * sides), block 256: one workgroup per listed token at a time.  The argmin of the distance
+// ||c_j||^2 - 2 x.c_j over EVERY centroid in double precision, lowest index on an exact tie.  x and c are bf16 numbers:
+// every product is exact and the sums of 128 of them fit a double in any order, so this is the argmin of the definition.
+//
+// What the launch takes is the time of ONE token (a head lists a few dozen), so the token is first compared with all
+// centroids in fp32 (wavefront w takes the centroid groups 64 (w + 4 i) .. + 64, lane l of it centroid l of the group,
+// read from the chunk-major copy so that the 64 lanes of a load read 1 KB of consecutive memory; two products per
+// instruction), and only the centroids within the error of that are measured in double: a few one after the other by all
+// lanes of the wavefront, more of them in one group (many equal centroids) one per lane.  With every centroid measured in
+// double, a few thousand instructions per group, the launch took 20 instead of 9 us at 24 heads of 16,384 tokens (100 and
+// 500 centroids), 27 instead of 12 us on average over 8 heads of 37,800 in 100 and in 2000.
+//
+// Error of the fp32 value x.c - ||c||^2 / 2: D / 2 steps with at most two roundings each of partial sums below ||x||^2 / 2 +
+// ||c||^2, below 2^-17 of that at D = 128; two values are compared, and the margin is twice what that makes.
+static constexpr float KM_SETTLE_MARGIN = 3.0517578125e-05f;  // 2^-15
+static constexpr int KM_SETTLE_FEW = 4;
+
 template <int D>
-__global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
+__global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter it)
 {
     __shared__ __align__(16) double s_x[D];
+    __shared__ __align__(16) bf16_t s_xb[D];
+    __shared__ float s_v[SVG2_MAX_CLUSTERS];
+    __shared__ float s_top[4], s_cmax[4];
     __shared__ double s_best[4];
     __shared__ int s_bj[4];
+    constexpr int EL = D / 64;
     const int side = blockIdx.y % a.nsides, h = blockIdx.y / a.nsides;
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
@@ -686,36 +702,96 @@ __global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
     const int cnt = min(S.flag_cnt[h], N);
     const bf16_t *Xh = reinterpret_cast<const bf16_t *>(S.X) + (size_t)h * N * D;
     const uint4 *ct = reinterpret_cast<const uint4 *>(S.cbT) + (size_t)h * (D / 8) * C;
+    const bf16_t *cbh = S.cb + (size_t)h * C * D;
     const double *cn = S.cn64 + (size_t)h * C;
     for (int t = blockIdx.x; t < cnt; t += gridDim.x) {
         const int n = S.flag_list[(size_t)h * N + t];
-        __syncthreads();                            // the previous token's s_x / s_best are no longer read
-        if (tid < D) s_x[tid] = (double)bf16_to_f32(Xh[(size_t)n * D + tid]);
+        __syncthreads();                            // the previous token's LDS is no longer read
+        if (tid < D) {
+            const bf16_t xb = Xh[(size_t)n * D + tid];
+            s_xb[tid] = xb;
+            s_x[tid] = (double)bf16_to_f32(xb);
+        }
         __syncthreads();
+        double x[EL];                               // this lane's elements, lane + 64 e
+        float x2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            x[e] = s_x[lane + 64 * e];
+            x2 = fmaf((float)x[e], (float)x[e], x2);
+        }
+        float top = -INFINITY, cmax = 0.f;
+        for (int j0 = 64 * wave; j0 < C; j0 += 256) {
+            const int j = min(j0 + lane, C - 1);
+            const float c2 = (float)cn[j];
+            float dot = 0.f;
+#pragma unroll 1
+            for (int q0 = 0; q0 < D / 8; q0 += 8) {     // eight pieces at a time: fewer registers, more workgroups per CU
+                uint4 w4[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) w4[q] = ct[(size_t)(q0 + q) * C + j];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint4 xq = reinterpret_cast<const uint4 *>(s_xb)[q0 + q];
+                    const unsigned w[4] = {w4[q].x, w4[q].y, w4[q].z, w4[q].w}, u[4] = {xq.x, xq.y, xq.z, xq.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        bf16x2_t p, r;
+                        __builtin_memcpy(&p, &w[e], 4);
+                        __builtin_memcpy(&r, &u[e], 4);
+                        dot = __builtin_amdgcn_fdot2_f32_bf16(p, r, dot, false);
+                    }
+                }
+            }
+            const float v = fmaf(-0.5f, c2, dot);   // the larger, the closer
+            s_v[j0 + lane < C ? j0 + lane : C - 1] = v;     // (the lanes past the end hold the last centroid as well)
+            top = fmaxf(top, v);
+            cmax = fmaxf(cmax, c2);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            top = fmaxf(top, __shfl_xor(top, o));
+            cmax = fmaxf(cmax, __shfl_xor(cmax, o));
+            x2 += __shfl_xor(x2, o);
+        }
+        if (lane == 0) { s_top[wave] = top; s_cmax[wave] = cmax; }
+        __syncthreads();
+        top = fmaxf(fmaxf(s_top[0], s_top[1]), fmaxf(s_top[2], s_top[3]));
+        cmax = fmaxf(fmaxf(s_cmax[0], s_cmax[1]), fmaxf(s_cmax[2], s_cmax[3]));
+        const float least = top - KM_SETTLE_MARGIN * (0.5f * x2 + cmax);
+
         double best = INFINITY;
         int bj = 0x7FFFFFFF;
         for (int j0 = 64 * wave; j0 < C; j0 += 256) {
-            // the token is read from LDS as it is used: kept in registers across this loop it takes 2 D of them, one
-            // workgroup then fills a CU, and most workgroups of a launch find nothing to do -- how fast they come
-            // and go decides how long the launch takes (55 us per launch on the Wan-like layer that way, 26 us so)
-            asm volatile("" ::: "memory");
-            const int j = min(j0 + lane, C - 1);
-            uint4 w4[D / 8];
+            // (what is no number is measured too)
+            unsigned long long m = __ballot(j0 + lane < C && !(s_v[min(j0 + lane, C - 1)] < least));
+            if (__popcll(m) <= KM_SETTLE_FEW) {
+                for (; m; m &= m - 1) {
+                    const int j = j0 + (int)__builtin_ctzll(m);
+                    double dot = 0.0;
 #pragma unroll
-            for (int q = 0; q < D / 8; ++q) w4[q] = ct[(size_t)q * C + j];
-            double dot = 0.0;
-#pragma unroll
-            for (int q = 0; q < D / 8; ++q) {
-                const unsigned w[4] = {w4[q].x, w4[q].y, w4[q].z, w4[q].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    dot = fma(s_x[8 * q + 2 * e], (double)__uint_as_float(w[e] << 16), dot);
-                    dot = fma(s_x[8 * q + 2 * e + 1], (double)__uint_as_float(w[e] & 0xFFFF0000u), dot);
+                    for (int e = 0; e < EL; ++e)
+                        dot = fma(x[e], (double)bf16_to_f32(cbh[(size_t)j * D + lane + 64 * e]), dot);
+                    for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+                    const double dist = cn[j] - 2.0 * dot;
+                    // ascending j: strict < keeps the lower index
+                    if (dist < best) { best = dist; bj = j; }
                 }
+            } else if (m >> lane & 1) {
+                const int j = j0 + lane;
+                double dot = 0.0;
+#pragma unroll 2
+                for (int q = 0; q < D / 8; ++q) {
+                    const uint4 w4 = ct[(size_t)q * C + j];
+                    const unsigned w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        dot = fma(s_x[8 * q + 2 * e], (double)__uint_as_float(w[e] << 16), dot);
+                        dot = fma(s_x[8 * q + 2 * e + 1], (double)__uint_as_float(w[e] & 0xFFFF0000u), dot);
+                    }
+                }
+                const double dist = cn[j] - 2.0 * dot;
+                if (dist < best) { best = dist; bj = j; }
             }
-            const double dist = cn[j] - 2.0 * dot;
-            // ascending j inside a lane: strict < keeps the lower index
-            if (j0 + lane < C && dist < best) { best = dist; bj = j; }
         }
         for (int o = 32; o > 0; o >>= 1) {
             const double ob = __shfl_xor(best, o);
@@ -728,7 +804,7 @@ __global__ __launch_bounds__(256) void kmeans_settle_kernel(KmArgs a, KmIter it)
 #pragma unroll
             for (int w = 1; w < 4; ++w)
                 if (s_best[w] < best || (s_best[w] == best && s_bj[w] < bj)) { best = s_best[w]; bj = s_bj[w]; }
-            labels[(size_t)h * N + n] = bj;
+            if (bj < C) labels[(size_t)h * N + n] = bj;     // (no distance is a number: the label stays)
         }
     }
 }
@@ -1094,7 +1170,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             }
             {
                 ProfileSpan sp(SVG2_K_KMEANS_SETTLE, st);
-                hipLaunchKernelGGL((kmeans_settle_kernel<D>), dim3(KM_SETTLE_BLOCKS, H * ns), dim3(256), 0, st, a, it);
+                hipLaunchKernelGGL((kmeans_settle_kernel<D>), dim3(std::max(KM_SETTLE_MIN, std::min(KM_SETTLE_BLOCKS, KM_SETTLE_WG / (H * ns))), H * ns), dim3(256),
+                                   0, st, a, it);
             }
         } else {
             ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);

@@ -279,6 +279,24 @@ def test_kmeans_tokens_on_and_next_to_bisectors_get_the_oracles_labels(svg2, ora
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("C,copies", [(70, 3), (300, 4), (300, 5), (600, 40), (1100, 1100)])
+def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
+    """Tokens with up to all centroids within the fp32 error of the best one (copies of a few centroids, moved by the last
+    bit of one element or not at all): a few per group of 64 are settled one after the other, more of them one per lane."""
+    r = np.random.default_rng(8800 + C + copies + d)
+    N = max(2 * C, 700)
+    base = wl.round_to_bf16(r.standard_normal((-(-C // copies), d)).astype(np.float32))
+    init = np.repeat(base, copies, axis=0)[:C].copy()
+    move = r.random(C) < 0.5
+    init[move, 3] *= np.float32(1.0 + 2.0 ** -7)           # the next bf16 number or the one after it
+    init = wl.round_to_bf16(init)[r.permutation(C)]
+    X = wl.round_to_bf16(base[r.integers(0, len(base), N)] + 0.1 * r.standard_normal((N, d)).astype(np.float32))
+    res = svg2.svg2_kmeans(to_dev(X[None], "bf16"), to_dev(init[None]), 1)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(res.labels[0]), oracle.kmeans(X, init, 1, True).labels)
+
+
+@pytest.mark.parametrize("d", [128, 64])
 def test_kmeans_duplicate_centroids_tie_everywhere(svg2, oracle, d):
     # two pairs of identical initial centroids: every token that is nearest to one of them is exactly tied with its
     # twin (thousands of near-ties for the double-precision pass at once); the lower index takes them all, the
