@@ -278,6 +278,22 @@ def test_kmeans_tokens_on_and_next_to_bisectors_get_the_oracles_labels(svg2, ora
     np.testing.assert_array_equal(to_np(res.counts[0]), ref.counts)
 
 
+@pytest.mark.parametrize("dtype,d,H,N,C", [
+    # one workgroup per cluster: clusters of 1 to all tokens, as many workgroups as that route takes and one more
+    ("bf16", 128, 1, 4096, 1), ("f32", 128, 1, 4096, 2), ("bf16", 64, 2, 4096, 512), ("f32", 64, 3, 600, 341),
+    # piece by piece
+    ("bf16", 128, 1, 4097, 2), ("bf16", 64, 1, 4096, 1025), ("f32", 64, 3, 600, 342)])
+def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
+    r = np.random.default_rng(6600 + N + C)
+    centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
+    X = np.stack([centres[h][r.integers(0, 5, size=N)] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
+    X = wl.round_to_bf16(X) if dtype == "bf16" else X.astype(np.float32)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
+    res = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), 4)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, 4, dtype == "bf16", H, C)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("C,copies", [(70, 3), (300, 4), (300, 5), (600, 40), (1100, 1100)])
 def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
