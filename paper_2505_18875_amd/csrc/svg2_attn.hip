@@ -40,13 +40,15 @@ namespace svg2 {
 static constexpr int ATT_NSTG = 2;         // K and V tile buffers in LDS (each); the schedule is written for two
 static constexpr int ATT_RUN_LDS = 1920;     // runs of a work item kept in LDS (15 KB: two workgroups of 80 KB still fit a CU)
 static constexpr int ATT_OPS_B = 16;       // vector operations of a block's probabilities done early (see phase B)
-// Largest sum of a block's probabilities before the reference level is moved: 2^40.  The level is the maximum of a
-// query's FIRST score block and no maximum is taken after that: fp32 and bf16 carry a probability of 2^40 with the
-// same relative precision as one of 1, and 2^40 times any sequence length stays far inside the fp32 range of the
-// accumulators.  (Taking every block's maximum and letting it lead the level by at most 2^8 cost 8 v_max3 and a chain of
-// eight dependent instructions per 32 keys: 3.22 against 3.09 ms for dense attention of 24 heads of 16,384 tokens,
-// 31.6 against 30.65 ms for a layer of 40 heads of 75,600 with 2 k-means iterations.)
-static constexpr float ATT_LEVEL_MAX = 1099511627776.0f;
+// The reference level of a query starts as the maximum of its first score block; a block whose maximum is more than 2^8
+// above it takes it up to that maximum, where the largest probability is 1 again.  (A level that may lag by more loses
+// precision: the probability that decides the row is then a rounded bf16 number.  With 2^40, log-sum-exp is off by up to
+// 2^-8 and its rms error over rows of ordinary layers is 1.1 to 1.25 times what it is with 2^8; 2^40 also leaves V only
+// 2^87 over the row length.)  The block's maximum itself is not looked for in every block: a probability above 2^8 makes
+// the block's sum at least 2^8, and only then is it taken.  (In every block it cost 8 v_max3 and a chain of eight dependent
+// instructions per 32 keys: 3.21 against 3.10 ms for dense attention of 24 heads of 16,384 tokens, with the same bits.)
+static constexpr float ATT_LEVEL_LOG2 = 8.0f;
+static constexpr float ATT_LEVEL_SUM = 256.0f;
 
 // ---------------------------------------------------------------- plan
 // grid (1 + ceil(Cq / 4), H), block 256.  Workgroup 0 of a head writes its tiles, the others take four CSR rows each, one
@@ -255,6 +257,8 @@ __device__ __forceinline__ bf16x8 pb_operand(const unsigned *pw, int k)
 
 // RUN_CAP: the launch was sized for at most ATT_RUN_LDS runs in LDS (more than that many key clusters); a work item
 // with more runs then reads them from global memory.  Without it the table always fits and that path does not exist.
+// What the kernel spills (62 registers at D = 128, 13 at D = 64) goes out and in around the last tile and in the rare copies of
+// `relevel`; the tile loop has no scratch access.
 // At D = 64 a third workgroup fits a CU as long as a wavefront takes 168 registers: without that limit the compiler takes
 // 183 and dense attention of 20 heads of 4000 tokens takes 138 instead of 121 us.
 template <int D, bool RUN_CAP>
@@ -467,8 +471,9 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
     //
     // The instruction stream is laid out by hand (ATT_FENCE keeps the compiler from moving
     // code across chunk boundaries).  The reference level m of a query is the maximum of its
-    // first score block; it only moves when a block's sum leaves the range (ATT_LEVEL_MAX),
-    // which is checked at the end of phase A, before the block is accumulated.
+    // first score block; it only moves to a block maximum more than 2^8 above it (ATT_LEVEL_LOG2),
+    // which is looked for at the end of phase A, before the block is accumulated, if the block's
+    // sum says that there may be one.
     // Accumulator i of a block is key 8 (i/4) + 4 half + i%4.
     //
     // Tile t lives in K buffer t % 2 and V buffer t % 2.  One barrier per tile: at the top of
@@ -510,15 +515,17 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
         for (int i = 0; i < 16; ++i)
             if (base + 8 * (i >> 2) + 4 * half + (i & 3) >= rem) S[i] = -INFINITY;
     };
-    // Sum of a block's probabilities out of range (above ATT_LEVEL_MAX, infinite or not a number): take the level of
-    // every query whose block maximum is more than 2^8 above it up to that maximum, bring the accumulators along and
-    // form the block's probabilities again.  S still holds the scores, and the block has not been accumulated yet.
+    // Sum of a block's probabilities 2^8 or more, infinite or not a number: take the level of every query whose block
+    // maximum is more than 2^8 above it up to that maximum, bring the accumulators along and form the block's
+    // probabilities again.  S still holds the scores, and the block has not been accumulated yet.
     auto relevel = [&](const f32x16 &S, unsigned *pw) {
         float mx = fmaxf(S[0], S[1]);
 #pragma unroll
         for (int i = 2; i < 16; ++i) mx = fmaxf(mx, S[i]);
         const float mx_s = max_xor32(mx) * scale_log2;
-        const float m_new = mx_s > m_run + 8.0f ? mx_s : m_run;
+        const bool upd = mx_s > m_run + ATT_LEVEL_LOG2;
+        if (!__any(upd)) return;
+        const float m_new = upd ? mx_s : m_run;
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         l_run *= alpha;
@@ -555,7 +562,7 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
         constexpr bool DO_S = decltype(do_s_tag)::value;
         constexpr int VFETCH = decltype(vfetch_tag)::value;     // >= 0: LDS byte offset of the V buffer to fill
         constexpr int KPF = KS / NPASS;                         // k-steps per load instruction
-        bool out_of_range = false;
+        bool high = false;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if (DO_S) {
@@ -574,13 +581,13 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
                  op < OPS_B + ((NOPS - OPS_B) * (s + 1)) / (KS - 1) && op < NOPS; ++op)
                 exp_op(Sexp, pw, op);
             // compared in front of the last matrix instruction, branched on behind it
-            if (s == KS - 2) out_of_range = __any(!(psum <= ATT_LEVEL_MAX));
+            if (s == KS - 2) high = __any(!(psum < ATT_LEVEL_SUM));
             if constexpr (VFETCH >= 0) {
                 if (s % KPF == KPF - 1) { ATT_FETCH1(s / KPF, off_nx, Vb, ld_voff, VFETCH) }
             }
             ATT_FENCE
         }
-        if (__builtin_expect(out_of_range, 0)) relevel(Sexp, pw);       // rare
+        if (__builtin_expect(high, 0)) relevel(Sexp, pw);       // rare
         l_run += psum;
         psum = 0.f;
     };

@@ -508,8 +508,8 @@ def test_attention_scores_that_climb_by_hundreds_between_tiles(svg2, oracle, dty
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("at", [32, 63, 64, 300])
 def test_attention_one_block_of_scores_far_above_the_first(svg2, oracle, d, at):
-    """The bf16 kernel's reference level is the maximum of a query's first 32 scores and moves only when a block's sum
-    of probabilities leaves the fp32 range it is given: from key `at` on, half of the queries see scores that are
+    """The bf16 kernel's reference level is the maximum of a query's first 32 scores and moves only to a block maximum that
+    is more than 2^8 above it: from key `at` on, half of the queries see scores that are
     hundreds above the level (their probabilities under it are infinite), the other half scores as far below."""
     r = np.random.default_rng(31 + at)
     N = 420
@@ -524,6 +524,29 @@ def test_attention_one_block_of_scores_far_above_the_first(svg2, oracle, d, at):
     lk = (np.arange(N) // 100).astype(np.int32)
     sel = [np.arange(5), np.arange(5)]
     _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "bf16", few_keys=True)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("bits", [4, 9, 12, 20, 38, 60])
+def test_attention_log_sum_exp_of_one_key_far_above_the_first(svg2, d, bits):
+    """bf16: one key beyond the first block scores 2^x above all others, x around `bits`.  Probabilities are rounded to bf16
+    (2^-8 relative at most), so the log-sum-exp carries 2^-8 of the mass of those that are not exactly 1: of all of
+    them while x is at most 8, of the others' once the level has moved up to the key.  1e-5: the fp32 score and logarithm."""
+    r = np.random.default_rng(bits)
+    N = 300
+    Q, K = np.zeros((N, d), np.float32), np.zeros((N, d), np.float32)
+    V = wl.round_to_bf16(r.standard_normal((N, d)).astype(np.float32))
+    Q[:, 0] = wl.round_to_bf16((1.0 + r.random(N)).astype(np.float32))
+    K[200, 0] = wl.round_to_bf16(np.array([0.9 * bits * np.log(2.0) * np.sqrt(d)], dtype=np.float32))[0]
+    one = lambda *a: torch.tensor([a], dtype=torch.int32, device="cuda")  # noqa: E731
+    res = svg2.svg2_sparse_attn(to_dev(Q[None], "bf16"), to_dev(K[None], "bf16"), to_dev(V[None], "bf16"), one(0, N),
+                                one(0, N), one(0, 1), one(0), want_lse=True)
+    torch.cuda.synchronize()
+    x = Q[:, 0].astype(np.float64) * float(K[200, 0]) / np.sqrt(d)
+    total = np.exp(x) + (N - 1)
+    rounded = np.where(x / np.log(2.0) > 8.0, (N - 1) / total, 1.0)
+    err = np.abs(to_np(res.lse[0]) - np.log(total))
+    assert np.all(err <= 2.0 ** -8 * rounded + 1e-5), (err / (2.0 ** -8 * rounded + 1e-5)).max()
 
 
 @pytest.mark.parametrize("d", [128, 64])
