@@ -898,9 +898,13 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
         load_v(bufB, off, 1);
         F32_FENCE
         if (j == nblk - 1) {
+            // keys past the end: no score, and no value either (zero times an infinite one would be NaN)
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if (32 * j + 8 * (i >> 2) + 4 * half + (i & 3) >= L) S[i] = -INFINITY;
+                if (32 * j + 8 * (i >> 2) + 4 * half + (i & 3) >= L) {
+                    S[i] = -INFINITY;
+                    __builtin_memset(reinterpret_cast<char *>(i < 8 ? bufA : bufB) + (i & 7) * (4 * DVB), 0, 4 * DVB);
+                }
         }
         float mx = fmaxf(S[0], S[1]);
 #pragma unroll
@@ -915,9 +919,10 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
         }
+        const float m_ref = (m == -INFINITY) ? 0.f : m;         // scores of -inf alone so far: weights 0, not NaN
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], scale_log2, -m));
+            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], scale_log2, -m_ref));
             l += S[i];
         }
         F32_FENCE
@@ -968,12 +973,13 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int w = 0; w < F32_NW; ++w) {
-            if (s_m[w][r] != -INFINITY) lt += s_l[w][r] * __builtin_amdgcn_exp2f(s_m[w][r] - mm);
+            lt += s_l[w][r] * (s_m[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[w][r] - mm));
             const float4 v = *reinterpret_cast<const float4 *>(s_o + (size_t)(w * 32 + r) * ROW + c4);
             acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
         }
         const size_t dst = (size_t)h * N + (perm_q ? perm_q[(size_t)h * N + row0 + r] : row0 + r);
-        const float inv = (lt > 0.f) ? 1.0f / lt : 0.f;
+        // (no key: 0; keys without any weight, or scores that are no numbers: the softmax is undefined)
+        const float inv = (lt > 0.f) ? 1.0f / lt : L > 0 ? NAN : 0.f;
         *reinterpret_cast<float4 *>(O + dst * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
         if (lse && c4 == 0) lse[dst] = (lt > 0.f) ? (mm + log2f(lt)) * 0.6931471805599453f : -INFINITY;
     }

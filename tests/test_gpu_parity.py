@@ -585,6 +585,39 @@ def test_attention_f32_key_blocks_shared_by_the_wavefronts(svg2, oracle, d):
         _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "f32", tol=(1e-4, 1e-5))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("lo,hi", [(64, 96), (224, 257), (100, 600), (32, 601)])
+def test_attention_keys_masked_by_the_lowest_value(svg2, d, lo, hi, dtype):
+    """Keys whose score overflows to -inf have no weight, also where a wavefront's share of the keys is masked whole, and an
+    infinite value of the last key stays an infinite result although the key block behind it is padding; a row with
+    nothing but such keys has no softmax."""
+    r = np.random.default_rng(5)
+    N = 601
+    Q, K, V = (wl.round_to_bf16(r.standard_normal((N, d)).astype(np.float32)) for _ in range(3))
+    Q[:, 0], K[:, 0] = 8.0, 0.0
+    K[lo:hi, 0] = -2.0 ** 127
+    V[-1 if hi < N else 3, 5] = np.inf
+    Q[7, 0], K[:, 1], Q[:, 1] = 0.0, -2.0 ** 127, 0.0
+    Q[7, 1] = 8.0
+    one = lambda *a: torch.tensor([a], dtype=torch.int32, device="cuda")  # noqa: E731
+    res = svg2.svg2_sparse_attn(to_dev(Q[None], dtype), to_dev(K[None], dtype), to_dev(V[None], dtype), one(0, N),
+                                one(0, N), one(0, 1), one(0), want_lse=True)
+    torch.cuda.synchronize()
+    O, lse = to_np(res.O[0]).astype(np.float64), to_np(res.lse[0]).astype(np.float64)
+    assert np.all(np.isnan(O[7])) and np.isneginf(lse[7])
+    rows = np.delete(np.arange(N), 7)
+    keys = np.delete(np.arange(N), np.arange(lo, hi))
+    S = Q[rows].astype(np.float64) @ K[keys].astype(np.float64).T / np.sqrt(d)
+    P = np.exp(S - S.max(axis=1, keepdims=True))
+    total = P.sum(axis=1, keepdims=True)
+    np.testing.assert_allclose(lse[rows], (S.max(axis=1, keepdims=True) + np.log(total))[:, 0], rtol=1e-3, atol=2e-3)
+    cols = np.delete(np.arange(d), 5)
+    err = np.abs(O[rows][:, cols] - (P / total @ V[keys].astype(np.float64))[:, cols])
+    assert err.max() <= (2e-2 if dtype == "bf16" else 1e-4)
+    assert np.all(np.isposinf(O[rows, 5]))
+
+
 def test_attention_more_selected_key_clusters_than_the_run_table_in_lds_holds(svg2, oracle):
     """The matrix-core kernel keeps the (first row, keys before) table of a query cluster's selected key clusters in LDS
     up to 1919 entries and reads it from global memory beyond: one row of this case selects 2600 of 2700 key clusters
