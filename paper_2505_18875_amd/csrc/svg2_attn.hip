@@ -798,8 +798,8 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     extern __shared__ __align__(16) float s_o[];        // [F32_NW][32][ROW]
     __shared__ float s_m[F32_NW][32], s_l[F32_NW][32];
     // the list of all heads' tiles, longest first, handed out in groups of `group` per XCD (as in the bf16 kernel)
-    const int tid = threadIdx.x, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    const int pos = (slot / group) * (8 * group) + xcd * group + slot % group;
+    const int tid = threadIdx.x;
+    const int pos = attn_list_pos(group);
     if (pos >= tile_base[H]) return;
     const int v = order[pos];
     int h = 0;
@@ -1062,7 +1062,7 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
         float *o = static_cast<float *>(O);
         static_assert(F32_BM == attn_bm(SVG2_F32), "the plan cuts query clusters into the tiles of this kernel");
         auto kern = d == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>;
-        hipLaunchKernelGGL(kern, dim3(nwg), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, H, N, Cq, Ck,
+        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, H, N, Cq, Ck,
                            row_ptr, perm_q, perm_k, tiles, tile_base, a.order, max_tiles, runs, row_keys, a.tile_run,
                            a.key_tiles, scale * 1.4426950408889634f, group, o, lse);
     }

@@ -85,6 +85,23 @@ __device__ __forceinline__ float sum_xor32(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// ---- launch grid of a kernel that takes one work item per workgroup from the list of all heads' tiles.  Consecutive
+// workgroup ids go round-robin over the 8 XCDs, each with its own L2: the list is handed out in groups of ATT_GROUP
+// consecutive tiles per XCD.  The threads of one grid dimension have to stay below 2^32 (a launch beyond that silently runs
+// a part of the grid), so longer lists continue in y.
+static constexpr int ATT_GRID_X = 1 << 22;              // workgroups of up to 512 threads; a multiple of 8 ATT_GROUP
+
+inline dim3 attn_list_grid(int items)
+{
+    const int nwg = cdiv(items, 8 * ATT_GROUP) * 8 * ATT_GROUP;
+    return nwg <= ATT_GRID_X ? dim3(nwg) : dim3(ATT_GRID_X, cdiv(nwg, ATT_GRID_X));
+}
+__device__ __forceinline__ int attn_list_pos(int group)
+{
+    const int wg = (int)(blockIdx.x + gridDim.x * blockIdx.y), xcd = wg % 8, slot = wg / 8;
+    return (slot / group) * (8 * group) + xcd * group + slot % group;
+}
+
 // ---- plan workspace (host)
 constexpr int attn_bm(int dtype) { return dtype == SVG2_BF16 ? 32 * ATT_NW : 32; }   // rows per tile
 

@@ -618,6 +618,21 @@ def test_attention_keys_masked_by_the_lowest_value(svg2, d, lo, hi, dtype):
     assert np.all(np.isposinf(O[rows, 5]))
 
 
+def test_attention_f32_more_work_items_than_one_grid_dimension_holds(svg2):
+    """65,535 heads of 128 one-row query clusters: 8.65 million places in the list of work items, more than 2^32 threads."""
+    H, N, d = 65535, 128, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q, K, V = (torch.randn((H, N, d), device="cuda", generator=g) for _ in range(3))
+    ptr = torch.arange(N + 1, dtype=torch.int32, device="cuda").repeat(H, 1)
+    whole = torch.tensor([[0, N]], dtype=torch.int32, device="cuda").repeat(H, 1)
+    col = torch.zeros((H, N), dtype=torch.int32, device="cuda")
+    res = svg2.svg2_sparse_attn(Q, K, V, ptr, whole, ptr, col)
+    torch.cuda.synchronize()
+    for h in range(0, H, 4369):                 # 15 equal parts of the heads
+        S = Q[h:h + 4369] @ K[h:h + 4369].transpose(1, 2).contiguous() / 8.0
+        assert (res.O[h:h + 4369] - torch.softmax(S, dim=2) @ V[h:h + 4369]).abs().max().item() <= 1e-4
+
+
 def test_attention_more_selected_key_clusters_than_the_run_table_in_lds_holds(svg2, oracle):
     """The matrix-core kernel keeps the (first row, keys before) table of a query cluster's selected key clusters in LDS
     up to 1919 entries and reads it from global memory beyond: one row of this case selects 2600 of 2700 key clusters
