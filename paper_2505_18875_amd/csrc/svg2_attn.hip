@@ -291,13 +291,9 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
     int32_t *s_rows = reinterpret_cast<int32_t *>(s_raw + 2 * NSTG * TILE_B);   // [2][64]
     int2 *s_run = reinterpret_cast<int2 *>(s_rows + 2 * ATT_BN);    // [nnz + 1]
 
-    // ---- which work item.  All tiles of all heads form one list (head-major, so
-    // neighbours share keys).  Consecutive workgroup ids go round-robin over the 8
-    // XCDs, each with its own L2: hand out the list in groups of ATT_GROUP
-    // consecutive tiles per XCD, so tiles that share keys share an L2 and every XCD
-    // gets the same amount of work whatever the per-head densities are.
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    const int pos = (slot / group) * (8 * group) + xcd * group + slot % group;
+    // ---- which work item.  All tiles of all heads form one list; tiles that share keys are neighbours in it and share
+    // an L2, and every XCD gets the same amount of work whatever the per-head densities are.
+    const int pos = attn_list_pos(group);
     if (pos >= tile_base[H]) return;
     const int v = order[pos];                   // longest work items first (attn_order_kernel)
     int h = 0;
@@ -1044,7 +1040,6 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
     if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)d);
     const int total = H * max_tiles;
     const int group = ATT_GROUP;
-    const int nwg = cdiv(total, 8 * group) * 8 * group;
     if (dtype == SVG2_BF16) {
         const float scale_log2 = scale * 1.4426950408889634f;
         const bf16_t *q = static_cast<const bf16_t *>(Qp), *k = static_cast<const bf16_t *>(Kp),
@@ -1054,7 +1049,7 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
         const bool cap = Ck + 1 > ATT_RUN_LDS;
         auto kern = d == 128 ? (cap ? attn_bf16_kernel<128, true> : attn_bf16_kernel<128, false>)
                              : (cap ? attn_bf16_kernel<64, true> : attn_bf16_kernel<64, false>);
-        hipLaunchKernelGGL(kern, dim3(nwg), dim3(64 * ATT_NW), lds, st, q, k, v, H, N, Cq, Ck, row_ptr, perm_q, perm_k, tiles,
+        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * ATT_NW), lds, st, q, k, v, H, N, Cq, Ck, row_ptr, perm_q, perm_k, tiles,
                            tile_base, a.order, max_tiles, runs, row_keys, a.tile_run, a.key_tiles, scale_log2, group, o, lse);
     } else {
         const float *q = static_cast<const float *>(Qp), *k = static_cast<const float *>(Kp),

@@ -211,8 +211,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     int2 *s_run = reinterpret_cast<int2 *>(s_rows + 2 * ATT_BN);    // [nnz + 1]
 
     // work item: as in the bf16 kernel (one list of all tiles, ATT_GROUP consecutive tiles per XCD)
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    const int pos = (slot / group) * (8 * group) + xcd * group + slot % group;
+    const int pos = attn_list_pos(group);
     if (pos >= tile_base[H]) return;
     const int v = order[pos];                   // longest work items first
     int h = 0;
@@ -635,11 +634,10 @@ int attn_fp8_main_launch(const void *Q8, const void *K8, const void *V8, const f
     if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)d);
     const int total = H * a.max_tiles;
     const int group = ATT_GROUP;
-    const int nwg = cdiv(total, 8 * group) * 8 * group;
     const float scale_log2 = scale * 1.4426950408889634f;
     const size_t lds = attn_fp8_lds_bytes(d, Ck);
     auto kern = attn_fp8_kernel<128>;
-    hipLaunchKernelGGL(kern, dim3(nwg), dim3(64 * ATT_NW), lds, st, static_cast<const uint8_t *>(Q8),
+    hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * ATT_NW), lds, st, static_cast<const uint8_t *>(Q8),
                        static_cast<const uint8_t *>(K8), static_cast<const uint8_t *>(V8), scale_q, scale_k, scale_v, H,
                        N, Cq, Ck, row_ptr, perm_q, perm_k, a.tiles, a.tile_base, a.order, a.max_tiles, a.runs, a.row_keys,
                        a.tile_run, a.key_tiles, scale_log2, group, static_cast<bf16_t *>(O), lse);
