@@ -837,7 +837,9 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     // ever read; its score is masked)
     auto row_off = [&](int j) -> unsigned {
         const int kk = min(32 * j + col, L - 1);
-        int c = trh[j >> 1];                    // run in which the 64-key tile starts
+        // run in which the 64-key tile starts (the table ends at N keys; a row may have more, if its list names a
+        // cluster twice)
+        int c = trh[min(j >> 1, key_tiles - 1)];
         while (c + 1 < nnz && kk >= rn[c + 1].y) ++c;
         const int2 rs = rn[c];
         int r = rs.x + kk - rs.y;

@@ -636,6 +636,34 @@ def test_attention_more_work_items_than_one_grid_dimension_holds(svg2, dtype, N)
         assert (o - torch.softmax(S, dim=2) @ v).abs().max().item() <= (1e-4 if dtype == torch.float32 else 2e-2)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [128, 64])
+def test_attention_rows_whose_list_names_a_cluster_more_than_once(svg2, d, dtype):
+    """Such a row has more keys than the head has tokens (here up to 10 N): each naming counts.  Equal to attention over
+    the keys repeated that often, with fp32 sums (1e-4) and bf16 storage (2^-8 of values below 2)."""
+    r = np.random.default_rng(77 + d)
+    N, Ck = 150, 12
+    Q, K, V = (wl.round_to_bf16(r.standard_normal((N, d)).astype(np.float32)) for _ in range(3))
+    ok = np.concatenate([[0], np.sort(r.choice(np.arange(1, 20), Ck - 1, replace=False)), [N]]).astype(np.int32)
+    rows = [np.full(Ck, Ck - 1), np.array([Ck - 1, 3, Ck - 1, Ck - 1, 5]), np.arange(Ck)]      # cluster Ck - 1: most tokens
+    oq = np.array([0, 40, 90, N], dtype=np.int32)
+    col = np.zeros(len(rows) * Ck, dtype=np.int32)
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in rows])]).astype(np.int32)
+    col[:ptr[-1]] = np.concatenate(rows)
+    res = svg2.svg2_sparse_attn(to_dev(Q[None], dtype), to_dev(K[None], dtype), to_dev(V[None], dtype), to_dev(oq[None]),
+                                to_dev(ok[None]), to_dev(ptr[None]), to_dev(col[None]), want_lse=True)
+    torch.cuda.synchronize()
+    O, lse = to_np(res.O[0]).astype(np.float64), to_np(res.lse[0]).astype(np.float64)
+    for i, sel in enumerate(rows):
+        keys = np.concatenate([np.arange(ok[c], ok[c + 1]) for c in sel])
+        S = Q[oq[i]:oq[i + 1]].astype(np.float64) @ K[keys].astype(np.float64).T / np.sqrt(d)
+        P = np.exp(S - S.max(axis=1, keepdims=True))
+        tot = P.sum(axis=1, keepdims=True)
+        err = np.abs(O[oq[i]:oq[i + 1]] - P / tot @ V[keys].astype(np.float64))
+        assert err.max() <= (1e-4 if dtype == "f32" else 2e-2)
+        assert np.abs(lse[oq[i]:oq[i + 1]] - (S.max(axis=1, keepdims=True) + np.log(tot))[:, 0]).max() <= 2e-3
+
+
 def test_attention_more_selected_key_clusters_than_the_run_table_in_lds_holds(svg2, oracle):
     """The matrix-core kernel keeps the (first row, keys before) table of a query cluster's selected key clusters in LDS
     up to 1919 entries and reads it from global memory beyond: one row of this case selects 2600 of 2700 key clusters
