@@ -45,8 +45,9 @@ static constexpr int KM_UB = 4;        // load instructions in flight per wavefr
 static constexpr int KM_SEG = 256;     // rows per piece of the segmented sum
 static constexpr int KM_FULL_EVERY = 16; // iterations between updates that sum every cluster afresh (the others move the changed tokens)
 // Workgroups per head and side that walk the list of near-ties: about as many as run at once (5 per CU) in the launch,
-// within these limits (24 heads of 16,384 tokens: 12.5 us with 64, 8.9 with 26; 40 of 75,600: 23 with 64, 26 with 16).
-static constexpr int KM_SETTLE_BLOCKS = 64, KM_SETTLE_MIN = 32, KM_SETTLE_WG = 1280;
+// within these limits (24 heads of 16,384 tokens, 100 and 500 centroids: 11.8 us with 26 workgroups, 14.7 with 32, 15.6 with
+// 64; 40 heads of 75,600: 23 us with 24, 28 with 32, 27 with 64, 29 with 16).
+static constexpr int KM_SETTLE_BLOCKS = 64, KM_SETTLE_MIN = 24, KM_SETTLE_WG = 1280;
 // A token is settled in double precision when the gap between its two best keys is at most
 //     KM_TIE_KEY * |best key|  +  KM_TIE_ACC * (||x||^2 / 2 + max_j ||c_j||^2).
 // First term: the 4 mantissa bits given to the position move a key by less than 16 units in its last place,
@@ -678,22 +679,22 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
 }
 
 // ---------------------------------------------------------------- settle near-ties, bf16 input
-// grid (workgroups per head and side, H * sides), block 256: one workgroup per listed token at a time.  The argmin of the distance
-// ||c_j||^2 - 2 x.c_j over EVERY centroid in double precision, lowest index on an exact tie.  x and c are bf16 numbers:
-// every product is exact and the sums of 128 of them fit a double in any order, so this is the argmin of the definition.
+// grid (workgroups per head and side, H * sides), block 256: one workgroup per listed token at a time.  The argmin of the
+// distance ||c_j||^2 - 2 x.c_j over EVERY centroid in double precision, lowest index on an exact tie.  x and c are bf16
+// numbers: every product is exact, and so are the sums of 128 of them while the products span no more than some 30 binary
+// orders; beyond that the sums round, which is why every distance is formed by the same chain of additions.
 //
 // What the launch takes is the time of ONE token (a head lists a few dozen), so the token is first compared with all
 // centroids in fp32 (wavefront w takes the centroid groups 64 (w + 4 i) .. + 64, lane l of it centroid l of the group,
 // read from the chunk-major copy so that the 64 lanes of a load read 1 KB of consecutive memory; two products per
-// instruction), and only the centroids within the error of that are measured in double: a few one after the other by all
-// lanes of the wavefront, more of them in one group (many equal centroids) one per lane.  With every centroid measured in
-// double, a few thousand instructions per group, the launch took 20 instead of 9 us at 24 heads of 16,384 tokens (100 and
-// 500 centroids), 27 instead of 12 us on average over 8 heads of 37,800 in 100 and in 2000.
+// instruction), and only the centroids within the error of that are measured in double, one per lane, the token's elements read
+// from LDS ahead of the chain (as they were needed: 15.4 instead of 14.7 us at 24 heads of 16,384 tokens, 32 workgroups). With every
+// centroid measured in double, a few thousand instructions per group, the launch took 20 instead of 12 us there, 27 instead
+// of 13 us on average over 8 heads of 37,800 in 100 and in 2000, and 28 instead of 23 us at 40 heads of 75,600.
 //
 // Error of the fp32 value x.c - ||c||^2 / 2: D / 2 steps with at most two roundings each of partial sums below ||x||^2 / 2 +
 // ||c||^2, below 2^-17 of that at D = 128; two values are compared, and the margin is twice what that makes.
 static constexpr float KM_SETTLE_MARGIN = 3.0517578125e-05f;  // 2^-15
-static constexpr int KM_SETTLE_FEW = 4;
 
 template <int D>
 __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter it)
@@ -704,7 +705,6 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
     __shared__ float s_top[4], s_cmax[4];
     __shared__ double s_best[4];
     __shared__ int s_bj[4];
-    constexpr int EL = D / 64;
     const int side = blockIdx.y % a.nsides, h = blockIdx.y / a.nsides;
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
@@ -724,12 +724,11 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
             s_x[tid] = (double)bf16_to_f32(xb);
         }
         __syncthreads();
-        double x[EL];                               // this lane's elements, lane + 64 e
         float x2 = 0.f;
 #pragma unroll
-        for (int e = 0; e < EL; ++e) {
-            x[e] = s_x[lane + 64 * e];
-            x2 = fmaf((float)x[e], (float)x[e], x2);
+        for (int e = 0; e < D / 64; ++e) {
+            const float x = bf16_to_f32(s_xb[lane + 64 * e]);
+            x2 = fmaf(x, x, x2);
         }
         float top = -INFINITY, cmax = 0.f;
         for (int j0 = 64 * wave; j0 < C; j0 += 256) {
@@ -774,35 +773,40 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
         int bj = 0x7FFFFFFF;
         for (int j0 = 64 * wave; j0 < C; j0 += 256) {
             // (what is no number is measured too)
-            unsigned long long m = __ballot(j0 + lane < C && !(s_v[min(j0 + lane, C - 1)] < least));
-            if (__popcll(m) <= KM_SETTLE_FEW) {
-                for (; m; m &= m - 1) {
-                    const int j = j0 + (int)__builtin_ctzll(m);
-                    double dot = 0.0;
+            const int j = j0 + lane;
+            if (j >= C || s_v[j] < least) continue;
+            // one chain of additions per centroid, k = 0 .. D - 1, so that equal centroids tie whatever the sum rounds;
+            // the token comes from LDS eight elements ahead of their use
+            const uint4 *row = reinterpret_cast<const uint4 *>(cbh + (size_t)j * D);
+            double dot = 0.0;
+#pragma unroll 1
+            for (int q0 = 0; q0 < D / 8; q0 += 8) {
+                asm volatile("" ::: "memory");      // (read here, not held in 2 D registers across the groups)
+                uint4 w4[8];
+                double2 x2d[2][4];
 #pragma unroll
-                    for (int e = 0; e < EL; ++e)
-                        dot = fma(x[e], (double)bf16_to_f32(cbh[(size_t)j * D + lane + 64 * e]), dot);
-                    for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
-                    const double dist = cn[j] - 2.0 * dot;
-                    // ascending j: strict < keeps the lower index
-                    if (dist < best) { best = dist; bj = j; }
-                }
-            } else if (m >> lane & 1) {
-                const int j = j0 + lane;
-                double dot = 0.0;
-#pragma unroll 2
-                for (int q = 0; q < D / 8; ++q) {
-                    const uint4 w4 = ct[(size_t)q * C + j];
-                    const unsigned w[4] = {w4.x, w4.y, w4.z, w4.w};
+                for (int q = 0; q < 8; ++q) w4[q] = row[q0 + q];
+                auto load_x = [&](int q) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x2d[q & 1][e] = reinterpret_cast<const double2 *>(s_x)[4 * (q0 + q) + e];
+                };
+                load_x(0);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    if (q < 7) load_x(q + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const unsigned w[4] = {w4[q].x, w4[q].y, w4[q].z, w4[q].w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        dot = fma(s_x[8 * q + 2 * e], (double)__uint_as_float(w[e] << 16), dot);
-                        dot = fma(s_x[8 * q + 2 * e + 1], (double)__uint_as_float(w[e] & 0xFFFF0000u), dot);
+                        dot = fma(x2d[q & 1][e].x, (double)__uint_as_float(w[e] << 16), dot);
+                        dot = fma(x2d[q & 1][e].y, (double)__uint_as_float(w[e] & 0xFFFF0000u), dot);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                const double dist = cn[j] - 2.0 * dot;
-                if (dist < best) { best = dist; bj = j; }
             }
+            const double dist = cn[j] - 2.0 * dot;
+            // ascending j: strict < keeps the lower index
+            if (dist < best) { best = dist; bj = j; }
         }
         for (int o = 32; o > 0; o >>= 1) {
             const double ob = __shfl_xor(best, o);

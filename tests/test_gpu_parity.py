@@ -298,7 +298,7 @@ def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
 @pytest.mark.parametrize("C,copies", [(70, 3), (300, 4), (300, 5), (600, 40), (1100, 1100)])
 def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
     """Tokens with up to all centroids within the fp32 error of the best one (copies of a few centroids, moved by the last
-    bit of one element or not at all): a few per group of 64 are settled one after the other, more of them one per lane."""
+    bit of one element or not at all): from a few per group of 64 to all of them are settled."""
     r = np.random.default_rng(8800 + C + copies + d)
     N = max(2 * C, 700)
     base = wl.round_to_bf16(r.standard_normal((-(-C // copies), d)).astype(np.float32))
@@ -310,6 +310,30 @@ def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
     res = svg2.svg2_kmeans(to_dev(X[None], "bf16"), to_dev(init[None]), 1)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(to_np(res.labels[0]), oracle.kmeans(X, init, 1, True).labels)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_kmeans_equal_centroids_spread_over_the_list_tie_whatever_their_sums_round(svg2, d):
+    """Ten centroids with one to six copies in each group of 64, channels that span twenty binary orders (the sums of
+    the double-precision distances then round): a token belongs to the lowest index among the copies of its nearest."""
+    r = np.random.default_rng(9900 + d)
+    ch = 2.0 ** r.permutation(np.linspace(-10.0, 10.0, d))
+    base = wl.round_to_bf16((r.standard_normal((10, d)) * ch).astype(np.float32))
+    init = 8.0 * r.standard_normal((192, d)) * ch
+    first = np.full(10, 192)
+    for g, per in enumerate([[1] * 5 + [6] * 5, [6] * 5 + [1] * 5, [3] * 10]):
+        slots = 64 * g + r.permutation(64)[:sum(per)]
+        for slot, b in zip(slots, np.repeat(np.arange(10), per)):
+            init[slot] = base[b]
+            first[b] = min(first[b], slot)
+    init = wl.round_to_bf16(init.astype(np.float32))
+    X = wl.round_to_bf16((base[r.integers(0, 10, 3000)] + 0.2 * ch * r.standard_normal((3000, d))).astype(np.float32))
+    dist = np.stack([((X.astype(np.float64) - c) ** 2).sum(axis=1) for c in init.astype(np.float64)], axis=1)
+    near = np.sort(dist[:, first], axis=1)
+    assert np.all(near[:, 1] > 1.01 * near[:, 0]) and np.all(dist.min(axis=1) >= (1.0 - 1e-12) * near[:, 0])
+    res = svg2.svg2_kmeans(to_dev(X[None], "bf16"), to_dev(init[None]), 1)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(res.labels[0]), first[dist[:, first].argmin(axis=1)])
 
 
 @pytest.mark.parametrize("d", [128, 64])
