@@ -441,8 +441,10 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
         const float n2 = fmaf(scale * scale, (float)(row.y & 0xFFFFu), c_n2);
         const float t = fmaf(-2.0f * scale * c_scale, (float)dot, n2) - 1e-6f * n2;
         const float lb = sqrtf(fmaxf(t, 0.f)) - (r + c_r);
-        // leave the token out only if the bound is an ordinary number and says so (inputs that are no numbers are measured)
-        const bool left = in && !(t < 1e37f && lb > 0.f && lb * lb > 1.00001f * d2_up);
+        // leave the token out only if the bound is an ordinary number and says so (inputs that are no numbers are measured).
+        // Below 1e-18 squares of digit errors and scales can underflow: what is lost of r is up to 1.2e-18 and of the terms
+        // of n2 up to 1e-31, against margins of 5e-16 and 1e-24 at t = 1e-18.
+        const bool left = in && !(t > 1e-18f && t < 1e37f && lb > 0.f && lb * lb > 1.00001f * d2_up);
         const unsigned long long m = __ballot(left);
         int pos = 0;
         if (lane == 0 && m) pos = atomicAdd(&s_nleft, __popcll(m));

@@ -87,10 +87,10 @@ def test_kmeans_pp_degenerate_inputs(svg2, oracle):
 
 @pytest.mark.parametrize("H,N,d,C,dtype,comps", [
     (1, 1, 64, 1, "bf16", 1), (1, 255, 128, 40, "f32", 5), (2, 257, 64, 257, "bf16", 30),
-    (3, 2000, 128, 300, "bf16", 2000),        # no structure: more distinct nearest centres per block than are looked at
+    (3, 2000, 128, 300, "bf16", 2000),        # no structure: hardly a token is left out
     (5, 6001, 64, 90, "f32", 12), (2, 400001, 64, 9, "bf16", 3), (1, 1700000, 64, 3, "bf16", 2)])
 def test_kmeans_pp_block_edges_and_skipped_tokens(svg2, oracle, H, N, d, C, dtype, comps):
-    """Lengths around a block, blocks of several chunks, more centres than the table of a block's nearest centres holds,
+    """Lengths around a chunk of 256 tokens, workgroups with one chunk and with several, one centre and as many as tokens,
     components far enough apart that most tokens are left out of a draw."""
     r = np.random.default_rng(700 + N)
     centres = (4.0 * r.standard_normal((comps, d))).astype(np.float32)
@@ -103,6 +103,24 @@ def test_kmeans_pp_block_edges_and_skipped_tokens(svg2, oracle, H, N, d, C, dtyp
         picked, rows = oracle.kmeans_pp(X[i], C, u[i])
         np.testing.assert_array_equal(to_np(res.picked[i]), picked)
         np.testing.assert_array_equal(to_np(res.centroids[i]), rows)
+
+
+@pytest.mark.parametrize("dtype,magnitude", [("bf16", 1e-9), ("bf16", 3e-10), ("f32", 1e-15), ("bf16", 1e-20), ("f32", 1e-20),
+                                             ("bf16", 1e-21), ("bf16", 2e-21), ("f32", 1e-21), ("bf16", 1e-25)])
+def test_kmeans_pp_tokens_whose_squares_underflow(svg2, oracle, dtype, magnitude):
+    """The fp32 bound that rules tokens out of a draw works with squares; the draws have to be the oracle's (fp64) also
+    where these are denormal or zero in fp32, and around the limit below which every token is measured."""
+    r = np.random.default_rng(41)
+    centres = 2.0 * r.standard_normal((40, 128))
+    X = centres[np.sort(r.integers(0, 40, size=4000))] + 0.3 * r.standard_normal((4000, 128))
+    X = (magnitude * X).astype(np.float32)
+    X = wl.round_to_bf16(X) if dtype == "bf16" else X
+    u = r.random((1, 120))
+    res = svg2.svg2_kmeans_pp_init(to_dev(X[None], dtype), 120, torch.from_numpy(u).cuda())
+    torch.cuda.synchronize()
+    picked, rows = oracle.kmeans_pp(X, 120, u[0])
+    np.testing.assert_array_equal(to_np(res.picked[0]), picked)
+    np.testing.assert_array_equal(to_np(res.centroids[0]), rows)
 
 
 def test_kmeans_pp_then_lloyd_lowers_the_objective(svg2):
