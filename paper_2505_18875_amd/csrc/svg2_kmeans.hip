@@ -942,6 +942,59 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     }
 }
 
+// A handful of centroids: one token per thread, the centroids in LDS, the same chain of fmaf over k.  The 32-row tile of the
+// matrix instruction would be mostly padding: 24 heads of 16,384 tokens, D = 128: 32 instead of 63 us with 2 centroids, 55
+// instead of 63 with 12; one head of 4096, D = 64: 4.6 instead of 5.2 us with 4.  With more than four centroids it takes
+// many tokens, or the wavefronts that share a token block there are faster (one head of 4096, D = 64: 5.4 against 5.2 us
+// with 6 centroids, 8.3 against 5.0 with 12; 4 heads of 9601, D = 128: 10.3 against 12.7 with 6, 14.5 against 13.2 with 12).
+static constexpr int KF_FEW = 12, KF_FEW_ANY = 4, KF_FEW_TOKENS = 8192;  // .. and tokens of all heads per centroid
+
+static bool kmeans_f32_few(int H, int N, int C)
+{
+    return C <= KF_FEW_ANY || (C <= KF_FEW && (long long)H * N >= (long long)KF_FEW_TOKENS * C);
+}
+
+template <int D, bool OBJ>
+__global__ __launch_bounds__(128) void kmeans_assign_f32_few_kernel(KmArgs a, KmIter it, int side)
+{
+    __shared__ __align__(16) float s_c[KF_FEW][D];
+    __shared__ float s_cn[KF_FEW];
+    const KmSide S = side ? a.s[1] : a.s[0];
+    int32_t *labels = side ? it.lab[1] : it.lab[0];
+    const int N = a.N, C = S.C, h = blockIdx.y, tid = threadIdx.x, n = blockIdx.x * 128 + tid;
+    const float4 *xr = reinterpret_cast<const float4 *>(static_cast<const float *>(S.X) + ((size_t)h * N + min(n, N - 1)) * D);
+    float x[D];
+#pragma unroll
+    for (int k = 0; k < D / 4; ++k) {
+        const float4 v = xr[k];
+        x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+    }
+    for (int e = tid; e < C * D; e += 128) {
+        const int j = e / D, k = e % D;
+        s_c[j][k] = S.ct[((((size_t)h * 2 + (k & 1)) * (D / 8) + (k >> 3)) * C + j) * 4 + ((k >> 1) & 3)];
+    }
+    if (tid < C) s_cn[tid] = S.hcn[(size_t)h * C + tid];
+    __syncthreads();
+    float best = INFINITY;
+    int bidx = 0;
+    for (int j = 0; j < C; ++j) {
+        float dot = 0.f;
+#pragma unroll
+        for (int k = 0; k < D; ++k) dot = fmaf(x[k], s_c[j][k], dot);
+        const float dist = fmaf(-2.f, dot, s_cn[j]);
+        if (dist < best) { best = dist; bidx = j; }
+    }
+    if (n < N) labels[(size_t)h * N + n] = bidx;
+    if (OBJ && S.objective) {
+        float x2 = 0.f;
+#pragma unroll
+        for (int k = 0; k < D; ++k) x2 = fmaf(x[k], x[k], x2);
+        float v = n < N ? x2 + best : 0.f;
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if ((tid & 63) == 0) atomicAdd(S.objective + (size_t)h * a.iters + it.t, v);
+    }
+}
+
 // ---------------------------------------------------------------- update
 // Segmented sum over the sorted order, one wavefront per piece (at most KM_SEG rows of one cluster).  A row is LPR
 // lanes of 16 bytes; 64 / LPR rows are read per instruction and KM_UB instructions are in flight before their
@@ -1218,9 +1271,10 @@ static int kmeans_run(KmArgs a, hipStream_t st)
     int ncu = 0;
     if (BF16) SVG2_TRY(device_cu_count(&ncu));
     int call = 0, pmax = 0, ncmax = 1;
-    bool any_obj = false;
+    bool any_obj = false, any_few = false;
     for (int s = 0; s < ns; ++s) {
         call += a.s[s].C;
+        any_few |= !BF16 && kmeans_f32_few(H, N, a.s[s].C);
         a.nc[s] = kmeans_f32_share(H, N, a.s[s].C);
         ncmax = std::max(ncmax, a.nc[s]);
         pmax = std::max(pmax, a.s[s].max_pieces);
@@ -1267,7 +1321,22 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         } else {
             ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);
             auto kern = any_obj ? kmeans_assign_f32_kernel<D, true> : kmeans_assign_f32_kernel<D, false>;
-            hipLaunchKernelGGL(kern, dim3(cdiv(N, 32 * (KF_NW / ncmax)), H, ns), dim3(64 * KF_NW), 0, st, a, it);
+            const dim3 grid(cdiv(N, 32 * (KF_NW / ncmax)), H, ns);
+            if (!any_few) {
+                hipLaunchKernelGGL(kern, grid, dim3(64 * KF_NW), 0, st, a, it);
+            } else {
+                auto few = any_obj ? kmeans_assign_f32_few_kernel<D, true> : kmeans_assign_f32_few_kernel<D, false>;
+                for (int s = 0; s < ns; ++s) {
+                    if (kmeans_f32_few(H, N, a.s[s].C)) {
+                        hipLaunchKernelGGL(few, dim3(cdiv(N, 128), H), dim3(128), 0, st, a, it, s);
+                        continue;
+                    }
+                    KmArgs one = a;                     // that side alone
+                    KmIter one_it = it;
+                    one.s[0] = a.s[s]; one.nc[0] = a.nc[s]; one_it.lab[0] = it.lab[s];
+                    hipLaunchKernelGGL(kern, dim3(grid.x, H), dim3(64 * KF_NW), 0, st, one, one_it);
+                }
+            }
         }
         // label-sorted order of the tokens and its pieces, then the segmented sum over it
         SortArgs sa = {};

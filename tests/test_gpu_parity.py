@@ -238,6 +238,28 @@ def test_kmeans_f32_row_blocks_shared_by_the_wavefronts(svg2, oracle, d, N, C):
     assert to_np(res.labels).max() < (C + 1) // 2
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N,C", [(1, 2, 1), (3, 130, 4), (1, 40960, 5), (1, 40959, 5), (17, 4001, 8), (16, 4001, 8), (25, 4096, 12), (27, 4096, 13)])
+def test_kmeans_f32_few_centroids(svg2, oracle, d, H, N, C):
+    """A handful of centroids go another way from so many tokens on: both sides of both limits, ragged lengths, two equal
+    centroids (the lower index wins)."""
+    r = np.random.default_rng(7300 + N + C + d)
+    X = r.standard_normal((H, N, d)).astype(np.float32)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
+    init[:, -1] = init[:, 0]
+    res = svg2.svg2_kmeans(to_dev(X), to_dev(init), 1, want_objective=True)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, 1, False, H, C)
+    assert C == 1 or not np.any(to_np(res.labels) == C - 1)
+
+
+@pytest.mark.parametrize("Cq,Ck", [(1, 70), (70, 1)])
+def test_forward_f32_one_side_with_few_centroids(svg2, oracle, Cq, Ck):
+    # 5 heads of 1920 tokens: the assign steps of the two sides are different kernels
+    w = wl.replace(wl.WORKLOADS["small"], grid=(4, 20, 24), d=64, dtype="f32", Cq=Cq, Ck=Ck, iters=3)
+    _check_forward(oracle, svg2, w, list(range(5)), sample_rows=40)
+
+
 @pytest.mark.parametrize("H,N,C", [(300, 700, 40), (77, 1300, 520)])
 def test_kmeans_many_heads_a_workgroups_share_crosses_head_boundaries(svg2, oracle, H, N, C):
     # The bf16 assign kernel gives every CU an equal share of the 512-token blocks of ALL heads: with a few blocks per
