@@ -1255,14 +1255,18 @@ static int device_cu_count(int *ncu)
 // least four row blocks where the token blocks alone are enough for two wavefronts per SIMD, and as few as one otherwise.
 // (One share per row block, up to four, whatever the number of token blocks:
 // 100 instead of 96 us per iteration for 4 heads of 9601 tokens against 100 and 500 centroids at D = 128.)
-static int kmeans_f32_share(int H, int N, int C)
+// The grid has 64 KF_NW threads per 32 (KF_NW / nc) tokens of a head, 2 nc N, and one grid dimension takes less than 2^32.
+static constexpr int kmeans_f32_share(int H, int N, int C)
 {
-    const int nrb = cdiv(C, 32);
-    const long long blocks = (long long)H * cdiv(N, 32);
+    const int nrb = (C + 31) / 32;
+    const long long blocks = H * (((long long)N + 31) / 32);
     int nc = 1;
-    while (nc < KF_NW && 2 * nc <= nrb && (nrb > 4 * nc || blocks * nc < 2048)) nc *= 2;
+    while (nc < KF_NW && 2 * nc <= nrb && (nrb > 4 * nc || blocks * nc < 2048) && 2ll * (2 * nc) * (N + 128ll) < 1ll << 32)
+        nc *= 2;
     return nc;
 }
+static_assert(kmeans_f32_share(1, 1 << 20, 4096) == 4 && kmeans_f32_share(1, 1 << 29, 4096) == 2 &&
+              kmeans_f32_share(1, 1 << 30, 4096) == 1, "the grid of the fp32 assign step stays below 2^32 threads");
 
 template <typename T, int D, bool BF16>
 static int kmeans_run(KmArgs a, hipStream_t st)
