@@ -1110,19 +1110,31 @@ __global__ __launch_bounds__(256) void kmeans_segsum_kernel(KmArgs a, KmIter it)
 // The whole update step of a cluster in one workgroup, for heads of at most KM_SMALL_N tokens: the pieces of the cluster
 // (mode 1: of the new order; mode 2: those that joined, then those that left) are dealt out to the wavefronts, their sums
 // stay in LDS, the first wavefront adds them in their order and finishes the cluster.  Same sums in the same order as the
-// two kernels; one launch and a round trip through memory less: 2 heads of 1024 tokens, 48 clusters each, D = 64: 6.0
-// instead of 9.6 us per iteration, the layer 175 -> 150 us.  In longer heads a cluster may have more pieces than a
-// workgroup should walk alone.
-static constexpr int KM_SMALL_N = 4096;
-static constexpr int KM_SMALL_WG = 1024;        // .. and with as many clusters as workgroups run at once (4 per CU)
+// two kernels; one launch and a round trip through memory less.
+//
+// A workgroup has to be able to walk a cluster that holds most of the head about as fast as the pieces would be walked side
+// by side: four wavefronts up to 2048 tokens, sixteen above, where fewer such workgroups run at once.  Time of an iteration
+// in us, this kernel / the two, clusters of equal size, then one of all tokens (bf16; D = 128, or 64 where named):
+//   1 head  x 1024, D = 64,  25 clusters:  20.9 / 25.4,  21.3 / 24.4        1 x 2048, 100:  26.5 / 30.9,  30.9 / 31.2
+//   40 heads x 2048, 25 clusters:          34.0 / 38.7,  33.0 / 32.4        1 x 4096, 100:  29.4 / 33.8,  33.5 / 34.2
+//   40 heads x 4096, 12 clusters (480):    45.3 / 45.3,  39.8 / 38.8        25 clusters (1000): 52.7 / 46.4, 42.1 / 39.3
+// (With four wavefronts at 4096 tokens one cluster of all tokens took 39.7 us in the fourth of these, 47.1 in the fifth.)
+static constexpr int KM_SMALL_N = 4096, KM_SMALL_N4 = 2048;     // tokens of a head, with 16 and with 4 wavefronts
+static constexpr int KM_SMALL_WG = 512, KM_SMALL_WG4 = 1024;    // .. and clusters of all heads
 
-template <typename T, int D, bool BF16>
-__global__ __launch_bounds__(256) void kmeans_update_small_kernel(KmArgs a, KmIter it, int mode)
+static bool kmeans_update_small(int H, int N, int C)
+{
+    return N <= KM_SMALL_N && (long long)C * H <= (N <= KM_SMALL_N4 ? KM_SMALL_WG4 : KM_SMALL_WG);
+}
+
+template <typename T, int D, bool BF16, int NW>
+__global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, KmIter it, int mode)
 {
     constexpr int EPL = 16 / sizeof(T), LPR = D / EPL, EL = D / 64;
-    __shared__ __align__(16) double s_ps[2 * KM_SMALL_N / KM_SEG][D];
-    __shared__ int32_t s_cnt[2 * KM_SMALL_N / KM_SEG];
-    __shared__ int32_t s_list[4][KM_SEG];
+    constexpr int NP = 2 * (NW == 4 ? KM_SMALL_N4 : KM_SMALL_N) / KM_SEG;       // most pieces of a cluster, joined and left
+    __shared__ __align__(16) double s_ps[NP][D];
+    __shared__ int32_t s_cnt[NP];
+    __shared__ int32_t s_list[NW][KM_SEG];
     const int h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, N = a.N;
     const int side = (int)blockIdx.x >= a.s[0].C ? 1 : 0;
     const KmSide S = side ? a.s[1] : a.s[0];
@@ -1137,7 +1149,7 @@ __global__ __launch_bounds__(256) void kmeans_update_small_kernel(KmArgs a, KmIt
         o1 = oo[1];
     }
     const int n_all = n_new + (o1 - o0 + KM_SEG - 1) / KM_SEG;
-    for (int q = wave; q < n_all; q += 4) {
+    for (int q = wave; q < n_all; q += NW) {
         const bool left = q >= n_new;
         const int row0 = left ? o0 + (q - n_new) * KM_SEG : n0 + q * KM_SEG, rows = min(KM_SEG, (left ? o1 : n1) - row0);
         const int32_t *pm = (left ? KM_SEL(S.perm, 1 - it.set) : KM_SEL(S.perm, it.set)) + (size_t)h * N;
@@ -1288,7 +1300,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
     }
     const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);
-    const bool small = N <= KM_SMALL_N && (long long)call * H <= KM_SMALL_WG;
+    const bool small = kmeans_update_small(H, N, call);
     {
         ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
         hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, KmIter{}, 0);
@@ -1364,7 +1376,10 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
         if (small) {
             ProfileSpan sp(full ? SVG2_K_KMEANS_SEGSUM_FULL : SVG2_K_KMEANS_SEGSUM_DELTA, st);
-            hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16>), dim3(call, H), dim3(256), 0, st, a, it, full ? 1 : 2);
+            if (N <= KM_SMALL_N4)
+                hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16, 4>), dim3(call, H), dim3(256), 0, st, a, it, full ? 1 : 2);
+            else
+                hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16, 16>), dim3(call, H), dim3(1024), 0, st, a, it, full ? 1 : 2);
             continue;
         }
         if (full) {

@@ -304,7 +304,10 @@ def test_kmeans_tokens_on_and_next_to_bisectors_get_the_oracles_labels(svg2, ora
     # one workgroup per cluster: clusters of 1 to all tokens, as many workgroups as that route takes and one more
     ("bf16", 128, 1, 4096, 1), ("f32", 128, 1, 4096, 2), ("bf16", 64, 2, 4096, 512), ("f32", 64, 3, 600, 341),
     # piece by piece
-    ("bf16", 128, 1, 4097, 2), ("bf16", 64, 1, 4096, 1025), ("f32", 64, 3, 600, 342)])
+    ("bf16", 128, 1, 4097, 2), ("bf16", 64, 1, 4096, 1025), ("f32", 64, 3, 600, 342),
+    # four wavefronts to the workgroup at the longest, sixteen at the shortest, and with the most clusters
+    ("bf16", 128, 1, 2048, 1), ("f32", 128, 2, 2049, 3), ("f32", 64, 1, 4096, 512), ("bf16", 128, 1, 4096, 513),
+    ("bf16", 128, 2, 2048, 512), ("bf16", 64, 1, 2048, 1025)])
 def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
     r = np.random.default_rng(6600 + N + C)
     centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
