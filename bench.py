@@ -279,7 +279,6 @@ def main():
         add("kmeans_segsum_kernel, all tokens (Q and K)", "kmeans_segsum_full", bound="hbm", nbytes=2 * tensor_bytes)
         add("kmeans_segsum_kernel, moved tokens only (Q and K)", "kmeans_segsum_delta")
         add("kmeans_finalize_kernel (Q and K)", "kmeans_finalize")
-        add("permute_hist/scan/scatter_kernel (pi_q, pi_k)", "permute_sort")
         # a4: Q', K', V' = three tensors read and written once (one launch)
         if kernel_ms["permute_gather"][1]:
             ms, _ = kernel_ms["permute_gather"]

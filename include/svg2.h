@@ -362,8 +362,8 @@ enum {
     SVG2_K_KMEANS_ASSIGN = 0,      /* assign step, Q and K side in one launch (Section 4.1) */
     SVG2_K_KMEANS_SETTLE = 1,      /* near-ties again in double precision                   */
     SVG2_K_KMEANS_SORT = 2,        /* counting sort of the labels                           */
-    SVG2_K_KMEANS_SEGSUM_FULL = 3, /* segmented sum over all tokens                         */
-    SVG2_K_KMEANS_SEGSUM_DELTA = 4,/* segmented sum over the tokens whose label changed     */
+    SVG2_K_KMEANS_SEGSUM_FULL = 3, /* segmented sum over all tokens (short heads: with the  */
+    SVG2_K_KMEANS_SEGSUM_DELTA = 4,/* means, in one kernel); over those whose label changed */
     SVG2_K_KMEANS_FINALIZE = 5,    /* means, bf16 copy, norms                               */
     SVG2_K_PERMUTE_SORT = 6,       /* index vectors of svg2_permute; in svg2_forward* the last
                                     * sort of k-means is the permutation                    */

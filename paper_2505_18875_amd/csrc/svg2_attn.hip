@@ -247,14 +247,6 @@ __device__ __forceinline__ float add_bf16x2(unsigned w, float acc)
     return __builtin_amdgcn_fdot2_f32_bf16(x, ones, acc, false);
 }
 
-// words 4 k .. 4 k + 3 of the packed probabilities as an MFMA operand
-__device__ __forceinline__ bf16x8 pb_operand(const unsigned *pw, int k)
-{
-    bf16x8 r;
-    __builtin_memcpy(&r, pw + 4 * k, 16);
-    return r;
-}
-
 // RUN_CAP: the launch was sized for at most ATT_RUN_LDS runs in LDS (more than that many key clusters); a work item
 // with more runs then reads them from global memory.  Without it the table always fits and that path does not exist.
 // What the kernel spills (62 registers at D = 128, 13 at D = 64) goes out and in around the last tile and in the rare copies of

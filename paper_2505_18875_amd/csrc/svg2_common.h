@@ -100,16 +100,6 @@ __device__ __forceinline__ void load_to_lds_16(const char *base, unsigned byte_o
 }
 #pragma clang diagnostic pop
 
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ float load(const float *p) { return *p; }
-    static __device__ __forceinline__ void store(float *p, float v) { *p = v; }
-};
-template <> struct Elem<bf16_t> {
-    static __device__ __forceinline__ float load(const bf16_t *p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void store(bf16_t *p, float v) { *p = f32_to_bf16(v); }
-};
-
 // ---- stage launchers (defined in the per-stage .hip files) -----------------
 // All of them assume validated arguments and a workspace of the right size.
 

@@ -9,7 +9,8 @@
 //             Each accumulator gets its position written into its 4 lowest mantissa bits; the largest and the
 //             second largest of these keys are tracked per token (max3 / med3 trees, no compare-and-select
 //             chains), which gives the label and the gap to the runner-up.
-//             fp32 input: MFMA 32x32x2 fp32, the centroids of a token dealt out to several wavefronts.
+//             fp32 input: MFMA 32x32x2 fp32, the centroids of a token dealt out to several wavefronts; a handful of
+//             centroids: one token per thread.
 //   settle    (bf16) every token whose gap is within the error bound of the fp32 contraction is assigned
 //             again in double precision, over all centroids, lowest index winning an exact tie.  Products of
 //             two bf16 numbers are exact and their sums fit a double, so these labels are THE argmin of the

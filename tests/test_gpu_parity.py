@@ -141,6 +141,18 @@ def test_select_edges_of_the_score_tiles_and_of_the_sort(svg2, oracle, H, Cq, Ck
         res = svg2.svg2_select_topp(to_dev(cq), to_dev(ck), to_dev(counts_q), to_dev(counts_k), p, want_p_est=True)
         torch.cuda.synchronize()
         assert _check_select(oracle, res, cq, ck, counts_q, counts_k, p, H) <= max(2, Cq // 20) * H
+    # the tie rule by itself, at many stopping points: a kept upper index implies that its lower twin is kept
+    inside = 0
+    for p in np.linspace(0.05, 0.95, 19):
+        res = svg2.svg2_select_topp(to_dev(cq), to_dev(ck), to_dev(counts_q), to_dev(counts_k), float(p))
+        torch.cuda.synchronize()
+        for h in range(H):
+            for row in _csr_rows(to_np(res.row_ptr[h]), to_np(res.col_idx[h])):
+                kept = np.zeros(Ck, dtype=bool)
+                kept[row] = True
+                assert not np.any(kept[Ck - t:] & ~kept[:t])
+                inside += int(np.sum(kept[:t] & ~kept[Ck - t:]))
+    assert t == 0 or inside > 0                 # rows that stop between two twins
 
 
 def test_select_ties_and_equal_sizes(svg2, oracle):
@@ -619,7 +631,7 @@ def test_attention_tile_loop_edges_random_small_shapes(svg2, oracle, d):
 
 @pytest.mark.parametrize("d", [128, 64])
 def test_attention_f32_key_blocks_shared_by_the_wavefronts(svg2, oracle, d):
-    """The fp32 kernel deals the 32-key blocks of a work item out to four wavefronts and adds their shares at the end:
+    """The fp32 kernel deals the 32-key blocks of a work item out to eight wavefronts and adds their shares at the end:
     key counts on both sides of every count of blocks from none to nine (some wavefronts then have nothing), query
     clusters of 1 to 70 rows, key clusters of a few rows, permuted and gather-free."""
     r = np.random.default_rng(9100 + d)
