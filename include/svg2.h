@@ -43,8 +43,9 @@
  *     stay fp32 means: the cluster sums are formed in double precision and
  *     rounded once) and its labels are those of exact arithmetic on these
  *     operands (a token whose two best candidates are closer than the rounding
- *     error of the fp32 contraction is re-decided in double precision); for
- *     fp32 input the labels are those of fp32 arithmetic; tokens keep their
+ *     error of the fp32 contraction is re-decided in double precision, whose
+ *     sums are exact while the products span no more than some 30 binary
+ *     orders); for fp32 input the labels are those of fp32 arithmetic; tokens keep their
  *     original order inside a cluster;
  *     top-p keeps the cluster whose mass crosses p; equal P' goes to the lower
  *     index; empty key clusters are never selected; softmax is renormalised
