@@ -271,23 +271,25 @@ __global__ __launch_bounds__(SCAN_THREADS) void permute_sort_head_kernel(SortArg
 }
 
 // dst[h, r, :] = src[h, perm[h, r], :] for up to three tensors, each with its permutation, in one launch; a row is
-// `lanes_per_row` lanes of 16 bytes, and a lane has GATHER_UB rows in flight (the compiler keeps three of the four in 16 KB of
-// LDS until they are stored).  (One row at a time, 256 rows per workgroup
-// whatever the size and a launch each for Q and for K and V: 42 instead of 26 us for 4 heads of 9601 tokens in fp32, 110
-// instead of 104 us for 24 heads of 16,384 in bf16; 40 of 75,600: 0.89 ms both, the rate of a large copy.)
+// `lanes_per_row` lanes of 16 bytes, and a lane has GATHER_UB rows in flight.  Large layers run at the rate of a large copy
+// (two tensors of 8 heads of 118,800 rows, fp32: 386 us), small ones at the latency of two dependent loads: 4 heads of 9601
+// rows in fp32, D = 128: 12.4 us, one head of 4096 in bf16: 3.0 us.  (One row at a time, 256 rows per workgroup whatever the
+// size: 22 and 7.6 us.  With the rows in flight as HIP's uint4, a class whose arrays the compiler moves to LDS: 22 and 10.2
+// us, and 20.7 instead of 9.8 us for one head of 118,800 rows of 128 bytes.)
 static constexpr int GATHER_UB = 4;
 
+typedef __attribute__((ext_vector_type(4))) unsigned gather_vec;
 struct GatherPtrs {
-    const uint4 *src[3];
-    uint4 *dst[3];
+    const gather_vec *src[3];
+    gather_vec *dst[3];
     const int32_t *perm[3];
 };
 
 __global__ __launch_bounds__(256) void permute_gather_kernel(GatherPtrs p, int N, int lanes_per_row, int rows_per_block)
 {
     const int h = blockIdx.y, t = blockIdx.z;
-    const uint4 *src = (t == 0 ? p.src[0] : t == 1 ? p.src[1] : p.src[2]) + (size_t)h * N * lanes_per_row;
-    uint4 *dst = (t == 0 ? p.dst[0] : t == 1 ? p.dst[1] : p.dst[2]) + (size_t)h * N * lanes_per_row;
+    const gather_vec *src = (t == 0 ? p.src[0] : t == 1 ? p.src[1] : p.src[2]) + (size_t)h * N * lanes_per_row;
+    gather_vec *dst = (t == 0 ? p.dst[0] : t == 1 ? p.dst[1] : p.dst[2]) + (size_t)h * N * lanes_per_row;
     const int32_t *pm = (t == 0 ? p.perm[0] : t == 1 ? p.perm[1] : p.perm[2]) + (size_t)h * N;
     const int r0 = blockIdx.x * rows_per_block;
     const int r1 = min(N, r0 + rows_per_block);
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(GatherPtrs p, int N
     const int sub = threadIdx.x / lanes_per_row, part = threadIdx.x % lanes_per_row;
     for (int r = r0 + sub; r < r1; r += GATHER_UB * rows_per_pass) {
         int s[GATHER_UB];
-        uint4 v[GATHER_UB];
+        gather_vec v[GATHER_UB];
 #pragma unroll
         for (int u = 0; u < GATHER_UB; ++u) s[u] = pm[min(r + u * rows_per_pass, r1 - 1)];
 #pragma unroll
@@ -347,8 +349,8 @@ static void gather_launch(const int32_t *const *perm, int H, int N, int n_tensor
 {
     GatherPtrs p = {};
     for (int t = 0; t < n_tensors; ++t) {
-        p.src[t] = static_cast<const uint4 *>(src[t]);
-        p.dst[t] = static_cast<uint4 *>(dst[t]);
+        p.src[t] = static_cast<const gather_vec *>(src[t]);
+        p.dst[t] = static_cast<gather_vec *>(dst[t]);
         p.perm[t] = perm[t];
     }
     const int row_bytes = d * (dtype == SVG2_BF16 ? 2 : 4);
