@@ -1,6 +1,6 @@
 // Centroid-based top-p selection (paper Section 4.2).
 //
-//   select_scores_kernel   cq_i . ck_j for all pairs, on the matrix cores
+//   select_scores_kernel   cq_i . ck_j for all pairs, on the matrix cores (not for few rows, select_fused)
 //   select_row_kernel      one workgroup per (head, query cluster i):
 //       S_ij  = cq_i . ck_j / sqrt(d)                                  (Eq. 1)
 //       P'_ij = |K_j| exp(S_ij) / sum_k |K_k| exp(S_ik)                (Eq. 2)
@@ -243,12 +243,12 @@ __device__ __forceinline__ void block_sort(unsigned long long (&key)[E], int n, 
     }
 }
 
-// `lists` comes in with the scores of the row (as floats) and goes out with the kept clusters.  E = next power of two of
+// `lists` comes in with the scores of the row (as floats; FUSED: they are formed here) and goes out with the kept clusters.  E = next power of two of
 // Ck over 256 (at least 1).
 // Dynamic LDS layout: u64 key[256 E], later the sorted order as int[256 E] | float P[Ck] | int flag[Ck]
-template <int E>
+template <int E, bool FUSED>
 __global__ __launch_bounds__(SEL_THREADS) void select_row_kernel(
-    const int32_t *__restrict__ counts_q, const int32_t *__restrict__ counts_k, int Cq, int Ck, int d, int npow2,
+    const float *__restrict__ cq, const float *__restrict__ ck, const int32_t *__restrict__ counts_q, const int32_t *__restrict__ counts_k, int Cq, int Ck, int d, int npow2,
     float top_p, float *__restrict__ p_est, int32_t *lists, int32_t *__restrict__ row_len,
     int32_t *__restrict__ row_keys)
 {
@@ -260,16 +260,35 @@ __global__ __launch_bounds__(SEL_THREADS) void select_row_kernel(
     __shared__ float s_red[SEL_THREADS / 64];
     __shared__ int32_t s_red_i[SEL_THREADS / 64];
     __shared__ float s_scan[SEL_THREADS];
+    __shared__ __align__(16) float s_cq[FUSED ? 128 : 1];
 
     const int i = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int32_t *cnt = counts_k + (size_t)h * Ck;
     const int32_t *sc = lists + ((size_t)h * Cq + i) * Ck;
+    if (FUSED) {
+        if (tid < d) s_cq[tid] = cq[((size_t)h * Cq + i) * d + tid];
+        __syncthreads();
+    }
+    auto score = [&](int j) {                           // cq_i . ck_j
+        if (!FUSED) return __int_as_float(sc[j]);
+        const float4 *row = reinterpret_cast<const float4 *>(ck + ((size_t)h * Ck + j) * d);
+        float acc = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < d / 4; ++k) {
+            const float4 v = row[k], q = reinterpret_cast<const float4 *>(s_cq)[k];
+            acc = fmaf(q.x, v.x, acc);
+            acc = fmaf(q.y, v.y, acc);
+            acc = fmaf(q.z, v.z, acc);
+            acc = fmaf(q.w, v.w, acc);
+        }
+        return acc;
+    };
 
     // Eq. 1
     const float inv_sqrt_d = 1.0f / sqrtf((float)d);
     float mx = -INFINITY;
     for (int j = tid; j < Ck; j += SEL_THREADS) {
-        const float s = __int_as_float(sc[j]) * inv_sqrt_d;
+        const float s = score(j) * inv_sqrt_d;
         s_P[j] = s;
         if (cnt[j] > 0) mx = fmaxf(mx, s);
     }
@@ -409,16 +428,28 @@ static size_t select_lds_bytes(int Ck)
     return (size_t)std::max(next_pow2(Ck), SEL_THREADS) * sizeof(unsigned long long) + (size_t)Ck * (sizeof(float) + sizeof(int32_t));
 }
 
-typedef void (*SelectRowKernel)(const int32_t *, const int32_t *, int, int, int, int, float, float *, int32_t *,
-                                int32_t *, int32_t *);
-static SelectRowKernel select_row(int Ck)
+// Scores in the row kernel, a key cluster per thread (the same chain of fmaf), or from a kernel of their own?  The former
+// saves a launch and a round trip through memory, but every query cluster reads the key centroids again, and a 32 x 128 tile
+// of the latter is used as far as Cq and Ck fill it.  Kernel times in us, in the row kernel / in their own (D = 64):
+//   1 head x 16 x 32: 11.1 / 12.9     1 x 200 x 256: 14.8 / 17.0     40 x 12 x 64 (480 rows): 13.1 / 15.4
+//   24 x 100 x 100 (2400 rows): 24.9 / 22.8     40 x 50 x 128: 22.3 / 19.7     2000 x 10 x 30: 92 / 83
+//   2000 x 3 x 5: 28 / 36             30,000 x 1 x 1: 146 / 250
+static bool select_fused(int H, int Cq, int Ck)
 {
+    return (Ck <= SEL_THREADS && (long long)H * Cq <= 1024) || (Ck <= 32 && Cq <= 8);
+}
+
+typedef void (*SelectRowKernel)(const float *, const float *, const int32_t *, const int32_t *, int, int, int, int, float,
+                                float *, int32_t *, int32_t *, int32_t *);
+static SelectRowKernel select_row(int Ck, bool fused)
+{
+    if (fused) return select_row_kernel<1, true>;
     const int e = next_pow2(Ck) / SEL_THREADS;
-    return e <= 1   ? select_row_kernel<1>
-           : e == 2 ? select_row_kernel<2>
-           : e == 4 ? select_row_kernel<4>
-           : e == 8 ? select_row_kernel<8>
-                    : select_row_kernel<16>;
+    return e <= 1   ? select_row_kernel<1, false>
+           : e == 2 ? select_row_kernel<2, false>
+           : e == 4 ? select_row_kernel<4, false>
+           : e == 8 ? select_row_kernel<8, false>
+                    : select_row_kernel<16, false>;
 }
 static_assert(SVG2_MAX_CLUSTERS == 16 * SEL_THREADS, "16 keys per thread cover the largest number of clusters");
 
@@ -426,7 +457,7 @@ static_assert(SVG2_MAX_CLUSTERS == 16 * SEL_THREADS, "16 keys per thread cover t
 int select_prepare()
 {
     SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(select_scores_kernel<128>), select_scores_lds<128>()));
-    return set_dynamic_lds(reinterpret_cast<const void *>(select_row_kernel<16>), select_lds_bytes(SVG2_MAX_CLUSTERS));
+    return set_dynamic_lds(reinterpret_cast<const void *>(select_row_kernel<16, false>), select_lds_bytes(SVG2_MAX_CLUSTERS));
 }
 
 int select_launch(const float *cq, const float *ck, const int32_t *counts_q, const int32_t *counts_k,
@@ -437,12 +468,15 @@ int select_launch(const float *cq, const float *ck, const int32_t *counts_q, con
     int32_t *lists = c.take<int32_t>((size_t)H * Cq * Ck);
     int32_t *row_len = c.take<int32_t>((size_t)H * Cq);
     int32_t *row_keys = c.take<int32_t>((size_t)H * Cq);
-    auto scores = d == 128 ? select_scores_kernel<128> : select_scores_kernel<64>;
-    hipLaunchKernelGGL(scores, dim3(cdiv(Ck, 128), cdiv(Cq, 32), H), dim3(256),
-                       d == 128 ? select_scores_lds<128>() : select_scores_lds<64>(), st, cq, ck, Cq, Ck,
-                       reinterpret_cast<float *>(lists));
-    hipLaunchKernelGGL(select_row(Ck), dim3(Cq, H), dim3(SEL_THREADS), select_lds_bytes(Ck), st, counts_q, counts_k, Cq, Ck,
-                       d, next_pow2(Ck), top_p, p_est, lists, row_len, row_keys);
+    const bool fused = select_fused(H, Cq, Ck);
+    if (!fused) {
+        auto scores = d == 128 ? select_scores_kernel<128> : select_scores_kernel<64>;
+        hipLaunchKernelGGL(scores, dim3(cdiv(Ck, 128), cdiv(Cq, 32), H), dim3(256),
+                           d == 128 ? select_scores_lds<128>() : select_scores_lds<64>(), st, cq, ck, Cq, Ck,
+                           reinterpret_cast<float *>(lists));
+    }
+    hipLaunchKernelGGL(select_row(Ck, fused), dim3(Cq, H), dim3(SEL_THREADS), select_lds_bytes(Ck), st, cq, ck, counts_q,
+                       counts_k, Cq, Ck, d, next_pow2(Ck), top_p, p_est, lists, row_len, row_keys);
     hipLaunchKernelGGL(select_compact_kernel, dim3(cdiv(Cq, SEL_ROWS), H), dim3(SEL_THREADS), 0, st, lists, row_len,
                        row_keys, counts_q, counts_k, Cq, Ck, row_ptr, col_idx, density);
     SVG2_HIP_CHECK(hipGetLastError());

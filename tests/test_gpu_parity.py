@@ -155,6 +155,22 @@ def test_select_edges_of_the_score_tiles_and_of_the_sort(svg2, oracle, H, Cq, Ck
     assert t == 0 or inside > 0                 # rows that stop between two twins
 
 
+@pytest.mark.parametrize("H,Cq,Ck,d", [(11, 100, 129, 128), (6, 171, 256, 64), (115, 9, 32, 64), (129, 8, 33, 128)])
+def test_select_scores_in_the_row_kernel_and_in_their_own(svg2, H, Cq, Ck, d):
+    """All heads in one call (rows enough that the scores come from their own kernel) and every head by itself (formed in
+    the row kernel): the same chain of fmaf, so the same bits."""
+    r = np.random.default_rng(1300 + H)
+    cq, ck = (to_dev((1.3 * r.standard_normal((H, c, d))).astype(np.float32)) for c in (Cq, Ck))
+    nq, nk = (to_dev(r.integers(0, 50, size=(H, c)).astype(np.int32)) for c in (Cq, Ck))
+    every = svg2.svg2_select_topp(cq, ck, nq, nk, 0.9, want_p_est=True)
+    for h in range(0, H, max(1, H // 12)):
+        one = svg2.svg2_select_topp(cq[h:h + 1], ck[h:h + 1], nq[h:h + 1], nk[h:h + 1], 0.9, want_p_est=True)
+        torch.cuda.synchronize()
+        n = int(one.row_ptr[0, -1])
+        assert torch.equal(every.row_ptr[h], one.row_ptr[0]) and torch.equal(every.p_est[h], one.p_est[0])
+        assert torch.equal(every.col_idx[h].flatten()[:n], one.col_idx[0].flatten()[:n])
+
+
 def test_select_ties_and_equal_sizes(svg2, oracle):
     # identical centroids: all P' equal, ties resolved towards the lower index on both sides
     cq = np.zeros((1, 3, 64), dtype=np.float32)
