@@ -743,8 +743,8 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
 }
 
 // ---------------------------------------------------------------- fp32 kernel
-// grid (tile list), block 64 * F32_NW.  A work item is 32 consecutive rows of one query cluster; its key sequence is
-// cut into blocks of 32 keys which the wavefronts take in turn (wavefront w: blocks w, w + F32_NW, ..), each with its own
+// grid (tile list), block 64 * NW.  A work item is 32 consecutive rows of one query cluster; its key sequence is
+// cut into blocks of 32 keys which the wavefronts take in turn (wavefront w: blocks w, w + NW, ..), each with its own
 // running softmax over its share of the keys; the shares are put together through LDS at the end.  So a short layer
 // (one head of 4096 tokens is 128 work items) still puts work on 512 SIMDs, and no wavefront waits for another
 // before the end.  The list runs longest first: 1400 work items of very different lengths on 256 CUs in head-major order
@@ -767,11 +767,14 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
 // 154 TFLOP/s a large fp32 product reaches; a seventh of the rows of the 32-row tiles is padding), and 760 instead of
 // 31 us for one head of 4096 tokens at d = 64.  K rows through LDS (whole rows, direct loads, read back by row) instead of
 // 16 bytes of a row of its own per lane: 0.88 instead of 0.81 ms, so it is not these loads that bound it.
-static constexpr int F32_NW = 8;
+// No more wavefronts than a head has key blocks, rounded up to a power of two (5000 heads of 16 tokens, D = 64: 58 us with one,
+// 105 with eight), and four instead of eight in short heads that are work items enough without (3000 heads of 100 tokens, 10
+// and 20 clusters, a quarter selected: 302 instead of 495 us; 200 of 500, 30 and 60 clusters, D = 128: 208 instead of 276).
+static constexpr int F32_NW = 8, F32_MANY = 1024, F32_SHORT = 512;
 static constexpr int F32_BM = 32;
 
-template <int D>
-__global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
     const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int Cq, int Ck,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ tile_base, const int32_t *__restrict__ order, int max_tiles,
@@ -783,8 +786,8 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     constexpr int ROW = D + 4;                  // LDS row of the final sum, padded
     constexpr int RB = D * 4;                   // bytes per row
     typedef float fvec __attribute__((ext_vector_type(DVB)));
-    extern __shared__ __align__(16) float s_o[];        // [F32_NW][32][ROW]
-    __shared__ float s_m[F32_NW][32], s_l[F32_NW][32];
+    extern __shared__ __align__(16) float s_o[];        // [NW][32][ROW]
+    __shared__ float s_m[NW][32], s_l[NW][32];
     // the list of all heads' tiles, longest first, handed out in groups of `group` per XCD (as in the bf16 kernel)
     const int tid = threadIdx.x;
     const int pos = attn_list_pos(group);
@@ -861,9 +864,9 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
         off = row_off(wave);
         load_k(bufA, off, 0);
     }
-    for (int j = wave; j < nblk; j += F32_NW) {
+    for (int j = wave; j < nblk; j += NW) {
         load_k(bufB, off, 1);
-        const int jn = j + F32_NW;
+        const int jn = j + NW;
         const unsigned off_n = row_off(min(jn, nblk - 1));
         F32_FENCE
         f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -942,7 +945,7 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     __syncthreads();
     float m_all = s_m[0][col];
 #pragma unroll
-    for (int w = 1; w < F32_NW; ++w) m_all = fmaxf(m_all, s_m[w][col]);
+    for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][col]);
     const float f = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_all);
     float *so = s_o + (size_t)(wave * 32 + col) * ROW;
 #pragma unroll
@@ -955,14 +958,14 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void attn_f32_kernel(
     }
     __syncthreads();
     constexpr int LPR = D / 4;                  // lanes per row of the result
-    for (int r = tid / LPR; r < nrows; r += 64 * F32_NW / LPR) {
+    for (int r = tid / LPR; r < nrows; r += 64 * NW / LPR) {
         const int c4 = (tid % LPR) * 4;
         float mm = s_m[0][r], lt = 0.f;
 #pragma unroll
-        for (int w = 1; w < F32_NW; ++w) mm = fmaxf(mm, s_m[w][r]);
+        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][r]);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int w = 0; w < F32_NW; ++w) {
+        for (int w = 0; w < NW; ++w) {
             lt += s_l[w][r] * (s_m[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[w][r] - mm));
             const float4 v = *reinterpret_cast<const float4 *>(s_o + (size_t)(w * 32 + r) * ROW + c4);
             acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
@@ -989,13 +992,25 @@ static size_t attn_lds_bytes(int d, int Ck)
            (size_t)std::min(Ck + 1, ATT_RUN_LDS) * sizeof(int2);
 }
 
-static size_t attn_f32_lds_bytes(int d) { return (size_t)F32_NW * F32_BM * (d + 4) * sizeof(float); }
+static size_t attn_f32_lds_bytes(int d, int nw) { return (size_t)nw * F32_BM * (d + 4) * sizeof(float); }
+
+static int attn_f32_nw(int H, int N)
+{
+    const bool many = (long long)H * cdiv(N, F32_BM) >= F32_MANY && N <= F32_SHORT;
+    int nw = 1;
+    while (nw < (many ? F32_NW / 2 : F32_NW) && 32 * nw < N) nw *= 2;
+    return nw;
+}
 
 int attn_prepare(int dtype, int d)
 {
     if (dtype != SVG2_BF16) {
-        if (d == 128) return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128>), attn_f32_lds_bytes(d));
-        return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<64>), attn_f32_lds_bytes(d));
+        // (with fewer wavefronts than F32_NW less than 64 KB of LDS except at D = 128 and four)
+        if (d == 128) {
+            SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, 4>), attn_f32_lds_bytes(d, 4)));
+            return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, F32_NW>), attn_f32_lds_bytes(d, F32_NW));
+        }
+        return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<64, F32_NW>), attn_f32_lds_bytes(d, F32_NW));
     }
     const size_t lds = attn_lds_bytes(d, SVG2_MAX_CLUSTERS);
     if (d == 128) {
@@ -1050,8 +1065,16 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
                     *v = static_cast<const float *>(Vp);
         float *o = static_cast<float *>(O);
         static_assert(F32_BM == attn_bm(SVG2_F32), "the plan cuts query clusters into the tiles of this kernel");
-        auto kern = d == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>;
-        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * F32_NW), attn_f32_lds_bytes(d), st, q, k, v, H, N, Cq, Ck,
+        const int nw = attn_f32_nw(H, N);
+        auto kern = d == 128 ? (nw == 1   ? attn_f32_kernel<128, 1>
+                                : nw == 2 ? attn_f32_kernel<128, 2>
+                                : nw == 4 ? attn_f32_kernel<128, 4>
+                                          : attn_f32_kernel<128, F32_NW>)
+                             : (nw == 1   ? attn_f32_kernel<64, 1>
+                                : nw == 2 ? attn_f32_kernel<64, 2>
+                                : nw == 4 ? attn_f32_kernel<64, 4>
+                                          : attn_f32_kernel<64, F32_NW>);
+        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * nw), attn_f32_lds_bytes(d, nw), st, q, k, v, H, N, Cq, Ck,
                            row_ptr, perm_q, perm_k, tiles, tile_base, a.order, max_tiles, runs, row_keys, a.tile_run,
                            a.key_tiles, scale * 1.4426950408889634f, group, o, lse);
     }
