@@ -249,8 +249,6 @@ __device__ __forceinline__ float add_bf16x2(unsigned w, float acc)
 
 // RUN_CAP: the launch was sized for at most ATT_RUN_LDS runs in LDS (more than that many key clusters); a work item
 // with more runs then reads them from global memory.  Without it the table always fits and that path does not exist.
-// What the kernel spills (62 registers at D = 128, 13 at D = 64) goes out and in around the last tile and in the rare copies of
-// `relevel`; the tile loop has no scratch access.
 // At D = 64 a third workgroup fits a CU as long as a wavefront takes 168 registers: without that limit the compiler takes
 // 183 and dense attention of 20 heads of 4000 tokens takes 138 instead of 121 us.
 template <int D, bool RUN_CAP>
@@ -703,9 +701,12 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
         if (kt >= ntile - 1) break;
         ATT_TILE(1, true)
     }
-    if (ntile > 0) {                            // the last tile: nothing follows it, maybe ragged
-        if (kt % NSTG == 0) ATT_TILE(0, false)
-        else ATT_TILE(1, false)
+    if (ntile > 0) {                            // the last tile: nothing follows it, maybe ragged; one copy for both buffers
+        if (kt % NSTG != 0) {
+#pragma unroll
+            for (int b = 0; b < DVB; ++b) voff[b] += TILE_B;
+        }
+        ATT_TILE(0, false)
     }
 #undef ATT_TILE
 #undef ATT_FENCE
