@@ -249,8 +249,8 @@ __device__ __forceinline__ float add_bf16x2(unsigned w, float acc)
 
 // RUN_CAP: the launch was sized for at most ATT_RUN_LDS runs in LDS (more than that many key clusters); a work item
 // with more runs then reads them from global memory.  Without it the table always fits and that path does not exist.
-// At D = 64 a third workgroup fits a CU as long as a wavefront takes 168 registers: without that limit the compiler takes
-// 183 and dense attention of 20 heads of 4000 tokens takes 138 instead of 121 us.
+// At D = 64 a third workgroup fits a CU as long as a wavefront takes 168 registers at most (the compiler takes 154): dense
+// attention of 20 heads of 4000 tokens took 138 us with 183 registers and two workgroups, 118 now.
 template <int D, bool RUN_CAP>
 __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, int H, int N, int Cq,
