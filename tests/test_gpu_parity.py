@@ -662,6 +662,23 @@ def test_attention_f32_key_blocks_shared_by_the_wavefronts(svg2, oracle, d):
         _attn_case(oracle, svg2, Q, K, V, lq, lk, sel, "f32", tol=(1e-4, 1e-5))
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N", [(1, 32), (2, 33), (3, 64), (1, 65), (2, 128), (5, 129), (64, 512), (63, 512), (61, 513), (205, 129)])
+def test_attention_f32_wavefronts_of_a_work_item(svg2, d, H, N):
+    """One to eight wavefronts by the length of a head, four up to 512 tokens from 1024 work items on: both sides of
+    these limits, dense attention against torch (1e-4: fp32 sums of up to 513 terms)."""
+    g = torch.Generator(device="cuda").manual_seed(N + H)
+    Q, K, V = (torch.randn((H, N, d), device="cuda", generator=g) for _ in range(3))
+    off = torch.tensor([[0, N]], dtype=torch.int32, device="cuda").repeat(H, 1)
+    ptr = torch.tensor([[0, 1]], dtype=torch.int32, device="cuda").repeat(H, 1)
+    col = torch.zeros((H, 1), dtype=torch.int32, device="cuda")
+    res = svg2.svg2_sparse_attn(Q, K, V, off, off, ptr, col, want_lse=True)
+    torch.cuda.synchronize()
+    S = Q @ K.transpose(1, 2).contiguous() / float(np.sqrt(d))
+    assert (res.O - torch.softmax(S, dim=2) @ V).abs().max().item() <= 1e-4
+    assert (res.lse - torch.logsumexp(S, dim=2)).abs().max().item() <= 1e-4
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("lo,hi", [(64, 96), (224, 257), (100, 600), (32, 601)])
