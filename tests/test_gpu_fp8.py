@@ -337,3 +337,28 @@ def test_sparse_attn_fp8_very_short_sequences(svg2, oracle, N):
     # with a handful of keys the rounding errors of a row do not average out: only the worst-case figures apply
     _check_head(oracle, O, lse, Q, K, V, d, ident, ident, off, off, np.array([0, 1], dtype=np.int32),
                 np.zeros(1, dtype=np.int32), lse_mean=LSE_MAX, statistical=False)
+
+
+@pytest.mark.parametrize("N", [192, 257, 447, 769, 1984, 1985, 2112])
+def test_sparse_attn_fp8_tile_counts_and_a_late_large_score(svg2, oracle, N):
+    # 3 to 33 tiles of 64 keys, last ones of 1, 63 and 64: every position of the loop over three buffers, and rows short of and
+    # beyond the 32 tiles from which a sample of the keys sets the level.  For a third of the queries the last key but one, which
+    # is in no sample, has a score far above all others: their level moves in the last tile.
+    r = np.random.default_rng(500 + N)
+    d = 128
+    Q, K, V = (r.standard_normal((N, d)).astype(np.float32) for _ in range(3))
+    Q[::3] = Q[0] + 0.3 * Q[::3]
+    K[N - 2] = Q[0]
+    Q, K, V = wl.round_to_bf16(Q), wl.round_to_bf16(K), wl.round_to_bf16(V)
+    (Q8, sq), (K8, sk), (V8, sv) = _quantise_all(svg2, to_dev(Q[None], "bf16"), to_dev(K[None], "bf16"),
+                                                 to_dev(V[None], "bf16"))
+    one = to_dev(np.array([[0, N]], dtype=np.int32))
+    res = svg2.svg2_sparse_attn_fp8(Q8, K8, V8, sq, sk, sv, one, one, to_dev(np.array([[0, 1]], dtype=np.int32)),
+                                    to_dev(np.zeros((1, 1), dtype=np.int32)), None, None, want_lse=True)
+    torch.cuda.synchronize()
+    O, lse = to_np(res.O[0]).astype(np.float64), to_np(res.lse[0]).astype(np.float64)
+    ident = np.arange(N, dtype=np.int32)
+    off = np.array([0, N], dtype=np.int32)
+    # one key holds most of the weight of a third of the rows: the worst-case bounds only
+    _check_head(oracle, O, lse, Q, K, V, d, ident, ident, off, off, np.array([0, 1], dtype=np.int32),
+                np.zeros(1, dtype=np.int32), lse_mean=LSE_MAX, statistical=False)
