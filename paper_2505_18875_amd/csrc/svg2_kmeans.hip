@@ -147,6 +147,41 @@ __device__ __forceinline__ KmHalves km_halves(unsigned x)
     return {r[0], r[1]};
 }
 
+// sum of a double over the wavefront, in every lane: v += (v of lane ^ o) for o = 32, 16, 8, 4, 2, 1 -- lane swaps and data-parallel
+// moves instead of shuffles through the LDS crossbar.  (Behind the steps 32 .. 8 lanes i and i ^ 8 hold the same, so a rotation by
+// 4 in a row of 16 is the exchange with lane ^ 4.)
+template <int CTRL> __device__ __forceinline__ double km_dpp(double v)
+{
+    const unsigned long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double km_join(unsigned lo, unsigned hi) { return __longlong_as_double(((unsigned long long)hi << 32) | lo); }
+__device__ __forceinline__ double km_sum_xor32(double v)
+{
+    const unsigned long long b = __double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return km_join(l[0], h[0]) + km_join(l[1], h[1]);
+}
+__device__ __forceinline__ double km_sum_xor16(double v)
+{
+    const unsigned long long b = __double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return km_join(l[0], h[0]) + km_join(l[1], h[1]);
+}
+__device__ __forceinline__ double km_wave_sum(double v)
+{
+    v = km_sum_xor16(km_sum_xor32(v));
+    v += km_dpp<0x128>(v);                      // row_ror:8
+    v += km_dpp<0x124>(v);                      // row_ror:4
+    v += km_dpp<0x4E>(v);                       // quad_perm [2,3,0,1]
+    v += km_dpp<0xB1>(v);                       // quad_perm [1,0,3,2]
+    return v;
+}
+
 // double -> bf16, round to nearest even, in ONE rounding: via float unless the float lands exactly on the midpoint
 // of two bf16 values, where the side the double was on decides (and an exact midpoint goes to even).
 __device__ __forceinline__ bf16_t f64_to_bf16(double m)
@@ -1180,6 +1215,284 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
     });
 }
 
+// ---------------------------------------------------------------- all iterations of a short head, bf16
+// grid (H, sides), block 1024: a head of at most KM_TINY_N tokens goes through all its iterations in one workgroup --
+// wavefront w holds tokens 64 w .. + 64 as the B operand of the assign step, and centroids, labels, order and the
+// sums of the pieces (KM_TINY_SEG rows of one cluster) stay in LDS.  Same labels, order, cluster sums and means as the kernels above:
+// near-ties are settled in double precision over every centroid, and the sums of the bf16 rows are exact.
+//
+// Such a head is bound by launches that depend on each other (four of 4 to 8 us per iteration), here by the chain of short
+// phases between barriers, most of all the sums: 12 us per iteration at D = 64 and 32 clusters.  Up to KM_TINY_CD / D clusters, beyond which
+// the pieces and means of one workgroup take longer than the launches.  Five iterations in us, the launches / this kernel:
+//   1 head x 1024, D = 64, 16 clusters: 104 / 48      2 x 1024, 64, 32: 98 / 59       2 x 1024, 64, 64: 102 / 87
+//   128 x 1024, 64, 32: 167 / 68                      2 x 1024, 128, 32: 125 / 101    2 x 1024, 128, 64: 116 / 124 (not taken)
+//   2000 x 300, 64, 8: 556 / 262                      one cluster of all tokens, 2 x 1024, 64, 32: 104 / 49
+static constexpr int KM_TINY_N = 1024, KM_TINY_CD = 4096, KM_TINY_SEG = 64, KM_TINY_NW = KM_TINY_N / 64;
+
+static size_t kmeans_tiny_lds(int d, int C)
+{
+    const size_t cp = (size_t)(C + 31) / 32 * 32;
+    return (KM_TINY_NW + C) * (size_t)d * sizeof(double) + cp * (d + 8) * sizeof(bf16_t) + cp * sizeof(float) + (C + 1) * sizeof(double) +
+           (size_t)KM_TINY_NW * C * sizeof(int32_t) + 2 * (size_t)(C + 1) * sizeof(int32_t) + (3 * (size_t)KM_TINY_N + KM_TINY_NW + C) * sizeof(int32_t);
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * KM_TINY_NW) void kmeans_tiny_bf16_kernel(KmArgs a)
+{
+    constexpr int KS = D / 16, ROW = D + 8, EL = D / 64, NW = KM_TINY_NW;
+    constexpr int LPR = D / 8, RPI = 64 / LPR;      // lanes per row and rows per load instruction of the sums
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    __shared__ int32_t s_nflag;
+    const KmSide S = blockIdx.y ? a.s[1] : a.s[0];
+    const int h = blockIdx.x, N = a.N, C = S.C, CP = (C + 31) & ~31, set = (a.iters - 1) & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    double *s_ps = reinterpret_cast<double *>(s_raw);                               // [NW + C][D] sums of the pieces
+    double *s_cn = s_ps + (NW + C) * D;                                             // [C] ||c||^2
+    bf16_t *s_c = reinterpret_cast<bf16_t *>(s_cn + C + (C & 1));                   // [CP][ROW]
+    float *s_hcn = reinterpret_cast<float *>(s_c + CP * ROW);                       // [CP] -||c||^2 / 2
+    int32_t *s_hist = reinterpret_cast<int32_t *>(s_hcn + CP);                      // [NW][C]
+    int32_t *s_off = s_hist + NW * C, *s_fp = s_off + C + 1;                        // [C + 1] first row, first piece
+    int32_t *s_lab = s_fp + C + 1, *s_perm = s_lab + KM_TINY_N, *s_flag = s_perm + KM_TINY_N;
+    int32_t *s_pc = s_flag + KM_TINY_N;                                             // [NW + C] cluster of a piece
+    const bf16_t *Xh = reinterpret_cast<const bf16_t *>(S.X) + (size_t)h * N * D;
+    const int n_own = wave * 64 + lane;
+    int nbits = 0;
+    while ((1 << nbits) < C) ++nbits;
+
+    bf16x8 xb[D == 64 ? 2 : 1][KS];             // lane (col, half): elements 16 s + 8 half .. + 8 of token 64 w + 32 b + col
+    float x2[2];                                // ||x||^2
+    auto load_x = [&](int b) {
+        bf16x8 (&x)[KS] = xb[D == 64 ? b : 0];
+        int n = min(N - 1, wave * 64 + 32 * b + col);
+        asm volatile("" : "+v"(n));
+        const uint4 *src = reinterpret_cast<const uint4 *>(Xh + (size_t)n * D + 8 * half);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const uint4 v = src[2 * s];
+            __builtin_memcpy(&x[s], &v, 16);
+        }
+        float q = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bf16x2_t p2 = {x[s][2 * e], x[s][2 * e + 1]};
+                q = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, q, false);
+            }
+        const KmHalves hx = km_halves(__float_as_uint(q));
+        x2[b] = __uint_as_float(hx.lo) + __uint_as_float(hx.hi);
+    };
+    if (D == 64) { load_x(0); load_x(1); }      // (at D = 128 read again in every iteration: 64 registers)
+    for (int e = tid; e < (CP - C) * ROW; e += 64 * NW) s_c[C * ROW + e] = 0;
+    for (int j = C + tid; j < CP; j += 64 * NW) s_hcn[j] = KM_PAD_HCN;
+    // centroid c[] (element lane + 64 e) of cluster j as the next assign step reads it
+    auto put_centroid = [&](int j, const double (&c)[EL]) {
+        double n2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            const bf16_t b = f64_to_bf16(c[e]);
+            s_c[j * ROW + lane + 64 * e] = b;
+            const double cr = (double)bf16_to_f32(b), sq = km_wave_sum(cr * cr);
+            n2 = e == 0 ? sq : n2 + sq;
+        }
+        if (lane == 0) {
+            s_cn[j] = n2;
+            s_hcn[j] = (float)(-0.5 * n2);
+        }
+    };
+    for (int j = wave; j < C; j += NW) {
+        double c[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) c[e] = (double)S.init[((size_t)h * C + j) * D + lane + 64 * e];
+        put_centroid(j, c);
+    }
+
+#pragma unroll 1
+    for (int t = 0; t < a.iters; ++t) {
+        if (tid == 0) s_nflag = 0;
+        for (int c = lane; c < C; c += 64) s_hist[wave * C + c] = 0;
+        __syncthreads();
+        // ---- assign: as in kmeans_assign_bf16_kernel
+        float cmax2 = 0.f;
+        for (int j = lane; j < C; j += 64) cmax2 = fmaxf(cmax2, -2.f * s_hcn[j]);
+        for (int o = 32; o > 0; o >>= 1) cmax2 = fmaxf(cmax2, __shfl_xor(cmax2, o));
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            if (D != 64) load_x(b);
+            const bf16x8 (&x)[KS] = xb[D == 64 ? b : 0];
+            float best = -INFINITY, second = -INFINITY;
+            int bbase = 0;
+#pragma unroll 1
+            for (int rb = 0; rb < CP / 32; ++rb) {
+                f32x16 acc;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 v = *reinterpret_cast<const float4 *>(&s_hcn[rb * 32 + 8 * g + 4 * half]);
+                    acc[4 * g] = v.x; acc[4 * g + 1] = v.y; acc[4 * g + 2] = v.z; acc[4 * g + 3] = v.w;
+                }
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    bf16x8 am;
+                    const uint4 v = *reinterpret_cast<const uint4 *>(&s_c[(rb * 32 + col) * ROW + 8 * half + 16 * s]);
+                    __builtin_memcpy(&am, &v, 16);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, x[s], acc, 0, 0, 0);
+                }
+                const float before = best;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float key = __uint_as_float((__float_as_uint(acc[i]) & 0xFFFFFFF0u) | (unsigned)i);
+                    second = km_med3(best, second, key);
+                    best = km_max(best, key);
+                }
+                bbase = best > before ? rb * 32 : bbase;
+            }
+            const unsigned kb = __float_as_uint(best);
+            const int cown = bbase + 4 * half + (int)(((kb & 12u) << 1) | (kb & 3u));
+            const KmHalves hb = km_halves(kb), hs = km_halves(__float_as_uint(second)), hi = km_halves((unsigned)cown);
+            const float b0 = __uint_as_float(hb.lo), b1 = __uint_as_float(hb.hi);
+            const float T = km_max(b0, b1), U = km_max3(km_min(b0, b1), __uint_as_float(hs.lo), __uint_as_float(hs.hi));
+            const int n = wave * 64 + 32 * b + col;
+            if (half == 0 && n < N) {
+                s_lab[n] = (b1 > b0) ? (int)hi.hi : (int)hi.lo;
+                const float tau = KM_TIE_KEY * fabsf(T) + KM_TIE_ACC * (0.5f * x2[b] + cmax2);
+                if (!(T - U > tau)) s_flag[atomicAdd(&s_nflag, 1)] = n;
+            }
+        }
+        __syncthreads();
+        // ---- settle: a wavefront per listed token, a centroid per lane, every distance by the same chain of additions
+        const int nflag = s_nflag;
+        for (int f = wave; f < nflag; f += NW) {
+            const int n = s_flag[f];
+            const uint4 *xr = reinterpret_cast<const uint4 *>(Xh + (size_t)n * D);
+            const uint4 *cr = reinterpret_cast<const uint4 *>(s_c + min(lane, C - 1) * ROW);
+            double dot = 0.0;
+#pragma unroll 1
+            for (int q0 = 0; q0 < D / 8; q0 += 8) {
+                uint4 xv[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) xv[q] = xr[q0 + q];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    const uint4 cv = cr[q0 + q];
+                    const unsigned u[4] = {xv[q].x, xv[q].y, xv[q].z, xv[q].w}, w[4] = {cv.x, cv.y, cv.z, cv.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        dot = fma((double)__uint_as_float(u[e] << 16), (double)__uint_as_float(w[e] << 16), dot);
+                        dot = fma((double)__uint_as_float(u[e] & 0xFFFF0000u), (double)__uint_as_float(w[e] & 0xFFFF0000u), dot);
+                    }
+                }
+            }
+            double best = INFINITY;
+            int bj = 0x7FFFFFFF;
+            const double dist = s_cn[min(lane, C - 1)] - 2.0 * dot;
+            if (lane < C && dist < best) { best = dist; bj = lane; }
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ob = __shfl_xor(best, o);
+                const int oj = __shfl_xor(bj, o);
+                if (ob < best || (ob == best && oj < bj)) { best = ob; bj = oj; }
+            }
+            if (lane == 0 && bj < C) s_lab[n] = bj;     // (no distance is a number: the label stays)
+        }
+        if (nflag > 0) __syncthreads();
+        // ---- stable counting sort: a wavefront's 64 tokens are one group
+        const bool valid = n_own < N;
+        const int l = valid ? s_lab[n_own] : 0;
+        unsigned long long peers = __ballot(valid);
+        for (int b = 0; b < nbits; ++b) {
+            const unsigned long long m = __ballot((l >> b) & 1);
+            peers &= (l >> b) & 1 ? m : ~m;
+        }
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+        if (valid && rank == 0) s_hist[wave * C + l] = __popcll(peers);
+        __syncthreads();
+        if (wave == 0) {                        // (C <= 64: one lane per cluster)
+            int size = 0, cnt[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) cnt[w] = lane < C ? s_hist[w * C + lane] : 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (lane < C) s_hist[w * C + lane] = size;
+                size += cnt[w];
+            }
+            const int np = (size + KM_TINY_SEG - 1) / KM_TINY_SEG;
+            int isz = size, inp = np;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int us = __shfl_up(isz, o), up = __shfl_up(inp, o);
+                if (lane >= o) { isz += us; inp += up; }
+            }
+            if (lane < C) {
+                s_off[lane] = isz - size;
+                s_fp[lane] = inp - np;
+                for (int p = inp - np; p < inp; ++p) s_pc[p] = lane;
+                if (lane == C - 1) { s_off[C] = isz; s_fp[C] = inp; }
+            }
+        }
+        __syncthreads();
+        if (valid) s_perm[s_off[l] + s_hist[wave * C + l] + rank] = n_own;
+        __syncthreads();
+        // ---- sums of the pieces, in double precision
+        for (int p = wave; p < s_fp[C]; p += NW) {
+            const int c = s_pc[p], r0 = s_off[c] + (p - s_fp[c]) * KM_TINY_SEG, rows = min(KM_TINY_SEG, s_off[c + 1] - r0);
+            const int sub = lane / LPR, part = lane % LPR;
+            double acc[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+#pragma unroll 1
+            for (int r = 0; r < rows; r += RPI * KM_UB) {
+                uint4 v[KM_UB];
+#pragma unroll
+                for (int u = 0; u < KM_UB; ++u)
+                    v[u] = reinterpret_cast<const uint4 *>(Xh + (size_t)s_perm[r0 + min(r + u * RPI + sub, rows - 1)] * D)[part];
+#pragma unroll
+                for (int u = 0; u < KM_UB; ++u) {
+                    if (r + u * RPI + sub >= rows) continue;
+                    const unsigned w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        acc[2 * q] += (double)__uint_as_float(w[q] << 16);
+                        acc[2 * q + 1] += (double)__uint_as_float(w[q] & 0xFFFF0000u);
+                    }
+                }
+            }
+            // lanes with the same `part` hold the same columns
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (LPR == 8) acc[e] += km_dpp<0x128>(acc[e]);      // row_ror:8
+                acc[e] = km_sum_xor32(km_sum_xor16(acc[e]));
+            }
+            if (lane < LPR) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s_ps[p * D + lane * 8 + e] = acc[e];
+            }
+        }
+        __syncthreads();
+        // ---- means: one wavefront per cluster (always the same one: what an empty cluster keeps is read back by its writer)
+        for (int j = wave; j < C; j += NW) {
+            const int cnt = s_off[j + 1] - s_off[j];
+            const size_t idx = ((size_t)h * C + j) * D + lane;
+            double c[EL];
+#pragma unroll
+            for (int e = 0; e < EL; ++e) {
+                double sum = 0.0;
+                for (int p = s_fp[j]; p < s_fp[j + 1]; ++p) sum += s_ps[p * D + lane + 64 * e];
+                c[e] = cnt > 0 ? sum / (double)cnt : t == 0 ? (double)S.init[idx + 64 * e] : S.cd[idx + 64 * e];
+                S.cd[idx + 64 * e] = c[e];
+                if (t + 1 == a.iters) S.centroids[idx + 64 * e] = (float)c[e];
+            }
+            put_centroid(j, c);
+        }
+    }
+    // (the last iteration's labels, offsets and order are complete since the barrier behind the scatter)
+    if (n_own < N) {
+        S.labels[(size_t)h * N + n_own] = s_lab[n_own];
+        KM_SEL(S.perm, set)[(size_t)h * N + n_own] = s_perm[n_own];
+    }
+    for (int c = tid; c <= C; c += 64 * NW) KM_SEL(S.offsets, set)[(size_t)h * (C + 1) + c] = s_off[c];
+    for (int c = tid; c < C; c += 64 * NW) S.counts[(size_t)h * C + c] = s_off[c + 1] - s_off[c];
+}
+
 __global__ void kmeans_zero_kernel(float *p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1238,6 +1551,9 @@ template <int D> static constexpr size_t kmeans_assign_lds()
 int kmeans_prepare(int dtype, int d)
 {
     if (dtype != SVG2_BF16) return SVG2_OK;
+    const void *tiny = d == 128 ? reinterpret_cast<const void *>(kmeans_tiny_bf16_kernel<128>)
+                                : reinterpret_cast<const void *>(kmeans_tiny_bf16_kernel<64>);
+    SVG2_TRY(set_dynamic_lds(tiny, kmeans_tiny_lds(d, KM_TINY_CD / d)));
     if (d == 128) {
         SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(kmeans_assign_bf16_kernel<128, true>), kmeans_assign_lds<128>()));
         SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(kmeans_assign_bf16_kernel<128, false>), kmeans_assign_lds<128>()));
@@ -1298,6 +1614,15 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         if (a.s[s].objective) {
             any_obj = true;
             hipLaunchKernelGGL(kmeans_zero_kernel, dim3(cdiv(H * iters, 256)), dim3(256), 0, st, a.s[s].objective, H * iters);
+        }
+    }
+    if constexpr (BF16) {
+        int cmax = 0;
+        for (int s = 0; s < ns; ++s) cmax = std::max(cmax, a.s[s].C);
+        if (N <= KM_TINY_N && cmax * D <= KM_TINY_CD && !any_obj) {
+            ProfileSpan sp(SVG2_K_KMEANS_ASSIGN, st);
+            hipLaunchKernelGGL((kmeans_tiny_bf16_kernel<D>), dim3(H, ns), dim3(64 * KM_TINY_NW), kmeans_tiny_lds(D, cmax), st, a);
+            return SVG2_OK;
         }
     }
     const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);

@@ -347,6 +347,25 @@ def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
     _check_kmeans(oracle, res, X, init, 4, dtype == "bf16", H, C)
 
 
+@pytest.mark.parametrize("d,H,N,C", [
+    # one workgroup goes through all iterations of a head: its largest sizes, and one token or cluster more than it takes
+    (64, 2, 1024, 64), (128, 2, 1024, 32), (64, 1, 1025, 64), (64, 1, 1024, 65), (128, 1, 1024, 33),
+    # wavefronts without tokens, with one token, with all 64; one row block of centroids and two
+    (64, 3, 63, 2), (128, 1, 64, 31), (64, 2, 65, 33), (128, 5, 961, 17), (64, 300, 100, 5)])
+@pytest.mark.parametrize("iters", [1, 4])
+def test_kmeans_short_heads(svg2, oracle, d, H, N, C, iters):
+    """Small whole numbers as coordinates: many tokens at exactly the same distance from two centroids (the lower index wins).
+    The last centroid is out of reach and stays empty."""
+    r = np.random.default_rng(8800 + N + C + d)
+    X = r.integers(-2, 3, size=(H, N, d)).astype(np.float32)
+    X[:, : N // 3] += 3.0                                       # a third of the tokens far from the others: uneven clusters
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
+    init[:, -1] = 500.0
+    res = svg2.svg2_kmeans(to_dev(X, "bf16"), to_dev(init), iters)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, iters, True, H, C)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("C,copies", [(70, 3), (300, 4), (300, 5), (600, 40), (1100, 1100)])
 def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
