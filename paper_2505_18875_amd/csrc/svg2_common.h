@@ -63,6 +63,8 @@ struct Carver {
     }
 };
 
+int device_cu_count(int *ncu);      // compute units of the current device
+
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // ---- bf16 ------------------------------------------------------------------

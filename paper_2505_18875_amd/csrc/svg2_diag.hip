@@ -205,7 +205,22 @@ struct KppBufs {
     uint2 *row;                 // [H,N] scale and r (bf16), sum of q^2 (16 bits) and D2 rounded up (bf16)
     int32_t *picked;            // [H,C]
     int nch, cpw;               // chunks per head, chunks per workgroup
+    // kpp_loop_kernel
+    unsigned long long *rec[2]; // [H,nch,2] the sum of a chunk's D2: high half and number of draws so far, low half and the same
+    int32_t *fail;              // [H] a workgroup has given up waiting
 };
+
+// What the workgroups of a head exchange inside a launch (D2, the records) goes through relaxed atomics at device scope: these are
+// coherent over the L2s of the XCDs, location by location.  Order between locations: a wavefront waits for its stores
+// (vmcnt) in front of the barrier behind which a record is written, and reads on only once it has seen the record.
+__device__ __forceinline__ double kpp_get(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void kpp_put(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void kpp_put_rec(unsigned long long *r, double sum, unsigned draws)
+{
+    const unsigned long long b = __double_as_longlong(sum);
+    __hip_atomic_store(r, (b & 0xFFFFFFFF00000000ull) | draws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(r + 1, (b << 32) | draws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // sum over the first 256 threads, in every thread (fixed order)
 __device__ __forceinline__ double block_sum_256(double v, double *s_w)
@@ -220,8 +235,9 @@ __device__ __forceinline__ double block_sum_256(double v, double *s_w)
 // First draw: token floor(u N); every token's D2 against it and its digits.  grid (workgroups, H), block 256.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void kpp_first_kernel(const T *__restrict__ X, const double *__restrict__ u, KppBufs w,
-                                                        int N, int C, float *__restrict__ centroids)
+                                                        int N, int C, float *__restrict__ centroids, bool again)
 {
+    if (again && !w.fail[blockIdx.y]) return;
     constexpr int LPT = D / 8, G = 256 / LPT, UB = 4;       // lanes per token, tokens per pass, passes in flight
     __shared__ double s_w[4];
     const int h = blockIdx.y, tid = threadIdx.x, grp = tid / LPT, part = tid % LPT;
@@ -230,7 +246,10 @@ __global__ __launch_bounds__(256) void kpp_first_kernel(const T *__restrict__ X,
     float c[8];
     load_8(Xh + (size_t)pick * D + part * 8, c);
     if (blockIdx.x == 0 && grp == 0) {
-        if (part == 0) w.picked[(size_t)h * C] = pick;
+        if (part == 0) {
+            w.picked[(size_t)h * C] = pick;
+            if (!again) w.fail[h] = 0;
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) centroids[(size_t)h * C * D + part * 8 + j] = c[j];
     }
@@ -270,6 +289,8 @@ __global__ __launch_bounds__(256) void kpp_first_kernel(const T *__restrict__ X,
         if (tid == 0) {
             w.csum[0][(size_t)h * w.nch + ch] = sum;
             w.chg[0][(size_t)h * w.nch + ch] = 1;
+            kpp_put_rec(w.rec[0] + ((size_t)h * w.nch + ch) * 2, sum, 1);
+            kpp_put_rec(w.rec[1] + ((size_t)h * w.nch + ch) * 2, 0.0, 0);
         }
     }
 }
@@ -286,7 +307,8 @@ __device__ __forceinline__ double wave_scan(double v, int lane)
 
 // The token of a draw, found by one wavefront: the first token whose running sum of D2 exceeds uk * sum(D2), from the
 // sums cs[nch] of the chunks and then the tokens dh[N] of the chunk in which the running sum crosses.
-__device__ __forceinline__ int kpp_pick(const double *dh, const double *cs, int N, int nch, double uk, int lane)
+template <typename F>
+__device__ __forceinline__ int kpp_pick(F dh, const double *cs, int N, int nch, double uk, int lane)
 {
     constexpr int M = KPP_CHUNK / 64;
     const int per = (nch + 63) / 64, b0 = min(nch, lane * per), b1 = min(nch, b0 + per);
@@ -313,7 +335,7 @@ __device__ __forceinline__ int kpp_pick(const double *dh, const double *cs, int 
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 const int n = ch * KPP_CHUNK + lane * M + i;
-                v[i] = n < N ? dh[n] : 0.0;
+                v[i] = n < N ? dh(n) : 0.0;
                 lb += v[i];
             }
             const double li = wave_scan(lb, lane);
@@ -333,12 +355,26 @@ __device__ __forceinline__ int kpp_pick(const double *dh, const double *cs, int 
         }
         if (pick < 0) {                         // rounding left the running sum at the threshold: last token with D2 > 0
             for (int n = lane; n < N; n += 64)
-                if (dh[n] > 0.0) pick = n;
+                if (dh(n) > 0.0) pick = n;
             for (int s = 32; s > 0; s >>= 1) pick = max(pick, __shfl_xor(pick, s));
         }
     }
     if (pick < 0) pick = (int)floor(uk * (double)N);        // every D2 is zero
     return max(0, min(N - 1, pick));
+}
+
+// Whether the bound rules a token out: not nearer to the centre than to an older one.  dot = q_x . q_c.
+__device__ __forceinline__ bool kpp_ruled_out(uint2 row, int dot, float c_scale, float c_r, float c_n2)
+{
+    // ||x^ - c^||^2 from below (its three terms are each within 3 units in the last place of n2)
+    const float scale = bf16_lo(row.x), r = bf16_hi(row.x), d2_up = bf16_hi(row.y);
+    const float n2 = fmaf(scale * scale, (float)(row.y & 0xFFFFu), c_n2);
+    const float t = fmaf(-2.0f * scale * c_scale, (float)dot, n2) - 1e-6f * n2;
+    const float lb = sqrtf(fmaxf(t, 0.f)) - (r + c_r);
+    // only if the bound is an ordinary number and says so (inputs that are no numbers are measured).  Below 1e-18 squares of
+    // digit errors and scales can underflow: what is lost of r is up to 1.2e-18 and of the terms of n2 up to 1e-31, against
+    // margins of 5e-16 and 1e-24 at t = 1e-18.
+    return t > 1e-18f && t < 1e37f && lb > 0.f && lb * lb > 1.00001f * d2_up;
 }
 
 // Draw k >= 1.  grid (workgroups, H), block 320: wavefront 4 finds the token and the digits of the centre while
@@ -385,7 +421,7 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
     if (!finder) {
         load_tok(ch_lo);
     } else {
-        const int pick = kpp_pick(dh, cs, N, nch, u[(size_t)h * C + k], lane);
+        const int pick = kpp_pick([&](int n) { return dh[n]; }, cs, N, nch, u[(size_t)h * C + k], lane);
         float c[8];
         load_8(Xh + (size_t)pick * D + part * 8, c);
         // digits q = 16 hi + lo with hi in -7 .. 7, lo in -8 .. 7
@@ -436,15 +472,7 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
             dlo = __builtin_amdgcn_sdot8((int)dig[p].w, a.w, dlo, false);
         }
         dot = 16 * dot + dlo;
-        // ||x^ - c^||^2 from below (its three terms are each within 3 units in the last place of n2)
-        const float scale = bf16_lo(row.x), r = bf16_hi(row.x), d2_up = bf16_hi(row.y);
-        const float n2 = fmaf(scale * scale, (float)(row.y & 0xFFFFu), c_n2);
-        const float t = fmaf(-2.0f * scale * c_scale, (float)dot, n2) - 1e-6f * n2;
-        const float lb = sqrtf(fmaxf(t, 0.f)) - (r + c_r);
-        // leave the token out only if the bound is an ordinary number and says so (inputs that are no numbers are measured).
-        // Below 1e-18 squares of digit errors and scales can underflow: what is lost of r is up to 1.2e-18 and of the terms
-        // of n2 up to 1e-31, against margins of 5e-16 and 1e-24 at t = 1e-18.
-        const bool left = in && !(t > 1e-18f && t < 1e37f && lb > 0.f && lb * lb > 1.00001f * d2_up);
+        const bool left = in && !kpp_ruled_out(row, dot, c_scale, c_r, c_n2);
         const unsigned long long m = __ballot(left);
         int pos = 0;
         if (lane == 0 && m) pos = atomicAdd(&s_nleft, __popcll(m));
@@ -509,6 +537,250 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
     }
 }
 
+// All draws but the first in one launch: the workgroups of a head stay and wait for each other.  grid (workgroups, heads), block
+// 512.  A workgroup has cpw chunks of its head, KPP_SLOTS pairs at a time (wavefronts 0..3 the even ones, 4..7 the odd ones, a
+// token per thread and pair); with HELD these are all it has, and their digits and rows stay in registers, their D2 in LDS.
+//
+// A draw: wavefront 0 waits for the records of all chunks of the head, finds the token as kpp_step_kernel does, and puts the centre
+// and its digits into LDS; all wavefronts rule out tokens by the bound and list the others; the list is measured by
+// all; changed D2 goes to memory, then the sum of every chunk as a record (of a head with one workgroup both stay in LDS).  Two generations of D2 and
+// of the records take turns: a workgroup that writes those of draw k has seen all records of draw k - 1, so every one
+// has finished reading those of draw k - 2.
+//
+// The wait is bounded.  Workgroups of a head that do not get onto the chip together -- the launch takes at most one workgroup
+// per CU of two that fit, but other launches may wait in the same way -- give up, set fail[h], and the head is done again by
+// a single workgroup, which waits for nobody (HELD = false, `again`).
+//
+// What bounds a draw is its chain of round trips: record out and seen, the D2 of one chunk, the new centre's row, the rows that are
+// measured, D2 out.  us per draw, a launch for each / this kernel: 24 heads of 16,384 tokens (d = 128, bf16, 64 components) 13.8 /
+// 8.9, 40 of 9000 14.9 / 9.2, 10 of 30,000 (d = 64) 8.4 / 7.6, 4 of 4096 (d = 64, fp32) 6.0 / 4.7, 1000 of 900 (one workgroup
+// each) 32.5 / 15.2.  From 65,536 tokens on (more than KPP_LOOKS records to a lane) and beyond a workgroup per CU a launch
+// for each draw stays: one head of 75,600 7.1 / 7.5.
+static constexpr int KPP_SLOTS = 4;
+static constexpr int KPP_HELD_CHUNKS = 2 * KPP_SLOTS;       // chunks of a workgroup whose digits fit its registers
+static constexpr int KPP_LOOKS = 4;                         // records a lane looks at together
+static constexpr unsigned KPP_PATIENCE = 1u << 20;          // looks of a draw, about a microsecond each
+
+template <typename T, int D, bool HELD>
+__global__ __launch_bounds__(512, 4) void kpp_loop_kernel(const T *__restrict__ X, const double *__restrict__ u, KppBufs w, int N,
+                                                          int C, unsigned patience, float *__restrict__ centroids, bool again)
+{
+    constexpr int LPT = D / 8, G = 512 / LPT, UB = 4 / sizeof(T);       // UB: rows in flight per group of lanes
+    constexpr int NW = D / 8, NQ = D / 32;      // digit words and 16-byte pieces per token
+    constexpr int TOK = 512 * KPP_SLOTS;        // tokens at a time
+    extern __shared__ __align__(16) double s_cs[];      // [nch] sums of the chunks
+    __shared__ __align__(16) int s_c[2 * NW];   // digits of the centre: high, then low halves
+    __shared__ double2 s_cd[D / 2];             // the centre: elements 8 p + 2 j, + 1 at j * LPT + p
+    __shared__ KppRow s_row;
+    __shared__ double s_d2[TOK];
+    __shared__ uint2 s_tok[TOK];                // KppBufs::row of the tokens
+    __shared__ uint16_t s_left[TOK];
+    __shared__ double s_w[KPP_SLOTS][8];
+    __shared__ int s_nleft, s_stop, s_chg[2 * KPP_SLOTS];
+
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int pair = wave >> 2, gt = tid & 255;
+    const int grp = tid / LPT, part = tid % LPT;
+    if (again && !w.fail[h]) return;
+    const int nch = w.nch;
+    const T *Xh = X + (size_t)h * N * D;
+    const uint4 *qh = w.dig + (size_t)h * NQ * N;
+    uint2 *rh = w.row + (size_t)h * N;
+    // chunk i of the workgroup: neighbours go to different workgroups (the tokens near a centre often lie together)
+    const int nwg = gridDim.x;
+    const bool alone = HELD && nwg == 1;        // the D2 of the whole head is in LDS, token n at s_d2[n]
+    auto chunk = [&](int i) { return (int)blockIdx.x + nwg * i; };
+
+    uint4 dig[KPP_SLOTS][NQ] = {};
+    unsigned chg_old = 0xFFFFFFFFu;             // HELD: bit s: the chunk of slot s changed in the draw before
+    auto load_tokens = [&](int i0, const double *d2) {
+#pragma unroll
+        for (int s = 0; s < KPP_SLOTS; ++s) {
+            const int n = min(N - 1, chunk(i0 + 2 * s + pair) * KPP_CHUNK + gt);
+            s_tok[s * 512 + tid] = rh[n];
+            s_d2[s * 512 + tid] = kpp_get(d2 + n);
+#pragma unroll
+            for (int p = 0; p < NQ; ++p) dig[s][p] = qh[(size_t)p * N + n];
+        }
+    };
+    if (HELD) load_tokens(0, w.d2[0] + (size_t)h * N);
+    if (tid == 0) s_stop = 0;
+
+#pragma unroll 1
+    for (int k = 1; k < C; ++k) {
+        const int o = k & 1;
+        const double *dh = (o ? w.d2[0] : w.d2[1]) + (size_t)h * N;
+        double *dn = (o ? w.d2[1] : w.d2[0]) + (size_t)h * N;
+        if (wave == 0) {
+            const unsigned long long *rec = (o ? w.rec[0] : w.rec[1]) + (size_t)h * nch * 2;
+            bool stop = false;
+            unsigned looks = 0;
+            for (int b0 = 0; (nwg > 1 || k == 1) && b0 < nch && !stop; b0 += 64 * KPP_LOOKS) {
+                unsigned long long hi[KPP_LOOKS], lo[KPP_LOOKS];
+                for (;;) {
+                    bool all = true;
+#pragma unroll
+                    for (int i = 0; i < KPP_LOOKS; ++i) {
+                        const int b = min(b0 + 64 * i + lane, nch - 1);
+                        hi[i] = __hip_atomic_load(rec + 2 * b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        lo[i] = __hip_atomic_load(rec + 2 * b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                    for (int i = 0; i < KPP_LOOKS; ++i) all &= (unsigned)hi[i] == (unsigned)k && (unsigned)lo[i] == (unsigned)k;
+                    if (__all(all)) break;
+                    // (a head that has been given up: its other workgroups need not wait as long)
+                    if (++looks >= patience || ((looks & 255) == 0 &&
+                                                __hip_atomic_load(w.fail + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                        stop = true;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < KPP_LOOKS; ++i)
+                    if (b0 + 64 * i + lane < nch)
+                        s_cs[b0 + 64 * i + lane] = __longlong_as_double((hi[i] & 0xFFFFFFFF00000000ull) | (lo[i] >> 32));
+            }
+            if (stop) {
+                if (lane == 0) {
+                    __hip_atomic_store(w.fail + h, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s_stop = 1;
+                }
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int pick = kpp_pick([&](int n) { return alone ? s_d2[n] : kpp_get(dh + n); }, s_cs, N, nch, u[(size_t)h * C + k], lane);
+                float c[8];
+                load_8(Xh + (size_t)pick * D + part * 8, c);
+                // digits q = 16 hi + lo with hi in -7 .. 7, lo in -8 .. 7
+                int q[8], hi[8], lo[8];
+                const KppRow r = kpp_digits<LPT, 119>(c, q);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    hi[j] = (q[j] + 8) >> 4;
+                    lo[j] = q[j] - 16 * hi[j];
+                }
+                if (lane < LPT) {
+                    s_c[part] = (int)pack_nibbles(hi);
+                    s_c[NW + part] = (int)pack_nibbles(lo);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s_cd[j * LPT + part] = make_double2((double)c[2 * j], (double)c[2 * j + 1]);
+                    if (part == 0) s_row = r;
+                    if (blockIdx.x == 0) {
+                        if (part == 0) w.picked[(size_t)h * C + k] = pick;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) centroids[((size_t)h * C + k) * D + part * 8 + j] = c[j];
+                    }
+                }
+            }
+        }
+        if (k + 1 == C) return;                 // (the last centre has nobody to be measured against)
+        for (int i1 = 0; chunk(i1) < nch; i1 += KPP_HELD_CHUNKS) {
+            if (!HELD) {
+                __syncthreads();                // (the tokens before: what is in LDS has been read)
+                load_tokens(i1, dh);
+            }
+            if (tid == 0) s_nleft = 0;
+            if (tid < 2 * KPP_SLOTS) s_chg[tid] = 0;
+            __syncthreads();
+            if (s_stop) return;
+            const float c_scale = s_row.scale, c_r = s_row.r, c_n2 = c_scale * c_scale * (float)s_row.q2;
+            // ---- the bound, as in kpp_step_kernel
+#pragma unroll
+            for (int s = 0; s < KPP_SLOTS; ++s) {
+                const int ch = chunk(i1 + 2 * s + pair);
+                if (ch >= nch) break;
+                int dot = 0, dlo = 0;
+#pragma unroll
+                for (int p = 0; p < NQ; ++p) {
+                    const int4 a = *reinterpret_cast<const int4 *>(&s_c[4 * p]), b = *reinterpret_cast<const int4 *>(&s_c[NW + 4 * p]);
+                    dot = __builtin_amdgcn_sdot8((int)dig[s][p].x, a.x, dot, false);
+                    dot = __builtin_amdgcn_sdot8((int)dig[s][p].y, a.y, dot, false);
+                    dot = __builtin_amdgcn_sdot8((int)dig[s][p].z, a.z, dot, false);
+                    dot = __builtin_amdgcn_sdot8((int)dig[s][p].w, a.w, dot, false);
+                    dlo = __builtin_amdgcn_sdot8((int)dig[s][p].x, b.x, dlo, false);
+                    dlo = __builtin_amdgcn_sdot8((int)dig[s][p].y, b.y, dlo, false);
+                    dlo = __builtin_amdgcn_sdot8((int)dig[s][p].z, b.z, dlo, false);
+                    dlo = __builtin_amdgcn_sdot8((int)dig[s][p].w, b.w, dlo, false);
+                }
+                const bool left = ch * KPP_CHUNK + gt < N && !kpp_ruled_out(s_tok[s * 512 + tid], 16 * dot + dlo, c_scale, c_r, c_n2);
+                const unsigned long long m = __ballot(left);
+                int pos = 0;
+                if (lane == 0 && m) pos = atomicAdd(&s_nleft, __popcll(m));
+                pos = __builtin_amdgcn_readfirstlane(pos) + __popcll(m & ((1ull << lane) - 1ull));
+                if (left) s_left[pos] = (uint16_t)(s * 512 + tid);
+            }
+            __syncthreads();
+            // ---- measure what is left
+            const int nleft = s_nleft;
+            for (int i0 = 0; i0 < nleft; i0 += G * UB) {
+                Raw8<T> raw[UB];
+                int at[UB];
+#pragma unroll
+                for (int b = 0; b < UB; ++b) {
+                    at[b] = s_left[min(nleft - 1, i0 + b * G + grp)];
+                    const int n = chunk(i1 + (at[b] >> 8)) * KPP_CHUNK + (at[b] & 255);
+                    raw[b] = load_raw(Xh + (size_t)n * D + part * 8);
+                }
+#pragma unroll
+                for (int b = 0; b < UB; ++b) {
+                    if (i0 + b * G >= nleft) break;
+                    float x[8];
+                    to_floats(raw[b], x);
+                    double a = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double2 c = s_cd[j * LPT + part];
+                        const double e0 = (double)x[2 * j] - c.x, e1 = (double)x[2 * j + 1] - c.y;
+                        a = fma(e0, e0, a);
+                        a = fma(e1, e1, a);
+                    }
+                    a = group_sum<LPT>(a);
+                    if (part == 0 && i0 + b * G + grp < nleft && a < s_d2[at[b]]) {
+                        s_d2[at[b]] = a;
+                        s_chg[at[b] >> 8] = 1;
+                    }
+                }
+            }
+            __syncthreads();
+            // ---- hand on: D2 of the chunks that changed in this draw or the last (the generation that is written is two draws
+            // old), and the sums
+#pragma unroll
+            for (int s = 0; s < KPP_SLOTS; ++s) {
+                const int ch = chunk(i1 + 2 * s + pair), n = ch * KPP_CHUNK + gt;
+                if (ch >= nch) break;
+                const bool chg = s_chg[2 * s + pair] != 0;
+                double v = 0.0;
+                if (n < N) {
+                    v = s_d2[s * 512 + tid];
+                    if (!HELD || (!alone && (chg || (chg_old >> s & 1)))) kpp_put(dn + n, v);
+                    if (chg) {
+                        const unsigned y = (s_tok[s * 512 + tid].y & 0xFFFFu) | (bf16_up((float)v) << 16);
+                        s_tok[s * 512 + tid].y = y;
+                        if (!HELD) rh[n].y = y;
+                    }
+                }
+                if (chg) {
+                    for (int x = 32; x > 0; x >>= 1) v += __shfl_xor(v, x);
+                    if (lane == 0) s_w[s][wave] = v;
+                }
+                chg_old = (chg_old & ~(1u << s)) | ((unsigned)chg << s);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): D2 is in place ..
+            __syncthreads();                    // .. all of the workgroup's
+            if (gt < KPP_SLOTS) {
+                const int ch = chunk(i1 + 2 * gt + pair);
+                if (ch < nch) {
+                    const double *sw = &s_w[gt][4 * pair];
+                    const double sum = s_chg[2 * gt + pair] ? ((sw[0] + sw[1]) + sw[2]) + sw[3] : s_cs[ch];
+                    if (nwg > 1) kpp_put_rec((o ? w.rec[1] : w.rec[0]) + ((size_t)h * nch + ch) * 2, sum, (unsigned)k + 1);
+                    else s_cs[ch] = sum;        // (nobody else wants it)
+                }
+            }
+        }
+        __syncthreads();                        // s_cs, s_w, s_chg and the centre have been read
+    }
+}
+
 // Chunks per workgroup: as many as it takes to have at most KPP_TARGET_WGS workgroups (each of them repeats the search
 // for the token of the draw).
 static KppBufs kpp_carve(void *ws, int H, int N, int d, int C, size_t *total)
@@ -525,6 +797,8 @@ static KppBufs kpp_carve(void *ws, int H, int N, int d, int C, size_t *total)
     k.dig = c.take<uint4>((size_t)H * N * (d / 32));
     k.row = c.take<uint2>((size_t)H * N);
     k.picked = c.take<int32_t>((size_t)H * C);
+    for (int i = 0; i < 2; ++i) k.rec[i] = c.take<unsigned long long>((size_t)H * k.nch * 2);
+    k.fail = c.take<int32_t>((size_t)H);
     *total = c.used;
     return k;
 }
@@ -537,33 +811,71 @@ size_t kpp_ws_bytes(int H, int N, int C)
     return total;
 }
 
+// Chunks per workgroup of kpp_loop_kernel, 0 if a launch per draw is the better way (see there): a single workgroup for a head
+// that it can hold; as few chunks as leave a workgroup per CU otherwise.
+static int kpp_loop_chunks(int H, int nch, int ncu)
+{
+    if (nch <= KPP_HELD_CHUNKS) return nch;
+    if (nch > 64 * KPP_LOOKS) return 0;
+    for (int cpw = 2; cpw <= KPP_HELD_CHUNKS; cpw += 2)
+        if ((long long)H * cdiv(nch, cpw) <= ncu) return cpw;
+    return 0;
+}
+
 template <typename T, int D>
 static int kpp_run(const T *X, int H, int N, int C, const double *u, float *centroids, int32_t *picked, void *ws,
-                   hipStream_t st)
+                   unsigned patience, hipStream_t st)
 {
     size_t total;
     KppBufs w = kpp_carve(ws, H, N, D, C, &total);
     if (picked) w.picked = picked;
     const int nwg = cdiv(w.nch, w.cpw);
-    hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(C > 1 ? nwg : 1, H), dim3(256), 0, st, X, u, w, N, C, centroids);
-    for (int k = 1; k < C; ++k)
-        hipLaunchKernelGGL((kpp_step_kernel<T, D>), dim3(k + 1 < C ? nwg : 1, H), dim3(320), 0, st, X, u, w, N, C, k,
-                           centroids);
+    hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(C > 1 ? nwg : 1, H), dim3(256), 0, st, X, u, w, N, C, centroids, false);
+    int cpw = 0, ncu = 0;
+    SVG2_TRY(device_cu_count(&ncu));
+    if (C > 2) cpw = kpp_loop_chunks(H, w.nch, ncu);
+    const size_t lds = (size_t)w.nch * sizeof(double);
+    if (cpw > 0) {
+        hipLaunchKernelGGL((kpp_loop_kernel<T, D, true>), dim3(cdiv(w.nch, cpw), H), dim3(512), lds, st, X, u, w, N, C, patience,
+                           centroids, false);
+        if (cpw < w.nch) {                      // heads that were given up
+            hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(nwg, H), dim3(256), 0, st, X, u, w, N, C, centroids, true);
+            hipLaunchKernelGGL((kpp_loop_kernel<T, D, false>), dim3(1, H), dim3(512), lds, st, X, u, w, N, C, patience, centroids, true);
+        }
+    } else {
+        for (int k = 1; k < C; ++k)
+            hipLaunchKernelGGL((kpp_step_kernel<T, D>), dim3(k + 1 < C ? nwg : 1, H), dim3(320), 0, st, X, u, w, N, C, k,
+                               centroids);
+    }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
 }
 
-int kpp_launch(const void *X, int dtype, int H, int N, int d, int C, const double *u, float *centroids,
-               int32_t *picked, void *ws, hipStream_t st)
+static int kpp_dispatch(const void *X, int dtype, int H, int N, int d, int C, const double *u, float *centroids,
+                        int32_t *picked, void *ws, unsigned patience, hipStream_t st)
 {
     if (dtype == SVG2_BF16) {
         const bf16_t *x = static_cast<const bf16_t *>(X);
-        return d == 128 ? kpp_run<bf16_t, 128>(x, H, N, C, u, centroids, picked, ws, st)
-                        : kpp_run<bf16_t, 64>(x, H, N, C, u, centroids, picked, ws, st);
+        return d == 128 ? kpp_run<bf16_t, 128>(x, H, N, C, u, centroids, picked, ws, patience, st)
+                        : kpp_run<bf16_t, 64>(x, H, N, C, u, centroids, picked, ws, patience, st);
     }
     const float *x = static_cast<const float *>(X);
-    return d == 128 ? kpp_run<float, 128>(x, H, N, C, u, centroids, picked, ws, st)
-                    : kpp_run<float, 64>(x, H, N, C, u, centroids, picked, ws, st);
+    return d == 128 ? kpp_run<float, 128>(x, H, N, C, u, centroids, picked, ws, patience, st)
+                    : kpp_run<float, 64>(x, H, N, C, u, centroids, picked, ws, patience, st);
+}
+
+int kpp_launch(const void *X, int dtype, int H, int N, int d, int C, const double *u, float *centroids, int32_t *picked,
+               void *ws, hipStream_t st)
+{
+    return kpp_dispatch(X, dtype, H, N, d, C, u, centroids, picked, ws, KPP_PATIENCE, st);
 }
 
 }  // namespace svg2
+
+// For tests only, not declared in the public header: svg2_kmeans_pp_init (checked arguments) whose workgroups wait for nothing, so
+// that heads of several workgroups are given up and done again.
+extern "C" int svg2_test_kmeans_pp_init_without_patience(const void *X, int dtype, int H, int N, int d, int C, const double *u,
+                                                         float *centroids, int32_t *picked, void *ws, void *stream)
+{
+    return svg2::kpp_dispatch(X, dtype, H, N, d, C, u, centroids, picked, ws, 0, static_cast<hipStream_t>(stream));
+}

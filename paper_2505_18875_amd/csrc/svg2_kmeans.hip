@@ -1565,7 +1565,7 @@ int kmeans_prepare(int dtype, int d)
 }
 
 // number of compute units of the current device (the bf16 assign kernel runs one workgroup on each)
-static int device_cu_count(int *ncu)
+int device_cu_count(int *ncu)
 {
     static std::atomic<int> known[64];
     int dev = -1;

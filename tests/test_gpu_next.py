@@ -1,5 +1,7 @@
 """GPU parity of the pieces around the layer path: attention recall (Section 3.1) and k-means++ seeding
 (Sections 4.3 / 5.3), each against the CPU oracle on the same seeded inputs."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -135,3 +137,36 @@ def test_kmeans_pp_then_lloyd_lowers_the_objective(svg2):
     torch.cuda.synchronize()
     obj = to_np(res.objective[0])
     assert np.all(np.diff(obj) <= 1e-4 * obj[0])
+
+
+@pytest.mark.parametrize("patient", [True, False])
+@pytest.mark.parametrize("dtype,H,N,d,C", [
+    # one workgroup per head, the most it holds and a chunk more; several, and a ragged last one; a launch per draw
+    ("bf16", 2, 2048, 64, 40), ("bf16", 2, 2049, 128, 40), ("f32", 3, 5000, 128, 60), ("bf16", 24, 16384, 128, 12),
+    ("bf16", 1, 65536, 64, 30), ("bf16", 1, 65537, 64, 5), ("bf16", 140, 2300, 64, 6)])
+def test_kmeans_pp_draws_of_one_launch(svg2, oracle, dtype, H, N, d, C, patient):
+    """All draws of a head in one launch: the tokens of the oracle's draws.  Without patience a workgroup gives its head up as soon as it
+    would have to wait, and the head is done again by a single workgroup."""
+    r = np.random.default_rng(9100 + N + d)
+    centres = 1.5 * r.standard_normal((H, 9, d)).astype(np.float32)
+    X = np.stack([centres[h][np.sort(r.integers(0, 9, size=N))] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
+    X = wl.round_to_bf16(X) if dtype == "bf16" else X.astype(np.float32)
+    u = r.random((H, C))
+    Xd, ud = to_dev(X, dtype), torch.from_numpy(u).cuda()
+    if patient:
+        picked, cent = (lambda x: (x.picked, x.centroids))(svg2.svg2_kmeans_pp_init(Xd, C, ud))
+    else:
+        lib = svg2.load_library()
+        picked = torch.full((H, C), -1, dtype=torch.int32, device="cuda")
+        cent = torch.zeros((H, C, d), dtype=torch.float32, device="cuda")
+        ws = torch.empty(lib.svg2_kmeans_pp_init_workspace_size(H, N, C), dtype=torch.uint8, device="cuda")
+        vp = ctypes.c_void_p
+        rc = lib.svg2_test_kmeans_pp_init_without_patience(
+            vp(Xd.data_ptr()), svg2.SVG2_BF16 if dtype == "bf16" else svg2.SVG2_F32, H, N, d, C, vp(ud.data_ptr()),
+            vp(cent.data_ptr()), vp(picked.data_ptr()), vp(ws.data_ptr()), vp(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+    torch.cuda.synchronize()
+    for h in range(0, H, max(1, H // 3)):
+        ref, centres = oracle.kmeans_pp(X[h], C, u[h])
+        np.testing.assert_array_equal(to_np(picked[h]), ref)
+        np.testing.assert_array_equal(to_np(cent[h]), centres)
