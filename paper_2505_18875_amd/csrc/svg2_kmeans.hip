@@ -98,6 +98,7 @@ struct KmArgs {
     KmSide s[2];
     int nsides, H, N, iters;
     int nc[2];                  // wavefronts that share a token block (fp32 assign)
+    bool want_order;            // the caller reads offsets and perm of the last iteration
 };
 
 // labels written / read by iteration t
@@ -211,9 +212,10 @@ __device__ __forceinline__ bf16_t f64_to_bf16(double m)
 static constexpr int KM_FIN_NW = 4;
 static constexpr int KM_FIN_UB = 8;             // pieces requested together
 
-// One cluster by one wavefront; add(s) adds the sums of its pieces to s.
-template <bool BF16, int D, typename F>
-__device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &S, const KmIter &it, int mode, int h, int j, F add)
+// One cluster by one wavefront; size() is the number of its tokens, add(s) adds the sums of its pieces to s.
+template <bool BF16, int D, typename G, typename F>
+__device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &S, const KmIter &it, int mode, int h, int j, G size,
+                                                 F add)
 {
     constexpr int EL = D / 64;
     const int lane = threadIdx.x & 63, C = S.C;
@@ -221,8 +223,7 @@ __device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &
     const size_t idx = ((size_t)h * C + j) * D + lane;
     double c[EL];
     if (mode != 0) {
-        const int32_t *off = KM_SEL(S.offsets, it.set) + (size_t)h * (C + 1);
-        const int cnt = off[j + 1] - off[j];
+        const int cnt = size();
         double s[EL], s_prev[EL];
 #pragma unroll
         for (int e = 0; e < EL; ++e) {
@@ -287,7 +288,11 @@ __global__ __launch_bounds__(64 * KM_FIN_NW) void kmeans_finalize_kernel(KmArgs 
     const KmSide S = side ? a.s[1] : a.s[0];
     const int C = S.C, j = side ? jj - a.s[0].C : jj;
     if (side >= a.nsides || j >= C) return;
-    finalize_cluster<BF16, D>(a, S, it, mode, h, j, [&](double (&s)[EL]) {
+    auto size = [&]() {
+        const int32_t *off = KM_SEL(S.offsets, set) + (size_t)h * (C + 1);
+        return off[j + 1] - off[j];
+    };
+    finalize_cluster<BF16, D>(a, S, it, mode, h, j, size, [&](double (&s)[EL]) {
         auto add_pieces = [&](int st, double sign) {
             const int32_t *fp = KM_SEL(S.first_piece, st) + (size_t)h * (C + 1);
             const int p0 = fp[j], np = fp[j + 1] - p0;
@@ -1042,6 +1047,20 @@ __global__ __launch_bounds__(128) void kmeans_assign_f32_few_kernel(KmArgs a, Km
 //                  labels -- the tokens that LEFT it.  A wavefront first scans its piece one row per lane and
 //                  packs the rows that qualify into a list, then reads only those rows of X.
 //
+template <typename T> __device__ __forceinline__ void add_row(const uint4 &v, double (&acc)[16 / sizeof(T)])
+{
+    const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if constexpr (sizeof(T) == 2) {
+            acc[2 * q] += (double)__uint_as_float(w[q] << 16);
+            acc[2 * q + 1] += (double)__uint_as_float(w[q] & 0xFFFF0000u);
+        } else {
+            acc[q] += (double)__uint_as_float(w[q]);
+        }
+    }
+}
+
 // One piece (rows row0 .. + nrows of the sorted order pm) of cluster cl by one wavefront: acc = the sum of its rows that
 // qualify, the elements part * EPL .. of every lane whose row part that is; returns how many rows there are (0: no acc).
 template <typename T, int D, bool DELTA>
@@ -1092,17 +1111,7 @@ __device__ __forceinline__ int sum_piece(const T *Xh, const int32_t *pm, const i
 #pragma unroll
         for (int u = 0; u < KM_UB; ++u) {
             if (!ok[u]) continue;
-            const unsigned w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            if (sizeof(T) == 2) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[2 * q] += (double)__uint_as_float(w[q] << 16);
-                    acc[2 * q + 1] += (double)__uint_as_float(w[q] & 0xFFFF0000u);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] += (double)__uint_as_float(w[q]);
-            }
+            add_row<T>(v[u], acc);
         }
     }
     // lanes with the same `part` hold the same columns
@@ -1143,20 +1152,21 @@ __global__ __launch_bounds__(256) void kmeans_segsum_kernel(KmArgs a, KmIter it)
     }
 }
 
-// The whole update step of a cluster in one workgroup, for heads of at most KM_SMALL_N tokens: the pieces of the cluster
-// (mode 1: of the new order; mode 2: those that joined, then those that left) are dealt out to the wavefronts, their sums
-// stay in LDS, the first wavefront adds them in their order and finishes the cluster.  Same sums in the same order as the
-// two kernels; one launch and a round trip through memory less.
+// The whole update step of a cluster in one workgroup, for heads of at most KM_SMALL_N tokens, straight from the labels: the
+// wavefronts go through the labels of the head, list the cluster's tokens (mode 1) or those that joined and those that left it
+// (mode 2) in token order, sum the lists in pieces of KM_SEG rows, and the first wavefront adds these in their order and finishes the
+// cluster.  So an iteration needs no sort; the last one sorts for the order that is handed on.
 //
 // A workgroup has to be able to walk a cluster that holds most of the head about as fast as the pieces would be walked side
-// by side: four wavefronts up to 2048 tokens, sixteen above, where fewer such workgroups run at once.  Time of an iteration
-// in us, this kernel / the two, clusters of equal size, then one of all tokens (bf16; D = 128, or 64 where named):
-//   1 head  x 1024, D = 64,  25 clusters:  20.9 / 25.4,  21.3 / 24.4        1 x 2048, 100:  26.5 / 30.9,  30.9 / 31.2
-//   40 heads x 2048, 25 clusters:          34.0 / 38.7,  33.0 / 32.4        1 x 4096, 100:  29.4 / 33.8,  33.5 / 34.2
-//   40 heads x 4096, 12 clusters (480):    45.3 / 45.3,  39.8 / 38.8        25 clusters (1000): 52.7 / 46.4, 42.1 / 39.3
-// (With four wavefronts at 4096 tokens one cluster of all tokens took 39.7 us in the fourth of these, 47.1 in the fifth.)
+// by side: four wavefronts up to 2048 tokens, sixteen above, where fewer such workgroups run at once.  Five iterations in us,
+// clusters of about equal size, then one of all tokens; the kernels of the longer heads / this one:
+//   40 heads x 2048, bf16, D = 128, 50 clusters (2000): 201 / 168, 169 / 155      100 x 1100, 64, 30 (3000): 168 / 145, 152 / 141
+//   40 x 2048, 128, 100 (4000): 198 / 189, 181 / 191                              24 x 4096, 128, 30 (720): 225 / 230, 170 / 164
+// the same workgroup behind a sort / this one:
+//   1 head x 4096, fp32, D = 64, 16 clusters: 105 / 77, 99 / 69                   1 x 2048, bf16, 128, 100: 137 / 112, 156 / 122
+//   1 x 4096, bf16, 128, 100: 155 / 128, 159 / 126                                40 x 4096, 128, 12: 255 / 237, 200 / 175
 static constexpr int KM_SMALL_N = 4096, KM_SMALL_N4 = 2048;     // tokens of a head, with 16 and with 4 wavefronts
-static constexpr int KM_SMALL_WG = 512, KM_SMALL_WG4 = 1024;    // .. and clusters of all heads
+static constexpr int KM_SMALL_WG = 512, KM_SMALL_WG4 = 3072;    // .. and clusters of all heads
 
 static bool kmeans_update_small(int H, int N, int C)
 {
@@ -1166,39 +1176,84 @@ static bool kmeans_update_small(int H, int N, int C)
 template <typename T, int D, bool BF16, int NW>
 __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, KmIter it, int mode)
 {
-    constexpr int EPL = 16 / sizeof(T), LPR = D / EPL, EL = D / 64;
-    constexpr int NP = 2 * (NW == 4 ? KM_SMALL_N4 : KM_SMALL_N) / KM_SEG;       // most pieces of a cluster, joined and left
+    constexpr int EPL = 16 / sizeof(T), LPR = D / EPL, RPI = 64 / LPR, EL = D / 64;
+    constexpr int NMAX = NW == 4 ? KM_SMALL_N4 : KM_SMALL_N, NG = NMAX / (64 * NW);    // groups of 64 labels per wavefront
+    constexpr int NP = 2 * NMAX / KM_SEG + 2;                                          // most pieces of a cluster, joined and left
     __shared__ __align__(16) double s_ps[NP][D];
-    __shared__ int32_t s_cnt[NP];
-    __shared__ int32_t s_list[NW][KM_SEG];
-    const int h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, N = a.N;
+    __shared__ uint16_t s_list[2 * NMAX];           // those that joined, then those that left
+    __shared__ int32_t s_cnt[3][NW];                // per wavefront: joined, left, in the cluster
+    const int h = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), N = a.N;
     const int side = (int)blockIdx.x >= a.s[0].C ? 1 : 0;
     const KmSide S = side ? a.s[1] : a.s[0];
-    const int C = S.C, j = (int)blockIdx.x - (side ? a.s[0].C : 0);
+    const int j = (int)blockIdx.x - (side ? a.s[0].C : 0);
     const T *Xh = reinterpret_cast<const T *>(S.X) + (size_t)h * N * D;
-    const int32_t *on = KM_SEL(S.offsets, it.set) + (size_t)h * (C + 1) + j;
-    const int n0 = on[0], n1 = on[1], n_new = (n1 - n0 + KM_SEG - 1) / KM_SEG;
-    int o0 = 0, o1 = 0;
-    if (mode == 2) {
-        const int32_t *oo = KM_SEL(S.offsets, 1 - it.set) + (size_t)h * (C + 1) + j;
-        o0 = oo[0];
-        o1 = oo[1];
-    }
-    const int n_all = n_new + (o1 - o0 + KM_SEG - 1) / KM_SEG;
-    for (int q = wave; q < n_all; q += NW) {
-        const bool left = q >= n_new;
-        const int row0 = left ? o0 + (q - n_new) * KM_SEG : n0 + q * KM_SEG, rows = min(KM_SEG, (left ? o1 : n1) - row0);
-        const int32_t *pm = (left ? KM_SEL(S.perm, 1 - it.set) : KM_SEL(S.perm, it.set)) + (size_t)h * N;
-        double acc[EPL];
-        int cnt;
-        if (mode == 2) {
-            const int32_t *other = (left ? (side ? it.lab[1] : it.lab[0]) : (side ? it.lab_prev[1] : it.lab_prev[0])) + (size_t)h * N;
-            cnt = sum_piece<T, D, true>(Xh, pm, other, j, row0, rows, s_list[wave], acc);
-        } else {
-            cnt = sum_piece<T, D, false>(Xh, pm, nullptr, j, row0, rows, s_list[wave], acc);
+    const int32_t *lab = (side ? it.lab[1] : it.lab[0]) + (size_t)h * N;
+    const int32_t *prev = mode == 2 ? (side ? it.lab_prev[1] : it.lab_prev[0]) + (size_t)h * N : lab;
+    unsigned long long in[NG], out[NG];
+    {
+        int l[NG], p[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int n = min((wave * NG + g) * 64 + lane, N - 1);
+            l[g] = lab[n];
+            p[g] = prev[n];
         }
-        if (lane == 0) s_cnt[q] = cnt;
-        if (cnt > 0 && lane < LPR) {
+        int n_in = 0, n_out = 0, n_all = 0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const bool ok = (wave * NG + g) * 64 + lane < N;
+            in[g] = __ballot(ok && l[g] == j && (mode != 2 || p[g] != j));
+            out[g] = __ballot(ok && l[g] != j && p[g] == j);
+            n_in += __popcll(in[g]);
+            n_out += __popcll(out[g]);
+            n_all += __popcll(__ballot(ok && l[g] == j));
+        }
+        if (lane == 0) { s_cnt[0][wave] = n_in; s_cnt[1][wave] = n_out; s_cnt[2][wave] = n_all; }
+    }
+    __syncthreads();
+    int tot_in = 0, tot_out = 0, cnt = 0, at_in = 0, at_out = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        at_in += w < wave ? s_cnt[0][w] : 0;
+        at_out += w < wave ? s_cnt[1][w] : 0;
+        tot_in += s_cnt[0][w];
+        tot_out += s_cnt[1][w];
+        cnt += s_cnt[2][w];
+    }
+    at_out += tot_in;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const unsigned long long lt = (1ull << lane) - 1ull;
+        const int n = (wave * NG + g) * 64 + lane;
+        if (in[g] >> lane & 1) s_list[at_in + __popcll(in[g] & lt)] = (uint16_t)n;
+        if (out[g] >> lane & 1) s_list[at_out + __popcll(out[g] & lt)] = (uint16_t)n;
+        at_in += __popcll(in[g]);
+        at_out += __popcll(out[g]);
+    }
+    __syncthreads();
+    const int np_in = (tot_in + KM_SEG - 1) / KM_SEG, np = np_in + (tot_out + KM_SEG - 1) / KM_SEG;
+    const int sub = lane / LPR, part = lane % LPR;
+    for (int q = wave; q < np; q += NW) {
+        const int r0 = q < np_in ? q * KM_SEG : tot_in + (q - np_in) * KM_SEG;
+        const int r1 = min(r0 + KM_SEG, q < np_in ? tot_in : tot_in + tot_out);
+        double acc[EPL];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = 0.0;
+        for (int r = r0; r < r1; r += RPI * KM_UB) {
+            uint4 v[KM_UB];
+#pragma unroll
+            for (int u = 0; u < KM_UB; ++u)
+                v[u] = reinterpret_cast<const uint4 *>(Xh + (size_t)s_list[min(r + u * RPI + sub, r1 - 1)] * D)[part];
+#pragma unroll
+            for (int u = 0; u < KM_UB; ++u)
+                if (r + u * RPI + sub < r1) add_row<T>(v[u], acc);
+        }
+        // lanes with the same `part` hold the same columns
+#pragma unroll
+        for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o);
+        if (lane < LPR) {
 #pragma unroll
             for (int e = 0; e < EPL; e += 2)
                 *reinterpret_cast<double2 *>(&s_ps[q][lane * EPL + e]) = make_double2(acc[e], acc[e + 1]);
@@ -1206,12 +1261,10 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
     }
     __syncthreads();
     if (wave != 0) return;
-    finalize_cluster<BF16, D>(a, S, it, mode, h, j, [&](double (&s)[EL]) {
-        for (int q = 0; q < n_all; ++q) {
-            if (s_cnt[q] == 0) continue;
+    finalize_cluster<BF16, D>(a, S, it, mode, h, j, [&]() { return cnt; }, [&](double (&s)[EL]) {
+        for (int q = 0; q < np; ++q)
 #pragma unroll
-            for (int e = 0; e < EL; ++e) s[e] += q < n_new ? s_ps[q][lane + 64 * e] : -s_ps[q][lane + 64 * e];
-        }
+            for (int e = 0; e < EL; ++e) s[e] += q < np_in ? s_ps[q][lane + 64 * e] : -s_ps[q][lane + 64 * e];
     });
 }
 
@@ -1690,13 +1743,13 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             sa.s[s].offsets = k.offsets[it.set];
             sa.s[s].perm = k.perm[it.set];
             sa.s[s].inv_perm = nullptr;
-            sa.s[s].pieces = small ? nullptr : k.pieces[it.set];
+            sa.s[s].pieces = small ? nullptr : k.pieces[it.set];         // (small: the order is handed on, not read here)
             sa.s[s].first_piece = k.first_piece[it.set];
             sa.s[s].n_pieces = k.n_pieces[it.set];
             sa.s[s].max_pieces = k.max_pieces;
             sa.s[s].seg = KM_SEG;
         }
-        {
+        if (!small || (t + 1 == iters && a.want_order)) {
             ProfileSpan sp(SVG2_K_KMEANS_SORT, st);
             SVG2_TRY(sort_launch(sa, ns, H, N, st));
         }
@@ -1775,6 +1828,7 @@ int kmeans_pair_launch(const void *Q, const void *K, int dtype, int H, int N, in
     a.s[0].perm[last] = perm_q;
     a.s[1].offsets[last] = offsets_k;
     a.s[1].perm[last] = perm_k;
+    a.want_order = true;
     return kmeans_dispatch(a, dtype, d, st);
 }
 

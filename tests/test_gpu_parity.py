@@ -335,7 +335,9 @@ def test_kmeans_tokens_on_and_next_to_bisectors_get_the_oracles_labels(svg2, ora
     ("bf16", 128, 1, 4097, 2), ("bf16", 64, 1, 4096, 1025), ("f32", 64, 3, 600, 342),
     # four wavefronts to the workgroup at the longest, sixteen at the shortest, and with the most clusters
     ("bf16", 128, 1, 2048, 1), ("f32", 128, 2, 2049, 3), ("f32", 64, 1, 4096, 512), ("bf16", 128, 1, 4096, 513),
-    ("bf16", 128, 2, 2048, 512), ("bf16", 64, 1, 2048, 1025)])
+    ("bf16", 128, 2, 2048, 512), ("bf16", 64, 1, 2048, 1025),
+    # as many clusters of all heads as the route with four wavefronts takes, and more; a last group of one token
+    ("f32", 64, 2, 2048, 1536), ("f32", 64, 2, 2048, 1537), ("bf16", 64, 1, 1985, 100), ("f32", 128, 1, 4033, 7)])
 def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
     r = np.random.default_rng(6600 + N + C)
     centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
