@@ -174,9 +174,9 @@ __device__ __forceinline__ long lds_read_tr8(const lds_u8 *p)
     return r;
 }
 
-// What bounds the kernel: a 64-key tile is 9 matrix instructions of 64 cycles and about 90 vector instructions (32 of them
-// exponentials) per wavefront, two wavefronts per SIMD, and the two kinds hardly overlap: the time of a tile is about the sum
-// of both.  So the loop holds no search for the block maxima (44 vector instructions per tile with the decisions, and two
+// What bounds the kernel: a 64-key tile is 9 matrix instructions of 64 cycles and about 115 vector instructions (counted at
+// 27 % selected; 32 of them exponentials) per wavefront, two wavefronts per SIMD, and the two kinds hardly overlap: the time of
+// a tile is about the sum of both.  So the loop holds no search for the block maxima (44 vector instructions per tile with the decisions, and two
 // chains from the scores to the exponentials), a level that a row keeps, operands that are read from LDS a tile
 // ahead of their use (three buffers), and the priority of a wavefront is raised from the last exponentials of a tile to the
 // first score instructions of the next, so that it gets past the barrier while the other one is at its exponentials.
