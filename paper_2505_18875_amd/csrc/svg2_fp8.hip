@@ -14,15 +14,15 @@
 //                      layout as the bf16 kernel, rows half as long.  What differs:
 //                      * one instruction contracts 64 values: two per 32-key score block,
 //                        and the second product is taken once per 64-key tile;
-//                      * a probability is exp2(s - m) with the reference level m put
-//                        2^7 below a maximum of the row; it moves only when a
-//                        score exceeds it by more than E4M3 holds (464, 2^8.9), so
-//                        probabilities span (2^-10 .. 448] and the small ones of a
-//                        flat row still land on normal E4M3 numbers;
+//                      * a probability is exp2(s - m) with the reference level m kept below
+//                        the running maximum of the row (2^6 or 2^7, see the kernel) and moved
+//                        only when a score exceeds it by 2^8 or by more than E4M3 holds
+//                        (464, 2^8.9), so the small ones of a flat row still land on normal
+//                        E4M3 numbers;
 //                      * the row sum is one more matrix instruction per tile (a V^T row
 //                        of ones), so it is the sum of the ROUNDED probabilities, the
 //                        same numbers that multiply V -- and it is NaN if one of them
-//                        did not fit, which is how the kernel finds out;
+//                        did not fit, which is how the loop without a search finds out;
 //                      * V^T comes out of LDS with the 8-bit transposing read
 //                        (ds_read_b64_tr_b8).
 //
@@ -174,25 +174,45 @@ __device__ __forceinline__ long lds_read_tr8(const lds_u8 *p)
     return r;
 }
 
-// What bounds the kernel: a 64-key tile is 9 matrix instructions of 64 cycles and about 115 vector instructions (counted at
+// Two tile loops in one kernel.
+//
+// SEARCH: the loop looks for the maximum of every 32-key block and moves the level of a query before its probabilities are
+// formed.  A wavefront's own matrix and vector instructions overlap from block to block (scores of the next block beside the
+// exponentials of this one), two tile buffers.
+//
+// Else: a 64-key tile is 9 matrix instructions of 64 cycles and about 115 vector instructions (counted at
 // 27 % selected; 32 of them exponentials) per wavefront, two wavefronts per SIMD, and the two kinds hardly overlap: the time of
-// a tile is about the sum of both.  So the loop holds no search for the block maxima (44 vector instructions per tile with the decisions, and two
-// chains from the scores to the exponentials), a level that a row keeps, operands that are read from LDS a tile
-// ahead of their use (three buffers), and the priority of a wavefront is raised from the last exponentials of a tile to the
+// a tile is about the sum of both.  So this loop holds no search for the block maxima (44 vector instructions per tile with the
+// decisions, and two chains from the scores to the exponentials), a level that a row keeps, operands that are read from LDS a
+// tile ahead of their use (three buffers), and the priority of a wavefront is raised from the last exponentials of a tile to the
 // first score instructions of the next, so that it gets past the barrier while the other one is at its exponentials.
-// 24 heads of 9601 tokens, everything selected: 0.85 -> 0.79 ms; 24 heads of 118,800 in 100 and 500 clusters, 30 % selected:
-// 32.2 -> 30.1 ms (1.73 PFLOP/s).  Of these 44 vector instructions and earlier operands alone give 2 %, the priorities 5 %.
-static constexpr int F8_NSTG = 3;           // K and V tile buffers in LDS (each)
-// The level is put where the largest probability is 2^7, a number that E4M3 holds exactly: the further below, the less often
-// the level has to move, but the more rows keep a largest probability that is rounded.  Error of the result against 64 bits
-// on the same operands, for a level of 2^6 / 2^7 below the maximum, as before (2^6, moved beyond 2^8): 4096 keys, scores of
-// standard deviation 1: 0.0266 / 0.0264, 0.0264; 3: 0.0145 / 0.0132, 0.0136; a clustered layer: 0.0151 / 0.0138, 0.0147.
+//
+// Which one (fp8_search): the second form takes longer to its first score (a sample of the keys, tile 0 by itself, five tile
+// fetches waited for: 2.5 us more for 16 tiles, 5 to 7 us from 32 tiles on) and wins that back over long rows.  us of the attention
+// launches (plan included), SEARCH / else; dense, then 50 to 100 query and 100 to 500 key clusters, about 30 % selected:
+//   40 x 2000   101 / 116       40 x 4000   265 / 282       16 x 6000   227 / 253       40 x 6000   537 / 504
+//    8 x 9601   337 / 358       16 x 9601   525 / 551       24 x 9601   789 / 743        4 x 9601   218 / 197
+//    1 x 16,384 262 / 260        4 x 16,384 361 / 323       16 x 16,384 1317 / 1227      4 x 30,000 1170 / 1022
+//    8 x 2000    43 / 46         8 x 4000    76 / 81        24 x 4000   115 / 117        2 x 6000    73 / 79
+//    4 x 8000   103 / 105       40 x 8000   521 / 500        4 x 12,000 169 / 172        8 x 12,000 200 / 186
+//    2 x 16,384 209 / 209       24 x 16,384 844 / 810       40 x 75,600 19,125 / 17,591  24 x 118,800 (Zipf) 44,934 / 41,274
+// Below 16,384 keys it depends on how the work items of all heads divide into rounds of two workgroups per CU; the rule leaves the number of heads
+// out, so that heads give the same bits whether they are computed together or on several GPUs.
+// LDS: 49 KB of tiles in the second form, so its run table (8 bytes per key cluster) leaves room for two workgroups per CU up to
+// 3999 key clusters only: 8 heads of 37,800 in 100 and 4096 clusters took 1679 us, 1018 in the first form.
+//
+// The level of the second form is put where the largest probability is 2^7, a number that E4M3 holds exactly: the further below,
+// the less often the level has to move, but the more rows keep a largest probability that is rounded.  Error of the result against
+// 64 bits on the same operands, SEARCH / else: 4096 keys, scores of standard deviation 1: 0.0262 / 0.0262; 3: 0.0139 / 0.0135;
+// 5: 0.0098 / 0.0093; 75,600 clustered keys: 0.0122 / 0.0112.
+static constexpr float F8_SEARCH_LEVEL = 6.0f;      // SEARCH: the level is put 2^6 below the block maximum ..
+static constexpr float F8_SEARCH_HEADROOM = 8.0f;   // .. and moves when a score exceeds it by 2^8
 static constexpr float F8_LEVEL = 7.0f;
 static constexpr float F8_HEADROOM = 8.0f;  // queries that take part when a wavefront moves its levels: their maximum is above 2^8
 static constexpr int F8_SAMPLE = 3;         // tiles of keys whose maximum gives a row its level, if it has at least ..
 static constexpr int F8_SAMPLE_MIN = 32;    // .. this many tiles (dense, 24 heads of 9601 tokens: 3 % faster with than without)
 
-template <int D>
+template <int D, bool SEARCH>
 __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     const uint8_t *__restrict__ Q, const uint8_t *__restrict__ K, const uint8_t *__restrict__ V,
     const float *__restrict__ scale_q, const float *__restrict__ scale_k, const float *__restrict__ scale_v, int H,
@@ -208,7 +228,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     constexpr int RB = D;                      // bytes per K / V row
     constexpr int CPR = RB / 16;               // 16-byte chunks per row
     constexpr int RPI = 1024 / RB;             // rows one direct-to-LDS load instruction fills
-    constexpr int NW = ATT_NW, NSTG = F8_NSTG;
+    constexpr int NW = ATT_NW, NSTG = SEARCH ? 2 : 3;         // NSTG: K and V tile buffers in LDS (each)
     constexpr int NPASS = ATT_BN / (NW * RPI);
     static_assert(NPASS >= 1, "a tile needs at least one load instruction per wavefront");
     constexpr int TILE_B = ATT_BN * RB;
@@ -221,7 +241,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     unsigned char *sK = s_raw;
     unsigned char *sV = s_raw + NSTG * TILE_B;
     int32_t *s_rows = reinterpret_cast<int32_t *>(s_raw + 2 * NSTG * TILE_B);   // [2][64]; [F8_SAMPLE][64] of the sample
-    int2 *s_run = reinterpret_cast<int2 *>(s_rows + F8_SAMPLE * ATT_BN);        // [nnz + 1]
+    int2 *s_run = reinterpret_cast<int2 *>(s_rows + (SEARCH ? 2 : F8_SAMPLE) * ATT_BN);     // [nnz + 1]
 
     // work item: as in the bf16 kernel (one list of all tiles, ATT_GROUP consecutive tiles per XCD)
     const int pos = attn_list_pos(group);
@@ -318,7 +338,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     unsigned off_nx[NPASS];
     // per-lane LDS read addresses (buffer 0): the two 16-byte halves of K operand u, V^T operand of column block b
     int koff[2 * KU], voff[DVB];
-    {
+    auto lds_addresses = [&]() {
         const int kz = (col >> 1) & 7;
 #pragma unroll
         for (int c = 0; c < 2 * KU; ++c) koff[c] = col * RB + (((4 * (c >> 1) + 2 * half + (c & 1)) ^ kz) * 16);
@@ -336,7 +356,270 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
         for (int c = 0; c < 2 * KU; ++c) { koff[c] += lds_base; asm volatile("" : "+v"(koff[c])); }
 #pragma unroll
         for (int b = 0; b < DVB; ++b) { voff[b] += lds_base; asm volatile("" : "+v"(voff[b])); }
+    };
+#define ATT_FENCE __builtin_amdgcn_sched_barrier(0);
+#define ATT_PIN(X) asm volatile("" : "+v"(X));
+    constexpr int NOPS = 40;                    // vector operations of one block's probabilities
+    const lds_u8 *lds = (const lds_u8 *)0;
+    i32x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = 0x38383838;          // E4M3 1.0
+
+    if constexpr (SEARCH) {
+    ATT_ROWS(0)
+    ATT_ROWS(1)
+    __syncthreads();
+    if (ntile > 0) {
+        ATT_OFFS(0, off_nx)
+        ATT_FETCH(off_nx, Kb, ld_koff, sK)
+        ATT_FETCH(off_nx, Vb, ld_voff, sV)
     }
+    if (ntile > 1) {
+        ATT_OFFS(1, off_nx)
+        ATT_FETCH(off_nx, Kb, ld_koff, sK + TILE_B)
+    }
+    __syncthreads();                            // everyone has read the rows of tiles 0 and 1
+    if (ntile > 2) { ATT_ROWS(2) }
+    // tile 3 is looked up here and parked at the top of tile 0; the start of tile 4 is requested for the look-up at
+    // the top of tile 0
+    if (ntile > 3) {
+        if (3 < key_tiles && wave == (3 & (NW - 1))) lk_hint = trh[3];
+        ATT_ROWS_ISSUE(3)
+    }
+    lk_hint = -1;
+    if (ntile > 4 && 4 < key_tiles && wave == (4 & (NW - 1))) lk_hint = trh[4];
+    // off_nx stays live: the rows of tile NSTG - 1, whose V is requested at the top of tile 0
+
+    lds_addresses();
+    __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0)
+    __syncthreads();
+
+    // ---- schedule.  Scores and probabilities are handled in blocks of 32 keys (two per tile), the second
+    // product once per 64-key tile (its contraction index is the whole tile).  Per tile t, with s0 = scores of
+    // its block 0 already there and the reference level m decided for them:
+    //   A:  s1 = K_{t,1} Q^T          (2 matrix instructions)  ||  pw[0..3] = exp2(s0 - m), LDS reads of V_t^T, K_{t+1,0}
+    //   B:  maximum of s1, decision about m.  If m moved (rare), pw[0..3] is recomputed under the new m, so that
+    //       both halves of the tile share one level.
+    //   C:  s0 = K_{t+1,0} Q^T        (2)                      ||  pw[4..7] = exp2(s1 - m), LDS reads of V_t^T, K_{t+1,1}
+    //   D:  accumulators brought to the level m if it moved since the last tile (rare);
+    //       O^T += V_t^T P^T (4), l += 1^T P^T (1, last)       ||  maximum of the new s0, decision about m
+    // Accumulator i of a score block is key 8 (i/4) + 4 half + i%4 of the block; word e of a block's probabilities
+    // holds accumulators 4 e .. 4 e + 3; the B operand of the second product is pw[0..7].
+    f32x16 s0, s1;
+    int pw[8];                                  // probabilities of the tile: words 0..3 block 0, 4..7 block 1
+    i32x8 ka[KU], va[DVB];                      // K operands of the next score block, V^T operands of this tile
+    float m_acc = 0.f, t0 = 0.f, t1 = 0.f, t2 = 0.f, t3 = 0.f;
+    for (int i = 0; i < 8; ++i) pw[i] = 0;
+    f32x16 lt;                                  // row sums of the tile just accumulated (every element the same)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lt[i] = 0.f;
+    bool any_upd = false;
+
+    auto exp_op = [&](const f32x16 &S, auto w0_tag, int op) {
+        const int e = op / 10, k = op % 10, w = decltype(w0_tag)::value + e;
+        if (k == 0) { t0 = fmaf(S[4 * e], scale_log2, -m_run); ATT_PIN(t0) }
+        else if (k == 1) { t1 = fmaf(S[4 * e + 1], scale_log2, -m_run); ATT_PIN(t1) }
+        else if (k == 2) { t2 = fmaf(S[4 * e + 2], scale_log2, -m_run); ATT_PIN(t2) }
+        else if (k == 3) { t3 = fmaf(S[4 * e + 3], scale_log2, -m_run); ATT_PIN(t3) }
+        else if (k == 4) { t0 = __builtin_amdgcn_exp2f(t0); ATT_PIN(t0) }
+        else if (k == 5) { t1 = __builtin_amdgcn_exp2f(t1); ATT_PIN(t1) }
+        else if (k == 6) { t2 = __builtin_amdgcn_exp2f(t2); ATT_PIN(t2) }
+        else if (k == 7) { t3 = __builtin_amdgcn_exp2f(t3); ATT_PIN(t3) }
+        else if (k == 8) { pw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(t0, t1, pw[w], false); ATT_PIN(pw[w]) }
+        else { pw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(t2, t3, pw[w], true); ATT_PIN(pw[w]) }
+    };
+    auto mask_block = [&](f32x16 &S, int base, int rem) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (base + 8 * (i >> 2) + 4 * half + (i & 3) >= rem) S[i] = -INFINITY;
+    };
+    auto decide = [&](float mx) {
+        const float mx_s = max_xor32(mx) * scale_log2;
+        const bool upd = mx_s > m_run + F8_SEARCH_HEADROOM;
+        any_upd = __any(upd);
+        m_run = upd ? mx_s - F8_SEARCH_LEVEL : m_run;
+        ATT_PIN(m_run)
+    };
+    // The accumulators are expressed under the level m_acc; bring them to m_run.  Called once per tile, right
+    // before the tile is accumulated (both decisions since the last tile are folded into one factor).  Ordinary
+    // multiplications: the compiler sees every reader and writer of the accumulators and places the wait states
+    // itself.  The matrix instructions of the previous tile have all completed here (its row sum, the last of
+    // them, was read at the end of that tile).
+    auto rescale_if_needed = [&]() {
+        if (__any(m_acc != m_run)) {
+            const float alpha = __builtin_amdgcn_exp2f(m_acc - m_run);
+            m_acc = m_run;
+            l_run *= alpha;
+#pragma unroll
+            for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+        }
+    };
+    // 16-byte half c (0 .. 2 KU - 1) of the K operands of a score block whose first row is at KBYTE
+    auto load_k = [&](auto kbyte_tag, int c) {
+        constexpr int KBYTE = decltype(kbyte_tag)::value;
+        const u32x4 w = lds_read_b128((lds + koff[c]) + KBYTE);
+        __builtin_memcpy(reinterpret_cast<char *>(&ka[c >> 1]) + 16 * (c & 1), &w, 16);
+    };
+    // 8-byte piece idx (0 .. 4 DVB - 1) of the V^T operands of the tile at VBYTE: column block b = idx / 4 (kept in
+    // va[b % 2]), key group idx % 4
+    auto load_v = [&](auto vbyte_tag, int idx) {
+        constexpr int VBYTE = decltype(vbyte_tag)::value;
+        const int b = idx / 4, t = idx % 4;
+        const long w = lds_read_tr8((lds + voff[b]) + (VBYTE + (t * 16) * RB));
+        __builtin_memcpy(reinterpret_cast<char *>(&va[b]) + 8 * t, &w, 8);
+    };
+    // phases A and C: Sacc = K Q^T from ka (if DO_S)  ||  pw = exp2(Sexp - m); pieces V0 .. V0 + 3 of V^T;
+    // each ka[u] is refilled with the operand of the block at KBYTE once its instruction has been issued (if DO_K)
+    auto phase_s = [&](auto do_s_tag, auto do_k_tag, auto vbyte_tag, auto v0_tag, auto kbyte_tag, f32x16 &Sacc,
+                       const f32x16 &Sexp, auto w0_tag) {
+        constexpr bool DO_S = decltype(do_s_tag)::value;
+        constexpr bool DO_K = decltype(do_k_tag)::value;
+        constexpr int V0 = decltype(v0_tag)::value;
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            if (DO_S) {
+                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                Sacc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ka[u], qreg[u], u == 0 ? zero : Sacc, 0, 0, 0, 0, 0,
+                                                                       0);
+            }
+            ATT_FENCE
+#pragma unroll
+            for (int idx = V0 + (8 * u) / KU; idx < V0 + (8 * (u + 1)) / KU; ++idx) load_v(vbyte_tag, idx);
+            if (DO_K) {
+#pragma unroll
+                for (int c = 2 * u; c < 2 * u + 2; ++c) load_k(kbyte_tag, c);
+            }
+#pragma unroll
+            for (int op = (NOPS * u) / KU; op < (NOPS * (u + 1)) / KU; ++op) exp_op(Sexp, w0_tag, op);
+            ATT_FENCE
+        }
+    };
+    auto block_max = [&](const f32x16 &S) {
+        float mx = max2_raw(fmaxf(S[0], S[1]), S[2]);
+#pragma unroll
+        for (int c = 1; c < 7; ++c) mx = max3_raw(mx, S[2 * c + 1], S[2 * c + 2]);
+        return max2_raw(mx, S[15]);
+    };
+    // phase D: O^T += V^T P^T, l += 1^T P^T  ||  maximum of Snext and the decision (if DO_MAX).  The V^T operands
+    // of column blocks 0 and 1 are there; those of blocks 2 and 3 are read into the same registers once the
+    // instructions that use them have been issued.  The row-sum instruction goes LAST and its result is read at
+    // the end of the phase: matrix instructions complete in order, so once that read is allowed every accumulator
+    // of the tile has been written.  (Without it, the register copies the compiler places on the way out of the
+    // tile loop read an accumulator that the last instruction is still writing: the wait states the compiler
+    // inserts for that cover one basic block, not the branches out of the loop.)
+    auto phase_pv = [&](auto do_max_tag, auto vbyte_tag, const f32x16 &Snext) {
+        constexpr bool DO_MAX = decltype(do_max_tag)::value;
+        static_assert(DVB == 4, "two operand registers serve four column blocks");
+        float mx = -INFINITY;
+        rescale_if_needed();
+        const i32x8 pb = {pw[0], pw[1], pw[2], pw[3], pw[4], pw[5], pw[6], pw[7]};
+#pragma unroll
+        for (int b = 0; b < DVB; ++b) {
+            oacc[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va[b], pb, oacc[b], 0, 0, 0, 0, 0, 0);
+            if (b == DVB - 1) {                 // every accumulator = the tile's row sum of this lane's query
+                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                lt = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones, pb, zero, 0, 0, 0, 0, 0, 0);
+            }
+            ATT_FENCE
+            if (DO_MAX && b >= 2) {             // in the shadow of the last three instructions
+#pragma unroll
+                for (int c = 4 * (b - 2); c < 4 * (b - 1); ++c) {
+                    if (c == 0) mx = max2_raw(fmaxf(Snext[0], Snext[1]), Snext[2]);
+                    else if (c < 7) mx = max3_raw(mx, Snext[2 * c + 1], Snext[2 * c + 2]);
+                    else mx = max2_raw(mx, Snext[15]);
+                    ATT_PIN(mx)
+                }
+                if (b == DVB - 1) decide(mx);
+            }
+            ATT_FENCE
+        }
+        l_run += lt[0];
+        // The compiler's wait states for this 16-pass instruction are two short of what the hardware needs before
+        // the LAST result registers may be touched (measured: 20, inserted: 18), so nothing may read an
+        // accumulator, or reuse a register of lt, right at that limit: four more wait states here, and lt stays
+        // claimed until the next tile has started (see the tile loop).
+        asm volatile("s_nop 3" : "+v"(lt));
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+
+    // ---- prologue: scores of block 0 of tile 0 and their level, K operands of block 1
+    if (wave_active && ntile > 0) {
+#pragma unroll
+        for (int c = 0; c < 2 * KU; ++c) load_k(std::integral_constant<int, 0>{}, c);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            s0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ka[u], qreg[u], u == 0 ? zero : s0, 0, 0, 0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int c = 0; c < 2 * KU; ++c) load_k(std::integral_constant<int, 32 * RB>{}, c);
+        if (L < 32) mask_block(s0, 0, L);
+        float mx = fmaxf(fmaxf(s0[0], s0[1]), s0[2]);
+#pragma unroll
+        for (int i = 3; i < 16; ++i) mx = fmaxf(mx, s0[i]);
+        decide(mx);                             // key 0 exists: the maximum is finite
+        m_acc = m_run;                          // the accumulators are zero: nothing to rescale
+    }
+
+#define ATT_TILE(BUF, HAS_NEXT)                                                            \
+    {                                                                                      \
+        /* the fetches issued NSTG - 1 tiles ago (V of this tile, K of the next) must have landed */ \
+        __builtin_amdgcn_s_waitcnt(0x0F70);         /* vmcnt(0) */                         \
+        __syncthreads();                                                                   \
+        if (HAS_NEXT) {                                                                    \
+            if (kt + NSTG + 1 < ntile) { ATT_ROWS_COMMIT(kt + NSTG + 1) }                  \
+            if (kt + NSTG - 1 < ntile) { ATT_FETCH(off_nx, Vb, ld_voff, sV + ((BUF + NSTG - 1) % NSTG) * TILE_B) } \
+            if (kt + NSTG < ntile) {                                                       \
+                ATT_OFFS(kt + NSTG, off_nx)                                                \
+                ATT_FETCH(off_nx, Kb, ld_koff, sK + BUF * TILE_B)                          \
+            }                                                                              \
+            /* rows of tile kt + NSTG + 2, parked at the top of the next tile (its start was requested a tile ago) */ \
+            if (kt + NSTG + 2 < ntile) { ATT_ROWS_ISSUE(kt + NSTG + 2) }                   \
+        }                                                                                  \
+        if (wave_active) {                                                                 \
+            asm volatile("" : "+v"(lt));            /* the registers of the last row sum are free from here on */ \
+            using HN = std::integral_constant<bool, HAS_NEXT>;                             \
+            constexpr int KB_ = ((BUF + 1) % NSTG) * TILE_B, VB_ = NSTG * TILE_B + BUF * TILE_B; \
+            using VB = std::integral_constant<int, VB_>;                                   \
+            phase_s(T{}, HN{}, VB{}, std::integral_constant<int, 0>{}, std::integral_constant<int, KB_>{}, s1, s0, \
+                    std::integral_constant<int, 0>{});                                     \
+            if (!HAS_NEXT) mask_block(s1, 32, L - kt * ATT_BN);                            \
+            decide(block_max(s1));                                                         \
+            if (any_upd) {                      /* rare: block 0 again, under the level both blocks share */ \
+                _Pragma("unroll") for (int op = 0; op < NOPS; ++op) exp_op(s0, std::integral_constant<int, 0>{}, op); \
+            }                                                                              \
+            phase_s(HN{}, HN{}, VB{}, std::integral_constant<int, 8>{},                    \
+                    std::integral_constant<int, KB_ + 32 * RB>{}, s0, s1, std::integral_constant<int, 4>{}); \
+            if (HAS_NEXT && kt + 2 == ntile && L - (kt + 1) * ATT_BN < 32)                 \
+                mask_block(s0, 0, L - (kt + 1) * ATT_BN);                                  \
+            phase_pv(HN{}, VB{}, s0);                                                      \
+        }                                                                                  \
+        {       /* where the tile looked up at the top of the next tile starts: requested here */ \
+            const int tn_ = kt + NSTG + 3;                                                 \
+            lk_hint = -1;                                                                  \
+            if (HAS_NEXT && tn_ < ntile && tn_ < key_tiles && wave == (tn_ & (NW - 1))) lk_hint = trh[tn_]; \
+        }                                                                                  \
+        ++kt;                                                                              \
+    }
+    static_assert(NSTG == 2, "the row look-up is parked behind the vmcnt(0) that opens a tile: written for two buffers");
+    int kt = 0;
+    while (kt < ntile - 1) {
+        ATT_TILE(0, true)
+        if (kt >= ntile - 1) break;
+        ATT_TILE(1, true)
+    }
+    if (ntile > 0) {
+        const int bl = kt % NSTG;
+        if (bl == 0) ATT_TILE(0, false)
+        else ATT_TILE(1, false)
+    }
+#undef ATT_TILE
+    asm volatile("s_nop 7" : "+v"(lt));         // (see phase D: margin before the accumulators are read)
+    } else {
+    lds_addresses();
     // ---- level of a long row: F8_LEVEL below the maximum over F8_SAMPLE tiles of keys spread over the whole sequence.  (The
     // scores are formed twice for these, but a row whose level starts at the maximum of its first 64 keys takes it up later,
     // and the wavefronts of the workgroup wait for the one that does.)
@@ -428,13 +711,6 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     // tile's probabilities formed again -- before they meet V, and with both blocks' scores still there.
     // Accumulator i of a score block is key 8 (i/4) + 4 half + i%4 of the block; word e of a block's probabilities
     // holds accumulators 4 e .. 4 e + 3; the B operand of the second product is pw[0..7].
-#define ATT_FENCE __builtin_amdgcn_sched_barrier(0);
-#define ATT_PIN(X) asm volatile("" : "+v"(X));
-    constexpr int NOPS = 40;                    // vector operations of one block's probabilities
-    const lds_u8 *lds = (const lds_u8 *)0;
-    i32x8 ones;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ones[i] = 0x38383838;          // E4M3 1.0
     f32x16 s0, s1;                              // scores of block 0 / block 1 of the tile that is prepared
     int pa[8], pb[8];                           // probabilities of the tile that is accumulated / prepared, in turn
     i32x8 ka[2][KU], va[DVB];                   // K operands of both score blocks, V^T operands of this tile
@@ -638,6 +914,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     }
 #undef ATT_TILE
 #undef ATT_EXP
+    }
 #undef ATT_FENCE
 #undef ATT_PIN
 #undef ATT_ROWS
@@ -671,15 +948,22 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     }
 }
 
-static size_t attn_fp8_lds_bytes(int d, int Ck)
+static size_t attn_fp8_lds_bytes(int d, int Ck, bool search)
 {
-    return (size_t)2 * F8_NSTG * ATT_BN * d + F8_SAMPLE * ATT_BN * sizeof(int32_t) + (size_t)(Ck + 1) * sizeof(int2);
+    const size_t tiles = (size_t)2 * (search ? 2 : 3) * ATT_BN * d, rows = (size_t)(search ? 2 : F8_SAMPLE) * ATT_BN * sizeof(int32_t);
+    return tiles + rows + (size_t)(Ck + 1) * sizeof(int2);
 }
 
 int attn_fp8_prepare()
 {
-    return set_dynamic_lds(reinterpret_cast<const void *>(attn_fp8_kernel<128>), attn_fp8_lds_bytes(128, SVG2_MAX_CLUSTERS));
+    SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(attn_fp8_kernel<128, true>), attn_fp8_lds_bytes(128, SVG2_MAX_CLUSTERS, true)));
+    return set_dynamic_lds(reinterpret_cast<const void *>(attn_fp8_kernel<128, false>), attn_fp8_lds_bytes(128, SVG2_MAX_CLUSTERS, false));
 }
+
+// Which tile loop (figures at attn_fp8_kernel).  The host does not know how long the rows are, only how many keys there are.
+static constexpr int F8_LONG_N = 16384;
+
+static bool fp8_search(int N, int Ck) { return N < F8_LONG_N || 2 * attn_fp8_lds_bytes(128, Ck, false) > 160 * 1024; }
 
 int attn_fp8_main_launch(const void *Q8, const void *K8, const void *V8, const float *scale_q, const float *scale_k,
                          const float *scale_v, int H, int N, int d, int Cq, int Ck, const int32_t *row_ptr,
@@ -691,8 +975,9 @@ int attn_fp8_main_launch(const void *Q8, const void *K8, const void *V8, const f
     const int total = H * a.max_tiles;
     const int group = ATT_GROUP;
     const float scale_log2 = scale * 1.4426950408889634f;
-    const size_t lds = attn_fp8_lds_bytes(d, Ck);
-    auto kern = attn_fp8_kernel<128>;
+    const bool search = fp8_search(N, Ck);
+    const size_t lds = attn_fp8_lds_bytes(d, Ck, search);
+    auto kern = search ? attn_fp8_kernel<128, true> : attn_fp8_kernel<128, false>;
     hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * ATT_NW), lds, st, static_cast<const uint8_t *>(Q8),
                        static_cast<const uint8_t *>(K8), static_cast<const uint8_t *>(V8), scale_q, scale_k, scale_v, H,
                        N, Cq, Ck, row_ptr, perm_q, perm_k, a.tiles, a.tile_base, a.order, a.max_tiles, a.runs, a.row_keys,

@@ -341,9 +341,8 @@ def test_sparse_attn_fp8_very_short_sequences(svg2, oracle, N):
 
 @pytest.mark.parametrize("N", [192, 257, 447, 769, 1984, 1985, 2112])
 def test_sparse_attn_fp8_tile_counts_and_a_late_large_score(svg2, oracle, N):
-    # 3 to 33 tiles of 64 keys, last ones of 1, 63 and 64: every position of the loop over three buffers, and rows short of and
-    # beyond the 32 tiles from which a sample of the keys sets the level.  For a third of the queries the last key but one, which
-    # is in no sample, has a score far above all others: their level moves in the last tile.
+    # 3 to 33 tiles of 64 keys, last ones of 1, 63 and 64.  For a third of the queries the last key but one has a score far above all
+    # others: their level moves in the last tile.
     r = np.random.default_rng(500 + N)
     d = 128
     Q, K, V = (r.standard_normal((N, d)).astype(np.float32) for _ in range(3))
@@ -362,3 +361,92 @@ def test_sparse_attn_fp8_tile_counts_and_a_late_large_score(svg2, oracle, N):
     # one key holds most of the weight of a third of the rows: the worst-case bounds only
     _check_head(oracle, O, lse, Q, K, V, d, ident, ident, off, off, np.array([0, 1], dtype=np.int32),
                 np.zeros(1, dtype=np.int32), lse_mean=LSE_MAX, statistical=False)
+
+
+@pytest.mark.parametrize("N,Ck", [(16383, 40), (16384, 40), (16384, 3999), (16384, 4000)])
+def test_sparse_attn_fp8_short_rows_in_both_tile_loops(svg2, oracle, N, Ck):
+    """Both sides of the limits between the two tile loops (16,384 keys; 3999 key clusters), rows of 3 to 33 tiles, last ones of 1, 63
+    and 64: every position of the loops over two and three buffers, and rows short of and beyond the 32 tiles from which the second
+    takes the level from a sample of the keys.  For a third of the queries the last key but one, which is in no sample, has a score far
+    above all others."""
+    r = np.random.default_rng(900 + Ck)
+    d, lens = 128, [192, 257, 447, 769, 1984, 1985, 2112]
+    rows_of, Cq = 140, len(lens) + 1                    # (the last query cluster has the other rows and no keys)
+    Q, K, V = (r.standard_normal((N, d)).astype(np.float32) for _ in range(3))
+    Q[::3] = Q[0] + 0.3 * Q[::3]
+    offq = np.array([rows_of * i for i in range(Cq)] + [N], dtype=np.int32)
+    # each row has two key clusters with one of the others in between; what is left of the clusters is split evenly
+    sizes, sel = [], []
+    for n in lens:
+        sel.append([len(sizes), len(sizes) + 2])
+        sizes += [n // 3, 0 if n == 769 else 5, n - n // 3]
+        K[sum(sizes) - 2] = Q[0]
+    rest, left = Ck - len(sizes), N - sum(sizes)
+    sizes += [left // rest + (1 if i < left % rest else 0) for i in range(rest)]
+    offk = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    sel.append([])
+    row_ptr = np.concatenate([[0], np.cumsum([len(x) for x in sel])]).astype(np.int32)
+    col = np.zeros(Cq * Ck, dtype=np.int32)
+    cat = np.array([c for x in sel for c in x], dtype=np.int32)
+    col[: cat.size] = cat
+    Q, K, V = wl.round_to_bf16(Q), wl.round_to_bf16(K), wl.round_to_bf16(V)
+    (Q8, sq), (K8, sk), (V8, sv) = _quantise_all(svg2, to_dev(Q[None], "bf16"), to_dev(K[None], "bf16"),
+                                                 to_dev(V[None], "bf16"))
+    res = svg2.svg2_sparse_attn_fp8(Q8, K8, V8, sq, sk, sv, to_dev(offq[None]), to_dev(offk[None]), to_dev(row_ptr[None]),
+                                    to_dev(col[None]), None, None, want_lse=True)
+    torch.cuda.synchronize()
+    O, lse = to_np(res.O[0]).astype(np.float64), to_np(res.lse[0]).astype(np.float64)
+    ident = np.arange(N, dtype=np.int32)
+    # one key holds most of the weight of a third of the rows: the worst-case bounds only
+    _check_head(oracle, O, lse, Q, K, V, d, ident, ident, offq, offk, row_ptr, col,
+                rows=np.arange(rows_of * len(lens), dtype=np.int32), lse_mean=LSE_MAX, statistical=False)
+
+
+@pytest.mark.parametrize("N", [9601, 16384])
+def test_sparse_attn_fp8_heads_do_not_depend_on_each_other(svg2, N):
+    # the same bits whether heads are computed together or one at a time (on several GPUs, say)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = [svg2.svg2_quantize_fp8(torch.randn((24, N, 128), device="cuda", generator=g).bfloat16()) for _ in range(3)]
+
+    def dense(h0, h1):
+        H = h1 - h0
+        off = torch.tensor([[0, N]] * H, dtype=torch.int32, device="cuda")
+        return svg2.svg2_sparse_attn_fp8(*(t[0][h0:h1].contiguous() for t in x), *(t[1][h0:h1].contiguous() for t in x), off, off,
+                                         torch.tensor([[0, 1]] * H, dtype=torch.int32, device="cuda"),
+                                         torch.zeros((H, 1), dtype=torch.int32, device="cuda"), want_lse=True)
+    whole = dense(0, 24)
+    for h0, h1 in ((0, 1), (5, 8), (12, 24)):
+        part = dense(h0, h1)
+        torch.cuda.synchronize()
+        assert torch.equal(part.O, whole.O[h0:h1]) and torch.equal(part.lse, whole.lse[h0:h1])
+
+
+def test_sparse_attn_fp8_scores_that_climb_in_the_loop_without_a_search(svg2, oracle):
+    # scores that grow along the key sequence of 16,384 tokens by more per 64-key tile than a probability may exceed the level: it
+    # moves in nearly every tile, and every move forms the tile's probabilities again.  The second cluster's queries have short
+    # rows (no sample of the keys), the third one's fall along the keys (a level that stays).
+    r = np.random.default_rng(31)
+    N, d, Cq, Ck = 16384, 128, 4, 3
+    u = r.standard_normal(d).astype(np.float32)
+    u /= np.linalg.norm(u)
+    sign = np.ones((N, 1), dtype=np.float32)
+    sign[200:300] = -1.0
+    Q = wl.round_to_bf16((sign * 4.0 * u[None] + 0.3 * r.standard_normal((N, d))).astype(np.float32) * 10.0)
+    ramp = np.concatenate([np.linspace(-12.0, 12.0, 3200), np.zeros(N - 3200)]).astype(np.float32)
+    K = wl.round_to_bf16((ramp[:, None] * u[None] + 0.3 * r.standard_normal((N, d))).astype(np.float32) * 10.0)
+    V = wl.round_to_bf16(r.standard_normal((N, d)).astype(np.float32))
+    offq = np.array([0, 130, 200, 300, N], dtype=np.int32)
+    offk = np.array([0, 1500, 3200, N], dtype=np.int32)
+    row_ptr = np.array([0, 2, 3, 5, 5], dtype=np.int32)
+    col = np.zeros(Cq * Ck, dtype=np.int32)
+    col[:5] = [0, 1, 1, 0, 1]
+    (Q8, sq), (K8, sk), (V8, sv) = _quantise_all(svg2, to_dev(Q[None], "bf16"), to_dev(K[None], "bf16"),
+                                                 to_dev(V[None], "bf16"))
+    res = svg2.svg2_sparse_attn_fp8(Q8, K8, V8, sq, sk, sv, to_dev(offq[None]), to_dev(offk[None]), to_dev(row_ptr[None]),
+                                    to_dev(col[None]), None, None, want_lse=True)
+    torch.cuda.synchronize()
+    O, lse = to_np(res.O[0]).astype(np.float64), to_np(res.lse[0]).astype(np.float64)
+    ident = np.arange(N, dtype=np.int32)
+    # (as in the test of climbing scores above)
+    _check_head(oracle, O, lse, Q, K, V, d, ident, ident, offq, offk, row_ptr, col, rows=np.arange(300, dtype=np.int32),
+                statistical=False, lse_mean=0.07)
