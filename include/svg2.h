@@ -275,6 +275,10 @@ int svg2_forward_gather_free(const void *Q, const void *K, const void *V, int dt
  *   fetched through perm_q / perm_k (as in svg2_sparse_attn_gather_free).
  *   O [H,N,d] bf16 out, lse [H,N] fp32 out or NULL (of the scores the kernel
  *   actually used, i.e. of the quantised operands).
+ *   Where a probability is rounded to E4M3 depends on its distance from a level
+ *   that follows the row's maximum.  The results are the same from run to run
+ *   and do not depend on the other heads of a call; from 16,384 keys on they
+ *   depend, within that rounding, on the queries of the same 32-row group.
  *   Workspace: svg2_sparse_attn_workspace_size(SVG2_BF16, ...).
  *
  * svg2_forward_fp8: svg2_forward_gather_free with the attention step on E4M3
