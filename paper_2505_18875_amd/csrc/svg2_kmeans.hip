@@ -60,7 +60,9 @@ static constexpr int KM_SETTLE_BLOCKS = 64, KM_SETTLE_MIN = 24, KM_SETTLE_WG = 1
 // double-precision definition and would show a violation as a label that differs away from a tie.)
 static constexpr float KM_TIE_KEY = 3.814697265625e-06f;      // 2^-18
 static constexpr float KM_TIE_ACC = 9.5367431640625e-07f;     // 2^-20
-static constexpr float KM_PAD_HCN = -3.0e38f;   // -||c||^2 / 2 of the padding rows of a centroid block: never wins, stays finite
+// -||c||^2 / 2 of the padding rows of a centroid block: stays finite, and wins only where no centroid's key is a larger number
+// (centroids that are NaN or beyond the range of fp32): such a token gets cluster 0 or is settled.
+static constexpr float KM_PAD_HCN = -3.0e38f;
 
 // One side of a k-means call: all heads of the Q tokens, or of the K tokens.
 struct KmSide {
@@ -113,7 +115,7 @@ struct KmIter {
 #define KM_SEL(arr, i) ((i) ? (arr)[1] : (arr)[0])
 
 // v_max / v_min / v_max3 / v_med3 as they are (fmaxf and friends first canonicalise operands the compiler cannot
-// prove quiet; the keys here are never NaN).  Not volatile: the scheduler may place them.
+// prove quiet).  A key that is no number loses against one that is.  Not volatile: the scheduler may place them.
 __device__ __forceinline__ float km_max(float a, float b)
 {
     float r;
@@ -692,7 +694,7 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
                     flagged = half == 0 && n < N && !(T - U > tau);
                     if (OBJ && S.objective && half == 0 && n < N) obj += x2 - 2.f * T;
                 }
-                pend_n[tb] = n; pend_c[tb] = cidx; pend_T[tb] = T; pend_U[tb] = U; pend_f[tb] = flagged;
+                pend_n[tb] = n; pend_c[tb] = cidx < C ? cidx : 0; pend_T[tb] = T; pend_U[tb] = U; pend_f[tb] = flagged;
             }
             pend = true;
             return g_next;
@@ -860,7 +862,7 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 #pragma unroll
             for (int w = 1; w < 4; ++w)
                 if (s_best[w] < best || (s_best[w] == best && s_bj[w] < bj)) { best = s_best[w]; bj = s_bj[w]; }
-            if (bj < C) labels[(size_t)h * N + n] = bj;     // (no distance is a number: the label stays)
+            labels[(size_t)h * N + n] = bj < C ? bj : 0;    // (no distance is a finite number: cluster 0)
         }
     }
 }
@@ -1407,7 +1409,8 @@ __global__ __launch_bounds__(64 * KM_TINY_NW) void kmeans_tiny_bf16_kernel(KmArg
             const float T = km_max(b0, b1), U = km_max3(km_min(b0, b1), __uint_as_float(hs.lo), __uint_as_float(hs.hi));
             const int n = wave * 64 + 32 * b + col;
             if (half == 0 && n < N) {
-                s_lab[n] = (b1 > b0) ? (int)hi.hi : (int)hi.lo;
+                const int cidx = (b1 > b0) ? (int)hi.hi : (int)hi.lo;
+                s_lab[n] = cidx < C ? cidx : 0;
                 const float tau = KM_TIE_KEY * fabsf(T) + KM_TIE_ACC * (0.5f * x2[b] + cmax2);
                 if (!(T - U > tau)) s_flag[atomicAdd(&s_nflag, 1)] = n;
             }
@@ -1446,7 +1449,7 @@ __global__ __launch_bounds__(64 * KM_TINY_NW) void kmeans_tiny_bf16_kernel(KmArg
                 const int oj = __shfl_xor(bj, o);
                 if (ob < best || (ob == best && oj < bj)) { best = ob; bj = oj; }
             }
-            if (lane == 0 && bj < C) s_lab[n] = bj;     // (no distance is a number: the label stays)
+            if (lane == 0) s_lab[n] = bj < C ? bj : 0;  // (no distance is a finite number: cluster 0)
         }
         if (nflag > 0) __syncthreads();
         // ---- stable counting sort: a wavefront's 64 tokens are one group

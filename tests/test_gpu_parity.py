@@ -368,6 +368,59 @@ def test_kmeans_short_heads(svg2, oracle, d, H, N, C, iters):
     _check_kmeans(oracle, res, X, init, iters, True, H, C)
 
 
+@pytest.mark.parametrize("dtype,d,N,C", [
+    # all iterations in one workgroup, update from the labels, sorted update, two chunks of centroids: with one padding row, with many
+    ("bf16", 64, 300, 31), ("bf16", 128, 1000, 1), ("bf16", 64, 2000, 31), ("bf16", 128, 5000, 33), ("bf16", 128, 5000, 543),
+    ("f32", 64, 2000, 31), ("f32", 128, 5000, 3)])
+@pytest.mark.parametrize("what", ["nan_cache", "nan_token", "inf_centroids"])
+def test_kmeans_labels_stay_in_range_without_finite_distances(svg2, oracle, dtype, d, N, C, what):
+    """Tokens no distance of which is a finite number go to cluster 0 (as in the oracle, whose argmin starts there)."""
+    r = np.random.default_rng(4100 + N + C)
+    X = (3.0 * r.standard_normal((1, 1, d)) + r.standard_normal((2, N, d))).astype(np.float32)
+    X = wl.round_to_bf16(X)
+    init = X[:, :C].copy()
+    iters = 2
+    if what == "nan_cache":
+        init[1] = np.nan
+    elif what == "nan_token":
+        if C > 1:
+            init[:] = init[:, :1]                       # everything in cluster 0, whose mean is no number from then on
+            init[:, 1:] = np.nan
+        X[1, 7, 3] = np.nan
+    else:
+        init[1, :, 0] = np.inf
+        iters = 1
+    res = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), iters)
+    perm = svg2.svg2_permute(res.labels, C)
+    torch.cuda.synchronize()
+    for h in range(2):
+        if h == 1 or dtype == "bf16":                   # (fp32 labels of head 0 are those of fp32 arithmetic)
+            ref = oracle.kmeans(X[h], init[h], iters, dtype == "bf16")
+            np.testing.assert_array_equal(to_np(res.labels[h]), ref.labels)
+            np.testing.assert_array_equal(to_np(res.counts[h]), ref.counts)
+        assert to_np(perm.offsets[h])[-1] == N
+        np.testing.assert_array_equal(np.sort(to_np(perm.perm[h])), np.arange(N))
+
+
+@pytest.mark.parametrize("d,N,C", [(64, 300, 31), (128, 1000, 1), (64, 2000, 31), (128, 5000, 33)])
+def test_forward_with_a_cache_that_is_no_number(svg2, oracle, d, N, C):
+    # one cluster per side: the layer is dense attention
+    r = np.random.default_rng(4200 + N)
+    Q, K, V = (wl.round_to_bf16(r.standard_normal((1, N, d)).astype(np.float32)) for _ in range(3))
+    cache = torch.full((1, C, d), float("nan"), dtype=torch.float32, device="cuda")
+    res = svg2.svg2_forward(to_dev(Q, "bf16"), to_dev(K, "bf16"), to_dev(V, "bf16"), cache, cache.clone(), 0.9, 2, want_aux=True)
+    torch.cuda.synchronize()
+    a = res.aux
+    ident = np.arange(N, dtype=np.int32)
+    for lab, off, perm in ((a.labels_q, a.offsets_q, a.perm_q), (a.labels_k, a.offsets_k, a.perm_k)):
+        assert not to_np(lab).any() and np.array_equal(to_np(off[0]), np.r_[0, np.full(C, N)])
+        np.testing.assert_array_equal(to_np(perm[0]), ident)
+    off = np.array([0, N], dtype=np.int32)
+    O, _ = oracle.sparse_attention(Q[0], K[0], V[0], off, off, np.array([0, 1], dtype=np.int32), np.zeros(1, dtype=np.int32))
+    err = np.abs(to_np(res.O[0]) - O)
+    assert err.max() <= 2e-2 and err.mean() <= 1e-3
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("C,copies", [(70, 3), (300, 4), (300, 5), (600, 40), (1100, 1100)])
 def test_kmeans_near_ties_of_several_centroids(svg2, oracle, d, C, copies):
