@@ -618,7 +618,7 @@ __global__ __launch_bounds__(512, 4) void kpp_loop_kernel(const T *__restrict__ 
             for (int b0 = 0; (nwg > 1 || k == 1) && b0 < nch && !stop; b0 += 64 * KPP_LOOKS) {
                 unsigned long long hi[KPP_LOOKS], lo[KPP_LOOKS];
                 for (;;) {
-                    bool all = true;
+                    bool all = patience > 0;
 #pragma unroll
                     for (int i = 0; i < KPP_LOOKS; ++i) {
                         const int b = min(b0 + 64 * i + lane, nch - 1);
@@ -836,11 +836,13 @@ static int kpp_run(const T *X, int H, int N, int C, const double *u, float *cent
     if (C > 2) cpw = kpp_loop_chunks(H, w.nch, ncu);
     const size_t lds = (size_t)w.nch * sizeof(double);
     if (cpw > 0) {
-        hipLaunchKernelGGL((kpp_loop_kernel<T, D, true>), dim3(cdiv(w.nch, cpw), H), dim3(512), lds, st, X, u, w, N, C, patience,
-                           centroids, false);
+        // (a head in one workgroup has nobody to wait for)
+        hipLaunchKernelGGL((kpp_loop_kernel<T, D, true>), dim3(cdiv(w.nch, cpw), H), dim3(512), lds, st, X, u, w, N, C,
+                           cpw < w.nch ? patience : KPP_PATIENCE, centroids, false);
         if (cpw < w.nch) {                      // heads that were given up
             hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(nwg, H), dim3(256), 0, st, X, u, w, N, C, centroids, true);
-            hipLaunchKernelGGL((kpp_loop_kernel<T, D, false>), dim3(1, H), dim3(512), lds, st, X, u, w, N, C, patience, centroids, true);
+            hipLaunchKernelGGL((kpp_loop_kernel<T, D, false>), dim3(1, H), dim3(512), lds, st, X, u, w, N, C, KPP_PATIENCE,
+                               centroids, true);
         }
     } else {
         for (int k = 1; k < C; ++k)
@@ -872,10 +874,20 @@ int kpp_launch(const void *X, int dtype, int H, int N, int d, int C, const doubl
 
 }  // namespace svg2
 
-// For tests only, not declared in the public header: svg2_kmeans_pp_init (checked arguments) whose workgroups wait for nothing, so
-// that heads of several workgroups are given up and done again.
-extern "C" int svg2_test_kmeans_pp_init_without_patience(const void *X, int dtype, int H, int N, int d, int C, const double *u,
-                                                         float *centroids, int32_t *picked, void *ws, void *stream)
+#ifdef SVG2_TEST_HOOKS
+// svg2_kmeans_pp_init with checked arguments and a patience of its own: with 0 a workgroup gives its head up at its first look
+// for the others' sums, and every head of several workgroups is done again.
+extern "C" int svg2_test_kmeans_pp_init(const void *X, int dtype, int H, int N, int d, int C, const double *u, float *centroids,
+                                        int32_t *picked, void *ws, unsigned patience, void *stream)
 {
-    return svg2::kpp_dispatch(X, dtype, H, N, d, C, u, centroids, picked, ws, 0, static_cast<hipStream_t>(stream));
+    return svg2::kpp_dispatch(X, dtype, H, N, d, C, u, centroids, picked, ws, patience, static_cast<hipStream_t>(stream));
 }
+
+// Byte of the workspace at which the call above leaves one int32 per head: 1 if the head has been given up.
+extern "C" size_t svg2_test_kmeans_pp_given_up(int H, int N, int d, int C)
+{
+    size_t total;
+    char *base = reinterpret_cast<char *>(256);         // (any aligned address: nothing is read)
+    return (size_t)(reinterpret_cast<char *>(svg2::kpp_carve(base, H, N, d, C, &total).fail) - base);
+}
+#endif

@@ -40,6 +40,12 @@ def test_library_exports_every_declared_symbol(lib):
     assert lib.svg2_last_error() == b""
 
 
+def test_library_has_no_entry_points_for_tests(lib):
+    from paper_2505_18875_amd import binding
+    with open(binding.LIB_PATH, "rb") as f:
+        assert b"svg2_test_" not in f.read()
+
+
 def test_workspace_queries_and_validation_run_on_the_host(lib):
     # size queries never touch the GPU
     assert lib.svg2_forward_workspace_size(1, 40, 75600, 128, 100, 500) > 3 * 40 * 75600 * 128 * 2

@@ -139,34 +139,59 @@ def test_kmeans_pp_then_lloyd_lowers_the_objective(svg2):
     assert np.all(np.diff(obj) <= 1e-4 * obj[0])
 
 
-@pytest.mark.parametrize("patient", [True, False])
-@pytest.mark.parametrize("dtype,H,N,d,C", [
-    # one workgroup per head, the most it holds and a chunk more; several, and a ragged last one; a launch per draw
-    ("bf16", 2, 2048, 64, 40), ("bf16", 2, 2049, 128, 40), ("f32", 3, 5000, 128, 60), ("bf16", 24, 16384, 128, 12),
-    ("bf16", 1, 65536, 64, 30), ("bf16", 1, 65537, 64, 5), ("bf16", 140, 2300, 64, 6)])
-def test_kmeans_pp_draws_of_one_launch(svg2, oracle, dtype, H, N, d, C, patient):
-    """All draws of a head in one launch: the tokens of the oracle's draws.  Without patience a workgroup gives its head up as soon as it
-    would have to wait, and the head is done again by a single workgroup."""
+def _seeding_case(dtype, H, N, d, C):
     r = np.random.default_rng(9100 + N + d)
     centres = 1.5 * r.standard_normal((H, 9, d)).astype(np.float32)
     X = np.stack([centres[h][np.sort(r.integers(0, 9, size=N))] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
     X = wl.round_to_bf16(X) if dtype == "bf16" else X.astype(np.float32)
     u = r.random((H, C))
-    Xd, ud = to_dev(X, dtype), torch.from_numpy(u).cuda()
-    if patient:
-        picked, cent = (lambda x: (x.picked, x.centroids))(svg2.svg2_kmeans_pp_init(Xd, C, ud))
-    else:
-        lib = svg2.load_library()
-        picked = torch.full((H, C), -1, dtype=torch.int32, device="cuda")
-        cent = torch.zeros((H, C, d), dtype=torch.float32, device="cuda")
-        ws = torch.empty(lib.svg2_kmeans_pp_init_workspace_size(H, N, C), dtype=torch.uint8, device="cuda")
-        vp = ctypes.c_void_p
-        rc = lib.svg2_test_kmeans_pp_init_without_patience(
-            vp(Xd.data_ptr()), svg2.SVG2_BF16 if dtype == "bf16" else svg2.SVG2_F32, H, N, d, C, vp(ud.data_ptr()),
-            vp(cent.data_ptr()), vp(picked.data_ptr()), vp(ws.data_ptr()), vp(torch.cuda.current_stream().cuda_stream))
-        assert rc == 0
-    torch.cuda.synchronize()
+    return X, u, to_dev(X, dtype), torch.from_numpy(u).cuda()
+
+
+def _check_draws(oracle, X, u, picked, cent):
+    H, C = u.shape
     for h in range(0, H, max(1, H // 3)):
         ref, centres = oracle.kmeans_pp(X[h], C, u[h])
         np.testing.assert_array_equal(to_np(picked[h]), ref)
         np.testing.assert_array_equal(to_np(cent[h]), centres)
+
+
+@pytest.mark.parametrize("dtype,H,N,d,C", [
+    # one workgroup per head, the most it holds and a chunk more; several, and a ragged last one; a launch per draw
+    ("bf16", 2, 2048, 64, 40), ("bf16", 2, 2049, 128, 40), ("f32", 3, 5000, 128, 60), ("bf16", 24, 16384, 128, 12),
+    ("bf16", 1, 65536, 64, 30), ("bf16", 1, 65537, 64, 5), ("bf16", 140, 2300, 64, 6)])
+def test_kmeans_pp_draws_of_one_launch(svg2, oracle, dtype, H, N, d, C):
+    """All draws of a head in one launch: the tokens of the oracle's draws."""
+    X, u, Xd, ud = _seeding_case(dtype, H, N, d, C)
+    res = svg2.svg2_kmeans_pp_init(Xd, C, ud)
+    torch.cuda.synchronize()
+    _check_draws(oracle, X, u, res.picked, res.centroids)
+
+
+def _test_library():
+    from paper_2505_18875_amd import build
+    lib = ctypes.CDLL(build.TEST_LIB)
+    lib.svg2_test_kmeans_pp_given_up.restype = ctypes.c_size_t
+    return lib
+
+
+@pytest.mark.parametrize("dtype,H,N,d,C", [
+    # several workgroups per head
+    ("bf16", 2, 2049, 128, 40), ("f32", 3, 5000, 128, 60), ("bf16", 24, 16384, 128, 12), ("bf16", 1, 65536, 64, 30)])
+def test_kmeans_pp_heads_that_are_given_up_are_done_again(svg2, oracle, dtype, H, N, d, C):
+    """Without patience a workgroup gives its head up at its first look for the others' sums; a single workgroup
+    then does the head again."""
+    X, u, Xd, ud = _seeding_case(dtype, H, N, d, C)
+    lib = _test_library()
+    picked = torch.full((H, C), -1, dtype=torch.int32, device="cuda")
+    cent = torch.zeros((H, C, d), dtype=torch.float32, device="cuda")
+    ws = torch.zeros(svg2.load_library().svg2_kmeans_pp_init_workspace_size(H, N, C), dtype=torch.uint8, device="cuda")
+    vp = ctypes.c_void_p
+    rc = lib.svg2_test_kmeans_pp_init(
+        vp(Xd.data_ptr()), svg2.SVG2_BF16 if dtype == "bf16" else svg2.SVG2_F32, H, N, d, C, vp(ud.data_ptr()),
+        vp(cent.data_ptr()), vp(picked.data_ptr()), vp(ws.data_ptr()), 0, vp(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    torch.cuda.synchronize()
+    at = lib.svg2_test_kmeans_pp_given_up(H, N, d, C)
+    assert torch.equal(ws[at:at + 4 * H].view(torch.int32), torch.ones(H, dtype=torch.int32, device="cuda"))
+    _check_draws(oracle, X, u, picked, cent)
