@@ -334,6 +334,11 @@ int svg2_attention_recall(const float *lse_selected, const float *lse_all, int H
  *   picked    [H,C]   int32 out or NULL their token indices
  * Every distance that decides a draw is fp64; tokens that a cheaper lower bound
  * already rules out are not measured.
+ * Up to 65,536 tokens per head the workgroups of a head wait for one another
+ * between draws, on the CUs that the stream may use.  The wait is bounded:
+ * where they cannot run together (several seedings at once, a process kept to a
+ * few CUs) a head is given up after some 20 ms and done again by one workgroup,
+ * at 60 us per draw for 16,384 tokens instead of 9.  The draws are the same.
  * ------------------------------------------------------------------------- */
 size_t svg2_kmeans_pp_init_workspace_size(int H, int N, int C);
 int svg2_kmeans_pp_init(const void *X, int dtype, int H, int N, int d, int C,

@@ -12,6 +12,8 @@
 //                                    input, so the draw is reproducible and can be checked.  All
 //                                    arithmetic is fp64 (the draw compares a running sum of D2
 //                                    with a threshold; fp32 would move the boundaries).
+#include <algorithm>
+
 #include "svg2_common.h"
 
 namespace svg2 {
@@ -547,19 +549,24 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
 // of the records take turns: a workgroup that writes those of draw k has seen all records of draw k - 1, so every one
 // has finished reading those of draw k - 2.
 //
-// The wait is bounded.  Workgroups of a head that do not get onto the chip together -- the launch takes at most one workgroup
-// per CU of two that fit, but other launches may wait in the same way -- give up, set fail[h], and the head is done again by
-// a single workgroup, which waits for nobody (HELD = false, `again`).
+// The wait is bounded.  The launch takes at most one workgroup per CU of two that fit, counted on the CUs that the stream may use
+// (kpp_stream_cus), so the workgroups of a head get onto the chip together -- unless other launches wait in the same way
+// (several seedings at once on other streams) or the process has been kept to less than half of the CUs from outside (HSA_CU_MASK, which
+// no call tells).  Workgroups that wait for one another in vain give up after KPP_PATIENCE looks, set fail[h], and the head is done again by
+// a single workgroup, which waits for nobody (HELD = false, `again`; 24 heads of 16,384: 60 instead of 9 us per draw, one of 65,536: 146
+// instead of 6).
 //
 // What bounds a draw is its chain of round trips: record out and seen, the D2 of one chunk, the new centre's row, the rows that are
 // measured, D2 out.  us per draw, a launch for each / this kernel: 24 heads of 16,384 tokens (d = 128, bf16, 64 components) 13.8 /
 // 8.9, 40 of 9000 14.9 / 9.2, 10 of 30,000 (d = 64) 8.4 / 7.6, 4 of 4096 (d = 64, fp32) 6.0 / 4.7, 1000 of 900 (one workgroup
-// each) 32.5 / 15.2.  From 65,536 tokens on (more than KPP_LOOKS records to a lane) and beyond a workgroup per CU a launch
+// each) 32.5 / 15.2.  Beyond 65,536 tokens (more than KPP_LOOKS records to a lane) and beyond a workgroup per CU a launch
 // for each draw stays: one head of 75,600 7.1 / 7.5.
 static constexpr int KPP_SLOTS = 4;
 static constexpr int KPP_HELD_CHUNKS = 2 * KPP_SLOTS;       // chunks of a workgroup whose digits fit its registers
 static constexpr int KPP_LOOKS = 4;                         // records a lane looks at together
-static constexpr unsigned KPP_PATIENCE = 1u << 20;          // looks of a draw, about a microsecond each
+// looks of a draw, about a microsecond each: a draw takes 9 us, all draws of the heads in front of one, which it may have to let
+// pass, 5 to 10 ms
+static constexpr unsigned KPP_PATIENCE = 1u << 14;
 
 template <typename T, int D, bool HELD>
 __global__ __launch_bounds__(512, 4) void kpp_loop_kernel(const T *__restrict__ X, const double *__restrict__ u, KppBufs w, int N,
@@ -811,6 +818,24 @@ size_t kpp_ws_bytes(int H, int N, int C)
     return total;
 }
 
+// CUs that launches on the stream may use: those of its mask (hipExtStreamCreateWithCUMask), else all of the device.  A stream that is
+// captured is not asked; its graph may run on any.
+static int kpp_stream_cus(hipStream_t st, int *ncu)
+{
+    SVG2_TRY(device_cu_count(ncu));
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    uint32_t mask[32] = {};
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
+        int n = 0;
+        for (uint32_t m : mask) n += __builtin_popcount(m);
+        if (n > 0) *ncu = std::min(*ncu, n);
+    } else {
+        (void)hipGetLastError();                // (not an error of this call)
+    }
+    return SVG2_OK;
+}
+
 // Chunks per workgroup of kpp_loop_kernel, 0 if a launch per draw is the better way (see there): a single workgroup for a head
 // that it can hold; as few chunks as leave a workgroup per CU otherwise.
 static int kpp_loop_chunks(int H, int nch, int ncu)
@@ -832,7 +857,7 @@ static int kpp_run(const T *X, int H, int N, int C, const double *u, float *cent
     const int nwg = cdiv(w.nch, w.cpw);
     hipLaunchKernelGGL((kpp_first_kernel<T, D>), dim3(C > 1 ? nwg : 1, H), dim3(256), 0, st, X, u, w, N, C, centroids, false);
     int cpw = 0, ncu = 0;
-    SVG2_TRY(device_cu_count(&ncu));
+    SVG2_TRY(kpp_stream_cus(st, &ncu));
     if (C > 2) cpw = kpp_loop_chunks(H, w.nch, ncu);
     const size_t lds = (size_t)w.nch * sizeof(double);
     if (cpw > 0) {
@@ -883,7 +908,16 @@ extern "C" int svg2_test_kmeans_pp_init(const void *X, int dtype, int H, int N, 
     return svg2::kpp_dispatch(X, dtype, H, N, d, C, u, centroids, picked, ws, patience, static_cast<hipStream_t>(stream));
 }
 
-// Byte of the workspace at which the call above leaves one int32 per head: 1 if the head has been given up.
+// Workgroups that wait for one another in a call on the stream; 0: none do.
+extern "C" int svg2_test_kmeans_pp_waiting(int H, int N, void *stream)
+{
+    int ncu = 0;
+    if (svg2::kpp_stream_cus(static_cast<hipStream_t>(stream), &ncu) != SVG2_OK) return -1;
+    const int nch = svg2::cdiv(N, svg2::KPP_CHUNK), cpw = svg2::kpp_loop_chunks(H, nch, ncu);
+    return cpw > 0 && cpw < nch ? H * svg2::cdiv(nch, cpw) : 0;
+}
+
+// Byte of the workspace at which svg2_test_kmeans_pp_init leaves one int32 per head: 1 if the head has been given up.
 extern "C" size_t svg2_test_kmeans_pp_given_up(int H, int N, int d, int C)
 {
     size_t total;

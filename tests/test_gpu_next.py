@@ -195,3 +195,39 @@ def test_kmeans_pp_heads_that_are_given_up_are_done_again(svg2, oracle, dtype, H
     at = lib.svg2_test_kmeans_pp_given_up(H, N, d, C)
     assert torch.equal(ws[at:at + 4 * H].view(torch.int32), torch.ones(H, dtype=torch.int32, device="cuda"))
     _check_draws(oracle, X, u, picked, cent)
+
+
+def test_kmeans_pp_waiting_workgroups_fit_the_streams_compute_units(svg2):
+    """The workgroups that wait for one another are at most as many as the CUs that the stream may use.  (The mask has bits in every
+    group of 32 and of 8 CUs; nothing is launched on the stream.)"""
+    lib, vp = _test_library(), ctypes.c_void_p
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    shapes = [(24, 16384), (1, 65536), (10, 30000), (1, 2048), (40, 75600)]
+    whole = [lib.svg2_test_kmeans_pp_waiting(H, N, vp(torch.cuda.current_stream().cuda_stream)) for H, N in shapes]
+    # chunks of 256 tokens, 2, 4, 6 or 8 of them to a workgroup
+    assert cus < 256 or whole == [192, 128, 200, 0, 0]
+    for bits, n in ((0xFFFF, cus // 2), (0xFF, cus // 4)):
+        mask = (ctypes.c_uint32 * (cus // 32))(*[bits] * (cus // 32))
+        st = vp()
+        assert lib.hipExtStreamCreateWithCUMask(ctypes.byref(st), len(mask), mask) == 0
+        part = [lib.svg2_test_kmeans_pp_waiting(H, N, st) for H, N in shapes]
+        assert lib.hipStreamDestroy(st) == 0
+        assert all(0 <= p <= n for p in part) and part[1] == min(whole[1], n)
+
+
+def test_kmeans_pp_in_a_graph(svg2):
+    # several workgroups per head; the draws change with u between replays
+    X, u, Xd, ud = _seeding_case("bf16", 3, 5000, 128, 20)
+    ws = torch.empty(svg2.load_library().svg2_kmeans_pp_init_workspace_size(3, 5000, 20), dtype=torch.uint8, device="cuda")
+    svg2.svg2_kmeans_pp_init(Xd, 20, ud, ws=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        res = svg2.svg2_kmeans_pp_init(Xd, 20, ud, ws=ws)
+    for i in range(4):
+        ud.copy_(torch.from_numpy(np.random.default_rng(i).random((3, 20))))
+        g.replay()
+        torch.cuda.synchronize()
+        eager = svg2.svg2_kmeans_pp_init(Xd, 20, ud)
+        torch.cuda.synchronize()
+        assert torch.equal(res.picked, eager.picked) and torch.equal(res.centroids, eager.centroids)
