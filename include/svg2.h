@@ -369,7 +369,9 @@ int svg2_kmeans_pp_init(const void *X, int dtype, int H, int N, int d, int C,
 #define SVG2_PROFILE_MAX_CALLS 256
 #define SVG2_PROFILE_MAX_SPANS 16384
 enum {
-    SVG2_K_KMEANS_ASSIGN = 0,      /* assign step, Q and K side in one launch (Section 4.1) */
+    SVG2_K_KMEANS_ASSIGN = 0,      /* assign step, Q and K side in one launch (Section 4.1);
+                                    * bf16 heads of up to 1024 tokens and 4096 / d clusters:
+                                    * all of k-means, in one kernel                        */
     SVG2_K_KMEANS_SETTLE = 1,      /* near-ties again in double precision                   */
     SVG2_K_KMEANS_SORT = 2,        /* counting sort of the labels                           */
     SVG2_K_KMEANS_SEGSUM_FULL = 3, /* segmented sum over all tokens (short heads: with the  */

@@ -557,8 +557,8 @@ __global__ __launch_bounds__(320, 8) void kpp_step_kernel(const T *__restrict__ 
 // instead of 6).
 //
 // What bounds a draw is its chain of round trips: record out and seen, the D2 of one chunk, the new centre's row, the rows that are
-// measured, D2 out.  us per draw, a launch for each / this kernel: 24 heads of 16,384 tokens (d = 128, bf16, 64 components) 13.8 /
-// 8.9, 40 of 9000 14.9 / 9.2, 10 of 30,000 (d = 64) 8.4 / 7.6, 4 of 4096 (d = 64, fp32) 6.0 / 4.7, 1000 of 900 (one workgroup
+// measured, D2 out.  us per draw, a launch for each / this kernel: 24 heads of 16,384 tokens (d = 128, bf16, 64 components) 13.0 /
+// 8.7, 40 of 9000 14.9 / 9.2, 10 of 30,000 (d = 64) 8.4 / 7.6, 4 of 4096 (d = 64, fp32) 6.0 / 4.7, 1000 of 900 (one workgroup
 // each) 32.5 / 15.2.  Beyond 65,536 tokens (more than KPP_LOOKS records to a lane) and beyond a workgroup per CU a launch
 // for each draw stays: one head of 75,600 7.1 / 7.5.
 static constexpr int KPP_SLOTS = 4;

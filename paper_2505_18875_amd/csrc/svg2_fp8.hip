@@ -210,7 +210,9 @@ static constexpr float F8_SEARCH_HEADROOM = 8.0f;   // .. and moves when a score
 static constexpr float F8_LEVEL = 7.0f;
 static constexpr float F8_HEADROOM = 8.0f;  // queries that take part when a wavefront moves its levels: their maximum is above 2^8
 static constexpr int F8_SAMPLE = 3;         // tiles of keys whose maximum gives a row its level, if it has at least ..
-static constexpr int F8_SAMPLE_MIN = 32;    // .. this many tiles (dense, 24 heads of 9601 tokens: 3 % faster with than without)
+// .. this many tiles.  Thresholds of 16 / 32 / 64 / 128 / none in us: 24 heads of 16,384 tokens, rows of 32 tiles: 397 / 398 / 404 / 403 /
+// 405; of 78 tiles: 816 / 810 / 817 / 827 / 821; 40 heads of 75,600 (338 tiles): 17,527 / 17,550 / 17,514 / 17,532 / 17,954.
+static constexpr int F8_SAMPLE_MIN = 32;
 
 template <int D, bool SEARCH>
 __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(

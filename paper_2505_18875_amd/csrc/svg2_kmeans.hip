@@ -20,6 +20,8 @@
 //             not depend on the order of the additions -- reproducible bit for bit, independent of how skewed
 //             the cluster sizes are, and the delta update below never drifts.  From the second iteration on
 //             only the tokens whose label changed are moved between the cluster sums.
+//             Short heads: straight from the labels, together with the means; the shortest bf16 heads go through
+//             all iterations in one workgroup (kmeans_update_small_kernel, kmeans_tiny_bf16_kernel).
 //   finalize  mean = sum / count in double (an empty cluster keeps its centroid), the fp32 centroid that is
 //             handed back, the bf16 copy the next assign reads (rounded from the DOUBLE mean, so it is the
 //             correctly rounded bf16 of the mean), and ||c||^2 of that copy.
