@@ -367,7 +367,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) ones[i] = 0x38383838;          // E4M3 1.0
 
-    if constexpr (SEARCH) {
+    if constexpr (SEARCH) {                     // ==== the loop that searches for block maxima, two buffers
     ATT_ROWS(0)
     ATT_ROWS(1)
     __syncthreads();
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     }
 #undef ATT_TILE
     asm volatile("s_nop 7" : "+v"(lt));         // (see phase D: margin before the accumulators are read)
-    } else {
+    } else {                                    // ==== the loop without a search, three buffers
     lds_addresses();
     // ---- level of a long row: F8_LEVEL below the maximum over F8_SAMPLE tiles of keys spread over the whole sequence.  (The
     // scores are formed twice for these, but a row whose level starts at the maximum of its first 64 keys takes it up later,
@@ -920,7 +920,7 @@ __global__ __launch_bounds__(64 * ATT_NW, 8 / ATT_NW) void attn_fp8_kernel(
     }
 #undef ATT_TILE
 #undef ATT_EXP
-    }
+    }                                           // ==== both
 #undef ATT_FENCE
 #undef ATT_PIN
 #undef ATT_ROWS
