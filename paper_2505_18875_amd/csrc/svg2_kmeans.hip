@@ -7,7 +7,7 @@
 //             the B operand (columns), so a lane's 16 accumulators are 16 centroids of ONE token.  The
 //             accumulators start at -||c||^2 / 2, so argmin ||c||^2 - 2 x.c is the argmax of the accumulator.
 //             Each accumulator gets its position written into its 4 lowest mantissa bits; the largest and the
-//             second largest of these keys are tracked per token (max3 / med3 trees, no compare-and-select
+//             second largest of these keys are tracked per token (max3 / med3 chains, no compare-and-select
 //             chains), which gives the label and the gap to the runner-up.
 //             fp32 input: MFMA 32x32x2 fp32, the centroids of a token dealt out to several wavefronts; a handful of
 //             centroids: one token per thread.
@@ -344,21 +344,15 @@ __global__ __launch_bounds__(64 * KM_FIN_NW) void kmeans_finalize_kernel(KmArgs 
 // between chunks.
 //
 // A wavefront takes 64 tokens at a time, as two blocks of 32.  Per 32-centroid row block it issues the 2 KS matrix
-// instructions of both, then reduces their accumulators to (best, runner-up) with max3 / med3 trees while the other wavefront of
+// instructions of both, then reduces their accumulators to (best, runner-up) with max3 / med3 chains while the other wavefront of
 // the SIMD has the matrix cores.
 //
 // Near-ties (see KM_TIE_*) are listed for kmeans_settle_kernel.
-struct KmTop2 {                 // temporaries of one top-2 reduction, alive across its chunks
-    float key[16], t3, s3, T[4], U[4], T01, U01, m01, T23, Tb, Ub;
-    bool upd;
-};
-
 template <int D, bool OBJ>
 __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArgs a, KmIter it)
 {
     constexpr int KS = D / 16;              // MFMA k-steps
     constexpr int ROW = D + 8;              // LDS row stride in elements (16 bytes of padding)
-    constexpr int NCH = 8;                  // chunks of a top-2 reduction
     extern __shared__ __align__(16) unsigned char s_raw[];
     // -||c||^2 / 2 first: its reads then have offsets below 64 KB, which fit the instruction, and cost no address
     // arithmetic in the step loop
@@ -374,7 +368,6 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
     static_assert(64 * KM_NW == KM_CMAX, "one -||c||^2/2 per thread");
 
 #define KM_FENCE __builtin_amdgcn_sched_barrier(0);
-#define KM_PIN(X)
     // this workgroup's part of the block sequence, the same for both sides
     const int part_q = nb_all / (int)gridDim.x, part_r = nb_all % (int)gridDim.x;
     int part_lo = (int)blockIdx.x * part_q + min((int)blockIdx.x, part_r);
@@ -556,63 +549,22 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
                 const uint4 v = *reinterpret_cast<const uint4 *>(&s_c[(rb * 32 + col) * ROW + 8 * half + 16 * s]);
                 __builtin_memcpy(&am[s], &v, 16);
             };
-            // chunk c (0 .. NCH - 1) of the top-2 reduction of A into (bst, snd, bse)
-            auto red_chunk = [&](int c, const f32x16 &A, KmTop2 &r, float &bst, float &snd, int &bse, int rbase) {
-                auto pack = [&](int i) {
-                    r.key[i] = __uint_as_float((__float_as_uint(A[i]) & 0xFFFFFFF0u) | (unsigned)i);
-                    KM_PIN(r.key[i])
-                };
-                if (c == 0) {
-                    pack(0); pack(1); pack(2); pack(3);
-                    r.t3 = km_max3(r.key[0], r.key[1], r.key[2]);
-                    r.s3 = km_med3(r.key[0], r.key[1], r.key[2]);
-                    KM_PIN(r.t3) KM_PIN(r.s3)
-                } else if (c == 1) {
-                    r.T[0] = km_max(r.t3, r.key[3]);
-                    r.U[0] = km_med3(r.t3, r.s3, r.key[3]);
-                    pack(4); pack(5); pack(6); pack(7);
-                    KM_PIN(r.T[0]) KM_PIN(r.U[0])
-                } else if (c == 2) {
-                    r.t3 = km_max3(r.key[4], r.key[5], r.key[6]);
-                    r.s3 = km_med3(r.key[4], r.key[5], r.key[6]);
-                    r.T[1] = km_max(r.t3, r.key[7]);
-                    r.U[1] = km_med3(r.t3, r.s3, r.key[7]);
-                    r.T01 = km_max(r.T[0], r.T[1]);
-                    r.m01 = km_min(r.T[0], r.T[1]);
-                    KM_PIN(r.U[1]) KM_PIN(r.T01) KM_PIN(r.m01)
-                } else if (c == 3) {
-                    r.U01 = km_max3(r.m01, r.U[0], r.U[1]);
-                    pack(8); pack(9); pack(10); pack(11);
-                    r.t3 = km_max3(r.key[8], r.key[9], r.key[10]);
-                    KM_PIN(r.U01) KM_PIN(r.t3)
-                } else if (c == 4) {
-                    r.s3 = km_med3(r.key[8], r.key[9], r.key[10]);
-                    r.T[2] = km_max(r.t3, r.key[11]);
-                    r.U[2] = km_med3(r.t3, r.s3, r.key[11]);
-                    pack(12); pack(13); pack(14);
-                    KM_PIN(r.T[2]) KM_PIN(r.U[2])
-                } else if (c == 5) {
-                    pack(15);
-                    r.t3 = km_max3(r.key[12], r.key[13], r.key[14]);
-                    r.s3 = km_med3(r.key[12], r.key[13], r.key[14]);
-                    r.T[3] = km_max(r.t3, r.key[15]);
-                    r.U[3] = km_med3(r.t3, r.s3, r.key[15]);
-                    r.T23 = km_max(r.T[2], r.T[3]);
-                    KM_PIN(r.U[3]) KM_PIN(r.T23)
-                } else if (c == 6) {
-                    const float m23 = km_min(r.T[2], r.T[3]);
-                    const float U23 = km_max3(m23, r.U[2], r.U[3]);
-                    r.Tb = km_max(r.T01, r.T23);
-                    const float mb = km_min(r.T01, r.T23);
-                    r.Ub = km_max3(mb, r.U01, U23);
-                    r.upd = r.Tb > bst;
-                    KM_PIN(r.Tb) KM_PIN(r.Ub)
-                } else {
-                    bse = r.upd ? rbase : bse;
-                    snd = km_max3(km_min(bst, r.Tb), snd, r.Ub);
-                    bst = km_max(bst, r.Tb);
-                    KM_PIN(bse) KM_PIN(snd) KM_PIN(bst)
+            // (largest, runner-up) of A's keys and the running pair.  Two keys at a time against the largest so far: max3 is
+            // the new largest, med3 what of the three may be the runner-up, and the medians meet the runner-up two by two:
+            // 2.5 instructions per pair of keys.  (Groups of four, each reduced to a pair of its own and the pairs merged, took 3.75:
+            // 487 instead of 480 us per launch at 40 heads of 75,600 tokens, 100 and 500 centroids.)
+            auto reduce = [&](const f32x16 &A, float &bst, float &snd, int &bse, int rbase) {
+                float key[16], med[8], top = bst;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) key[i] = __uint_as_float((__float_as_uint(A[i]) & 0xFFFFFFF0u) | (unsigned)i);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    med[i] = km_med3(top, key[2 * i], key[2 * i + 1]);
+                    top = km_max3(top, key[2 * i], key[2 * i + 1]);
+                    if (i & 1) snd = km_max3(snd, med[i - 1], med[i]);
                 }
+                bse = top > bst ? rbase : bse;
+                bst = top;
             };
             // One step = one 32-centroid row block against both token blocks: 2 KS matrix instructions back to back,
             // the LDS reads of the next row block's operands, then the two top-2 reductions on the vector ALU
@@ -646,11 +598,7 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
                 KM_FENCE
                 const int rbase = c0 + rb * 32;
 #pragma unroll
-                for (int q = 0; q < KM_TB; ++q) {
-                    KmTop2 r;
-#pragma unroll
-                    for (int c = 0; c < NCH; ++c) red_chunk(c, acc[q], r, best[q], second[q], bbase[q], rbase);
-                }
+                for (int q = 0; q < KM_TB; ++q) reduce(acc[q], best[q], second[q], bbase[q], rbase);
                 KM_FENCE
             }
             KM_FENCE
@@ -720,7 +668,6 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
     }   // spans
     }   // sides
 #undef KM_FENCE
-#undef KM_PIN
 }
 
 // ---------------------------------------------------------------- settle near-ties, bf16 input
