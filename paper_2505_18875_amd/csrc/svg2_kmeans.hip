@@ -20,8 +20,9 @@
 //             not depend on the order of the additions -- reproducible bit for bit, independent of how skewed
 //             the cluster sizes are, and the delta update below never drifts.  From the second iteration on
 //             only the tokens whose label changed are moved between the cluster sums.
-//             Short heads: straight from the labels, together with the means; the shortest bf16 heads go through
-//             all iterations in one workgroup (kmeans_update_small_kernel, kmeans_tiny_bf16_kernel).
+//             Shorter heads: straight from the labels, together with the means (kmeans_update_kernel, with a few clusters of few
+//             heads kmeans_update_small_kernel); the shortest bf16 heads go through all iterations in one workgroup
+//             (kmeans_tiny_bf16_kernel).
 //   finalize  mean = sum / count in double (an empty cluster keeps its centroid), the fp32 centroid that is
 //             handed back, the bf16 copy the next assign reads (rounded from the DOUBLE mean, so it is the
 //             correctly rounded bf16 of the mean), and ||c||^2 of that copy.
@@ -102,6 +103,7 @@ struct KmArgs {
     KmSide s[2];
     int nsides, H, N, iters;
     int nc[2];                  // wavefronts that share a token block (fp32 assign)
+    int gc[2];                  // clusters of a workgroup of the update kernel
     bool want_order;            // the caller reads offsets and perm of the last iteration
 };
 
@@ -216,42 +218,32 @@ __device__ __forceinline__ bf16_t f64_to_bf16(double m)
 static constexpr int KM_FIN_NW = 4;
 static constexpr int KM_FIN_UB = 8;             // pieces requested together
 
-// One cluster by one wavefront; size() is the number of its tokens, add(s) adds the sums of its pieces to s.
-template <bool BF16, int D, typename G, typename F>
-__device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &S, const KmIter &it, int mode, int h, int j, G size,
-                                                 F add)
+// One cluster by one wavefront: s = its new sum (element lane + 64 e), cnt its tokens; s_prev, prev: sum and tokens before, read
+// only of a cluster without tokens.
+template <bool BF16, int D>
+__device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &S, const KmIter &it, int mode, int h, int j,
+                                                 const double (&s)[D / 64], int cnt, const double (&s_prev)[D / 64], int prev)
 {
     constexpr int EL = D / 64;
     const int lane = threadIdx.x & 63, C = S.C;
-    if (j == 0 && lane == 0) S.flag_cnt[h] = 0;         // the next assign step starts an empty list
     const size_t idx = ((size_t)h * C + j) * D + lane;
     double c[EL];
     if (mode != 0) {
-        const int cnt = size();
-        double s[EL], s_prev[EL];
-#pragma unroll
-        for (int e = 0; e < EL; ++e) {
-            s_prev[e] = (mode == 2 || (cnt == 0 && it.t > 0)) ? S.csum[idx + 64 * e] : 0.0;
-            s[e] = mode == 2 ? s_prev[e] : 0.0;
-        }
-        add(s);
         if (cnt > 0) {
 #pragma unroll
             for (int e = 0; e < EL; ++e) c[e] = s[e] / (double)cnt;
         } else {                                        // an empty cluster keeps its centroid
-            const int prev = it.t > 0 ? S.counts[(size_t)h * C + j] : 0;
 #pragma unroll
             for (int e = 0; e < EL; ++e) {
                 c[e] = it.t == 0 ? (double)S.init[idx + 64 * e]
                        : prev > 0 ? s_prev[e] / (double)prev
                                   : S.cd[idx + 64 * e];
                 S.cd[idx + 64 * e] = c[e];
-                s[e] = 0.0;
             }
         }
 #pragma unroll
         for (int e = 0; e < EL; ++e) {
-            S.csum[idx + 64 * e] = s[e];
+            S.csum[idx + 64 * e] = cnt > 0 ? s[e] : 0.0;
             if (it.t + 1 == a.iters) S.centroids[idx + 64 * e] = (float)c[e];
         }
         if (lane == 0) S.counts[(size_t)h * C + j] = cnt;
@@ -272,8 +264,7 @@ __device__ __forceinline__ void finalize_cluster(const KmArgs &a, const KmSide &
         } else {
             S.ct[((((size_t)h * 2 + (k & 1)) * (D / 8) + (k >> 3)) * C + j) * 4 + ((k >> 1) & 3)] = (float)c[e];
         }
-        double sq = cr * cr;
-        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        const double sq = km_wave_sum(cr * cr);
         n2 = e == 0 ? sq : n2 + sq;
     }
     if (lane == 0) {
@@ -292,11 +283,23 @@ __global__ __launch_bounds__(64 * KM_FIN_NW) void kmeans_finalize_kernel(KmArgs 
     const KmSide S = side ? a.s[1] : a.s[0];
     const int C = S.C, j = side ? jj - a.s[0].C : jj;
     if (side >= a.nsides || j >= C) return;
-    auto size = [&]() {
+    if (j == 0 && lane == 0) S.flag_cnt[h] = 0;         // the next assign step starts an empty list
+    int cnt = 0, prev = 0;
+    double s[EL], s_prev[EL];
+#pragma unroll
+    for (int e = 0; e < EL; ++e) s[e] = s_prev[e] = 0.0;
+    if (mode != 0) {
         const int32_t *off = KM_SEL(S.offsets, set) + (size_t)h * (C + 1);
-        return off[j + 1] - off[j];
-    };
-    finalize_cluster<BF16, D>(a, S, it, mode, h, j, size, [&](double (&s)[EL]) {
+        cnt = off[j + 1] - off[j];
+        if (mode == 2 || (cnt == 0 && it.t > 0)) {
+            prev = cnt == 0 ? S.counts[(size_t)h * C + j] : 0;
+#pragma unroll
+            for (int e = 0; e < EL; ++e) s_prev[e] = S.csum[((size_t)h * C + j) * D + lane + 64 * e];
+        }
+        if (mode == 2) {
+#pragma unroll
+            for (int e = 0; e < EL; ++e) s[e] = s_prev[e];
+        }
         auto add_pieces = [&](int st, double sign) {
             const int32_t *fp = KM_SEL(S.first_piece, st) + (size_t)h * (C + 1);
             const int p0 = fp[j], np = fp[j + 1] - p0;
@@ -329,7 +332,8 @@ __global__ __launch_bounds__(64 * KM_FIN_NW) void kmeans_finalize_kernel(KmArgs 
         };
         add_pieces(set, 1.0);
         if (mode == 2) add_pieces(1 - set, -1.0);
-    });
+    }
+    finalize_cluster<BF16, D>(a, S, it, mode, h, j, s, cnt, s_prev, prev);
 }
 
 // ---------------------------------------------------------------- assign, bf16 MFMA
@@ -1012,16 +1016,39 @@ template <typename T> __device__ __forceinline__ void add_row(const uint4 &v, do
     }
 }
 
+// acc = sum of the rows row(0) .. row(cnt - 1) of Xh, by one wavefront: the elements part * EPL .. of every lane whose row part that is
+template <typename T, int D, int UB, typename R>
+__device__ __forceinline__ void sum_rows(const T *Xh, int cnt, R row, double (&acc)[16 / sizeof(T)])
+{
+    constexpr int EPL = 16 / sizeof(T);            // elements per lane
+    constexpr int LPR = D / EPL;                   // lanes per row
+    constexpr int RPI = 64 / LPR;                  // rows per instruction
+    const int lane = threadIdx.x & 63, sub = lane / LPR, part = lane % LPR;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.0;
+    for (int r = 0; r < cnt; r += RPI * UB) {
+        uint4 v[UB];
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            v[u] = reinterpret_cast<const uint4 *>(Xh + (size_t)row(min(r + u * RPI + sub, cnt - 1)) * D)[part];
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            if (r + u * RPI + sub < cnt) add_row<T>(v[u], acc);
+    }
+    // lanes with the same `part` hold the same columns
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o);
+}
+
 // One piece (rows row0 .. + nrows of the sorted order pm) of cluster cl by one wavefront: acc = the sum of its rows that
 // qualify, the elements part * EPL .. of every lane whose row part that is; returns how many rows there are (0: no acc).
 template <typename T, int D, bool DELTA>
 __device__ __forceinline__ int sum_piece(const T *Xh, const int32_t *pm, const int32_t *other, int cl, int row0, int nrows,
                                          int32_t *list, double (&acc)[16 / sizeof(T)])
 {
-    constexpr int EPL = 16 / sizeof(T);            // elements per lane
-    constexpr int LPR = D / EPL;                   // lanes per row
-    constexpr int RPI = 64 / LPR;                  // rows per instruction
-    const int lane = threadIdx.x & 63, sub = lane / LPR, part = lane % LPR;
+    const int lane = threadIdx.x & 63;
     int cnt = nrows;
     if (DELTA) {
         const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -1047,29 +1074,7 @@ __device__ __forceinline__ int sum_piece(const T *Xh, const int32_t *pm, const i
         }
         if (cnt == 0) return 0;
     }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.0;
-    for (int r = 0; r < cnt; r += RPI * KM_UB) {
-        uint4 v[KM_UB];
-        bool ok[KM_UB];
-#pragma unroll
-        for (int u = 0; u < KM_UB; ++u) {
-            const int rr = r + u * RPI + sub;
-            ok[u] = rr < cnt;
-            const int src = DELTA ? list[min(rr, cnt - 1)] : pm[row0 + min(rr, cnt - 1)];
-            v[u] = reinterpret_cast<const uint4 *>(Xh + (size_t)src * D)[part];
-        }
-#pragma unroll
-        for (int u = 0; u < KM_UB; ++u) {
-            if (!ok[u]) continue;
-            add_row<T>(v[u], acc);
-        }
-    }
-    // lanes with the same `part` hold the same columns
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1)
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o);
+    sum_rows<T, D, KM_UB>(Xh, cnt, [&](int r) { return DELTA ? list[r] : pm[row0 + r]; }, acc);
     return cnt;
 }
 
@@ -1183,6 +1188,15 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
     }
     __syncthreads();
     const int np_in = (tot_in + KM_SEG - 1) / KM_SEG, np = np_in + (tot_out + KM_SEG - 1) / KM_SEG;
+    double s_prev[EL];
+    int n_prev = 0;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) s_prev[e] = 0.0;
+    if (wave == 0 && it.t > 0) {            // used behind the last barrier
+        n_prev = S.counts[(size_t)h * S.C + j];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) s_prev[e] = S.csum[((size_t)h * S.C + j) * D + lane + 64 * e];
+    }
     const int sub = lane / LPR, part = lane % LPR;
     for (int q = wave; q < np; q += NW) {
         const int r0 = q < np_in ? q * KM_SEG : tot_in + (q - np_in) * KM_SEG;
@@ -1212,11 +1226,223 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
     }
     __syncthreads();
     if (wave != 0) return;
-    finalize_cluster<BF16, D>(a, S, it, mode, h, j, [&]() { return cnt; }, [&](double (&s)[EL]) {
-        for (int q = 0; q < np; ++q)
+    double s[EL];
 #pragma unroll
-            for (int e = 0; e < EL; ++e) s[e] += q < np_in ? s_ps[q][lane + 64 * e] : -s_ps[q][lane + 64 * e];
-    });
+    for (int e = 0; e < EL; ++e) s[e] = mode == 2 ? s_prev[e] : 0.0;
+    for (int q = 0; q < np; ++q)
+#pragma unroll
+        for (int e = 0; e < EL; ++e) s[e] += q < np_in ? s_ps[q][lane + 64 * e] : -s_ps[q][lane + 64 * e];
+    if (j == 0 && lane == 0) S.flag_cnt[h] = 0;         // the next assign step starts an empty list
+    finalize_cluster<BF16, D>(a, S, it, mode, h, j, s, cnt, s_prev, n_prev);
+}
+
+// The update step of up to KU_G clusters of a head in one workgroup, straight from the labels (mode 1: all tokens of the clusters, mode 2:
+// those that joined and those that left one): the wavefronts go through the labels of the head, each through its share of
+// them, and list the tokens in token order; the lists are sorted by (cluster, joined / left) in LDS, stably, summed in pieces of
+// KU_PIECE rows by one wavefront each, KU_SLOTS pieces at a time, and the pieces added to the clusters' sums in their order -- so
+// that fp32 sums are the same in every run.  A wavefront whose list is full waits for the next round of this.  At the
+// end the wavefronts finish the clusters.  So an iteration needs no sort; the last one sorts for the order that is handed on.
+//
+// What bounds it is the chain of round trips (labels, rows) and the labels, which every workgroup reads whole; sort, sums and means of
+// the longer heads are a chain of three to five launches.  Five iterations in us, those / this kernel:
+//   24 heads x 16,384, bf16, D = 128, 100 / 500 clusters: 384 / 334, 568 / 505      24 x 9601, 500: 446 / 368      6 x 11,000, 150: 257 / 203
+//   24 x 30,000, 500: 823 / 762      2 x 30,000, 300: 295 / 250      4 x 20,000, D = 64, 1000: 369 / 283      4 x 9601, fp32, 500: 540 / 488
+// Beyond KU_N tokens the labels cost as much as is gained (8 x 37,800, 500: 523 / 499; 1 x 75,600: 341 / 357; 1 x 118,800, 64: 237 / 439).
+// All tokens are summed this way (mode 1) up to KU_FULL_N: a workgroup then has all rows of its clusters to add, about 100 rows per us, and of
+// a cluster that holds most of a long head the pieces side by side are faster.  Two iterations, sorted in the first / not at all:
+// 4 x 6000, 200 clusters: 82 / 69; 24 x 8000, 100: 112 / 103; all tokens in one cluster: 12 x 8000, 81 / 133, 12 x 12,000, 99 / 187.
+// As few workgroups as give every CU one read the labels (three times as many: 24 x 16,384, 500 clusters: 544; 6 x 11,000, 150: 232).
+static constexpr int KU_N = 32768, KU_FULL_N = 8192;
+static constexpr int KU_NW = 8;                 // wavefronts
+static constexpr int KU_G = 16;                 // most clusters of a workgroup
+static constexpr int KU_CAP = 448;              // entries of a wavefront's list (three workgroups fit a CU)
+static constexpr int KU_PIECE = 64, KU_SLOTS = 16, KU_UB = 4;
+static constexpr int KU_LB = 4;                 // groups of 64 labels requested together
+static constexpr int KU_B = 2 * KU_G;           // (cluster, left) pairs
+static_assert(KU_B * KU_NW == 256 && KU_B <= 32, "the scan below: four wavefronts, a lane of half a wavefront per pair");
+static_assert(KU_SLOTS == KU_G, "the sums of the clusters go out through the pieces' LDS");
+
+template <typename T, int D, bool BF16, bool DELTA>
+__global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, KmIter it)
+{
+    constexpr int EPL = 16 / sizeof(T), LPR = D / EPL, EL = D / 64;
+    __shared__ __align__(16) double s_ps[KU_SLOTS][D];
+    __shared__ int32_t s_ent[KU_NW][KU_CAP];    // listed tokens
+    __shared__ uint8_t s_bkt[KU_NW][KU_CAP];    // and their 2 * cluster + left
+    __shared__ int32_t s_tok[KU_NW * KU_CAP];   // sorted
+    __shared__ int32_t s_hist[KU_NW][KU_B];
+    __shared__ int32_t s_start[KU_B + 1], s_fp[KU_B + 1], s_tot[KU_B], s_sum[4];
+    __shared__ int32_t s_more;
+    const int h = blockIdx.y, N = a.N, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ng0 = (a.s[0].C + a.gc[0] - 1) / a.gc[0];
+    const int side = (int)blockIdx.x >= ng0 ? 1 : 0;
+    const KmSide S = side ? a.s[1] : a.s[0];
+    const int gc = KM_SEL(a.gc, side), c0 = ((int)blockIdx.x - (side ? ng0 : 0)) * gc, nc = min(gc, S.C - c0);
+    const T *Xh = reinterpret_cast<const T *>(S.X) + (size_t)h * N * D;
+    const int32_t *lab = (side ? it.lab[1] : it.lab[0]) + (size_t)h * N;
+    const int32_t *prev = (side ? it.lab_prev[1] : it.lab_prev[0]) + (size_t)h * N;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    // this wavefront's share of the tokens, whole groups of 64
+    const int ngrp = (N + 63) / 64, per = (ngrp + KU_NW - 1) / KU_NW, hi = min(ngrp, (wave + 1) * per);
+    int pos = min(ngrp, wave * per);
+
+    // thread (msub, mk): element mk of the sums of the clusters msub, msub + NSUB, ..
+    constexpr int NSUB = 64 * KU_NW / D, JN = KU_G / NSUB;
+    const int mk = tid % D, msub = tid / D;
+    double csum[JN];
+#pragma unroll
+    for (int i = 0; i < JN; ++i) {
+        const int j = msub + NSUB * i;
+        csum[i] = DELTA && j < nc ? S.csum[((size_t)h * S.C + c0 + j) * D + mk] : 0.0;
+    }
+    int total = 0;                              // wavefront 0, lane b: entries of pair b so far
+
+    for (bool more = true; more;) {
+        int cnt = 0;
+        if (tid < KU_B * KU_NW) (&s_hist[0][0])[tid] = 0;
+        if (tid == 0) s_more = 0;
+        __syncthreads();
+        auto put = [&](bool take, int n, int pair) {
+            const unsigned long long m = __ballot(take);
+            if (m == 0) return;
+            if (take) {
+                const int at = cnt + __popcll(m & lt);
+                s_ent[wave][at] = n;
+                s_bkt[wave][at] = (uint8_t)pair;
+                atomicAdd(&s_hist[wave][pair], 1);
+            }
+            cnt += __popcll(m);
+        };
+        constexpr int MOST = DELTA ? 128 : 64;  // entries of a group at most
+        while (pos < hi && cnt + MOST <= KU_CAP) {
+            int tl[KU_LB], tp[KU_LB];
+#pragma unroll
+            for (int u = 0; u < KU_LB; ++u) {
+                const int n = min(64 * (pos + u) + lane, N - 1);
+                tl[u] = lab[n];
+                if (DELTA) tp[u] = prev[n];
+            }
+#pragma unroll
+            for (int u = 0; u < KU_LB; ++u)
+                if (pos < hi && cnt + MOST <= KU_CAP) {
+                    const int n = 64 * pos + lane;
+                    const bool ok = n < N && (!DELTA || tl[u] != tp[u]);
+                    put(ok && (unsigned)(tl[u] - c0) < (unsigned)nc, n, 2 * (tl[u] - c0));
+                    if (DELTA) put(ok && (unsigned)(tp[u] - c0) < (unsigned)nc, n, 2 * (tp[u] - c0) + 1);
+                    ++pos;
+                }
+        }
+        if (pos < hi && lane == 0) s_more = 1;
+        __syncthreads();
+        // ---- sort by pair, then wavefront, then token
+        {
+            int v = 0, incl = 0;
+            if (tid < 256) {
+                v = s_hist[tid % KU_NW][tid / KU_NW];
+                incl = v;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int u = __shfl_up(incl, o);
+                    if (lane >= o) incl += u;
+                }
+                if (lane == 63) s_sum[wave] = incl;
+            }
+            __syncthreads();
+            if (tid < 256) {
+                int first = incl - v;
+#pragma unroll
+                for (int w = 0; w < 3; ++w) first += w < wave ? s_sum[w] : 0;
+                s_hist[tid % KU_NW][tid / KU_NW] = first;
+                if (tid % KU_NW == 0) s_start[tid / KU_NW] = first;
+                if (tid == 255) s_start[KU_B] = first + v;
+            }
+            __syncthreads();
+        }
+        if (wave == 0) {
+            const int size = lane < KU_B ? s_start[lane + 1] - s_start[lane] : 0, np = (size + KU_PIECE - 1) / KU_PIECE;
+            total += size;
+            int incl = np;
+            for (int o = 1; o < KU_B; o <<= 1) {
+                const int u = __shfl_up(incl, o);
+                if (lane >= o) incl += u;
+            }
+            if (lane < KU_B) {
+                s_fp[lane] = incl - np;
+                s_tot[lane] = total;
+                if (lane == KU_B - 1) s_fp[KU_B] = incl;
+            }
+        }
+        for (int e0 = 0; e0 < cnt; e0 += 64) {
+            const bool ok = e0 + lane < cnt;
+            const int n = ok ? s_ent[wave][e0 + lane] : 0, b = ok ? s_bkt[wave][e0 + lane] : 0;
+            unsigned long long peers = __ballot(ok);
+#pragma unroll
+            for (int q = 1; q < KU_B; q <<= 1) {
+                const unsigned long long m = __ballot((b & q) != 0);
+                peers &= (b & q) ? m : ~m;
+            }
+            const int rank = __popcll(peers & lt);
+            if (ok) s_tok[s_hist[wave][b] + rank] = n;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (ok && rank == 0) s_hist[wave][b] += __popcll(peers);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // ---- sums
+        more = s_more != 0;
+        const int np = s_fp[KU_B];
+        for (int r0 = 0; r0 < np; r0 += KU_SLOTS) {
+            for (int q = r0 + wave; q < min(np, r0 + KU_SLOTS); q += KU_NW) {
+                const int fp = s_fp[lane % KU_B];
+                const int b = __popcll(__ballot(lane < KU_B && fp <= q)) - 1;   // (the last of equal ones has the pieces)
+                const int row0 = s_start[b] + (q - s_fp[b]) * KU_PIECE;
+                double acc[EPL];
+                sum_rows<T, D, KU_UB>(Xh, min(KU_PIECE, s_start[b + 1] - row0), [&](int r) { return s_tok[row0 + r]; }, acc);
+                if (lane < LPR) {
+#pragma unroll
+                    for (int e = 0; e < EPL; e += 2)
+                        *reinterpret_cast<double2 *>(&s_ps[q - r0][lane * EPL + e]) = make_double2(acc[e], acc[e + 1]);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < JN; ++i) {
+                const int b = 2 * (msub + NSUB * i);
+                const int p0 = s_fp[b], p1 = s_fp[b + 1], p2 = s_fp[b + 2];
+                for (int p = max(p0, r0); p < min(p1, r0 + KU_SLOTS); ++p) csum[i] += s_ps[p - r0][mk];
+                for (int p = max(p1, r0); p < min(p2, r0 + KU_SLOTS); ++p) csum[i] -= s_ps[p - r0][mk];
+            }
+            __syncthreads();
+        }
+    }
+    if (c0 == 0 && tid == 0) S.flag_cnt[h] = 0;     // the next assign step starts an empty list
+#pragma unroll
+    for (int i = 0; i < JN; ++i) s_ps[msub + NSUB * i][mk] = csum[i];
+    __syncthreads();
+    for (int j = wave; j < nc; j += KU_NW) {
+        const int joined = s_tot[2 * j], left = s_tot[2 * j + 1];
+        // nothing moved: sum, mean and what the next assign step reads of them stay
+        if (DELTA && joined + left == 0 && it.t + 1 < a.iters) continue;
+        const int n_prev = it.t > 0 ? S.counts[(size_t)h * S.C + c0 + j] : 0, size = (DELTA ? n_prev : 0) + joined - left;
+        double sum[EL], s_prev[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            sum[e] = s_ps[j][lane + 64 * e];
+            s_prev[e] = size == 0 && it.t > 0 ? S.csum[((size_t)h * S.C + c0 + j) * D + lane + 64 * e] : 0.0;
+        }
+        finalize_cluster<BF16, D>(a, S, it, DELTA ? 2 : 1, h, c0 + j, sum, size, s_prev, n_prev);
+    }
+}
+
+// Clusters of a workgroup of the update kernel: as many as leave a workgroup per CU over all heads and sides, and no more than a sixteenth
+// of the side's (few large clusters: their tokens are shared out over more CUs).
+static int kmeans_update_group(int H, int C, int call)
+{
+    int g = KU_G;
+    while (g > 1 && ((long long)call * H < 256ll * g || 16 * g > C)) g >>= 1;
+    return g;
 }
 
 // ---------------------------------------------------------------- all iterations of a short head, bf16
@@ -1610,8 +1836,11 @@ static int kmeans_run(KmArgs a, hipStream_t st)
     if (BF16) SVG2_TRY(device_cu_count(&ncu));
     int call = 0, pmax = 0, ncmax = 1;
     bool any_obj = false, any_few = false;
+    for (int s = 0; s < ns; ++s) call += a.s[s].C;
+    int ngroups = 0;
     for (int s = 0; s < ns; ++s) {
-        call += a.s[s].C;
+        a.gc[s] = kmeans_update_group(H, a.s[s].C, call);
+        ngroups += cdiv(a.s[s].C, a.gc[s]);
         any_few |= !BF16 && kmeans_f32_few(H, N, a.s[s].C);
         a.nc[s] = kmeans_f32_share(H, N, a.s[s].C);
         ncmax = std::max(ncmax, a.nc[s]);
@@ -1631,7 +1860,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
     }
     const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);
-    const bool small = kmeans_update_small(H, N, call);
+    const bool small = kmeans_update_small(H, N, call), direct = !small && N <= KU_N;
     {
         ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
         hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, KmIter{}, 0);
@@ -1685,7 +1914,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
                 }
             }
         }
-        // label-sorted order of the tokens and its pieces, then the segmented sum over it
+        // label-sorted order of the tokens and its pieces, then the segmented sum over it; or sums and means straight from the labels
+        const bool straight = small || (direct && (!full || N <= KU_FULL_N));
         SortArgs sa = {};
         for (int s = 0; s < ns; ++s) {
             const KmSide &k = a.s[s];
@@ -1695,22 +1925,26 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             sa.s[s].offsets = k.offsets[it.set];
             sa.s[s].perm = k.perm[it.set];
             sa.s[s].inv_perm = nullptr;
-            sa.s[s].pieces = small ? nullptr : k.pieces[it.set];         // (small: the order is handed on, not read here)
+            sa.s[s].pieces = straight ? nullptr : k.pieces[it.set];      // (straight: the order is handed on, not read here)
             sa.s[s].first_piece = k.first_piece[it.set];
             sa.s[s].n_pieces = k.n_pieces[it.set];
             sa.s[s].max_pieces = k.max_pieces;
             sa.s[s].seg = KM_SEG;
         }
-        if (!small || (t + 1 == iters && a.want_order)) {
+        if (!straight || (t + 1 == iters && a.want_order)) {
             ProfileSpan sp(SVG2_K_KMEANS_SORT, st);
             SVG2_TRY(sort_launch(sa, ns, H, N, st));
         }
-        if (small) {
+        if (straight) {
             ProfileSpan sp(full ? SVG2_K_KMEANS_SEGSUM_FULL : SVG2_K_KMEANS_SEGSUM_DELTA, st);
-            if (N <= KM_SMALL_N4)
+            if (small && N <= KM_SMALL_N4)
                 hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16, 4>), dim3(call, H), dim3(256), 0, st, a, it, full ? 1 : 2);
-            else
+            else if (small)
                 hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16, 16>), dim3(call, H), dim3(1024), 0, st, a, it, full ? 1 : 2);
+            else if (full)
+                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, false>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
+            else
+                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, true>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
             continue;
         }
         if (full) {

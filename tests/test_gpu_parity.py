@@ -349,6 +349,50 @@ def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
     _check_kmeans(oracle, res, X, init, 4, dtype == "bf16", H, C)
 
 
+@pytest.mark.parametrize("dtype,d,H,N,C", [
+    # straight from the labels: all tokens summed that way (up to 8192) or only those that moved (up to 32,768), and one more
+    ("bf16", 128, 1, 8192, 520), ("bf16", 128, 1, 8193, 520), ("f32", 64, 1, 32768, 70), ("bf16", 64, 1, 32769, 70),
+    # one cluster to a workgroup, whose lists overflow again and again; a last workgroup with one cluster, with all its clusters
+    ("bf16", 64, 1, 8192, 2), ("f32", 128, 2, 8129, 3), ("bf16", 64, 12, 4200, 257), ("f32", 128, 12, 4097, 256),
+    # a last group of labels with one token, wavefronts without tokens; many heads
+    ("bf16", 128, 40, 2049, 77), ("f32", 64, 700, 65, 20), ("bf16", 128, 2, 20481, 40)])
+def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
+    r = np.random.default_rng(9900 + N + C)
+    centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
+    X = np.stack([centres[h][r.integers(0, 5, size=N)] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
+    X = wl.round_to_bf16(X) if dtype == "bf16" else X.astype(np.float32)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
+    if C > 2:
+        init[:, 1] += 60.0                                      # nothing is near it: stays empty
+    res = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), 4)
+    again = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), 4)
+    torch.cuda.synchronize()
+    assert torch.equal(res.centroids, again.centroids) and torch.equal(res.labels, again.labels)    # fp32 sums: in a fixed order
+    if dtype == "bf16":
+        _check_kmeans(oracle, res, X, init, 4, True, min(H, 3), C)
+        return
+    # fp32 labels: a token on the border of two clusters that fp32 arithmetic gives to the other one moves both means, and from
+    # there on the run is another one than the oracle's (32,768 x 70: 0.998 equal labels, by this route and by the sorted one).  So the
+    # run is held to the definition, with its own labels: every mean is that of the members, rounded once (the sums are
+    # doubles); one more iteration from them gives every token a centroid at the least distance, up to what 2 d roundings of
+    # numbers below |x|^2 + |c|^2 make of a difference of two distances.
+    step = svg2.svg2_kmeans(to_dev(X, dtype), res.centroids.clone(), 1)
+    torch.cuda.synchronize()
+    for h in range(min(H, 3)):
+        lab, cnt = to_np(res.labels[h]), to_np(res.counts[h])
+        cen = to_np(res.centroids[h]).astype(np.float64)
+        np.testing.assert_array_equal(cnt, np.bincount(lab, minlength=C))
+        sums = np.zeros((C, d))
+        np.add.at(sums, lab, X[h].astype(np.float64))
+        has = cnt > 0
+        mean = sums[has] / cnt[has, None]
+        assert np.all(np.abs(cen[has] - mean) <= 2.0 ** -24 * np.abs(mean) + 1e-12 * np.abs(X[h]).max())
+        x2, c2 = (X[h].astype(np.float64) ** 2).sum(1), (cen ** 2).sum(1)
+        dist = c2[None] - 2.0 * X[h].astype(np.float64) @ cen.T
+        got = dist[np.arange(N), to_np(step.labels[h])]
+        assert np.all(got - dist.min(1) <= 4 * d * 2.0 ** -24 * (x2 + c2.max()))
+
+
 @pytest.mark.parametrize("d,H,N,C", [
     # one workgroup goes through all iterations of a head: its largest sizes, and one token or cluster more than it takes
     (64, 2, 1024, 64), (128, 2, 1024, 32), (64, 1, 1025, 64), (64, 1, 1024, 65), (128, 1, 1024, 33),
