@@ -97,7 +97,15 @@ struct KmSide {
     double *psum[2];            // [H,max_pieces,d]
     int32_t *moved[2];          // [H,max_pieces] whether the delta update found a token in the piece (else no psum)
     int max_pieces;
+    // bf16, KmArgs::lists: the tokens of every group of 64 whose label changed in this iteration, or may still change as they are
+    // settled (KM_MV_OPEN), in the place of the second set, which is then not used: [H,N], those of group g from 64 g on (token % 64,
+    // previous label << 6, label << 18), and [H, 4 max_pieces] their number
+    unsigned *mv_list;
+    int32_t *mv_cnt;
 };
+
+static constexpr unsigned KM_MV_OPEN = 1u << 30;       // (labels are below 2^12)
+static_assert(SVG2_MAX_CLUSTERS <= 1 << 12, "two labels and the position in a group fit an entry");
 
 struct KmArgs {
     KmSide s[2];
@@ -105,6 +113,7 @@ struct KmArgs {
     int nc[2];                  // wavefronts that share a token block (fp32 assign)
     int gc[2];                  // clusters of a workgroup of the update kernel
     bool want_order;            // the caller reads offsets and perm of the last iteration
+    bool lists;                 // the assign step lists the tokens whose label changed, the update step reads these lists (bf16)
 };
 
 // labels written / read by iteration t
@@ -390,6 +399,7 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
     const int side = one_block || (blockIdx.x & 1) ? sd : a.nsides - 1 - sd;
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
+    const int32_t *labels_prev = side ? it.lab_prev[1] : it.lab_prev[0];
     const int C = S.C;
     const int nchunk = (C + KM_CMAX - 1) / KM_CMAX;
 #pragma unroll 1
@@ -488,25 +498,38 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
         // What a block of tokens writes (label; running pair or the near-tie list) is held back until the tokens of
         // the next block have been waited for: that wait is for ALL outstanding memory operations, and behind the
         // stores it would last a round trip to memory although the tokens arrived long ago.
-        int pend_n[KM_TB], pend_c[KM_TB];
+        // The halves of a wavefront hold the same results; lane l writes those of token l of the group.
+        static_assert(KM_TB == 2, "a lane writes one token");
+        int pend_tok0 = 0, pend_c[KM_TB], pend_prev = 0;
         float pend_T[KM_TB], pend_U[KM_TB];
         bool pend_f[KM_TB], pend = false;
         auto flush = [&]() {
             if (!pend) return;
             pend = false;
-#pragma unroll
-            for (int tb = 0; tb < KM_TB; ++tb) {
-                const int n = pend_n[tb];
-                if (half == 0 && n < N) {
-                    labels[(size_t)h * N + n] = pend_c[tb];
-                    if (!last_chunk) {
-                        S.best[(size_t)h * N + n] = pend_T[tb];
-                        S.second[(size_t)h * N + n] = pend_U[tb];
-                    } else if (pend_f[tb]) {
-                        const int pos = atomicAdd(&S.flag_cnt[h], 1);
-                        S.flag_list[(size_t)h * N + pos] = n;
-                    }
+            const int n = pend_tok0 + lane, c = half ? pend_c[1] : pend_c[0];
+            const bool flagged = half ? pend_f[1] : pend_f[0];
+            if (n < N) {
+                labels[(size_t)h * N + n] = c;
+                if (!last_chunk) {
+                    S.best[(size_t)h * N + n] = half ? pend_T[1] : pend_T[0];
+                    S.second[(size_t)h * N + n] = half ? pend_U[1] : pend_U[0];
+                } else if (flagged) {
+                    const int pos = atomicAdd(&S.flag_cnt[h], 1);
+                    S.flag_list[(size_t)h * N + pos] = n;
                 }
+            }
+            if (a.lists && last_chunk && pend_tok0 < N) {
+                int sd_o = side;                                // (read here from the arguments, not held in registers)
+                asm volatile("" : "+s"(sd_o));
+                unsigned *mv_list = sd_o ? a.s[1].mv_list : a.s[0].mv_list;
+                int32_t *mv_cnt = sd_o ? a.s[1].mv_cnt : a.s[0].mv_cnt;
+                const int mvs = 4 * (sd_o ? a.s[1].max_pieces : a.s[0].max_pieces);
+                const bool moved = n < N && (flagged || c != pend_prev);
+                const unsigned long long m = __ballot(moved);
+                if (moved)
+                    mv_list[(size_t)h * N + pend_tok0 + __popcll(m & ((1ull << lane) - 1ull))] =
+                        (unsigned)lane | (unsigned)pend_prev << 6 | (unsigned)c << 18 | (flagged ? KM_MV_OPEN : 0u);
+                if (lane == 0) mv_cnt[(size_t)h * mvs + pend_tok0 / 64] = __popcll(m);
             }
         };
         // Accumulator i of a lane is centroid 8 (i/4) + 4 half + i%4 of the row block; its key is the accumulator
@@ -597,7 +620,10 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
                     if (rb == 0) load_part(NB{}, g_next, std::integral_constant<int, 0>{});
                     if (rb == pstep) load_part(NB{}, g_next, std::integral_constant<int, 1>{});
                     if (rb == 2 * pstep) load_part(NB{}, g_next, std::integral_constant<int, 2>{});
-                    if (rb == 3 * pstep) load_part(NB{}, g_next, std::integral_constant<int, 3>{});
+                    if (rb == 3 * pstep) {
+                        load_part(NB{}, g_next, std::integral_constant<int, 3>{});
+                        pend_prev = labels_prev[(size_t)h * N + min(N - 1, tok0 + lane)];
+                    }
                 }
                 KM_FENCE
                 const int rbase = c0 + rb * 32;
@@ -645,11 +671,12 @@ __global__ __launch_bounds__(64 * KM_NW, 1) void kmeans_assign_bf16_kernel(KmArg
                     // runner-up within the error of this contraction: the token is settled in double precision
                     // (a tie, including an exact one, always is)
                     const float tau = KM_TIE_KEY * fabsf(T) + KM_TIE_ACC * (0.5f * x2 + cmax2);
-                    flagged = half == 0 && n < N && !(T - U > tau);
+                    flagged = !(T - U > tau);
                     if (OBJ && S.objective && half == 0 && n < N) obj += x2 - 2.f * T;
                 }
-                pend_n[tb] = n; pend_c[tb] = cidx < C ? cidx : 0; pend_T[tb] = T; pend_U[tb] = U; pend_f[tb] = flagged;
+                pend_c[tb] = cidx < C ? cidx : 0; pend_T[tb] = T; pend_U[tb] = U; pend_f[tb] = flagged;
             }
+            pend_tok0 = tok0;
             pend = true;
             return g_next;
         };
@@ -1251,6 +1278,9 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
 // All tokens are summed this way (mode 1) up to KU_FULL_N: a workgroup then has all rows of its clusters to add, about 100 rows per us, and of
 // a cluster that holds most of a long head the pieces side by side are faster.  Two iterations, sorted in the first / not at all:
 // 4 x 6000, 200 clusters: 82 / 69; 24 x 8000, 100: 112 / 103; all tokens in one cluster: 12 x 8000, 81 / 133, 12 x 12,000, 99 / 187.
+// bf16 heads of more than KU_FULL_N tokens: the assign step lists the tokens that moved (KU_LISTS, kmeans_update_lists).  With four wavefronts in place of eight, so that all workgroups of 24 heads of 16,384 tokens run at once, a late iteration
+// took 21 instead of 26 us and the first of them 97 instead of 60; with 32 clusters to a workgroup and several workgroups for the tokens
+// of few clusters 34 and 88.
 // As few workgroups as give every CU one read the labels (three times as many: 24 x 16,384, 500 clusters: 544; 6 x 11,000, 150: 232).
 static constexpr int KU_N = 32768, KU_FULL_N = 8192;
 static constexpr int KU_NW = 8;                 // wavefronts
@@ -1262,9 +1292,12 @@ static constexpr int KU_B = 2 * KU_G;           // (cluster, left) pairs
 static_assert(KU_B * KU_NW == 256 && KU_B <= 32, "the scan below: four wavefronts, a lane of half a wavefront per pair");
 static_assert(KU_SLOTS == KU_G, "the sums of the clusters go out through the pieces' LDS");
 
-template <typename T, int D, bool BF16, bool DELTA>
+enum { KU_ALL = 0, KU_LABELS = 1, KU_LISTS = 2 };     // all tokens; those that moved, by the labels; by the assign step's lists
+
+template <typename T, int D, bool BF16, int MODE>
 __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, KmIter it)
 {
+    constexpr bool DELTA = MODE != KU_ALL;
     constexpr int EPL = 16 / sizeof(T), LPR = D / EPL, EL = D / 64;
     __shared__ __align__(16) double s_ps[KU_SLOTS][D];
     __shared__ int32_t s_ent[KU_NW][KU_CAP];    // listed tokens
@@ -1286,6 +1319,9 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
     // this wavefront's share of the tokens, whole groups of 64
     const int ngrp = (N + 63) / 64, per = (ngrp + KU_NW - 1) / KU_NW, hi = min(ngrp, (wave + 1) * per);
     int pos = min(ngrp, wave * per);
+    const unsigned *mv = S.mv_list + (size_t)h * N;
+    const int32_t *mvc = S.mv_cnt + (size_t)h * 4 * S.max_pieces;
+    int ent = 0;                                // lists: next entry of the 64 groups from pos on
 
     // thread (msub, mk): element mk of the sums of the clusters msub, msub + NSUB, ..
     constexpr int NSUB = 64 * KU_NW / D, JN = KU_G / NSUB;
@@ -1315,23 +1351,64 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
             cnt += __popcll(m);
         };
         constexpr int MOST = DELTA ? 128 : 64;  // entries of a group at most
-        while (pos < hi && cnt + MOST <= KU_CAP) {
-            int tl[KU_LB], tp[KU_LB];
-#pragma unroll
-            for (int u = 0; u < KU_LB; ++u) {
-                const int n = min(64 * (pos + u) + lane, N - 1);
-                tl[u] = lab[n];
-                if (DELTA) tp[u] = prev[n];
-            }
-#pragma unroll
-            for (int u = 0; u < KU_LB; ++u)
-                if (pos < hi && cnt + MOST <= KU_CAP) {
-                    const int n = 64 * pos + lane;
-                    const bool ok = n < N && (!DELTA || tl[u] != tp[u]);
-                    put(ok && (unsigned)(tl[u] - c0) < (unsigned)nc, n, 2 * (tl[u] - c0));
-                    if (DELTA) put(ok && (unsigned)(tp[u] - c0) < (unsigned)nc, n, 2 * (tp[u] - c0) + 1);
-                    ++pos;
+        if constexpr (MODE == KU_LISTS) {
+            while (pos < hi && cnt + MOST <= KU_CAP) {
+                int incl = pos + lane < hi ? mvc[pos + lane] : 0;
+                const int own = incl;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int u = __shfl_up(incl, o);
+                    if (lane >= o) incl += u;
                 }
+                const int excl = incl - own, all = __builtin_amdgcn_readlane(incl, 63);
+                while (ent < all && cnt + MOST <= KU_CAP) {
+                    unsigned w[KU_LB];
+                    int n0[KU_LB];
+#pragma unroll
+                    for (int u = 0; u < KU_LB; ++u) {
+                        const int e = min(ent + 64 * u + lane, all - 1);
+                        int g = 0;                          // groups whose entries end in front of e
+#pragma unroll
+                        for (int o = 32; o > 0; o >>= 1)
+                            if (__shfl(incl, g + o - 1) <= e) g += o;
+                        n0[u] = 64 * (pos + g);
+                        w[u] = mv[n0[u] + e - __shfl(excl, g)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < KU_LB; ++u)
+                        if (ent < all && cnt + MOST <= KU_CAP) {
+                            const bool ok = ent + lane < all;
+                            const int n = n0[u] + (int)(w[u] & 63u), p = (int)(w[u] >> 6 & 4095u) - c0;
+                            int l = (int)(w[u] >> 18 & 4095u) - c0;
+                            if (w[u] & KM_MV_OPEN) l = lab[n] - c0;
+                            put(ok && l != p && (unsigned)l < (unsigned)nc, n, 2 * l);
+                            put(ok && l != p && (unsigned)p < (unsigned)nc, n, 2 * p + 1);
+                            ent += 64;
+                        }
+                }
+                if (ent >= all) {
+                    ent = 0;
+                    pos += 64;
+                }
+            }
+        } else {
+            while (pos < hi && cnt + MOST <= KU_CAP) {
+                int tl[KU_LB], tp[KU_LB];
+#pragma unroll
+                for (int u = 0; u < KU_LB; ++u) {
+                    const int n = min(64 * (pos + u) + lane, N - 1);
+                    tl[u] = lab[n];
+                    if (DELTA) tp[u] = prev[n];
+                }
+#pragma unroll
+                for (int u = 0; u < KU_LB; ++u)
+                    if (pos < hi && cnt + MOST <= KU_CAP) {
+                        const int n = 64 * pos + lane;
+                        const bool ok = n < N && (!DELTA || tl[u] != tp[u]);
+                        put(ok && (unsigned)(tl[u] - c0) < (unsigned)nc, n, 2 * (tl[u] - c0));
+                        if (DELTA) put(ok && (unsigned)(tp[u] - c0) < (unsigned)nc, n, 2 * (tp[u] - c0) + 1);
+                        ++pos;
+                    }
+            }
         }
         if (pos < hi && lane == 0) s_more = 1;
         __syncthreads();
@@ -1434,6 +1511,20 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
         }
         finalize_cluster<BF16, D>(a, S, it, DELTA ? 2 : 1, h, c0 + j, sum, size, s_prev, n_prev);
     }
+}
+
+// Whether the assign step of bf16 heads lists the tokens that moved.  The update kernel then reads a few per cent of what the labels of two iterations are; the assign step pays for
+// it with a comparison per token, which up to KU_FULL_N tokens is what is gained (24 heads x 6000, 200 clusters, five iterations: 240
+// us by the labels, 247 by lists; 24 x 8000, 500: 349 / 351; 40 x 9000, D = 64, 100: 247 / 241).
+//   24 x 16,384, D = 128, 100 / 500 clusters: 339 / 321, 505 / 491      2 x 30,000, 300: 261 / 235      24 x 30,000, 100, Zipf sizes: 520 / 480
+// Beyond KU_N tokens, where the labels are too much for every workgroup to read, it is the sorted order that they replace.  A
+// workgroup has all rows of its clusters to add, so it takes clusters that are not too large for that:
+//   8 x 37,800, 1000 / 2000 clusters: 837 / 730, 1392 / 1222 (Zipf sizes 842 / 758, 1436 / 1297)      8 x 75,600, 4000: 3951 / 3648
+//   1 x 118,800, 500, Zipf sizes (not taken): 392 / 513      8 x 37,800, 100 (not taken): 379 / 391
+static constexpr int KU_LISTS_SIZE = 64;        // tokens per cluster, beyond KU_N tokens
+static bool kmeans_update_lists(int H, int N, int call, int cmin)
+{
+    return !kmeans_update_small(H, N, call) && N > KU_FULL_N && (N <= KU_N || N <= (long long)KU_LISTS_SIZE * cmin);
 }
 
 // Clusters of a workgroup of the update kernel: as many as leave a workgroup per CU over all heads and sides, and no more than a sixteenth
@@ -1753,6 +1844,8 @@ static void kmeans_carve_side(Carver &c, KmSide &k, int H, int N, int d, int C)
     }
     k.labels_alt = c.take<int32_t>((size_t)H * N);
     k.flag_cnt = c.take<int32_t>((size_t)H);
+    k.mv_list = reinterpret_cast<unsigned *>(k.perm[1]);        // (the memory, whatever perm[1] points to later)
+    k.mv_cnt = reinterpret_cast<int32_t *>(k.pieces[1]);        // 16 bytes per 256 tokens and more
     k.flag_list = c.take<int32_t>((size_t)H * N);
     k.best = c.take<float>(C > KM_CMAX ? (size_t)H * N : 0);
     k.second = c.take<float>(C > KM_CMAX ? (size_t)H * N : 0);
@@ -1834,9 +1927,12 @@ static int kmeans_run(KmArgs a, hipStream_t st)
     const int H = a.H, N = a.N, iters = a.iters, ns = a.nsides;
     int ncu = 0;
     if (BF16) SVG2_TRY(device_cu_count(&ncu));
-    int call = 0, pmax = 0, ncmax = 1;
+    int call = 0, cmin = a.s[0].C, pmax = 0, ncmax = 1;
     bool any_obj = false, any_few = false;
-    for (int s = 0; s < ns; ++s) call += a.s[s].C;
+    for (int s = 0; s < ns; ++s) {
+        call += a.s[s].C;
+        cmin = std::min(cmin, a.s[s].C);
+    }
     int ngroups = 0;
     for (int s = 0; s < ns; ++s) {
         a.gc[s] = kmeans_update_group(H, a.s[s].C, call);
@@ -1861,6 +1957,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
     }
     const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);
     const bool small = kmeans_update_small(H, N, call), direct = !small && N <= KU_N;
+    a.lists = BF16 && kmeans_update_lists(H, N, call, cmin);
     {
         ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
         hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, KmIter{}, 0);
@@ -1915,7 +2012,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             }
         }
         // label-sorted order of the tokens and its pieces, then the segmented sum over it; or sums and means straight from the labels
-        const bool straight = small || (direct && (!full || N <= KU_FULL_N));
+        const bool straight = small || (full ? direct && N <= KU_FULL_N : direct || a.lists);
         SortArgs sa = {};
         for (int s = 0; s < ns; ++s) {
             const KmSide &k = a.s[s];
@@ -1942,9 +2039,11 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             else if (small)
                 hipLaunchKernelGGL((kmeans_update_small_kernel<T, D, BF16, 16>), dim3(call, H), dim3(1024), 0, st, a, it, full ? 1 : 2);
             else if (full)
-                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, false>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
+                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, KU_ALL>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
+            else if (a.lists)
+                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, BF16 ? KU_LISTS : KU_LABELS>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
             else
-                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, true>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
+                hipLaunchKernelGGL((kmeans_update_kernel<T, D, BF16, KU_LABELS>), dim3(ngroups, H), dim3(64 * KU_NW), 0, st, a, it);
             continue;
         }
         if (full) {

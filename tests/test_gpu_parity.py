@@ -393,6 +393,25 @@ def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
         assert np.all(got - dist.min(1) <= 4 * d * 2.0 ** -24 * (x2 + c2.max()))
 
 
+@pytest.mark.parametrize("d,H,N,C,iters", [
+    # by the lists of the assign step: its shortest and longest heads, a last group with one token, centroids in two chunks
+    (128, 1, 8193, 520, 3), (64, 2, 32768, 300, 3), (128, 1, 32769, 520, 3), (64, 1, 33280, 520, 4), (64, 1, 33281, 520, 3),
+    # one cluster to a workgroup, with all tokens listed: the lists overflow again and again
+    (64, 1, 20000, 2, 4), (128, 3, 10047, 33, 4),
+    # an update that sums all clusters afresh in between
+    (64, 2, 8200, 40, 18)])
+def test_kmeans_update_from_lists(svg2, oracle, d, H, N, C, iters):
+    r = np.random.default_rng(9950 + N + C)
+    centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
+    X = np.stack([centres[h][r.integers(0, 5, size=N)] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
+    X = wl.round_to_bf16(X)
+    init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
+    init[:, C - 1] = init[:, 0]         # every token whose nearest centroid is one of these is settled, and moves as that decides
+    res = svg2.svg2_kmeans(to_dev(X, "bf16"), to_dev(init), iters)
+    torch.cuda.synchronize()
+    _check_kmeans(oracle, res, X, init, iters, True, H, C)
+
+
 @pytest.mark.parametrize("d,H,N,C", [
     # one workgroup goes through all iterations of a head: its largest sizes, and one token or cluster more than it takes
     (64, 2, 1024, 64), (128, 2, 1024, 32), (64, 1, 1025, 64), (64, 1, 1024, 65), (128, 1, 1024, 33),
