@@ -443,7 +443,8 @@ static int forward_impl(const void *Q, const void *K, const void *V, int dtype, 
                            nullptr, L.density, L.stage_ws, st));
     profile_mark(pb, 3, st);
     // Section 4.3: attention over the selected pairs, result back in token order
-    SVG2_TRY(attn_plan_launch(dtype, H, N, Cq, Ck, L.offsets_q, L.offsets_k, L.row_ptr, L.col_idx, L.stage_ws, st));
+    SVG2_TRY(attn_plan_launch(gather_free ? K : L.Kp, gather_free ? V : L.Vp, dtype, H, N, d, Cq, Ck, L.offsets_q, L.offsets_k, L.row_ptr,
+                              L.col_idx, L.stage_ws, st));
     profile_mark(pb, 4, st);
     if (mode == FWD_FP8)
         SVG2_TRY(attn_fp8_main_launch(L.Q8, L.K8, L.V8, L.sq, L.sk, L.sv, H, N, d, Cq, Ck, L.row_ptr, L.perm_q, L.perm_k,
@@ -529,7 +530,7 @@ int svg2_sparse_attn_fp8(const void *Q8, const void *K8, const void *V8, const f
     SVG2_TRY(check_ws(ws, ws_bytes, attn_ws_bytes(SVG2_BF16, H, N, d, Cq, Ck)));
     SVG2_TRY(attn_fp8_prepare());
     hipStream_t st = static_cast<hipStream_t>(stream);
-    SVG2_TRY(attn_plan_launch(SVG2_BF16, H, N, Cq, Ck, offsets_q, offsets_k, row_ptr, col_idx, ws, st));
+    SVG2_TRY(attn_plan_launch(nullptr, nullptr, SVG2_BF16, H, N, d, Cq, Ck, offsets_q, offsets_k, row_ptr, col_idx, ws, st));
     return attn_fp8_main_launch(Q8, K8, V8, scale_q, scale_k, scale_v, H, N, d, Cq, Ck, row_ptr, perm_q, perm_k, scale,
                                 O, lse, ws, st);
 }

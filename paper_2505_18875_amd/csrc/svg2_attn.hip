@@ -18,7 +18,8 @@
 //                      already laid out as the B operand of O^T += V^T P^T.
 //                      V^T comes out of LDS through the transposing 64-bit
 //                      read (ds_read_b64_tr_b16).
-//   attn_f32_kernel    fp32 storage: MFMA 32x32x2 fp32, the keys of a work item split over the wavefronts.
+//   attn_f32_kernel    fp32 storage: operands as two fp16 halves or, where these would lose bits, MFMA 32x32x2 fp32; the keys of
+//                      a work item split over the wavefronts.
 //
 // The result of sorted row r is stored at row perm_q[r] (Section 4.1: the
 // inverse query permutation restores the original order).
@@ -66,12 +67,13 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t *__restric
                                                         int32_t *__restrict__ n_tiles, int2 *__restrict__ runs,
                                                         int32_t *__restrict__ row_keys,
                                                         int32_t *__restrict__ cl_first, int key_tiles,
-                                                        int32_t *__restrict__ tile_run)
+                                                        int32_t *__restrict__ tile_run, unsigned *__restrict__ range)
 {
     __shared__ int32_t s_wave[4];
     const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     if (blockIdx.x == 0) {
+        if (range && tid < F32_RANGE) range[(size_t)h * F32_RANGE + tid] = 0;      // (attn_range fills it in the next launch)
         // tiles: running count over clusters, 256 clusters per pass
         const int32_t *oq = offsets_q + (size_t)h * (Cq + 1);
         int4 *tl = tiles + (size_t)h * max_tiles;
@@ -187,14 +189,67 @@ __device__ __forceinline__ int ord_scan(int v, int32_t *s_wave, int *total)
     return before + incl - v;
 }
 
+// Range of the K and V values of a head (fp32 storage), for the rule that lets the attention kernel split them (below):
+// all entries are maxima of |x| as bits, so that a NaN or an infinity is above every number.
+//   [0], [1]  largest of K, of V         [2], [3]  ~(smallest row maximum of K, of V; rows of zeros left out)
+//   [4 ..]    largest of every V column
+// Workgroups 1 .. of the order kernel's launch, RANGE_PASSES rows per row slot: one pass over K and V next to the one workgroup
+// that sorts the list, which takes longer.
+static constexpr int RANGE_PASSES = 4;
+static inline int attn_range_blocks(int H, int N, int d) { return 2 * H * cdiv(N, RANGE_PASSES * (1024 / (d / 4))); }
+
+__device__ __forceinline__ void attn_range(int blk, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int d,
+                                           unsigned *__restrict__ range, unsigned *s_max)
+{
+    const int tid = threadIdx.x, lpr = d / 4, step = 1024 / lpr, nb = (N + RANGE_PASSES * step - 1) / (RANGE_PASSES * step);
+    const int side = blk / (H * nb), h = blk / nb % H, r0 = blk % nb * RANGE_PASSES * step;
+    const int chunk = tid % lpr;
+    const uint4 *X = reinterpret_cast<const uint4 *>((side ? V : K) + (size_t)h * N * d);
+    if (tid < 2 + 128) s_max[tid] = 0;
+    __syncthreads();
+    uint4 v[RANGE_PASSES];
+#pragma unroll
+    for (int p = 0; p < RANGE_PASSES; ++p) v[p] = X[(size_t)min(r0 + p * step + tid / lpr, N - 1) * lpr + chunk];
+    unsigned most = 0, least = 0, col[4] = {0, 0, 0, 0};        // least: ~ of the smallest
+#pragma unroll
+    for (int p = 0; p < RANGE_PASSES; ++p) {
+        const unsigned b[4] = {v[p].x & 0x7FFFFFFFu, v[p].y & 0x7FFFFFFFu, v[p].z & 0x7FFFFFFFu, v[p].w & 0x7FFFFFFFu};
+        unsigned m = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { col[e] = max(col[e], b[e]); m = max(m, b[e]); }
+        for (int o = 1; o < lpr; o <<= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+        most = max(most, m);
+        if (m != 0) least = max(least, ~m);
+    }
+    for (int o = lpr; o < 64; o <<= 1) {
+        most = max(most, (unsigned)__shfl_xor((int)most, o));
+        least = max(least, (unsigned)__shfl_xor((int)least, o));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) col[e] = max(col[e], (unsigned)__shfl_xor((int)col[e], o));
+    }
+    if ((tid & 63) == 0) { atomicMax(&s_max[0], most); atomicMax(&s_max[1], least); }
+    if (side && (tid & 63) < lpr)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) atomicMax(&s_max[2 + 4 * chunk + e], col[e]);
+    __syncthreads();
+    unsigned *rg = range + (size_t)h * F32_RANGE;
+    if (tid < 2) atomicMax(&rg[2 * tid + side], s_max[tid]);
+    if (side && tid < d) atomicMax(&rg[4 + tid], s_max[2 + tid]);
+}
+
 __global__ __launch_bounds__(1024) void attn_order_kernel(const int32_t *__restrict__ offsets_q,
                                                           const int32_t *__restrict__ n_tiles, int32_t *tile_base,
                                                           const int32_t *__restrict__ row_keys,
                                                           const int32_t *__restrict__ cl_first, int H, int Cq, int BM,
-                                                          int32_t *__restrict__ order)
+                                                          int32_t *__restrict__ order, const float *__restrict__ K,
+                                                          const float *__restrict__ V, int N, int d, unsigned *__restrict__ range)
 {
     __shared__ int32_t s_cnt[ORD_BUCKETS];
     __shared__ int32_t s_wave[16];
+    if (blockIdx.x > 0) {                       // (fp32 storage only)
+        attn_range((int)blockIdx.x - 1, K, V, H, N, d, range, reinterpret_cast<unsigned *>(s_cnt));
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     for (int b = tid; b < ORD_BUCKETS; b += 1024) s_cnt[b] = 0;
     int all = 0;
@@ -784,24 +839,45 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
 // wavefronts share a work item rather than four for the small layers, where a CU has one at most (one head of 4096 tokens,
 // d = 64: 31 instead of 35 us).
 //
-// Matrix instruction 32x32x2 (fp32 in, fp32 out: the products and sums of the definition, at twice the rate of the
-// vector ALU; 64 cycles each).  S^T = K Q^T: a lane supplies key `col`, and its half of d is the half of the row the
-// lane half names (the contraction index may be taken in any order), so K goes from memory to the operand registers
-// in 16-byte loads.  Accumulator i is key 8 (i / 4) + 4 half + i % 4 of query `col` -- which is what O^T += V^T P^T wants
-// as its other operand, step i contracting the keys of accumulator i of the two lane halves.  Row m of output block b
-// is column DVB m + b, so that one load of DVB consecutive floats is the operand of all DVB blocks, and the DVB
-// accumulators of a row are consecutive floats of the result.
+// S^T = K Q^T: accumulator i is key 8 (i / 4) + 4 half + i % 4 of query `col`, which is what O^T += V^T P^T wants as its other
+// operand.  Row m of output block b is column DVB m + b, so that one load of DVB consecutive floats is the operand of all DVB
+// blocks, and the DVB accumulators of a row are consecutive floats of the result.
 //
-// Nothing is staged in LDS: a 32-key block is 128 matrix instructions (8192 cycles, d = 128) and 32 loads of 1 KB per
-// wavefront, so the loads hide behind the arithmetic with two register buffers that take turns (A: first halves of K
-// and of V, B: second halves).  One query per thread with K and V in LDS (64 queries per wavefront, one wavefront per
-// workgroup) took 13.8 instead of 0.66 ms for 4 heads of 9601 tokens at d = 128 (31 % selected: 58 GFLOP, so 88 of the
-// 154 TFLOP/s a large fp32 product reaches; a seventh of the rows of the 32-row tiles is padding), and 760 instead of
-// 31 us for one head of 4096 tokens at d = 64.  K rows through LDS (whole rows, direct loads, read back by row) instead of
-// 16 bytes of a row of its own per lane: 0.88 instead of 0.81 ms, so it is not these loads that bound it.
+// Operands in two halves (the first of the two loops).  The fp32 instruction takes 13 times as long as the fp16 one for the same
+// work, so where the values allow it a value x is taken as hi + lo, both fp16 (rounded to nearest: hi + lo is x to 2^-23), and a
+// product as hi hi + hi lo + lo hi, three 32x32x16 instructions.  K and V of a head and every Q row are first brought to 2^14 ..
+// 2^15 by a power of two and probabilities by 2^F32_LIFT, so that a lo keeps its bits down to 2^-17 of the largest value and is
+// off by at most 2^-39 of that below.  The rule: all values finite, the largest of K, of V and of a Q row within 2^+-40, no K or V
+// row and no V column whose largest value is more than 2^F32_SPREAD below the head's (rows and columns of zeros aside), and
+// scores that can reach F32_SCORE.  What the split drops is then below the roundings of the sums: an accumulator rounds behind
+// each of 3 instructions per 16 products instead of behind each of 16 products.  Relative error of O against 64 bits over 100 shapes of 98 to
+// 4200 keys, scores of standard deviation 3 to 16: 0.58 to 0.69 of the fp32 instruction's, of the log-sum-exp 0.62 to 1.0.  With scores that
+// cannot reach F32_SCORE the fp32 sums hardly err (O off by 1.6e-7 with scores around 0.01 and 500 keys, 2.7e-7 split; 3.2e-7 and 3.5e-7
+// with normal Q and K at D = 64), so these, infinities, NaN and outliers go through the fp32 instruction: the second loop.
+//
+// Time: 4 heads of 9601 tokens in 100 and 500 clusters, D = 128, 31 % selected (58 GFLOP; a seventh of the rows of the 32-row tiles is
+// padding) 0.67 -> 0.40 ms, one head of 4096 at D = 64 31 -> 22 us.  What bounds the first loop is the traffic into the CUs, 32 KB per
+// wavefront and 32 keys (10.8 TB/s of K and V in all); matrix and vector instructions are at 23 and 37 % of their rates.  Therefore K goes by whole
+// rows straight to LDS (a wavefront's own 32 rows, fetched while the block before is in its second product) instead of 16 bytes of a row per
+// lane, and the rows of a block are found from one load of 64 runs issued a block ahead, not by a walk through memory: 0.47 -> 0.40 ms together.  V
+// goes to registers, requested in front of the first product; Q, split, is read from LDS, which leaves the registers for that.
+// The second loop has K and V in two register buffers each: a 32-key block is 128 matrix instructions (8192 cycles, D = 128), which cover
+// its 32 loads.  One query per thread with K and V in LDS took 13.8 ms on the same shape.
 // No more wavefronts than a head has key blocks, rounded up to a power of two (5000 heads of 16 tokens, D = 64: 58 us with one,
 // 105 with eight), and four instead of eight in short heads that are work items enough without (3000 heads of 100 tokens, 10
 // and 20 clusters, a quarter selected: 302 instead of 495 us; 200 of 500, 30 and 60 clusters, D = 128: 208 instead of 276).
+static constexpr unsigned F32_EXP_LO = 127 - 40, F32_EXP_HI = 127 + 40, F32_SPREAD = 12;
+static constexpr float F32_LIFT = 14.f, F32_LIFT_BY = 16384.f, F32_SCORE = 256.f;
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// element e of the two halves of x * up (a power of two: exact); the compiler makes these v_cvt_pk_f16_f32 and v_fma_mix_f32
+__device__ __forceinline__ void f32_split(float x, float up, f16x8 &hi, f16x8 &lo, int e)
+{
+    const _Float16 h = (_Float16)fmaf(x, up, 0.f);
+    hi[e] = h;
+    lo[e] = (_Float16)fmaf(x, up, -(float)h);
+}
+
 static constexpr int F32_NW = 8, F32_MANY = 1024, F32_SHORT = 512;
 static constexpr int F32_BM = 32;
 
@@ -811,7 +887,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ tile_base, const int32_t *__restrict__ order, int max_tiles,
     const int2 *__restrict__ runs, const int32_t *__restrict__ row_keys, const int32_t *__restrict__ tile_run,
-    int key_tiles, float scale_log2, int group, float *__restrict__ O, float *__restrict__ lse)
+    int key_tiles, float scale_log2, int group, const unsigned *__restrict__ range, float *__restrict__ O, float *__restrict__ lse)
 {
     constexpr int DVB = D / 32;                 // output blocks of 32 columns
     constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's share of K or V
@@ -842,16 +918,47 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
     const char *Vb = reinterpret_cast<const char *>(V + (size_t)h * N * D);
     const int nblk = (L + 31) / 32;
 
-    float q[D / 2];
+    int qrow = row0 + min(nrows - 1, col);
+    if (perm_k) qrow = perm_q[(size_t)h * N + qrow];    // gather-free: Q is in token order
+    const float *Qr = Q + ((size_t)h * N + qrow) * D;
+    // Split operands or not: the same for all wavefronts of the work item (same Q rows, same head)
+    // split Q in LDS behind the wavefronts' shares: lane's part of step t is elements 16 t + 8 half .. of its row
+    f16x8 *s_q = reinterpret_cast<f16x8 *>(s_o + (size_t)NW * 32 * ROW);
+    bool split;
+    float k_up, v_up, q_up;                     // powers of two that bring the largest K, V of the head, Q of the row to 2^14 .. 2^15
     {
-        int r = row0 + min(nrows - 1, col);
-        if (perm_k) r = perm_q[(size_t)h * N + r];      // gather-free: Q is in token order
-        const float4 *src = reinterpret_cast<const float4 *>(Q + ((size_t)h * N + r) * D + half * (D / 2));
+        float q[D / 2];
 #pragma unroll
-        for (int k = 0; k < D / 8; ++k) {
-            const float4 w = src[k];
-            q[4 * k] = w.x; q[4 * k + 1] = w.y; q[4 * k + 2] = w.z; q[4 * k + 3] = w.w;
+        for (int t = 0; t < D / 16; ++t) {
+            const float4 *src = reinterpret_cast<const float4 *>(Qr + 16 * t + 8 * half);
+            const float4 w0 = src[0], w1 = src[1];
+            q[8 * t] = w0.x; q[8 * t + 1] = w0.y; q[8 * t + 2] = w0.z; q[8 * t + 3] = w0.w;
+            q[8 * t + 4] = w1.x; q[8 * t + 5] = w1.y; q[8 * t + 6] = w1.z; q[8 * t + 7] = w1.w;
         }
+        const unsigned *rg = range + (size_t)h * F32_RANGE;
+        const unsigned ke = rg[0] >> 23, ve = rg[1] >> 23;
+        unsigned qb = 0;
+#pragma unroll
+        for (int k = 0; k < D / 2; ++k) qb = max(qb, __float_as_uint(q[k]) & 0x7FFFFFFFu);
+        qb = max(qb, (unsigned)__shfl_xor((int)qb, 32));
+        const unsigned qe = qb == 0 ? 127u : qb >> 23;
+        bool ok = ke - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO && ve - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO &&
+                  qe - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO && (~rg[2] >> 23) + F32_SPREAD >= ke && (~rg[3] >> 23) + F32_SPREAD >= ve;
+        for (int c = lane; c < D; c += 64) ok = ok && (rg[4 + c] == 0 || (rg[4 + c] >> 23) + F32_SPREAD >= ve);
+        split = __all(ok) && __any(__uint_as_float(qb) * __uint_as_float(rg[0]) * ((float)D * scale_log2) >= F32_SCORE);
+        k_up = __uint_as_float((127 + 14 + 127 - ke) << 23);
+        v_up = __uint_as_float((127 + 14 + 127 - ve) << 23);
+        q_up = __uint_as_float((127 + 14 + 127 - qe) << 23);
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t)
+            if (t % NW == wave) {               // (wave-uniform; every wavefront holds the same row parts)
+                f16x8 qh, ql;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f32_split(q[8 * t + e], q_up, qh, ql, e);
+                s_q[2 * t * 64 + lane] = qh;
+                s_q[(2 * t + 1) * 64 + lane] = ql;
+            }
+        __syncthreads();
     }
     f32x16 oacc[DVB];
 #pragma unroll
@@ -861,7 +968,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
     float m = -INFINITY, l = 0.f;
 
     // byte offset of the row of key 32 j + col (past the end: the last key's row, so that nothing but selected rows is
-    // ever read; its score is masked)
+    // ever read here; its score is masked)
     auto row_off = [&](int j) -> unsigned {
         const int kk = min(32 * j + col, L - 1);
         // run in which the 64-key tile starts (the table ends at N keys; a row may have more, if its list names a
@@ -873,68 +980,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
         if (perm_k) r = pkh[r];                 // gather-free: sorted row -> token
         return (unsigned)r * RB;
     };
-    float4 bufA[NB], bufB[NB];
-    auto load_k = [&](float4 (&buf)[NB], unsigned off, int hf) {
-        const float4 *src = reinterpret_cast<const float4 *>(Kb + (off + (unsigned)(half * (RB / 2) + hf * (RB / 4))));
-#pragma unroll
-        for (int i = 0; i < NB; ++i) buf[i] = src[i];
-    };
     // V of contraction steps 8 hf .. 8 hf + 7: step i takes key 8 (i / 4) + 4 half + i % 4, columns DVB col ..
-    auto load_v = [&](float4 (&buf)[NB], unsigned off, int hf) {
+    auto load_v = [&](fvec (&buf)[8], unsigned off, int hf) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int st = 8 * hf + i;
             const unsigned r = (unsigned)__shfl((int)off, 8 * (st / 4) + 4 * half + st % 4);
-            const fvec v = *reinterpret_cast<const fvec *>(Vb + (r + (unsigned)(col * (4 * DVB))));
-            __builtin_memcpy(reinterpret_cast<char *>(buf) + i * (4 * DVB), &v, 4 * DVB);
+            buf[i] = *reinterpret_cast<const fvec *>(Vb + (r + (unsigned)(col * (4 * DVB))));
         }
     };
-#define F32_FENCE __builtin_amdgcn_sched_barrier(0);
-
-    unsigned off = 0;
-    if (wave < nblk) {
-        off = row_off(wave);
-        load_k(bufA, off, 0);
-    }
-    for (int j = wave; j < nblk; j += NW) {
-        load_k(bufB, off, 1);
-        const int jn = j + NW;
-        const unsigned off_n = row_off(min(jn, nblk - 1));
-        F32_FENCE
-        f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, q[4 * i], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, q[4 * i + 1], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, q[4 * i + 2], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, q[4 * i + 3], S, 0, 0, 0);
-        }
-        F32_FENCE
-        load_v(bufA, off, 0);
-        F32_FENCE
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, q[4 * (NB + i)], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, q[4 * (NB + i) + 1], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, q[4 * (NB + i) + 2], S, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, q[4 * (NB + i) + 3], S, 0, 0, 0);
-        }
-        F32_FENCE
-        load_v(bufB, off, 1);
-        F32_FENCE
-        if (j == nblk - 1) {
-            // keys past the end: no score, and no value either (zero times an infinite one would be NaN)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (32 * j + 8 * (i >> 2) + 4 * half + (i & 3) >= L) {
-                    S[i] = -INFINITY;
-                    __builtin_memset(reinterpret_cast<char *>(i < 8 ? bufA : bufB) + (i & 7) * (4 * DVB), 0, 4 * DVB);
-                }
-        }
+    // scores of block j -> its probabilities, running level and sum; mul: the scores' factor, lift: log2 of the probabilities' factor
+    auto softmax = [&](f32x16 &S, float mul, float lift) {
         float mx = fmaxf(S[0], S[1]);
 #pragma unroll
         for (int i = 2; i < 16; ++i) mx = fmaxf(mx, S[i]);
-        mx = fmaxf(m, max_xor32(mx) * scale_log2);
+        mx = fmaxf(m, max_xor32(mx) * mul);
         if (__any(mx > m)) {
             const float alpha = __builtin_amdgcn_exp2f(m - mx);
             m = mx;
@@ -944,30 +1004,183 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
         }
-        const float m_ref = (m == -INFINITY) ? 0.f : m;         // scores of -inf alone so far: weights 0, not NaN
+        const float m_ref = (m == -INFINITY) ? 0.f : m - lift;      // scores of -inf alone so far: weights 0, not NaN
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], scale_log2, -m_ref));
+            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], mul, -m_ref));
             l += S[i];
         }
-        F32_FENCE
-        auto pv = [&](const float4 (&buf)[NB], int hf) {
+    };
+    // keys past the end: no score, and no value either (zero times an infinite one would be NaN)
+    auto mask = [&](f32x16 &S, fvec (&v0)[8], fvec (&v1)[8], int j) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                fvec v;
-                __builtin_memcpy(&v, reinterpret_cast<const char *>(buf) + i * (4 * DVB), 4 * DVB);
+        for (int i = 0; i < 16; ++i)
+            if (32 * j + 8 * (i >> 2) + 4 * half + (i & 3) >= L) {
+                S[i] = -INFINITY;
+                (i < 8 ? v0 : v1)[i & 7] = fvec{};
+            }
+    };
+#define F32_FENCE __builtin_amdgcn_sched_barrier(0);
+
+    if (split) {
+        fvec vA[8], vB[8];
+        float *sk = s_o + wave * (32 * D);      // this wavefront's K block
+        const float mul = scale_log2 * (1.f / q_up) * (1.f / k_up);
+        constexpr int CPR = D / 4;              // 16-byte chunks per row
+        // chunk c of row r sits at c ^ (r % 16): 16 rows read at one chunk hit different banks
+        auto fetch_k = [&](unsigned off) {
+            unsigned o[CPR / 2];
 #pragma unroll
-                for (int b = 0; b < DVB; ++b)
-                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[b], S[8 * hf + i], oacc[b], 0, 0, 0);
+            for (int i = 0; i < CPR / 2; ++i) o[i] = (unsigned)__shfl((int)off, i * (64 / CPR) + lane / CPR);
+#pragma unroll
+            for (int i = 0; i < CPR / 2; ++i) {
+                const int r = i * (64 / CPR) + lane / CPR;
+                load_to_lds_16(Kb, o[i] + 16u * (unsigned)((lane % CPR) ^ (r % 16)), reinterpret_cast<const unsigned char *>(sk) + 1024 * i);
             }
         };
-        pv(bufA, 0);
-        F32_FENCE
-        load_k(bufA, off_n, 0);                 // (after the last block: a valid row, not used)
-        F32_FENCE
-        pv(bufB, 1);
-        F32_FENCE
-        off = off_n;
+        auto qk = [&](f32x16 &S) {
+#pragma unroll
+            for (int t = 0; t < D / 16; ++t) {
+                f16x8 kh, kl;
+#pragma unroll
+                for (int e4 = 0; e4 < 2; ++e4) {
+                    const float4 w = *reinterpret_cast<const float4 *>(sk + col * D + 4 * ((4 * t + 2 * half + e4) ^ (col % 16)));
+                    f32_split(w.x, k_up, kh, kl, 4 * e4);
+                    f32_split(w.y, k_up, kh, kl, 4 * e4 + 1);
+                    f32_split(w.z, k_up, kh, kl, 4 * e4 + 2);
+                    f32_split(w.w, k_up, kh, kl, 4 * e4 + 3);
+                }
+                const f16x8 qh = s_q[2 * t * 64 + lane], ql = s_q[(2 * t + 1) * 64 + lane];
+                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qh, S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, ql, S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qh, S, 0, 0, 0);
+            }
+        };
+        auto pv = [&](const f32x16 &P, const fvec (&v)[8], int hf) {
+            f16x8 ph, pl;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f32_split(P[8 * hf + i], 1.f, ph, pl, i);
+#pragma unroll
+            for (int b = 0; b < DVB; ++b) {
+                f16x8 vh, vl;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) f32_split(v[i][b], v_up, vh, vl, i);
+                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, ph, oacc[b], 0, 0, 0);
+                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, pl, oacc[b], 0, 0, 0);
+                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, ph, oacc[b], 0, 0, 0);
+            }
+        };
+        // The rows of a block two ahead, in two steps between which its loads are on their way: the 64 runs from the one in which the
+        // 64-key tile starts, one per lane; then each lane counts those that start at or before its key.
+        auto first_run = [&](int j) -> int { return trh[min(min(j, nblk - 1) >> 1, key_tiles - 1)]; };
+        auto load_runs = [&](int c0) -> int2 { return rn[min(c0 + lane, nnz - 1)]; };
+        auto find_rows = [&](int j, int c0, const int2 &rv) -> unsigned {
+            if (j >= nblk) return 0;
+            const int kk = min(32 * j + col, L - 1), last = min(32 * j + 31, L - 1);
+            const int start = c0 + lane < nnz ? rv.y : 0x7FFFFFFF;
+            int c = 0, i = 1;
+            for (; i < 64; ++i) {
+                const int s = __builtin_amdgcn_readlane(start, i);
+                if (s > last) break;
+                c += kk >= s;
+            }
+            if (i == 64) return row_off(j);     // (runs of one key, or of none)
+            int r = __shfl(rv.x - rv.y, c) + kk;
+            if (perm_k) r = pkh[r];
+            return (unsigned)r * RB;
+        };
+        unsigned off = 0, off_n = 0;
+        int c0 = 0;
+        if (wave < nblk) {
+            off = row_off(wave);
+            fetch_k(off);
+            off_n = row_off(min(wave + NW, nblk - 1));
+            c0 = first_run(wave + 2 * NW);
+        }
+        for (int j = wave; j < nblk; j += NW) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // block j of K is in LDS, its rows are known
+            load_v(vA, off, 0);
+            load_v(vB, off, 1);
+            const int2 rv = load_runs(c0);
+            F32_FENCE
+            f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            qk(S);
+            F32_FENCE
+            // V is waited for here, in front of the fetches of the next K, which the compiler does not see
+#pragma unroll
+            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(vA[i]), "+v"(vB[i]));
+            F32_FENCE
+            if (j + NW < nblk) fetch_k(off_n);
+            const unsigned off_2 = find_rows(j + 2 * NW, c0, rv);
+            c0 = first_run(j + 3 * NW);
+            F32_FENCE
+            if (j == nblk - 1) mask(S, vA, vB, j);
+            softmax(S, mul, F32_LIFT);
+            F32_FENCE
+            pv(S, vA, 0);
+            pv(S, vB, 1);
+            F32_FENCE
+            off = off_n;
+            off_n = off_2;
+        }
+    } else {
+        float4 bufA[NB], bufB[NB];
+        fvec vA[8], vB[8];
+        float q[D / 2];                         // this lane's half of the row
+#pragma unroll
+        for (int k = 0; k < D / 8; ++k) {
+            const float4 w = reinterpret_cast<const float4 *>(Qr + half * (D / 2))[k];
+            q[4 * k] = w.x; q[4 * k + 1] = w.y; q[4 * k + 2] = w.z; q[4 * k + 3] = w.w;
+        }
+        auto load_k = [&](float4 (&buf)[NB], unsigned off, int hf) {
+            const float4 *src = reinterpret_cast<const float4 *>(Kb + (off + (unsigned)(half * (RB / 2) + hf * (RB / 4))));
+#pragma unroll
+            for (int i = 0; i < NB; ++i) buf[i] = src[i];
+        };
+        auto qk = [&](f32x16 &S, const float4 (&buf)[NB], int hf) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                S = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[i].x, q[4 * (hf * NB + i)], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[i].y, q[4 * (hf * NB + i) + 1], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[i].z, q[4 * (hf * NB + i) + 2], S, 0, 0, 0);
+                S = __builtin_amdgcn_mfma_f32_32x32x2f32(buf[i].w, q[4 * (hf * NB + i) + 3], S, 0, 0, 0);
+            }
+        };
+        auto pv = [&](const f32x16 &P, const fvec (&v)[8], int hf) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int b = 0; b < DVB; ++b) oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[i][b], P[8 * hf + i], oacc[b], 0, 0, 0);
+        };
+        unsigned off = 0;
+        if (wave < nblk) {
+            off = row_off(wave);
+            load_k(bufA, off, 0);
+        }
+        for (int j = wave; j < nblk; j += NW) {
+            load_k(bufB, off, 1);
+            const unsigned off_n = row_off(min(j + NW, nblk - 1));
+            F32_FENCE
+            f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            qk(S, bufA, 0);
+            F32_FENCE
+            load_v(vA, off, 0);
+            F32_FENCE
+            qk(S, bufB, 1);
+            F32_FENCE
+            load_v(vB, off, 1);
+            F32_FENCE
+            if (j == nblk - 1) mask(S, vA, vB, j);
+            softmax(S, scale_log2, 0.f);
+            F32_FENCE
+            pv(S, vA, 0);
+            F32_FENCE
+            load_k(bufA, off_n, 0);             // (after the last block: a valid row, not used)
+            F32_FENCE
+            pv(S, vB, 1);
+            F32_FENCE
+            off = off_n;
+        }
     }
 #undef F32_FENCE
 
@@ -1005,8 +1218,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
         const size_t dst = (size_t)h * N + (perm_q ? perm_q[(size_t)h * N + row0 + r] : row0 + r);
         // (no key: 0; keys without any weight, or scores that are no numbers: the softmax is undefined)
         const float inv = (lt > 0.f) ? 1.0f / lt : L > 0 ? NAN : 0.f;
-        *reinterpret_cast<float4 *>(O + dst * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-        if (lse && c4 == 0) lse[dst] = (lt > 0.f) ? (mm + log2f(lt)) * 0.6931471805599453f : -INFINITY;
+        const float down = split ? 1.f / v_up : 1.f;
+        *reinterpret_cast<float4 *>(O + dst * D + c4) =
+            make_float4(acc.x * inv * down, acc.y * inv * down, acc.z * inv * down, acc.w * inv * down);
+        if (lse && c4 == 0)
+            lse[dst] = (lt > 0.f) ? (mm + log2f(split ? lt * (1.f / F32_LIFT_BY) : lt)) * 0.6931471805599453f : -INFINITY;
     }
 }
 
@@ -1024,7 +1240,7 @@ static size_t attn_lds_bytes(int d, int Ck)
            (size_t)std::min(Ck + 1, ATT_RUN_LDS) * sizeof(int2);
 }
 
-static size_t attn_f32_lds_bytes(int d, int nw) { return (size_t)nw * F32_BM * (d + 4) * sizeof(float); }
+static size_t attn_f32_lds_bytes(int d, int nw) { return (size_t)nw * F32_BM * (d + 4) * sizeof(float) + F32_BM * d * sizeof(float); }
 
 static int attn_f32_nw(int H, int N)
 {
@@ -1055,15 +1271,17 @@ int attn_prepare(int dtype, int d)
     return SVG2_OK;
 }
 
-int attn_plan_launch(int dtype, int H, int N, int Cq, int Ck, const int32_t *offsets_q, const int32_t *offsets_k,
+int attn_plan_launch(const void *Kp, const void *Vp, int dtype, int H, int N, int d, int Cq, int Ck, const int32_t *offsets_q, const int32_t *offsets_k,
                      const int32_t *row_ptr, const int32_t *col_idx, void *ws, hipStream_t st)
 {
     const AttnWs a = attn_carve(ws, dtype, H, N, Cq, Ck);
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + cdiv(Cq, 4), H), dim3(256), 0, st, offsets_q, offsets_k, row_ptr, col_idx,
                        Cq, Ck, attn_bm(dtype), a.max_tiles, a.tiles, a.n_tiles, a.runs, a.row_keys, a.cl_first,
-                       a.key_tiles, a.tile_run);
-    hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(1024), 0, st, offsets_q, a.n_tiles, a.tile_base, a.row_keys,
-                       a.cl_first, H, Cq, attn_bm(dtype), a.order);
+                       a.key_tiles, a.tile_run, a.range);
+    const bool f32 = dtype == SVG2_F32;
+    hipLaunchKernelGGL(attn_order_kernel, dim3(1 + (f32 ? attn_range_blocks(H, N, d) : 0)), dim3(1024), 0, st, offsets_q, a.n_tiles,
+                       a.tile_base, a.row_keys, a.cl_first, H, Cq, attn_bm(dtype), a.order,
+                       f32 ? static_cast<const float *>(Kp) : nullptr, f32 ? static_cast<const float *>(Vp) : nullptr, N, d, a.range);
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
 }
@@ -1108,7 +1326,7 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
                                           : attn_f32_kernel<64, F32_NW>);
         hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * nw), attn_f32_lds_bytes(d, nw), st, q, k, v, H, N, Cq, Ck,
                            row_ptr, perm_q, perm_k, tiles, tile_base, a.order, max_tiles, runs, row_keys, a.tile_run,
-                           a.key_tiles, scale * 1.4426950408889634f, group, o, lse);
+                           a.key_tiles, scale * 1.4426950408889634f, group, a.range, o, lse);
     }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
@@ -1119,7 +1337,7 @@ int attn_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, int H
                 const int32_t *col_idx, const int32_t *perm_q, const int32_t *perm_k, float scale, void *O,
                 float *lse, void *ws, hipStream_t st)
 {
-    const int rc = attn_plan_launch(dtype, H, N, Cq, Ck, offsets_q, offsets_k, row_ptr, col_idx, ws, st);
+    const int rc = attn_plan_launch(Kp, Vp, dtype, H, N, d, Cq, Ck, offsets_q, offsets_k, row_ptr, col_idx, ws, st);
     if (rc != SVG2_OK) return rc;
     return attn_main_launch(Qp, Kp, Vp, dtype, H, N, d, Cq, Ck, row_ptr, perm_q, perm_k, scale, O, lse, ws, st);
 }

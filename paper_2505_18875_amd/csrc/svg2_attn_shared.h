@@ -105,6 +105,8 @@ __device__ __forceinline__ int attn_list_pos(int group)
 // ---- plan workspace (host)
 constexpr int attn_bm(int dtype) { return dtype == SVG2_BF16 ? 32 * ATT_NW : 32; }   // rows per tile
 
+static constexpr int F32_RANGE = 4 + 128;        // entries per head, attn_range
+
 struct AttnWs {
     int4 *tiles;
     int32_t *n_tiles, *tile_base;
@@ -114,6 +116,7 @@ struct AttnWs {
     int32_t *order;                     // [all tiles] work items, longest first
     int32_t *tile_run;                  // [H][Cq][key_tiles] CSR entry (relative to the row's first) of the run that
                                         // holds key 64 t of the row's virtual key sequence
+    unsigned *range;                    // [H][F32_RANGE] range of the K and V values (fp32 storage, else null)
     int max_tiles, key_tiles;
     size_t bytes;
 };
@@ -132,6 +135,7 @@ inline AttnWs attn_carve(void *ws, int dtype, int H, int N, int Cq, int Ck)
     a.cl_first = c.take<int32_t>((size_t)H * Cq);
     a.order = c.take<int32_t>((size_t)H * a.max_tiles);
     a.tile_run = c.take<int32_t>((size_t)H * Cq * a.key_tiles);
+    a.range = dtype == SVG2_F32 ? c.take<unsigned>((size_t)H * F32_RANGE) : nullptr;
     a.bytes = c.used;
     return a;
 }

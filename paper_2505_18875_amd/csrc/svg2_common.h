@@ -164,7 +164,8 @@ int attn_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, int H
 
 // perm_k == nullptr: Qp, Kp, Vp are permuted copies; perm_k given: they are in token order (gather-free).
 // the two halves of attn_launch, separately (so a caller can time them)
-int attn_plan_launch(int dtype, int H, int N, int Cq, int Ck, const int32_t *offsets_q, const int32_t *offsets_k,
+// (fp32: the plan looks at the values of K and V too)
+int attn_plan_launch(const void *Kp, const void *Vp, int dtype, int H, int N, int d, int Cq, int Ck, const int32_t *offsets_q, const int32_t *offsets_k,
                      const int32_t *row_ptr, const int32_t *col_idx, void *ws, hipStream_t st);
 int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, int H, int N, int d, int Cq, int Ck,
                      const int32_t *row_ptr, const int32_t *perm_q, const int32_t *perm_k, float scale, void *O,

@@ -816,6 +816,60 @@ def test_attention_f32_wavefronts_of_a_work_item(svg2, d, H, N):
     assert (res.lse - torch.logsumexp(S, dim=2)).abs().max().item() <= 1e-4
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("N,runs,change", [
+    (1, 1, ""), (31, 3, ""), (33, 2, ""), (65, 60, ""), (257, 256, ""), (700, 650, ""), (1300, 40, ""),
+    # both sides of what sends a head through the fp32 instruction: range of K and V, rows and columns far below the largest
+    (300, 9, "k+39"), (300, 9, "k+41"), (300, 9, "k-42"), (300, 9, "v+37"), (300, 9, "v+41"), (300, 9, "v-42"), (300, 9, "krow-11"),
+    (300, 9, "krow-20"), (300, 9, "vrow-11"), (300, 9, "vrow-20"), (300, 9, "vcol-20"), (300, 9, "zero"), (300, 9, "vinf"), (300, 9, "flat")])
+def test_attention_f32_split_operands(svg2, oracle, d, N, runs, change):
+    """fp32 attention with operands in two halves, and what it leaves to the fp32 instruction: runs of one key and of none, blocks
+    of 32 keys with a remainder.  Bound per element: scores are off by at most d + 8 roundings of 2^-24 of the sum of |q k| (either kind of product),
+    which moves a weight by as much, and 64 more for exp2, the sums over keys and the division."""
+    r = np.random.default_rng(77 + N + runs)
+    Q, K, V = (r.standard_normal((N, d)).astype(np.float32) * np.float32(f) for f in (3, 2, 1))
+    scale = 1.0
+    if change.startswith("k") and not change.startswith("krow"):
+        e = int(change[1:])
+        K, Q = np.ldexp(K, e), np.ldexp(Q, -e // 2)
+        scale = 2.0 ** -(e + -e // 2)
+    elif change.startswith("krow"):
+        K[N // 2] = np.ldexp(K[N // 2], int(change[4:]))
+    elif change.startswith("vrow"):
+        V[N // 2] = np.ldexp(V[N // 2], int(change[4:]))
+    elif change.startswith("vcol"):
+        V[:, 3] = np.ldexp(V[:, 3], int(change[4:]))
+    elif change == "zero":
+        Q[5], K[7], V[9], V[:, 2] = 0, 0, 0, 0
+    elif change == "vinf":
+        V[11, 4] = np.inf
+    elif change == "flat":
+        Q *= np.float32(0.01)
+    elif change.startswith("v"):
+        V = np.ldexp(V, int(change[1:]))
+    lk = np.sort(r.integers(0, runs, size=N)).astype(np.int32)
+    pk = oracle.permute(lk, runs)
+    one = lambda a: torch.from_numpy(np.asarray(a)[None].astype(np.int32)).cuda()  # noqa: E731
+    res = svg2.svg2_sparse_attn(to_dev(Q[None], "f32"), to_dev(K[None], "f32"), to_dev(V[None], "f32"), one([0, N]), one(pk.offsets),
+                                one([0, runs]), one(np.arange(runs)), scale=scale / float(np.sqrt(d)), want_lse=True)
+    torch.cuda.synchronize()
+    s = scale / np.sqrt(d)
+    S = (Q.astype(np.float64) @ K.astype(np.float64).T) * s
+    lse = np.log(np.exp(S - S.max(1, keepdims=True)).sum(1)) + S.max(1)
+    P = np.exp(S - lse[:, None])
+    eps = 2.0 ** -24
+    dS = (d + 8) * eps * (np.abs(Q).astype(np.float64) @ np.abs(K).astype(np.float64).T).max(1) * s + 64 * eps
+    with np.errstate(invalid="ignore"):
+        bound = 2.0 * dS[:, None] * (P @ np.abs(V).astype(np.float64)) + 1e-300
+        O_ref = P @ V.astype(np.float64)
+        O = to_np(res.O[0]).astype(np.float64)
+        fin = np.isfinite(O_ref)
+        assert np.all(np.abs(O - O_ref)[fin] <= bound[fin]), (np.abs(O - O_ref)[fin] / bound[fin]).max()
+    if change == "vinf":
+        assert np.all(np.isinf(O[:, 4]) | np.isnan(O[:, 4])) and fin.sum() == N * (d - 1)
+    assert np.all(np.abs(to_np(res.lse[0]) - lse) <= 2 * dS + 4 * eps * np.abs(lse))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("lo,hi", [(64, 96), (224, 257), (100, 600), (32, 601)])
