@@ -868,16 +868,6 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
 // and 20 clusters, a quarter selected: 302 instead of 495 us; 200 of 500, 30 and 60 clusters, D = 128: 208 instead of 276).
 static constexpr unsigned F32_EXP_LO = 127 - 40, F32_EXP_HI = 127 + 40, F32_SPREAD = 12;
 static constexpr float F32_LIFT = 14.f, F32_LIFT_BY = 16384.f, F32_SCORE = 256.f;
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-// element e of the two halves of x * up (a power of two: exact); the compiler makes these v_cvt_pk_f16_f32 and v_fma_mix_f32
-__device__ __forceinline__ void f32_split(float x, float up, f16x8 &hi, f16x8 &lo, int e)
-{
-    const _Float16 h = (_Float16)fmaf(x, up, 0.f);
-    hi[e] = h;
-    lo[e] = (_Float16)fmaf(x, up, -(float)h);
-}
-
 static constexpr int F32_NW = 8, F32_MANY = 1024, F32_SHORT = 512;
 static constexpr int F32_BM = 32;
 

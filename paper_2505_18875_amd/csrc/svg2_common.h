@@ -80,6 +80,17 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f)
     return (bf16_t)(u >> 16);
 }
 
+// ---- fp32 as two fp16 halves (fp32 storage: attention, k-means assign)
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// element e of the two halves of x * up (a power of two: exact); the compiler makes these v_cvt_pk_f16_f32 and v_fma_mix*
+__device__ __forceinline__ void f32_split(float x, float up, f16x8 &hi, f16x8 &lo, int e)
+{
+    const _Float16 h = (_Float16)fmaf(x, up, 0.f);
+    hi[e] = h;
+    lo[e] = (_Float16)fmaf(x, up, -(float)h);
+}
+
 typedef __attribute__((address_space(3))) unsigned char lds_u8;      // byte in LDS (32-bit address)
 
 // 16 bytes per lane from global memory (base + per-lane byte offset) straight into LDS: lane l lands at dst + 16 l.

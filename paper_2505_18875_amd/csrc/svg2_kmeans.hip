@@ -849,20 +849,29 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 
 // ---------------------------------------------------------------- assign, fp32
 // grid (token blocks, H, sides), block 64 * KF_NW; the side with more work (the last one: the K tokens of a layer) comes
-// first.  Matrix instruction 32x32x2 fp32 (fp32 products and sums, 64 cycles): the centroid tile is the A operand, 32
-// tokens are the B operand, a lane's 16 accumulators are 16 centroids of ONE token.  The contraction index runs in its
-// natural order (lane half h supplies the elements of parity h): the instruction adds its two products one after the
-// other with a rounding behind each, so an accumulator is bit for bit the chain of fmaf over k = 0 .. D - 1.
+// first.  The centroid tile is the A operand, 32 tokens are the B operand, a lane's 16 accumulators are 16 centroids of ONE token.
 //
-// The instruction is slow enough (a row block of 32 centroids is D/2 of them, 4096 cycles at D = 128) that the
-// centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
-// register buffers that take turns.  What decides is how many SIMDs have work, so the row blocks of a token block are
-// dealt out to up to four wavefronts (KF_NW / nc token blocks per workgroup, nc wavefronts each, kmeans_f32_share) and the
-// shares compared through LDS.  One token per thread with the centroids in LDS (300 workgroups
-// for 4 heads of 9601 tokens, every FMA waiting for its LDS read) took 770 instead of 96 us per iteration for 4 heads of
-// 9601 tokens against 100 and 500 centroids at D = 128 (5.9 GFLOP), and 28 instead of 5.4 us for one head of 4096 against
-// 16 and 32 at D = 64.
+// With more than KF_SPLIT centroids the operands are taken as two fp16 halves (f32_split: x to 2^-23) and a product as hi hi +
+// hi lo + lo hi, three 32x32x16 instructions that take a fifth of the time of the eight 32x32x2 fp32 ones, which bound the kernel.
+// A token is brought to 2^14 .. 2^15 by a power of two, the centroids of a head by one that follows from their largest norm.  The rule
+// (`split`): tokens of a block and the largest centroid finite and within 2^+-KF_EXP, no ||c||^2 more than 2^KF_SPREAD below the
+// largest (zeros aside).  Anything else, and up to KF_SPLIT centroids, where splitting 32 tokens costs what it saves (2 x 1000 in
+// 60: 69.5 against 67.4 us per five iterations; one head of 700 in 24 54.8 against 53.0), goes through the fp32 instruction:
+// contraction index in its natural order (lane half h supplies the elements of parity h), the instruction adds its two
+// products one after the other with a rounding behind each, so an accumulator is bit for bit the chain of fmaf over k = 0 .. D - 1.
+// A split accumulator rounds 3 times per 16 products instead of 16 times, and what the split drops is less than the difference:
+// of 480,000 tokens a millionth from the border of two of 100 or 500 centroids 5500 get the wrong one at D = 128 and 4200 at D = 64, 9100
+// and 6800 before, and the mean gap between the two is 0.6 of what it was.
+//
+// The centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
+// register buffers, the halves of a row block, each requested again as soon as it has been used.  What decides for few tokens is how
+// many SIMDs have work, so the row blocks of a token block are dealt out to up to four wavefronts (KF_NW / nc token blocks
+// per workgroup, nc wavefronts each, kmeans_f32_share) and the shares compared through LDS.  k-means of five iterations, D = 128,
+// fp32 instruction -> split: 4 x 9601 in 500 centroids 490 -> 275 us, 24 x 16,384 in 500 3295 -> 1327, 6 x 12,000 in 1000 1349 -> 602.  One
+// token per thread with the centroids in LDS took 770 us per iteration for 4 heads of 9601 tokens against 100 and 500.
 static constexpr int KF_NW = 4;
+static constexpr int KF_SPLIT = 64;             // most centroids that go through the fp32 instruction whatever the values
+static constexpr int KF_EXP = 40, KF_SPREAD = 24;
 
 template <int D, bool OBJ>
 __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs a, KmIter it)
@@ -871,6 +880,7 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     __shared__ float s_cn[SVG2_MAX_CLUSTERS];
     __shared__ float s_best[KF_NW][32];
     __shared__ int s_idx[KF_NW][32];
+    __shared__ unsigned s_most[KF_NW], s_least[KF_NW];
     const int side = (int)(gridDim.z - 1 - blockIdx.z);
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
@@ -898,48 +908,129 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             x[2 * k + 1] = __uint_as_float(q[0]); x[D / 4 + 2 * k + 1] = __uint_as_float(q[1]);
         }
     }
-    const float4 *ct = reinterpret_cast<const float4 *>(S.ct) + ((size_t)h * 2 + half) * (D / 8) * C;
-    float4 bufA[NB], bufB[NB];
+    const char *ct = reinterpret_cast<const char *>(S.ct + (size_t)h * D * C);
     auto load_c = [&](float4 (&buf)[NB], int rb, int hf) {
-        const int j = min(rb * 32 + col, C - 1);
+        const unsigned off = 16u * (unsigned)(half * (D / 8) * C + min(rb * 32 + col, C - 1));     // (a head is 2 MB at most)
 #pragma unroll
-        for (int i = 0; i < NB; ++i) buf[i] = ct[(size_t)(hf * NB + i) * C + j];
+        for (int i = 0; i < NB; ++i) buf[i] = *reinterpret_cast<const float4 *>(ct + 16 * (size_t)(hf * NB + i) * C + off);
     };
+    float4 bufA[NB], bufB[NB];                  // the two halves of a row block
     load_c(bufA, min(wc, nrb - 1), 0);
-    for (int c = tid; c < 32 * nrb; c += 64 * KF_NW) s_cn[c] = c < C ? S.hcn[(size_t)h * C + c] : INFINITY;
+    unsigned cn_most = 0, cn_least = ~0u;       // of ||c||^2, as bits; the least without zeros
+    for (int c = tid; c < 32 * nrb; c += 64 * KF_NW) {
+        const float v = c < C ? S.hcn[(size_t)h * C + c] : INFINITY;
+        s_cn[c] = v;
+        if (c < C) {
+            cn_most = max(cn_most, __float_as_uint(v));
+            if (v != 0.f) cn_least = min(cn_least, __float_as_uint(v));
+        }
+    }
+    if (C > KF_SPLIT) {
+        for (int o = 32; o > 0; o >>= 1) {
+            cn_most = max(cn_most, (unsigned)__shfl_xor((int)cn_most, o));
+            cn_least = min(cn_least, (unsigned)__shfl_xor((int)cn_least, o));
+        }
+        if (lane == 0) { s_most[wave] = cn_most; s_least[wave] = cn_least; }
+    }
+    float x2 = 0.f;
+    if (OBJ && S.objective) {
+#pragma unroll
+        for (int k = 0; k < D / 2; ++k) x2 = fmaf(x[k], x[k], x2);
+        x2 += __shfl_xor(x2, 32);
+    }
     __syncthreads();
 
     float best = INFINITY;
     int bidx = 0;
-    for (int rb = wc; rb < nrb; rb += nc) {
-        load_c(bufB, rb, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        load_c(bufA, min(rb + nc, nrb - 1), 0);         // (past the last row block: a valid one, not used)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // accumulator i is centroid 8 (i / 4) + 4 half + i % 4 of the row block: ascending in a lane, so strict <
-        // keeps the lowest index; the padding rows of the last block are at infinity
+    // accumulator i is centroid 8 (i / 4) + 4 half + i % 4 of the row block: ascending in a lane, so strict <
+    // keeps the lowest index; the padding rows of the last block are at infinity
+    auto compare = [&](const f32x16 &acc, int rb, float mul) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int j = rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-            const float dist = fmaf(-2.f, acc[i], s_cn[j]);
+            const float dist = fmaf(mul, acc[i], s_cn[j]);
             if (dist < best) { best = dist; bidx = j; }
+        }
+    };
+    // split operands or not (the comment above)
+    float x_up = 1.f, c_up = 1.f;
+    bool split = false;
+    if (C > KF_SPLIT) {
+        cn_most = s_most[0]; cn_least = s_least[0];
+#pragma unroll
+        for (int w = 1; w < KF_NW; ++w) { cn_most = max(cn_most, s_most[w]); cn_least = min(cn_least, s_least[w]); }
+        unsigned xb = 0;
+#pragma unroll
+        for (int k = 0; k < D / 2; ++k) xb = max(xb, __float_as_uint(x[k]) & 0x7FFFFFFFu);
+        xb = max(xb, (unsigned)__shfl_xor((int)xb, 32));
+        const int xe = xb == 0 ? 0 : (int)(xb >> 23) - 127, ce = (int)(cn_most >> 23) - 127;
+        split = abs(ce) <= 2 * KF_EXP && (int)(cn_least >> 23) - 127 + KF_SPREAD >= ce && __all(abs(xe) <= KF_EXP);
+        x_up = __uint_as_float((unsigned)(127 + 14 - xe) << 23);
+        c_up = __uint_as_float((unsigned)(127 + 15 - ((ce + 2) >> 1)) << 23);       // |c| < 2^((ce + 1) / 2)
+    }
+    if (split) {
+        f16x8 xh[D / 16], xl[D / 16];
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f32_split(x[8 * t + e], x_up, xh[t], xl[t], e);
+        const float mul = -2.f * (1.f / x_up) * (1.f / c_up);
+        auto half_block = [&](f32x16 &acc, float4 (&buf)[NB], int hf) {
+            // (pinned: the compiler otherwise splits ahead of the loads' turn, all halves at once, and spills)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(buf[i].x), "+v"(buf[i].y), "+v"(buf[i].z), "+v"(buf[i].w));
+#pragma unroll
+            for (int t = 0; t < NB / 2; ++t) {
+                const float c[8] = {buf[2 * t].x, buf[2 * t].y, buf[2 * t].z, buf[2 * t].w,
+                                    buf[2 * t + 1].x, buf[2 * t + 1].y, buf[2 * t + 1].z, buf[2 * t + 1].w};
+                f16x8 ch, cl;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f32_split(c[e], c_up, ch, cl, e);
+                const int i = hf * (NB / 2) + t;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cl, xh[i], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch, xl[i], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch, xh[i], acc, 0, 0, 0);
+            }
+        };
+        load_c(bufB, min(wc, nrb - 1), 1);
+        for (int rb = wc; rb < nrb; rb += nc) {
+            const int next = min(rb + nc, nrb - 1);     // (past the last row block: a valid one, not used)
+            f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            half_block(acc, bufA, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_c(bufA, next, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            half_block(acc, bufB, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            load_c(bufB, next, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compare(acc, rb, mul);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        for (int rb = wc; rb < nrb; rb += nc) {
+            load_c(bufB, rb, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_c(bufA, min(rb + nc, nrb - 1), 0);     // (past the last row block: a valid one, not used)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            compare(acc, rb, -2.f);
         }
     }
     // the two lane halves, then the wavefronts of a token block, hold disjoint centroids of the same token
@@ -955,10 +1046,6 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     }
     if (half == 0 && n < N) labels[(size_t)h * N + n] = bidx;
     if (OBJ && S.objective) {
-        float x2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < D / 2; ++k) x2 = fmaf(x[k], x[k], x2);
-        x2 += __shfl_xor(x2, 32);
         float v = (half == 0 && n < N) ? x2 + best : 0.f;
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
         if (lane == 0) atomicAdd(S.objective + (size_t)h * a.iters + it.t, v);
@@ -1904,22 +1991,23 @@ int device_cu_count(int *ncu)
     return SVG2_OK;
 }
 
-// Wavefronts that share a token block of the fp32 assign step: every one of them loads the tokens, so a share has at
-// least four row blocks where the token blocks alone are enough for two wavefronts per SIMD, and as few as one otherwise.
-// (One share per row block, up to four, whatever the number of token blocks:
-// 100 instead of 96 us per iteration for 4 heads of 9601 tokens against 100 and 500 centroids at D = 128.)
+// Wavefronts that share a token block of the fp32 assign step: every one of them loads (and splits) the tokens, so a share has at
+// least 16 row blocks where there are 512 token blocks, whatever their number from 4096 on, and as few as one with fewer
+// (k-means of five iterations with one, two, four wavefronts, us: 4 x 9601 in 500 288, 275, 290; in 100 192, 203, 201; 6 x 12,000 in
+// 1000 653, 602, 625; 24 x 16,384 in 500 1327, 1489, 1910; 3 x 3000 in 300 131, 106, 118; 1 x 12,000 in 1000 300, 211, 206, all D = 128;
+// 1 x 4096 in 200, D = 64 84, 75, 69).  Up to KF_SPLIT centroids, a row block for each while two wavefronts per SIMD take one.
 // The grid has 64 KF_NW threads per 32 (KF_NW / nc) tokens of a head, 2 nc N, and one grid dimension takes less than 2^32.
 static constexpr int kmeans_f32_share(int H, int N, int C)
 {
     const int nrb = (C + 31) / 32;
     const long long blocks = H * (((long long)N + 31) / 32);
     int nc = 1;
-    while (nc < KF_NW && 2 * nc <= nrb && (nrb > 4 * nc || blocks * nc < 2048) && 2ll * (2 * nc) * (N + 128ll) < 1ll << 32)
+    while (nc < KF_NW && 2 * nc <= nrb && 2ll * (2 * nc) * (N + 128ll) < 1ll << 32 &&
+           (C <= KF_SPLIT ? blocks * nc < 2048 : blocks * nc < 512 || (nrb >= 16 * nc && blocks * nc < 4096)))
         nc *= 2;
     return nc;
 }
-static_assert(kmeans_f32_share(1, 1 << 20, 4096) == 4 && kmeans_f32_share(1, 1 << 29, 4096) == 2 &&
-              kmeans_f32_share(1, 1 << 30, 4096) == 1, "the grid of the fp32 assign step stays below 2^32 threads");
+static_assert(kmeans_f32_share(1, 1000, 4096) == 4 && kmeans_f32_share(1, 1 << 30, 4096) == 1, "the grid of the fp32 assign step stays below 2^32 threads");
 
 template <typename T, int D, bool BF16>
 static int kmeans_run(KmArgs a, hipStream_t st)

@@ -281,6 +281,45 @@ def test_kmeans_f32_few_centroids(svg2, oracle, d, H, N, C):
     assert C == 1 or not np.any(to_np(res.labels) == C - 1)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N,C,change", [
+    (2, 300, 64, ""), (2, 300, 65, ""), (1, 97, 97, ""), (3, 2000, 129, ""), (1, 12000, 1000, ""), (6, 6001, 513, ""),
+    # both sides of what sends tokens through the fp32 instruction: ranges, one token or centroid out of range
+    (2, 500, 100, "all+39"), (2, 500, 100, "all+41"), (2, 500, 100, "all-39"), (2, 500, 100, "all-41"), (2, 500, 100, "token+41"),
+    (2, 500, 100, "token-41"), (2, 500, 100, "token0"), (2, 500, 100, "centroid-11"), (2, 500, 100, "centroid-13"), (2, 500, 100, "centroid0"),
+    (2, 500, 100, "inf"), (2, 500, 100, "nan")])
+def test_kmeans_f32_split_operands(svg2, d, H, N, C, change):
+    """Labels of one fp32 assign step against float64, operands in two halves and not: a label that differs is a near-tie, its
+    distance larger than the smallest by no more than the roundings of two chains, (2 d + 8) 2^-24 (|x|^2 + |c|^2) and |c| the largest."""
+    g = torch.Generator(device="cuda").manual_seed(C + N)
+    X = (2.0 * torch.randn((H, C, d), device="cuda", generator=g))[:, torch.randint(C, (N,), device="cuda", generator=g)]
+    X = X + torch.randn((H, N, d), device="cuda", generator=g)
+    c0 = X[:, torch.randperm(N, device="cuda", generator=g)[:C]].clone()
+    if change.startswith("all"):
+        f = 2.0 ** int(change[3:])
+        X, c0 = X * f, c0 * f
+    elif change.startswith("token"):
+        X[:, 70] *= 2.0 ** int(change[5:]) if change[5:] != "0" else 0.0
+    elif change.startswith("centroid"):
+        c0[:, 40] *= 2.0 ** int(change[8:]) if change[8:] != "0" else 0.0
+    elif change:
+        X[:, 70, 5] = float(change)
+    lab = svg2.svg2_kmeans(X.contiguous(), c0.contiguous(), 1).labels.long()
+    torch.cuda.synchronize()
+    finite = torch.isfinite(X).all(2)
+    for h in range(H):
+        x, c = X[h].double(), c0[h].double()
+        dist = (c * c).sum(1)[None] - 2.0 * (x @ c.T)
+        over = dist.gather(1, lab[h][:, None])[:, 0] - dist.min(1).values
+        bound = (2 * d + 8) * 2.0 ** -24 * ((x * x).sum(1) + (c * c).sum(1).max())
+        assert bool((over <= bound)[finite[h]].all())
+    if change == "nan":
+        assert bool((lab[:, 70] == 0).all())            # no distance is a number: cluster 0
+    if change == "inf":
+        # the first centroid in the token's direction: its distance is -inf
+        assert torch.equal(lab[:, 70], (c0[:, :, 5] > 0).int().argmax(1))
+
+
 @pytest.mark.parametrize("Cq,Ck", [(1, 70), (70, 1)])
 def test_forward_f32_one_side_with_few_centroids(svg2, oracle, Cq, Ck):
     # 5 heads of 1920 tokens: the assign steps of the two sides are different kernels
