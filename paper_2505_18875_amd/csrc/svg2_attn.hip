@@ -872,7 +872,7 @@ static constexpr int F32_NW = 8, F32_MANY = 1024, F32_SHORT = 512;
 static constexpr int F32_BM = 32;
 
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
+__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
     const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int Cq, int Ck,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ tile_base, const int32_t *__restrict__ order, int max_tiles,
@@ -914,9 +914,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(
     // Split operands or not: the same for all wavefronts of the work item (same Q rows, same head)
     // split Q in LDS behind the wavefronts' shares: lane's part of step t is elements 16 t + 8 half .. of its row
     f16x8 *s_q = reinterpret_cast<f16x8 *>(s_o + (size_t)NW * 32 * ROW);
-    bool split;
-    float k_up, v_up, q_up;                     // powers of two that bring the largest K, V of the head, Q of the row to 2^14 .. 2^15
-    {
+    bool split = false;
+    float k_up = 1.f, v_up = 1.f, q_up = 1.f;   // powers of two that bring the largest K, V of the head, Q of the row to 2^14 .. 2^15
+    if (range) {
         float q[D / 2];
 #pragma unroll
         for (int t = 0; t < D / 16; ++t) {
@@ -1230,7 +1230,15 @@ static size_t attn_lds_bytes(int d, int Ck)
            (size_t)std::min(Ck + 1, ATT_RUN_LDS) * sizeof(int2);
 }
 
-static size_t attn_f32_lds_bytes(int d, int nw) { return (size_t)nw * F32_BM * (d + 4) * sizeof(float) + F32_BM * d * sizeof(float); }
+// The ranges that let a head's operands be split: none for short heads, where looking at K and V costs more than it saves and the
+// LDS that split Q takes leaves a CU fewer work items (1000 heads of 256 tokens, D = 128: 537 instead of 430 us; 5000 of 16, D = 64: 134
+// instead of 55; 200 of 600 340 instead of 457).  Longer heads have eight wavefronts per work item, which share a CU with no other at D = 128.
+static unsigned *attn_range_of(const AttnWs &a, int N) { return N > F32_SHORT ? a.range : nullptr; }
+
+static size_t attn_f32_lds_bytes(int d, int nw, bool ranged)
+{
+    return (size_t)nw * F32_BM * (d + 4) * sizeof(float) + (ranged ? F32_BM * d * sizeof(float) : 0);
+}
 
 static int attn_f32_nw(int H, int N)
 {
@@ -1245,10 +1253,10 @@ int attn_prepare(int dtype, int d)
     if (dtype != SVG2_BF16) {
         // (with fewer wavefronts than F32_NW less than 64 KB of LDS except at D = 128 and four)
         if (d == 128) {
-            SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, 4>), attn_f32_lds_bytes(d, 4)));
-            return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, F32_NW>), attn_f32_lds_bytes(d, F32_NW));
+            SVG2_TRY(set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, 4>), attn_f32_lds_bytes(d, 4, false)));
+            return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<128, F32_NW>), attn_f32_lds_bytes(d, F32_NW, true));
         }
-        return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<64, F32_NW>), attn_f32_lds_bytes(d, F32_NW));
+        return set_dynamic_lds(reinterpret_cast<const void *>(attn_f32_kernel<64, F32_NW>), attn_f32_lds_bytes(d, F32_NW, true));
     }
     const size_t lds = attn_lds_bytes(d, SVG2_MAX_CLUSTERS);
     if (d == 128) {
@@ -1267,8 +1275,8 @@ int attn_plan_launch(const void *Kp, const void *Vp, int dtype, int H, int N, in
     const AttnWs a = attn_carve(ws, dtype, H, N, Cq, Ck);
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + cdiv(Cq, 4), H), dim3(256), 0, st, offsets_q, offsets_k, row_ptr, col_idx,
                        Cq, Ck, attn_bm(dtype), a.max_tiles, a.tiles, a.n_tiles, a.runs, a.row_keys, a.cl_first,
-                       a.key_tiles, a.tile_run, a.range);
-    const bool f32 = dtype == SVG2_F32;
+                       a.key_tiles, a.tile_run, attn_range_of(a, N));
+    const bool f32 = attn_range_of(a, N) != nullptr;
     hipLaunchKernelGGL(attn_order_kernel, dim3(1 + (f32 ? attn_range_blocks(H, N, d) : 0)), dim3(1024), 0, st, offsets_q, a.n_tiles,
                        a.tile_base, a.row_keys, a.cl_first, H, Cq, attn_bm(dtype), a.order,
                        f32 ? static_cast<const float *>(Kp) : nullptr, f32 ? static_cast<const float *>(Vp) : nullptr, N, d, a.range);
@@ -1314,9 +1322,9 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
                                 : nw == 2 ? attn_f32_kernel<64, 2>
                                 : nw == 4 ? attn_f32_kernel<64, 4>
                                           : attn_f32_kernel<64, F32_NW>);
-        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * nw), attn_f32_lds_bytes(d, nw), st, q, k, v, H, N, Cq, Ck,
+        hipLaunchKernelGGL(kern, attn_list_grid(total), dim3(64 * nw), attn_f32_lds_bytes(d, nw, attn_range_of(a, N) != nullptr), st, q, k, v, H, N, Cq, Ck,
                            row_ptr, perm_q, perm_k, tiles, tile_base, a.order, max_tiles, runs, row_keys, a.tile_run,
-                           a.key_tiles, scale * 1.4426950408889634f, group, a.range, o, lse);
+                           a.key_tiles, scale * 1.4426950408889634f, group, attn_range_of(a, N), o, lse);
     }
     SVG2_HIP_CHECK(hipGetLastError());
     return SVG2_OK;
