@@ -111,6 +111,7 @@ struct KmArgs {
     KmSide s[2];
     int nsides, H, N, iters;
     int nc[2];                  // wavefronts that share a token block (fp32 assign)
+    int split[2];               // whether its operands may be split
     int gc[2];                  // clusters of a workgroup of the update kernel
     bool want_order;            // the caller reads offsets and perm of the last iteration
     bool lists;                 // the assign step lists the tokens whose label changed, the update step reads these lists (bf16)
@@ -855,30 +856,34 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 // hi lo + lo hi, three 32x32x16 instructions that take a fifth of the time of the eight 32x32x2 fp32 ones, which bound the kernel.
 // A token is brought to 2^14 .. 2^15 by a power of two, the centroids of a head by one that follows from their largest norm.  The rule
 // (`split`): tokens of a block and the largest centroid finite and within 2^+-KF_EXP, no ||c||^2 more than 2^KF_SPREAD below the
-// largest (zeros aside).  Anything else, and up to KF_SPLIT centroids, where splitting 32 tokens costs what it saves (2 x 1000 in
-// 60: 69.5 against 67.4 us per five iterations; one head of 700 in 24 54.8 against 53.0), goes through the fp32 instruction:
-// contraction index in its natural order (lane half h supplies the elements of parity h), the instruction adds its two
-// products one after the other with a rounding behind each, so an accumulator is bit for bit the chain of fmaf over k = 0 .. D - 1.
-// A split accumulator rounds 3 times per 16 products instead of 16 times, and what the split drops is less than the difference:
-// of 480,000 tokens a millionth from the border of two of 100 or 500 centroids 5500 get the wrong one at D = 128 and 4200 at D = 64, 9100
-// and 6800 before, and the mean gap between the two is 0.6 of what it was.
+// largest (zeros aside).  Anything else, up to KF_SPLIT centroids, where splitting 32 tokens costs what it saves (2 x 1000 in 60: 69.5
+// against 67.4 us per five iterations; one head of 700 in 24 54.8 against 53.0), and calls with little to do (kmeans_f32_split) go
+// through the fp32 instruction: contraction index in its natural order (lane half h supplies the elements of parity h), the
+// instruction adds its two products one after the other with a rounding behind each, so an accumulator is bit for bit the chain
+// of fmaf over k = 0 .. D - 1.  That chain decides the label in either case: the split products leave the tokens whose two best distances are
+// closer than KF_TIE (|x|^2 + max |c|^2), a few per launch, to it.  (Largest error of a difference of two distances seen on 7.7 million
+// tokens next to a border: 0.7e-6 of that bracket for the chain, 0.5e-6 split.)
 //
 // The centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
 // register buffers, the halves of a row block, each requested again as soon as it has been used.  What decides for few tokens is how
 // many SIMDs have work, so the row blocks of a token block are dealt out to up to four wavefronts (KF_NW / nc token blocks
 // per workgroup, nc wavefronts each, kmeans_f32_share) and the shares compared through LDS.  k-means of five iterations, D = 128,
-// fp32 instruction -> split: 4 x 9601 in 500 centroids 490 -> 275 us, 24 x 16,384 in 500 3295 -> 1327, 6 x 12,000 in 1000 1349 -> 602.  One
+// fp32 instruction -> split: 4 x 9601 in 500 centroids 490 -> 281 us, 24 x 16,384 in
+// 500 3295 -> 1314, 6 x 12,000 in 1000 1349 -> 621.  One
 // token per thread with the centroids in LDS took 770 us per iteration for 4 heads of 9601 tokens against 100 and 500.
 static constexpr int KF_NW = 4;
 static constexpr int KF_SPLIT = 64;             // most centroids that go through the fp32 instruction whatever the values
 static constexpr int KF_EXP = 40, KF_SPREAD = 24;
+static constexpr long long KF_SPLIT_BLOCKS = 2048;      // fewest row blocks, over all token blocks
+static constexpr float KF_TIE = 3.814697265625e-06f;    // 2^-18
+static constexpr int KF_CHAINS = 4;                     // centroids of a lane side by side
 
 template <int D, bool OBJ>
 __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs a, KmIter it)
 {
     constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's half row
     __shared__ float s_cn[SVG2_MAX_CLUSTERS];
-    __shared__ float s_best[KF_NW][32];
+    __shared__ float s_best[KF_NW][32], s_second[KF_NW][32];
     __shared__ int s_idx[KF_NW][32];
     __shared__ unsigned s_most[KF_NW], s_least[KF_NW];
     const int side = (int)(gridDim.z - 1 - blockIdx.z);
@@ -925,7 +930,8 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             if (v != 0.f) cn_least = min(cn_least, __float_as_uint(v));
         }
     }
-    if (C > KF_SPLIT) {
+    const bool may_split = KM_SEL(a.split, side);
+    if (may_split) {
         for (int o = 32; o > 0; o >>= 1) {
             cn_most = max(cn_most, (unsigned)__shfl_xor((int)cn_most, o));
             cn_least = min(cn_least, (unsigned)__shfl_xor((int)cn_least, o));
@@ -933,29 +939,30 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
         if (lane == 0) { s_most[wave] = cn_most; s_least[wave] = cn_least; }
     }
     float x2 = 0.f;
-    if (OBJ && S.objective) {
+    if ((OBJ && S.objective) || may_split) {
 #pragma unroll
         for (int k = 0; k < D / 2; ++k) x2 = fmaf(x[k], x[k], x2);
         x2 += __shfl_xor(x2, 32);
     }
     __syncthreads();
 
-    float best = INFINITY;
+    float best = INFINITY, second = INFINITY;           // (second: of the split loop only)
     int bidx = 0;
     // accumulator i is centroid 8 (i / 4) + 4 half + i % 4 of the row block: ascending in a lane, so strict <
     // keeps the lowest index; the padding rows of the last block are at infinity
-    auto compare = [&](const f32x16 &acc, int rb, float mul) {
+    auto compare = [&](const f32x16 &acc, int rb, float mul, auto with_second) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int j = rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
             const float dist = fmaf(mul, acc[i], s_cn[j]);
+            if constexpr (decltype(with_second)::value) second = __builtin_amdgcn_fmed3f(best, second, dist);
             if (dist < best) { best = dist; bidx = j; }
         }
     };
     // split operands or not (the comment above)
     float x_up = 1.f, c_up = 1.f;
     bool split = false;
-    if (C > KF_SPLIT) {
+    if (may_split) {
         cn_most = s_most[0]; cn_least = s_least[0];
 #pragma unroll
         for (int w = 1; w < KF_NW; ++w) { cn_most = max(cn_most, s_most[w]); cn_least = min(cn_least, s_least[w]); }
@@ -1004,7 +1011,7 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             __builtin_amdgcn_sched_barrier(0);
             load_c(bufB, next, 1);
             __builtin_amdgcn_sched_barrier(0);
-            compare(acc, rb, mul);
+            compare(acc, rb, mul, std::true_type{});
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
@@ -1030,19 +1037,60 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            compare(acc, rb, -2.f);
+            compare(acc, rb, -2.f, std::false_type{});
         }
     }
     // the two lane halves, then the wavefronts of a token block, hold disjoint centroids of the same token
-    auto merge = [&](float ob, int oj) {
+    auto merge = [&](float ob, int oj, float os) {
+        second = fminf(fminf(second, os), fmaxf(best, ob));
         if (ob < best || (ob == best && oj < bidx)) { best = ob; bidx = oj; }
     };
-    merge(__shfl_xor(best, 32), __shfl_xor(bidx, 32));
+    merge(__shfl_xor(best, 32), __shfl_xor(bidx, 32), __shfl_xor(second, 32));
     if (nc > 1) {
-        if (half == 0) { s_best[wave][col] = best; s_idx[wave][col] = bidx; }
+        if (half == 0) { s_best[wave][col] = best; s_idx[wave][col] = bidx; s_second[wave][col] = second; }
         __syncthreads();
         if (wc != 0) return;
-        for (int w = 1; w < nc; ++w) merge(s_best[wave + w][col], s_idx[wave + w][col]);
+        for (int w = 1; w < nc; ++w) merge(s_best[wave + w][col], s_idx[wave + w][col], s_second[wave + w][col]);
+    }
+    // Near-ties of the split products go by the chain of fmaf, as all tokens do without them: a token at a time, KF_CHAINS centroids per
+    // lane (one after the other, its loads all requested at once: 6 x 12,000 in 1000 721 instead of 621 us, 1 x 12,000 287 instead of 222).
+    if (split) {
+        unsigned near = (unsigned)__ballot(n < N && second - best <= KF_TIE * (x2 + __uint_as_float(cn_most)));
+        for (; near; near &= near - 1) {
+            const int c32 = __builtin_ctz(near);
+            const float *xr = static_cast<const float *>(S.X) + ((size_t)h * N + n0 + c32) * D;     // (uniform)
+            float tb = INFINITY;
+            int tj = 0;
+            for (int j0 = lane; j0 < C; j0 += 64 * KF_CHAINS) {
+                float dot[KF_CHAINS] = {};
+#pragma unroll 2
+                for (int q = 0; q < D / 8; ++q) {
+                    const float4 x0 = *reinterpret_cast<const float4 *>(xr + 8 * q), x1 = *reinterpret_cast<const float4 *>(xr + 8 * q + 4);
+#pragma unroll
+                    for (int u = 0; u < KF_CHAINS; ++u) {
+                        const int j = min(j0 + 64 * u, C - 1);
+                        const float4 ev = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)q * C + j));
+                        const float4 od = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)(D / 8 + q) * C + j));
+                        dot[u] = fmaf(ev.x, x0.x, dot[u]); dot[u] = fmaf(od.x, x0.y, dot[u]);
+                        dot[u] = fmaf(ev.y, x0.z, dot[u]); dot[u] = fmaf(od.y, x0.w, dot[u]);
+                        dot[u] = fmaf(ev.z, x1.x, dot[u]); dot[u] = fmaf(od.z, x1.y, dot[u]);
+                        dot[u] = fmaf(ev.w, x1.z, dot[u]); dot[u] = fmaf(od.w, x1.w, dot[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < KF_CHAINS; ++u) {
+                    const int j = min(j0 + 64 * u, C - 1);      // (past the last one: that one again, which changes nothing)
+                    const float dist = fmaf(-2.f, dot[u], s_cn[j]);
+                    if (dist < tb) { tb = dist; tj = j; }
+                }
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                const float ob = __shfl_xor(tb, o);
+                const int oj = __shfl_xor(tj, o);
+                if (ob < tb || (ob == tb && oj < tj)) { tb = ob; tj = oj; }
+            }
+            if (col == c32) { best = tb; bidx = tj; }
+        }
     }
     if (half == 0 && n < N) labels[(size_t)h * N + n] = bidx;
     if (OBJ && S.objective) {
@@ -1995,15 +2043,21 @@ int device_cu_count(int *ncu)
 // least 16 row blocks where there are 512 token blocks, whatever their number from 4096 on, and as few as one with fewer
 // (k-means of five iterations with one, two, four wavefronts, us: 4 x 9601 in 500 288, 275, 290; in 100 192, 203, 201; 6 x 12,000 in
 // 1000 653, 602, 625; 24 x 16,384 in 500 1327, 1489, 1910; 3 x 3000 in 300 131, 106, 118; 1 x 12,000 in 1000 300, 211, 206, all D = 128;
-// 1 x 4096 in 200, D = 64 84, 75, 69).  Up to KF_SPLIT centroids, a row block for each while two wavefronts per SIMD take one.
+// 1 x 4096 in 200, D = 64 84, 75, 69).  Without splitting a share has at least four row blocks where the token blocks alone are enough
+// for two wavefronts per SIMD, and as few as one otherwise.  Splitting pays from two row blocks per SIMD on (1 x 4096 in 200, D = 64, with
+// fewer: 75 instead of 69 us).
 // The grid has 64 KF_NW threads per 32 (KF_NW / nc) tokens of a head, 2 nc N, and one grid dimension takes less than 2^32.
+static constexpr bool kmeans_f32_split(int H, int N, int C)
+{
+    return C > KF_SPLIT && H * (((long long)N + 31) / 32) * ((C + 31) / 32) >= KF_SPLIT_BLOCKS;
+}
 static constexpr int kmeans_f32_share(int H, int N, int C)
 {
     const int nrb = (C + 31) / 32;
     const long long blocks = H * (((long long)N + 31) / 32);
     int nc = 1;
     while (nc < KF_NW && 2 * nc <= nrb && 2ll * (2 * nc) * (N + 128ll) < 1ll << 32 &&
-           (C <= KF_SPLIT ? blocks * nc < 2048 : blocks * nc < 512 || (nrb >= 16 * nc && blocks * nc < 4096)))
+           (!kmeans_f32_split(H, N, C) ? nrb > 4 * nc || blocks * nc < 2048 : blocks * nc < 512 || (nrb >= 16 * nc && blocks * nc < 4096)))
         nc *= 2;
     return nc;
 }
@@ -2026,6 +2080,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         a.gc[s] = kmeans_update_group(H, a.s[s].C, call);
         ngroups += cdiv(a.s[s].C, a.gc[s]);
         any_few |= !BF16 && kmeans_f32_few(H, N, a.s[s].C);
+        a.split[s] = kmeans_f32_split(H, N, a.s[s].C);
         a.nc[s] = kmeans_f32_share(H, N, a.s[s].C);
         ncmax = std::max(ncmax, a.nc[s]);
         pmax = std::max(pmax, a.s[s].max_pieces);
@@ -2094,7 +2149,7 @@ static int kmeans_run(KmArgs a, hipStream_t st)
                     }
                     KmArgs one = a;                     // that side alone
                     KmIter one_it = it;
-                    one.s[0] = a.s[s]; one.nc[0] = a.nc[s]; one_it.lab[0] = it.lab[s];
+                    one.s[0] = a.s[s]; one.nc[0] = a.nc[s]; one.split[0] = a.split[s]; one_it.lab[0] = it.lab[s];
                     hipLaunchKernelGGL(kern, dim3(grid.x, H), dim3(64 * KF_NW), 0, st, one, one_it);
                 }
             }

@@ -283,14 +283,14 @@ def test_kmeans_f32_few_centroids(svg2, oracle, d, H, N, C):
 
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("H,N,C,change", [
-    (2, 300, 64, ""), (2, 300, 65, ""), (1, 97, 97, ""), (3, 2000, 129, ""), (1, 12000, 1000, ""), (6, 6001, 513, ""),
+    (2, 300, 64, ""), (40, 4000, 65, ""), (1, 97, 97, ""), (13, 2000, 129, ""), (1, 12000, 1000, ""), (6, 6001, 513, ""), (9, 2400, 96, ""),
     # both sides of what sends tokens through the fp32 instruction: ranges, one token or centroid out of range
-    (2, 500, 100, "all+39"), (2, 500, 100, "all+41"), (2, 500, 100, "all-39"), (2, 500, 100, "all-41"), (2, 500, 100, "token+41"),
-    (2, 500, 100, "token-41"), (2, 500, 100, "token0"), (2, 500, 100, "centroid-11"), (2, 500, 100, "centroid-13"), (2, 500, 100, "centroid0"),
-    (2, 500, 100, "inf"), (2, 500, 100, "nan")])
+    (40, 500, 100, "all+39"), (40, 500, 100, "all+41"), (40, 500, 100, "all-39"), (40, 500, 100, "all-41"), (40, 500, 100, "token+41"),
+    (40, 500, 100, "token-41"), (40, 500, 100, "token0"), (40, 500, 100, "centroid-11"), (40, 500, 100, "centroid-13"), (40, 500, 100, "centroid0"),
+    (40, 500, 100, "inf"), (40, 500, 100, "nan")])
 def test_kmeans_f32_split_operands(svg2, d, H, N, C, change):
-    """Labels of one fp32 assign step against float64, operands in two halves and not: a label that differs is a near-tie, its
-    distance larger than the smallest by no more than the roundings of two chains, (2 d + 8) 2^-24 (|x|^2 + |c|^2) and |c| the largest."""
+    """Labels of one fp32 assign step against float64, operands in two halves and not (40 x 500 in 100 is 2560 row blocks, 2048 is
+    the fewest): a label that differs is a near-tie, its distance larger than the smallest by no more than the roundings of two chains, (2 d + 8) 2^-24 (|x|^2 + |c|^2) and |c| the largest."""
     g = torch.Generator(device="cuda").manual_seed(C + N)
     X = (2.0 * torch.randn((H, C, d), device="cuda", generator=g))[:, torch.randint(C, (N,), device="cuda", generator=g)]
     X = X + torch.randn((H, N, d), device="cuda", generator=g)
@@ -318,6 +318,29 @@ def test_kmeans_f32_split_operands(svg2, d, H, N, C, change):
     if change == "inf":
         # the first centroid in the token's direction: its distance is -inf
         assert torch.equal(lab[:, 70], (c0[:, :, 5] > 0).int().argmax(1))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("C", [65, 500])
+def test_kmeans_f32_split_operands_leave_near_ties_to_the_fmaf_chain(svg2, d, C):
+    """Tokens next to the border of two centroids, and exact ties (a centroid twice: the lower index): the heads together, which are split,
+    get the labels that few heads get, which are too little to split."""
+    g = torch.Generator(device="cuda").manual_seed(C)
+    H, N = 30, 3001
+    c0 = 1.5 * torch.randn((1, C, d), device="cuda", generator=g)
+    c0[:, 60] = c0[:, 7]
+    i = torch.randint(C, (N,), device="cuda", generator=g)
+    j = torch.randint(C, (N,), device="cuda", generator=g)
+    t = 1e-6 * torch.randn((H, N, 1), device="cuda", generator=g, dtype=torch.float64)
+    a, b = c0[0, i].double(), c0[0, j].double()
+    X = (0.5 * (a + b) + t * (a - b)).float().contiguous()
+    X[:, :64] = c0[0, 60]
+    lab = svg2.svg2_kmeans(X, c0.repeat(H, 1, 1), 1).labels
+    assert bool((lab[:, :64] == 7).all())
+    n = 500                                             # 16 token blocks of 16 row blocks at most
+    for h in range(H):
+        few = svg2.svg2_kmeans(X[h:h + 1, :n].contiguous(), c0, 1).labels if C <= n else None
+        assert few is None or torch.equal(few[0], lab[h, :n])
 
 
 @pytest.mark.parametrize("Cq,Ck", [(1, 70), (70, 1)])
