@@ -18,7 +18,7 @@
 //                      already laid out as the B operand of O^T += V^T P^T.
 //                      V^T comes out of LDS through the transposing 64-bit
 //                      read (ds_read_b64_tr_b16).
-//   attn_f32_kernel    fp32 storage: operands as two fp16 halves or, where these would lose bits, MFMA 32x32x2 fp32; the keys of
+//   attn_f32_kernel    fp32 storage: operands in three bf16 parts or, where these would lose bits, MFMA 32x32x2 fp32; the keys of
 //                      a work item split over the wavefronts.
 //
 // The result of sorted row r is stored at row perm_q[r] (Section 4.1: the
@@ -189,13 +189,18 @@ __device__ __forceinline__ int ord_scan(int v, int32_t *s_wave, int *total)
     return before + incl - v;
 }
 
-// Range of the K and V values of a head (fp32 storage), for the rule that lets the attention kernel split them (below):
-// all entries are maxima of |x| as bits, so that a NaN or an infinity is above every number.
-//   [0], [1]  largest of K, of V         [2], [3]  ~(smallest row maximum of K, of V; rows of zeros left out)
-//   [4 ..]    largest of every V column
+// Range of the K and V values of a head (fp32 storage), for the rule that lets the attention kernel split them (below), of |x| as
+// bits, so that a NaN or an infinity is above every number:
+//   [0], [1]  largest of K, of V         [2], [3]  minus the smallest of K, of V, zeros left out (0: zeros alone)
 // Workgroups 1 .. of the order kernel's launch, RANGE_PASSES rows per row slot: one pass over K and V next to the one workgroup
 // that sorts the list, which takes longer.
 static constexpr int RANGE_PASSES = 4;
+__device__ __forceinline__ void f32_range(unsigned bits, unsigned &most, unsigned &least)
+{
+    const unsigned b = bits & 0x7FFFFFFFu;
+    most = max(most, b);
+    least = max(least, 0u - b);
+}
 static inline int attn_range_blocks(int H, int N, int d) { return 2 * H * cdiv(N, RANGE_PASSES * (1024 / (d / 4))); }
 
 __device__ __forceinline__ void attn_range(int blk, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int d,
@@ -203,38 +208,25 @@ __device__ __forceinline__ void attn_range(int blk, const float *__restrict__ K,
 {
     const int tid = threadIdx.x, lpr = d / 4, step = 1024 / lpr, nb = (N + RANGE_PASSES * step - 1) / (RANGE_PASSES * step);
     const int side = blk / (H * nb), h = blk / nb % H, r0 = blk % nb * RANGE_PASSES * step;
-    const int chunk = tid % lpr;
     const uint4 *X = reinterpret_cast<const uint4 *>((side ? V : K) + (size_t)h * N * d);
-    if (tid < 2 + 128) s_max[tid] = 0;
+    if (tid < 2) s_max[tid] = 0;
     __syncthreads();
     uint4 v[RANGE_PASSES];
 #pragma unroll
-    for (int p = 0; p < RANGE_PASSES; ++p) v[p] = X[(size_t)min(r0 + p * step + tid / lpr, N - 1) * lpr + chunk];
-    unsigned most = 0, least = 0, col[4] = {0, 0, 0, 0};        // least: ~ of the smallest
+    for (int p = 0; p < RANGE_PASSES; ++p) v[p] = X[(size_t)min(r0 + p * step + tid / lpr, N - 1) * lpr + tid % lpr];
+    unsigned most = 0, least = 0;               // least: minus the smallest
 #pragma unroll
     for (int p = 0; p < RANGE_PASSES; ++p) {
-        const unsigned b[4] = {v[p].x & 0x7FFFFFFFu, v[p].y & 0x7FFFFFFFu, v[p].z & 0x7FFFFFFFu, v[p].w & 0x7FFFFFFFu};
-        unsigned m = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { col[e] = max(col[e], b[e]); m = max(m, b[e]); }
-        for (int o = 1; o < lpr; o <<= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
-        most = max(most, m);
-        if (m != 0) least = max(least, ~m);
+        f32_range(v[p].x, most, least); f32_range(v[p].y, most, least);
+        f32_range(v[p].z, most, least); f32_range(v[p].w, most, least);
     }
-    for (int o = lpr; o < 64; o <<= 1) {
+    for (int o = 32; o > 0; o >>= 1) {
         most = max(most, (unsigned)__shfl_xor((int)most, o));
         least = max(least, (unsigned)__shfl_xor((int)least, o));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) col[e] = max(col[e], (unsigned)__shfl_xor((int)col[e], o));
     }
     if ((tid & 63) == 0) { atomicMax(&s_max[0], most); atomicMax(&s_max[1], least); }
-    if (side && (tid & 63) < lpr)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) atomicMax(&s_max[2 + 4 * chunk + e], col[e]);
     __syncthreads();
-    unsigned *rg = range + (size_t)h * F32_RANGE;
-    if (tid < 2) atomicMax(&rg[2 * tid + side], s_max[tid]);
-    if (side && tid < d) atomicMax(&rg[4 + tid], s_max[2 + tid]);
+    if (tid < 2) atomicMax(&range[(size_t)h * F32_RANGE + 2 * tid + side], s_max[tid]);
 }
 
 __global__ __launch_bounds__(1024) void attn_order_kernel(const int32_t *__restrict__ offsets_q,
@@ -843,33 +835,60 @@ __global__ __launch_bounds__(64 * ATT_NW, D == 64 ? 3 : 2) void attn_bf16_kernel
 // operand.  Row m of output block b is column DVB m + b, so that one load of DVB consecutive floats is the operand of all DVB
 // blocks, and the DVB accumulators of a row are consecutive floats of the result.
 //
-// Operands in two halves (the first of the two loops).  The fp32 instruction takes 13 times as long as the fp16 one for the same
-// work, so where the values allow it a value x is taken as hi + lo, both fp16 (rounded to nearest: hi + lo is x to 2^-23), and a
-// product as hi hi + hi lo + lo hi, three 32x32x16 instructions.  K and V of a head and every Q row are first brought to 2^14 ..
-// 2^15 by a power of two and probabilities by 2^F32_LIFT, so that a lo keeps its bits down to 2^-17 of the largest value and is
-// off by at most 2^-39 of that below.  The rule: all values finite, the largest of K, of V and of a Q row within 2^+-40, no K or V
-// row and no V column whose largest value is more than 2^F32_SPREAD below the head's (rows and columns of zeros aside), and
-// scores that can reach F32_SCORE.  What the split drops is then below the roundings of the sums: an accumulator rounds behind
-// each of 3 instructions per 16 products instead of behind each of 16 products.  Relative error of O against 64 bits over 100 shapes of 98 to
-// 4200 keys, scores of standard deviation 3 to 16: 0.58 to 0.69 of the fp32 instruction's, of the log-sum-exp 0.62 to 1.0.  With scores that
-// cannot reach F32_SCORE the fp32 sums hardly err (O off by 1.6e-7 with scores around 0.01 and 500 keys, 2.7e-7 split; 3.2e-7 and 3.5e-7
-// with normal Q and K at D = 64), so these, infinities, NaN and outliers go through the fp32 instruction: the second loop.
+// Operands in three parts (the first of the two loops).  The fp32 instruction takes 13 times as long as the bf16 one for the same
+// work, so where the values allow it a value x is taken as the sum of three bf16, each rounded to nearest from what the ones before
+// leave: exactly x.  Of the nine products of two operands the six of 2^-17 and more go through the 32x32x16 instruction, the other
+// three are below 2^-24 of it, without a common sign.  Small products have an accumulator of their own, the second product of 16 keys is
+// summed from zero: added one by one to a long sum, the third parts of V rows that are alike would be rounded away each time (V rows
+// all the same, 9601 keys: 8.7e-7 instead of 1.3e-7).  The rule: every K and V value of the head and Q value of the tile is zero or
+// between 2^-60 and 2^40 and the scale no more than 2^40, so that no part is subnormal and no sum overflows; infinities, NaN and the rest go
+// through the fp32 instruction: the second loop.  Error of O against 64 bits, of the fp32 instruction's, over 600 to 9601 keys, scores of
+// deviation 0 to 8, means, channels of any size in Q and K, V rows alike: 0.38 to 0.93, of the log-sum-exp 0.42 to 1.03; with V values of all
+// sizes no element further off.  (Two fp16 halves, hi hi + hi lo + lo hi, took 0.41 instead of 0.56 ms below, but lost what lies
+// 2^-28 below the largest value of K, of V or of a Q row.)
 //
 // Time: 4 heads of 9601 tokens in 100 and 500 clusters, D = 128, 31 % selected (58 GFLOP; a seventh of the rows of the 32-row tiles is
-// padding) 0.67 -> 0.40 ms, one head of 4096 at D = 64 31 -> 22 us.  What bounds the first loop is the traffic into the CUs, 32 KB per
-// wavefront and 32 keys (10.8 TB/s of K and V in all); matrix and vector instructions are at 23 and 37 % of their rates.  Therefore K goes by whole
+// padding) 0.61 -> 0.56 ms with the plan, one head of 4096 at D = 64 38 -> 36 us;
+// dense, D = 128, 4 x 9601 1.59 -> 1.39 ms, 2 x 3000 124 -> 103 us.  What bounds the first loop is the vector ALU, 5.5 instructions per
+// value for the parts, and the matrix cores behind one another with two wavefronts per SIMD.  K goes by whole
 // rows straight to LDS (a wavefront's own 32 rows, fetched while the block before is in its second product) instead of 16 bytes of a row per
-// lane, and the rows of a block are found from one load of 64 runs issued a block ahead, not by a walk through memory: 0.47 -> 0.40 ms together.  V
+// lane, and the rows of a block are found from one load of 64 runs issued a block ahead, not by a walk through memory.  V
 // goes to registers, requested in front of the first product; Q, split, is read from LDS, which leaves the registers for that.
 // The second loop has K and V in two register buffers each: a 32-key block is 128 matrix instructions (8192 cycles, D = 128), which cover
 // its 32 loads.  One query per thread with K and V in LDS took 13.8 ms on the same shape.
 // No more wavefronts than a head has key blocks, rounded up to a power of two (5000 heads of 16 tokens, D = 64: 58 us with one,
 // 105 with eight), and four instead of eight in short heads that are work items enough without (3000 heads of 100 tokens, 10
 // and 20 clusters, a quarter selected: 302 instead of 495 us; 200 of 500, 30 and 60 clusters, D = 128: 208 instead of 276).
-static constexpr unsigned F32_EXP_LO = 127 - 40, F32_EXP_HI = 127 + 40, F32_SPREAD = 12;
-static constexpr float F32_LIFT = 14.f, F32_LIFT_BY = 16384.f, F32_SCORE = 256.f;
+static constexpr unsigned F32_LEAST = (127 - 60) << 23, F32_MOST = (127 + 40) << 23;       // 2^-60, 2^40 as bits
+static constexpr float F32_SCALE = 1099511627776.f;                                        // 2^40
 static constexpr int F32_NW = 8, F32_MANY = 1024, F32_SHORT = 512;
 static constexpr int F32_BM = 32;
+
+// elements 2 i and 2 i + 1 of the three parts of a and b; the differences are exact
+__device__ __forceinline__ void f32_split3(float a, float b, u32x4 (&part)[3], int i)
+{
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const unsigned w = pack_bf16x2(a, b);
+        part[p][i] = w;
+        a -= __uint_as_float(w << 16);
+        b -= __uint_as_float(w & 0xFFFF0000u);
+    }
+}
+
+// products of two operands in three parts: large += first parts, small += the others, smallest first
+__device__ __forceinline__ void f32_mfma3(const u32x4 (&x)[3], const u32x4 (&y)[3], f32x16 &large, f32x16 &small)
+{
+    auto mfma = [&](int i, int j, f32x16 &acc) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x[i]), __builtin_bit_cast(bf16x8, y[j]), acc, 0, 0, 0);
+    };
+    mfma(2, 0, small);
+    mfma(0, 2, small);
+    mfma(1, 1, small);
+    mfma(1, 0, small);
+    mfma(0, 1, small);
+    mfma(0, 0, large);
+}
 
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
@@ -912,11 +931,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
     if (perm_k) qrow = perm_q[(size_t)h * N + qrow];    // gather-free: Q is in token order
     const float *Qr = Q + ((size_t)h * N + qrow) * D;
     // Split operands or not: the same for all wavefronts of the work item (same Q rows, same head)
-    // split Q in LDS behind the wavefronts' shares: lane's part of step t is elements 16 t + 8 half .. of its row
-    f16x8 *s_q = reinterpret_cast<f16x8 *>(s_o + (size_t)NW * 32 * ROW);
+    // split Q in LDS behind the wavefronts' K blocks: lane's part of step t is elements 16 t + 8 half .. of its row
+    u32x4 *s_q = reinterpret_cast<u32x4 *>(s_o + (size_t)NW * 32 * D);
     bool split = false;
-    float k_up = 1.f, v_up = 1.f, q_up = 1.f;   // powers of two that bring the largest K, V of the head, Q of the row to 2^14 .. 2^15
-    if (range) {
+    if constexpr (NW == F32_NW) {
+      if (range) {
         float q[D / 2];
 #pragma unroll
         for (int t = 0; t < D / 16; ++t) {
@@ -926,29 +945,21 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
             q[8 * t + 4] = w1.x; q[8 * t + 5] = w1.y; q[8 * t + 6] = w1.z; q[8 * t + 7] = w1.w;
         }
         const unsigned *rg = range + (size_t)h * F32_RANGE;
-        const unsigned ke = rg[0] >> 23, ve = rg[1] >> 23;
-        unsigned qb = 0;
+        unsigned most = max(rg[0], rg[1]), least = max(rg[2], rg[3]);
 #pragma unroll
-        for (int k = 0; k < D / 2; ++k) qb = max(qb, __float_as_uint(q[k]) & 0x7FFFFFFFu);
-        qb = max(qb, (unsigned)__shfl_xor((int)qb, 32));
-        const unsigned qe = qb == 0 ? 127u : qb >> 23;
-        bool ok = ke - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO && ve - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO &&
-                  qe - F32_EXP_LO <= F32_EXP_HI - F32_EXP_LO && (~rg[2] >> 23) + F32_SPREAD >= ke && (~rg[3] >> 23) + F32_SPREAD >= ve;
-        for (int c = lane; c < D; c += 64) ok = ok && (rg[4 + c] == 0 || (rg[4 + c] >> 23) + F32_SPREAD >= ve);
-        split = __all(ok) && __any(__uint_as_float(qb) * __uint_as_float(rg[0]) * ((float)D * scale_log2) >= F32_SCORE);
-        k_up = __uint_as_float((127 + 14 + 127 - ke) << 23);
-        v_up = __uint_as_float((127 + 14 + 127 - ve) << 23);
-        q_up = __uint_as_float((127 + 14 + 127 - qe) << 23);
+        for (int k = 0; k < D / 2; ++k) f32_range(__float_as_uint(q[k]), most, least);
+        split = __all(most <= F32_MOST && least <= 0u - F32_LEAST) && scale_log2 <= F32_SCALE;
 #pragma unroll
         for (int t = 0; t < D / 16; ++t)
             if (t % NW == wave) {               // (wave-uniform; every wavefront holds the same row parts)
-                f16x8 qh, ql;
+                u32x4 part[3];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) f32_split(q[8 * t + e], q_up, qh, ql, e);
-                s_q[2 * t * 64 + lane] = qh;
-                s_q[(2 * t + 1) * 64 + lane] = ql;
+                for (int e = 0; e < 4; ++e) f32_split3(q[8 * t + 2 * e], q[8 * t + 2 * e + 1], part, e);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) s_q[(3 * t + i) * 64 + lane] = part[i];
             }
         __syncthreads();
+      }
     }
     f32x16 oacc[DVB];
 #pragma unroll
@@ -979,12 +990,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
             buf[i] = *reinterpret_cast<const fvec *>(Vb + (r + (unsigned)(col * (4 * DVB))));
         }
     };
-    // scores of block j -> its probabilities, running level and sum; mul: the scores' factor, lift: log2 of the probabilities' factor
-    auto softmax = [&](f32x16 &S, float mul, float lift) {
+    // scores of a block -> its probabilities, running level and sum
+    auto softmax = [&](f32x16 &S) {
         float mx = fmaxf(S[0], S[1]);
 #pragma unroll
         for (int i = 2; i < 16; ++i) mx = fmaxf(mx, S[i]);
-        mx = fmaxf(m, max_xor32(mx) * mul);
+        mx = fmaxf(m, max_xor32(mx) * scale_log2);
         if (__any(mx > m)) {
             const float alpha = __builtin_amdgcn_exp2f(m - mx);
             m = mx;
@@ -994,10 +1005,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
         }
-        const float m_ref = (m == -INFINITY) ? 0.f : m - lift;      // scores of -inf alone so far: weights 0, not NaN
+        const float m_ref = (m == -INFINITY) ? 0.f : m;         // scores of -inf alone so far: weights 0, not NaN
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], mul, -m_ref));
+            S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], scale_log2, -m_ref));
             l += S[i];
         }
     };
@@ -1012,52 +1023,59 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
     };
 #define F32_FENCE __builtin_amdgcn_sched_barrier(0);
 
-    if (split) {
+    if (NW == F32_NW && split) {
         fvec vA[8], vB[8];
         float *sk = s_o + wave * (32 * D);      // this wavefront's K block
-        const float mul = scale_log2 * (1.f / q_up) * (1.f / k_up);
         constexpr int CPR = D / 4;              // 16-byte chunks per row
         // chunk c of row r sits at c ^ (r % 16): 16 rows read at one chunk hit different banks
+        const unsigned chunk = 16u * (unsigned)((lane % CPR) ^ (lane / CPR));
         auto fetch_k = [&](unsigned off) {
+            unsigned x = chunk;
+            asm volatile("" : "+v"(x));
             unsigned o[CPR / 2];
 #pragma unroll
             for (int i = 0; i < CPR / 2; ++i) o[i] = (unsigned)__shfl((int)off, i * (64 / CPR) + lane / CPR);
 #pragma unroll
-            for (int i = 0; i < CPR / 2; ++i) {
-                const int r = i * (64 / CPR) + lane / CPR;
-                load_to_lds_16(Kb, o[i] + 16u * (unsigned)((lane % CPR) ^ (r % 16)), reinterpret_cast<const unsigned char *>(sk) + 1024 * i);
-            }
+            for (int i = 0; i < CPR / 2; ++i)           // (row i * (64 / CPR) + lane / CPR)
+                load_to_lds_16(Kb, o[i] + (x ^ (16u * (i * (64 / CPR) % 16))), reinterpret_cast<const unsigned char *>(sk) + 1024 * i);
         };
+        const float *krow = sk + col * D;
+        const unsigned kx = (unsigned)(col % 16 ^ 2 * half);
         auto qk = [&](f32x16 &S) {
+            unsigned x = kx;
+            asm volatile("" : "+v"(x));         // (the addresses are formed here, not held in registers)
+            f32x16 small = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int t = 0; t < D / 16; ++t) {
-                f16x8 kh, kl;
+                u32x4 kp[3];
 #pragma unroll
                 for (int e4 = 0; e4 < 2; ++e4) {
-                    const float4 w = *reinterpret_cast<const float4 *>(sk + col * D + 4 * ((4 * t + 2 * half + e4) ^ (col % 16)));
-                    f32_split(w.x, k_up, kh, kl, 4 * e4);
-                    f32_split(w.y, k_up, kh, kl, 4 * e4 + 1);
-                    f32_split(w.z, k_up, kh, kl, 4 * e4 + 2);
-                    f32_split(w.w, k_up, kh, kl, 4 * e4 + 3);
+                    const float4 w = *reinterpret_cast<const float4 *>(krow + 4 * (x ^ (unsigned)(4 * t + e4)));      // chunk 4 t + 2 half + e4
+                    f32_split3(w.x, w.y, kp, 2 * e4);
+                    f32_split3(w.z, w.w, kp, 2 * e4 + 1);
                 }
-                const f16x8 qh = s_q[2 * t * 64 + lane], ql = s_q[(2 * t + 1) * 64 + lane];
-                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qh, S, 0, 0, 0);
-                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, ql, S, 0, 0, 0);
-                S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qh, S, 0, 0, 0);
+                const u32x4 qp[3] = {s_q[3 * t * 64 + lane], s_q[(3 * t + 1) * 64 + lane], s_q[(3 * t + 2) * 64 + lane]};
+                f32_mfma3(kp, qp, S, D == 128 ? small : S);         // (D == 64: no registers left)
             }
-        };
-        auto pv = [&](const f32x16 &P, const fvec (&v)[8], int hf) {
-            f16x8 ph, pl;
+            if (D == 128)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) f32_split(P[8 * hf + i], 1.f, ph, pl, i);
+                for (int i = 0; i < 16; ++i) S[i] += small[i];
+        };
+        // The products of 16 keys are summed by themselves and meet the running sum as one: term by term the third parts of values
+        // that many keys share would be rounded away, one key like the other.
+        auto pv = [&](const f32x16 &P, const fvec (&v)[8], int hf) {
+            u32x4 pp[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f32_split3(P[8 * hf + 2 * i], P[8 * hf + 2 * i + 1], pp, i);
 #pragma unroll
             for (int b = 0; b < DVB; ++b) {
-                f16x8 vh, vl;
+                u32x4 vp[3];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) f32_split(v[i][b], v_up, vh, vl, i);
-                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, ph, oacc[b], 0, 0, 0);
-                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, pl, oacc[b], 0, 0, 0);
-                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, ph, oacc[b], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) f32_split3(v[2 * i][b], v[2 * i + 1][b], vp, i);
+                f32x16 sum = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                f32_mfma3(vp, pp, sum, sum);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[b][i] += sum[i];
             }
         };
         // The rows of a block two ahead, in two steps between which its loads are on their way: the 64 runs from the one in which the
@@ -1105,7 +1123,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
             c0 = first_run(j + 3 * NW);
             F32_FENCE
             if (j == nblk - 1) mask(S, vA, vB, j);
-            softmax(S, mul, F32_LIFT);
+            softmax(S);
             F32_FENCE
             pv(S, vA, 0);
             pv(S, vB, 1);
@@ -1161,7 +1179,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
             load_v(vB, off, 1);
             F32_FENCE
             if (j == nblk - 1) mask(S, vA, vB, j);
-            softmax(S, scale_log2, 0.f);
+            softmax(S);
             F32_FENCE
             pv(S, vA, 0);
             F32_FENCE
@@ -1208,11 +1226,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
         const size_t dst = (size_t)h * N + (perm_q ? perm_q[(size_t)h * N + row0 + r] : row0 + r);
         // (no key: 0; keys without any weight, or scores that are no numbers: the softmax is undefined)
         const float inv = (lt > 0.f) ? 1.0f / lt : L > 0 ? NAN : 0.f;
-        const float down = split ? 1.f / v_up : 1.f;
-        *reinterpret_cast<float4 *>(O + dst * D + c4) =
-            make_float4(acc.x * inv * down, acc.y * inv * down, acc.z * inv * down, acc.w * inv * down);
-        if (lse && c4 == 0)
-            lse[dst] = (lt > 0.f) ? (mm + log2f(split ? lt * (1.f / F32_LIFT_BY) : lt)) * 0.6931471805599453f : -INFINITY;
+        *reinterpret_cast<float4 *>(O + dst * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+        if (lse && c4 == 0) lse[dst] = (lt > 0.f) ? (mm + log2f(lt)) * 0.6931471805599453f : -INFINITY;
     }
 }
 
@@ -1235,9 +1250,11 @@ static size_t attn_lds_bytes(int d, int Ck)
 // instead of 55; 200 of 600 340 instead of 457).  Longer heads have eight wavefronts per work item, which share a CU with no other at D = 128.
 static unsigned *attn_range_of(const AttnWs &a, int N) { return N > F32_SHORT ? a.range : nullptr; }
 
+// (split Q lies behind the K blocks; the padding of the final sum's rows is not there yet)
 static size_t attn_f32_lds_bytes(int d, int nw, bool ranged)
 {
-    return (size_t)nw * F32_BM * (d + 4) * sizeof(float) + (ranged ? F32_BM * d * sizeof(float) : 0);
+    const size_t sum = (size_t)nw * F32_BM * (d + 4) * sizeof(float);
+    return ranged ? std::max(sum, (size_t)nw * F32_BM * d * sizeof(float) + 3 * F32_BM * d * sizeof(bf16_t)) : sum;
 }
 
 static int attn_f32_nw(int H, int N)

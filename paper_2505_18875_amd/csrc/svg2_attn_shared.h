@@ -105,7 +105,7 @@ __device__ __forceinline__ int attn_list_pos(int group)
 // ---- plan workspace (host)
 constexpr int attn_bm(int dtype) { return dtype == SVG2_BF16 ? 32 * ATT_NW : 32; }   // rows per tile
 
-static constexpr int F32_RANGE = 4 + 128;        // entries per head, attn_range
+static constexpr int F32_RANGE = 4;        // entries per head, attn_range
 
 struct AttnWs {
     int4 *tiles;

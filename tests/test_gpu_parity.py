@@ -932,6 +932,42 @@ def test_attention_f32_split_operands(svg2, oracle, d, N, runs, change):
     assert np.all(np.abs(to_np(res.lse[0]) - lse) <= 2 * dS + 4 * eps * np.abs(lse))
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("N,change", [(600, "channel"), (1001, "channel"), (600, "values"), (1001, "values"), (9601, "alike")])
+def test_attention_f32_keeps_the_small_bits(svg2, d, N, change):
+    """What parts of the operands could lose: a channel that is 2^30 times as large in Q and as small in K, V values of all sizes under
+    weights that single out a key, V rows that are alike in all their bits.  Bounds per element as in test_attention_f32_split_operands.  Rows
+    alike: their mean is the row, and a sum over a wavefront's n = N / 8 keys that is rounded at every key is off by 2^-24 sqrt(n) / 3 of
+    itself (a random walk whose steps grow with the sum), the mean of eight of them by 1 / sqrt(8) of that; twice that, for the weights' sum."""
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    Q, K, V = (torch.randn((1, N, d), device="cuda", generator=g) for _ in range(3))
+    if change == "channel":
+        Q[..., 3] *= 2.0 ** 30
+        K[..., 3] *= 2.0 ** -30
+    elif change == "values":
+        Q *= 40.0
+        V[:, :, ::2] *= 2.0 ** -torch.randint(0, 30, (1, N, d // 2), device="cuda", generator=g).float()
+    else:
+        Q *= 0.5
+        V = V[:, :1].repeat(1, N, 1)
+    one = lambda *a: torch.tensor([a], dtype=torch.int32, device="cuda")  # noqa: E731
+    res = svg2.svg2_sparse_attn(Q, K, V, one(0, N), one(0, N), one(0, 1), one(0), want_lse=True)
+    torch.cuda.synchronize()
+    q, k, v = Q[0].double(), K[0].double(), V[0].double()
+    S = q @ k.T.contiguous() / float(np.sqrt(d))
+    lse = torch.logsumexp(S, 1)
+    P = torch.exp(S - lse[:, None])
+    eps = 2.0 ** -24
+    dS = (d + 8) * eps * (q.abs() @ k.abs().T.contiguous()).max(1).values / float(np.sqrt(d)) + 64 * eps
+    err = (res.O[0].double() - P @ v).abs()
+    bound = 2.0 * dS[:, None] * (P @ v.abs())
+    assert bool((err <= bound).all()), (err / bound).max().item()
+    assert bool(((res.lse[0].double() - lse).abs() <= 2 * dS + 4 * eps * lse.abs()).all())
+    if change == "alike":
+        rms = ((err / v[:1].abs()) ** 2).mean().sqrt().item()
+        assert rms <= 2 * eps * (N / 8) ** 0.5 / 3 / 8 ** 0.5, rms
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("lo,hi", [(64, 96), (224, 257), (100, 600), (32, 601)])
