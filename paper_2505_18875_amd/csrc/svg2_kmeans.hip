@@ -1052,6 +1052,15 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
         if (wc != 0) return;
         for (int w = 1; w < nc; ++w) merge(s_best[wave + w][col], s_idx[wave + w][col], s_second[wave + w][col]);
     }
+    // elements 8 q .. 8 q + 7 of the chain of fmaf for centroid j
+    auto chain8 = [&](float &dot, int q, int j, const float4 &x0, const float4 &x1) {
+        const float4 ev = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)q * C + j));
+        const float4 od = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)(D / 8 + q) * C + j));
+        dot = fmaf(ev.x, x0.x, dot); dot = fmaf(od.x, x0.y, dot);
+        dot = fmaf(ev.y, x0.z, dot); dot = fmaf(od.y, x0.w, dot);
+        dot = fmaf(ev.z, x1.x, dot); dot = fmaf(od.z, x1.y, dot);
+        dot = fmaf(ev.w, x1.z, dot); dot = fmaf(od.w, x1.w, dot);
+    };
     // Near-ties of the split products go by the chain of fmaf, as all tokens do without them: a token at a time, KF_CHAINS centroids per
     // lane (one after the other, its loads all requested at once: 6 x 12,000 in 1000 721 instead of 621 us, 1 x 12,000 287 instead of 222).
     if (split) {
@@ -1067,15 +1076,7 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
                 for (int q = 0; q < D / 8; ++q) {
                     const float4 x0 = *reinterpret_cast<const float4 *>(xr + 8 * q), x1 = *reinterpret_cast<const float4 *>(xr + 8 * q + 4);
 #pragma unroll
-                    for (int u = 0; u < KF_CHAINS; ++u) {
-                        const int j = min(j0 + 64 * u, C - 1);
-                        const float4 ev = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)q * C + j));
-                        const float4 od = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)(D / 8 + q) * C + j));
-                        dot[u] = fmaf(ev.x, x0.x, dot[u]); dot[u] = fmaf(od.x, x0.y, dot[u]);
-                        dot[u] = fmaf(ev.y, x0.z, dot[u]); dot[u] = fmaf(od.y, x0.w, dot[u]);
-                        dot[u] = fmaf(ev.z, x1.x, dot[u]); dot[u] = fmaf(od.z, x1.y, dot[u]);
-                        dot[u] = fmaf(ev.w, x1.z, dot[u]); dot[u] = fmaf(od.w, x1.w, dot[u]);
-                    }
+                    for (int u = 0; u < KF_CHAINS; ++u) chain8(dot[u], q, min(j0 + 64 * u, C - 1), x0, x1);
                 }
 #pragma unroll
                 for (int u = 0; u < KF_CHAINS; ++u) {
@@ -1094,6 +1095,17 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     }
     if (half == 0 && n < N) labels[(size_t)h * N + n] = bidx;
     if (OBJ && S.objective) {
+        if (split) {
+            // The distance of the chain, whatever found the label: hi hi + hi lo + lo hi lacks lo lo, which is a square for a token near its
+            // centroid, so all distances were too large by up to 2^-22 |x|^2.
+            const float *xr = static_cast<const float *>(S.X) + ((size_t)h * N + min(n, N - 1)) * D;
+            float dot = 0.f;
+            for (int q = 0; q < D / 8; ++q) {
+                const float4 x0 = *reinterpret_cast<const float4 *>(xr + 8 * q), x1 = *reinterpret_cast<const float4 *>(xr + 8 * q + 4);
+                chain8(dot, q, bidx, x0, x1);
+            }
+            best = fmaf(-2.f, dot, s_cn[bidx]);
+        }
         float v = (half == 0 && n < N) ? x2 + best : 0.f;
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
         if (lane == 0) atomicAdd(S.objective + (size_t)h * a.iters + it.t, v);

@@ -343,6 +343,25 @@ def test_kmeans_f32_split_operands_leave_near_ties_to_the_fmaf_chain(svg2, d, C)
         assert few is None or torch.equal(few[0], lab[h, :n])
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N,C", [(10, 1000, 500), (70, 500, 100)])
+def test_kmeans_f32_objective_of_split_operands(svg2, d, H, N, C):
+    """Tokens near their centroids: the heads together, which are split, have the objective that each has alone, too little to split.  The
+    same N terms are added in 32s and then in any order, at most 5 + N / 32 roundings of 2^-24 of the sum of their sizes, each at most the squared
+    distance and the error of its chain, (2 d + 8) 2^-24 (|x|^2 + |c|^2)."""
+    g = torch.Generator(device="cuda").manual_seed(C + d)
+    c0 = 1.5 * torch.randn((H, C, d), device="cuda", generator=g)
+    j = torch.randint(C, (H, N), device="cuda", generator=g)
+    X = torch.gather(c0, 1, j[..., None].expand(H, N, d))
+    X = (X + 1e-3 * torch.randn((H, N, d), device="cuda", generator=g)).contiguous()
+    obj = svg2.svg2_kmeans(X, c0, 1, want_objective=True).objective[:, 0].double()
+    for h in range(H):
+        alone = svg2.svg2_kmeans(X[h:h + 1].contiguous(), c0[h:h + 1].contiguous(), 1, want_objective=True).objective[0, 0].double()
+        x2, d2 = (X[h].double() ** 2).sum(), ((X[h].double() - c0[h, j[h]].double()) ** 2).sum()
+        size = d2 + (2 * d + 8) * 2.0 ** -24 * 2.01 * x2
+        assert abs(obj[h] - alone) <= (5 + N / 32) * 2.0 ** -24 * size, ((obj[h] - alone) / x2).item()
+
+
 @pytest.mark.parametrize("Cq,Ck", [(1, 70), (70, 1)])
 def test_forward_f32_one_side_with_few_centroids(svg2, oracle, Cq, Ck):
     # 5 heads of 1920 tokens: the assign steps of the two sides are different kernels
