@@ -860,9 +860,11 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 // against 67.4 us per five iterations; one head of 700 in 24 54.8 against 53.0), and calls with little to do (kmeans_f32_split) go
 // through the fp32 instruction: contraction index in its natural order (lane half h supplies the elements of parity h), the
 // instruction adds its two products one after the other with a rounding behind each, so an accumulator is bit for bit the chain
-// of fmaf over k = 0 .. D - 1.  That chain decides the label in either case: the split products leave the tokens whose two best distances are
-// closer than KF_TIE (|x|^2 + max |c|^2), a few per launch, to it.  (Largest error of a difference of two distances seen on 7.7 million
-// tokens next to a border: 0.7e-6 of that bracket for the chain, 0.5e-6 split.)
+// of fmaf over k = 0 .. D - 1.  That chain decides the label in either case: the split products leave the tokens whose two best distances
+// are closer than KF_TIE D |x| max |c| + 2^-22 (|best| + |second|) to it.  The first term is four times the most that two dot products may
+// be apart: D roundings of 2^-24 |x| |c| for the chain, which partial sums in one direction nearly reach, and twice that for the split
+// products (2^-21 for the parts and lo lo; their sums measured at less than the chain's: of differences of two distances 0.5e-6 of
+// |x|^2 + |c|^2 on 7.7 million tokens next to a border, 0.7e-6 by the chain).  The second term is for the rounding of the distances themselves.
 //
 // The centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
 // register buffers, the halves of a row block, each requested again as soon as it has been used.  What decides for few tokens is how
@@ -875,7 +877,7 @@ static constexpr int KF_NW = 4;
 static constexpr int KF_SPLIT = 64;             // most centroids that go through the fp32 instruction whatever the values
 static constexpr int KF_EXP = 40, KF_SPREAD = 24;
 static constexpr long long KF_SPLIT_BLOCKS = 2048;      // fewest row blocks, over all token blocks
-static constexpr float KF_TIE = 3.814697265625e-06f;    // 2^-18
+static constexpr float KF_TIE = 7.152557373046875e-07f;  // 4 (1 + 2) 2^-24
 static constexpr int KF_CHAINS = 4;                     // centroids of a lane side by side
 
 template <int D, bool OBJ>
@@ -1064,7 +1066,9 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     // Near-ties of the split products go by the chain of fmaf, as all tokens do without them: a token at a time, KF_CHAINS centroids per
     // lane (one after the other, its loads all requested at once: 6 x 12,000 in 1000 721 instead of 621 us, 1 x 12,000 287 instead of 222).
     if (split) {
-        unsigned near = (unsigned)__ballot(n < N && second - best <= KF_TIE * (x2 + __uint_as_float(cn_most)));
+        const float tie = KF_TIE * D * __builtin_amdgcn_sqrtf(x2) * __builtin_amdgcn_sqrtf(__uint_as_float(cn_most)) +
+                          0x1p-22f * (fabsf(best) + fabsf(second));
+        unsigned near = (unsigned)__ballot(n < N && !(second - best > tie));
         for (; near; near &= near - 1) {
             const int c32 = __builtin_ctz(near);
             const float *xr = static_cast<const float *>(S.X) + ((size_t)h * N + n0 + c32) * D;     // (uniform)

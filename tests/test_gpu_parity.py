@@ -321,17 +321,58 @@ def test_kmeans_f32_split_operands(svg2, d, H, N, C, change):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+def test_kmeans_f32_split_operands_where_the_chain_errs_most(svg2, d):
+    """A token of ones and two centroids whose elements make every sum of the chain of fmaf round up, and down, by almost half a unit: the
+    chain is off by 2^-24 of every partial sum, and finds the first centroid nearer although it is further off by 0.9 of that."""
+    r = np.random.default_rng(d)
+    f32 = np.float32
+
+    def centroid(sign):
+        c, acc = np.zeros(d, f32), f32(0)
+        for k in range(d - 1):
+            v = f32(r.uniform(0.9, 1.0))
+            ulp = np.spacing(f32(acc + v))                      # acc + c is half a unit (and a bit less) away from the next acc
+            target = f32(np.round(float(acc + v) / ulp) * ulp)
+            c[k] = f32(float(target) - float(acc) - sign * 0.48 * float(ulp))
+            assert abs(float(f32(acc + c[k])) - float(target)) <= float(ulp)
+            acc = f32(acc + c[k])
+        return c, float(acc), float(c[: d - 1].astype(np.float64).sum())
+
+    cj, chain_j, dot_j = centroid(1.0)
+    cb, chain_b, dot_b = centroid(-1.0)
+    off = 2.0 * (chain_j - dot_j - (chain_b - dot_b))
+    assert off > (2.0 if d == 128 else 0.5) * 2.0 ** -24 * d * d / 2    # what the two chains are apart
+    sq = lambda c: float((c.astype(np.float64) ** 2).sum())     # noqa: E731
+    # the last element, where the token is zero, sets the distances
+    extra = 0.9 * off - (sq(cj) - 2.0 * dot_j - sq(cb) + 2.0 * dot_b)
+    cj[-1], cb[-1] = f32(np.sqrt(max(extra, 0.0))), f32(np.sqrt(max(-extra, 0.0)))
+    exact = sq(cj) - 2.0 * dot_j - (sq(cb) - 2.0 * dot_b)
+    assert exact > 0.8 * off and (sq(cj) - 2.0 * chain_j) - (sq(cb) - 2.0 * chain_b) < -0.05 * off
+    g = torch.Generator(device="cuda").manual_seed(d)
+    H, N, C = 70, 500, 100
+    X = 0.25 * torch.randn((H, N, d), device="cuda", generator=g)
+    c0 = 0.25 * torch.randn((H, C, d), device="cuda", generator=g)
+    X[:, 70, : d - 1], X[:, 70, d - 1] = 1.0, 0.0
+    c0[:, 30], c0[:, 40] = torch.from_numpy(cb).cuda(), torch.from_numpy(cj).cuda()
+    lab = svg2.svg2_kmeans(X, c0, 1).labels
+    alone = svg2.svg2_kmeans(X[:1].contiguous(), c0[:1].contiguous(), 1).labels
+    assert int(alone[0, 70]) == 40 and bool((lab[:, 70] == 40).all())
+    assert torch.equal(lab[:1], alone)
+
+
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("C", [65, 500])
-def test_kmeans_f32_split_operands_leave_near_ties_to_the_fmaf_chain(svg2, d, C):
-    """Tokens next to the border of two centroids, and exact ties (a centroid twice: the lower index): the heads together, which are split,
-    get the labels that few heads get, which are too little to split."""
+@pytest.mark.parametrize("offset,spread", [(0.0, 1e-6), (0.0, 1e-4), (3.0, 1e-4), (30.0, 1e-3)])
+def test_kmeans_f32_split_operands_leave_near_ties_to_the_fmaf_chain(svg2, d, C, offset, spread):
+    """Tokens next to the border of two centroids, and exact ties (a centroid twice: the lower index), around the origin and far from it: the
+    heads together, which are split, get the labels that few heads get, which are too little to split."""
     g = torch.Generator(device="cuda").manual_seed(C)
     H, N = 30, 3001
-    c0 = 1.5 * torch.randn((1, C, d), device="cuda", generator=g)
+    c0 = 1.5 * torch.randn((1, C, d), device="cuda", generator=g) + offset
     c0[:, 60] = c0[:, 7]
     i = torch.randint(C, (N,), device="cuda", generator=g)
     j = torch.randint(C, (N,), device="cuda", generator=g)
-    t = 1e-6 * torch.randn((H, N, 1), device="cuda", generator=g, dtype=torch.float64)
+    t = spread * torch.randn((H, N, 1), device="cuda", generator=g, dtype=torch.float64)
     a, b = c0[0, i].double(), c0[0, j].double()
     X = (0.5 * (a + b) + t * (a - b)).float().contiguous()
     X[:, :64] = c0[0, 60]
