@@ -855,8 +855,9 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 // With more than KF_SPLIT centroids the operands are taken as two fp16 halves (f32_split: x to 2^-23) and a product as hi hi +
 // hi lo + lo hi, three 32x32x16 instructions that take a fifth of the time of the eight 32x32x2 fp32 ones, which bound the kernel.
 // A token is brought to 2^14 .. 2^15 by a power of two, the centroids of a head by one that follows from their largest norm.  The rule
-// (`split`): tokens of a block and the largest centroid finite and within 2^+-KF_EXP, no ||c||^2 more than 2^KF_SPREAD below the
-// largest (zeros aside).  Anything else, up to KF_SPLIT centroids, where splitting 32 tokens costs what it saves (2 x 1000 in 60: 69.5
+// (`split`): tokens of a block and the largest centroid finite and within 2^+-KF_EXP, some token of the block with |x|^2 at least KF_FAR of the
+// largest ||c||^2 (else most distances are near-ties, below), no near-ties in numbers in an iteration before.  Anything else, up to KF_SPLIT
+// centroids, where splitting 32 tokens costs what it saves (2 x 1000 in 60: 69.5
 // against 67.4 us per five iterations; one head of 700 in 24 54.8 against 53.0), and calls with little to do (kmeans_f32_split) go
 // through the fp32 instruction: contraction index in its natural order (lane half h supplies the elements of parity h), the
 // instruction adds its two products one after the other with a rounding behind each, so an accumulator is bit for bit the chain
@@ -865,29 +866,37 @@ __global__ __launch_bounds__(256, 5) void kmeans_settle_kernel(KmArgs a, KmIter 
 // be apart: D roundings of 2^-24 |x| |c| for the chain, which partial sums in one direction nearly reach, and twice that for the split
 // products (2^-21 for the parts and lo lo; their sums measured at less than the chain's: of differences of two distances 0.5e-6 of
 // |x|^2 + |c|^2 on 7.7 million tokens next to a border, 0.7e-6 by the chain).  The second term is for the rounding of the distances themselves.
+// Up to KF_TIES such tokens of a block are taken one at a time; a block with more goes through the fp32 instruction as well, and in the
+// iterations that follow through that alone (a word of flag_list per block).  Tokens that come twice as centroids, and tokens far from the
+// origin, are near-ties all of them.  Five iterations, us, fp32 instruction alone / one token at a time without a limit / now: 4 x 9601 in 500, D =
+// 128, a third of the tokens equal 575 / 1069 / 477, all equal 536 / 2497 / 422, one centroid 2^10 times as long 536 / 2487 / 388; 24 x 16,384, D = 64, a
+// third equal 1924 / 3626 / 1482.  (The update step is faster than it was with the first figure.)  With limits of 1, 2, 4 tokens: 6 x 12,000 in 1000,
+// D = 64, one token in twenty equal 846, 753, 690, offset of 30 deviations 671, 755, 1038; 4 x 9601 in 500, D = 128, the same, 575, 490, 445 and 444, 439, 439.
 //
 // The centroids need no LDS: they come from a chunk-major copy (`ct`, consecutive lanes read consecutive 16 bytes) with two
 // register buffers, the halves of a row block, each requested again as soon as it has been used.  What decides for few tokens is how
 // many SIMDs have work, so the row blocks of a token block are dealt out to up to four wavefronts (KF_NW / nc token blocks
 // per workgroup, nc wavefronts each, kmeans_f32_share) and the shares compared through LDS.  k-means of five iterations, D = 128,
-// fp32 instruction -> split: 4 x 9601 in 500 centroids 490 -> 281 us, 24 x 16,384 in
-// 500 3295 -> 1314, 6 x 12,000 in 1000 1349 -> 621.  One
+// fp32 instruction -> split: 4 x 9601 in 500 centroids 406 -> 304 us, 24 x 16,384 in
+// 500 2769 -> 1410, 6 x 12,000 in 1000 1021 -> 659.  One
 // token per thread with the centroids in LDS took 770 us per iteration for 4 heads of 9601 tokens against 100 and 500.
 static constexpr int KF_NW = 4;
 static constexpr int KF_SPLIT = 64;             // most centroids that go through the fp32 instruction whatever the values
-static constexpr int KF_EXP = 40, KF_SPREAD = 24;
-static constexpr long long KF_SPLIT_BLOCKS = 2048;      // fewest row blocks, over all token blocks
+static constexpr int KF_EXP = 40;
+static constexpr float KF_FAR = 0x1p-8f;
+static constexpr int KF_TIES64 = 2, KF_TIES128 = 4;
+static constexpr long long KF_SPLIT_BLOCKS = 1024;      // token blocks of 128 elements, over all heads
 static constexpr float KF_TIE = 7.152557373046875e-07f;  // 4 (1 + 2) 2^-24
 static constexpr int KF_CHAINS = 4;                     // centroids of a lane side by side
 
 template <int D, bool OBJ>
-__global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs a, KmIter it)
+__global__ __launch_bounds__(64 * KF_NW, D == 64 ? 4 : 2) void kmeans_assign_f32_kernel(KmArgs a, KmIter it)
 {
     constexpr int NB = D / 16;                  // float4 per register buffer: half of a lane's half row
     __shared__ float s_cn[SVG2_MAX_CLUSTERS];
     __shared__ float s_best[KF_NW][32], s_second[KF_NW][32];
     __shared__ int s_idx[KF_NW][32];
-    __shared__ unsigned s_most[KF_NW], s_least[KF_NW];
+    __shared__ unsigned s_most[KF_NW];
     const int side = (int)(gridDim.z - 1 - blockIdx.z);
     const KmSide S = side ? a.s[1] : a.s[0];
     int32_t *labels = side ? it.lab[1] : it.lab[0];
@@ -902,7 +911,7 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     const int n0 = wg_tok0 + wt * 32, n = n0 + col;
 
     float x[D / 2];                             // x[s]: element 2 s + half of the token
-    {
+    auto load_x = [&]() {
         const float4 *src = reinterpret_cast<const float4 *>(static_cast<const float *>(S.X) +
                                                              ((size_t)h * N + min(n, N - 1)) * D + half * (D / 2));
 #pragma unroll
@@ -914,7 +923,8 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             x[2 * k] = __uint_as_float(p[0]); x[D / 4 + 2 * k] = __uint_as_float(p[1]);
             x[2 * k + 1] = __uint_as_float(q[0]); x[D / 4 + 2 * k + 1] = __uint_as_float(q[1]);
         }
-    }
+    };
+    load_x();
     const char *ct = reinterpret_cast<const char *>(S.ct + (size_t)h * D * C);
     auto load_c = [&](float4 (&buf)[NB], int rb, int hf) {
         const unsigned off = 16u * (unsigned)(half * (D / 8) * C + min(rb * 32 + col, C - 1));     // (a head is 2 MB at most)
@@ -923,22 +933,17 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     };
     float4 bufA[NB], bufB[NB];                  // the two halves of a row block
     load_c(bufA, min(wc, nrb - 1), 0);
-    unsigned cn_most = 0, cn_least = ~0u;       // of ||c||^2, as bits; the least without zeros
+    unsigned cn_most = 0;                       // largest ||c||^2, as bits
     for (int c = tid; c < 32 * nrb; c += 64 * KF_NW) {
         const float v = c < C ? S.hcn[(size_t)h * C + c] : INFINITY;
         s_cn[c] = v;
-        if (c < C) {
-            cn_most = max(cn_most, __float_as_uint(v));
-            if (v != 0.f) cn_least = min(cn_least, __float_as_uint(v));
-        }
+        if (c < C) cn_most = max(cn_most, __float_as_uint(v));
     }
     const bool may_split = KM_SEL(a.split, side);
+    int32_t *ties = S.flag_list + (size_t)h * N + n0;          // of this token block: whether it had many in an iteration before
     if (may_split) {
-        for (int o = 32; o > 0; o >>= 1) {
-            cn_most = max(cn_most, (unsigned)__shfl_xor((int)cn_most, o));
-            cn_least = min(cn_least, (unsigned)__shfl_xor((int)cn_least, o));
-        }
-        if (lane == 0) { s_most[wave] = cn_most; s_least[wave] = cn_least; }
+        for (int o = 32; o > 0; o >>= 1) cn_most = max(cn_most, (unsigned)__shfl_xor((int)cn_most, o));
+        if (lane == 0) s_most[wave] = cn_most;
     }
     float x2 = 0.f;
     if ((OBJ && S.objective) || may_split) {
@@ -961,19 +966,36 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             if (dist < best) { best = dist; bidx = j; }
         }
     };
+    // the two lane halves, then the wavefronts of a token block, hold disjoint centroids of the same token
+    auto merge = [&](float ob, int oj, float os) {
+        second = fminf(fminf(second, os), fmaxf(best, ob));
+        if (ob < best || (ob == best && oj < bidx)) { best = ob; bidx = oj; }
+    };
+    auto merge_halves = [&]() {
+        merge(__shfl_xor(best, 32), __shfl_xor(bidx, 32), __shfl_xor(second, 32));
+        if (nc > 1 && half == 0) { s_best[wave][col] = best; s_idx[wave][col] = bidx; s_second[wave][col] = second; }
+    };
+    auto merge_waves = [&]() {
+        for (int w = 1; w < nc; ++w) {
+            const int o = wave - wc + (wc + w) % nc;
+            merge(s_best[o][col], s_idx[o][col], s_second[o][col]);
+        }
+    };
     // split operands or not (the comment above)
     float x_up = 1.f, c_up = 1.f;
-    bool split = false;
+    bool split = false, tied = false;
+    unsigned near = 0;
     if (may_split) {
-        cn_most = s_most[0]; cn_least = s_least[0];
+        cn_most = s_most[0];
 #pragma unroll
-        for (int w = 1; w < KF_NW; ++w) { cn_most = max(cn_most, s_most[w]); cn_least = min(cn_least, s_least[w]); }
+        for (int w = 1; w < KF_NW; ++w) cn_most = max(cn_most, s_most[w]);
         unsigned xb = 0;
 #pragma unroll
         for (int k = 0; k < D / 2; ++k) xb = max(xb, __float_as_uint(x[k]) & 0x7FFFFFFFu);
         xb = max(xb, (unsigned)__shfl_xor((int)xb, 32));
         const int xe = xb == 0 ? 0 : (int)(xb >> 23) - 127, ce = (int)(cn_most >> 23) - 127;
-        split = abs(ce) <= 2 * KF_EXP && (int)(cn_least >> 23) - 127 + KF_SPREAD >= ce && __all(abs(xe) <= KF_EXP);
+        tied = it.t > 0 && n0 < N && *ties != 0;
+        split = !tied && abs(ce) <= 2 * KF_EXP && __all(abs(xe) <= KF_EXP) && __any(x2 >= KF_FAR * __uint_as_float(cn_most));
         x_up = __uint_as_float((unsigned)(127 + 14 - xe) << 23);
         c_up = __uint_as_float((unsigned)(127 + 15 - ((ce + 2) >> 1)) << 23);       // |c| < 2^((ce + 1) / 2)
     }
@@ -1016,44 +1038,60 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
             compare(acc, rb, mul, std::true_type{});
             __builtin_amdgcn_sched_barrier(0);
         }
-    } else {
-        for (int rb = wc; rb < nrb; rb += nc) {
-            load_c(bufB, rb, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        merge_halves();
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc, 0, 0, 0);
+        for (int k = 0; k < D / 2; ++k) x[k] = 0.f;             // (read again below, not held over the loop)
+    }
+    if (may_split) {                                            // (the same for the workgroup)
+        if (nc > 1) __syncthreads();
+        if (split) {
+            merge_waves();
+            const float tie = KF_TIE * D * __builtin_amdgcn_sqrtf(x2) * __builtin_amdgcn_sqrtf(__uint_as_float(cn_most)) +
+                              0x1p-22f * (fabsf(best) + fabsf(second));
+            near = (unsigned)__ballot(n < N && !(second - best > tie));
+            if (__popc(near) > (D == 64 ? KF_TIES64 : KF_TIES128)) {
+                split = false;
+                tied = true;
+                best = second = INFINITY;
+                bidx = 0;
+                load_x();
+                load_c(bufA, min(wc, nrb - 1), 0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            load_c(bufA, min(rb + nc, nrb - 1), 0);     // (past the last row block: a valid one, not used)
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            compare(acc, rb, -2.f, std::false_type{});
         }
+        if (lane == 0 && wc == 0 && n0 < N) *ties = tied;
     }
-    // the two lane halves, then the wavefronts of a token block, hold disjoint centroids of the same token
-    auto merge = [&](float ob, int oj, float os) {
-        second = fminf(fminf(second, os), fmaxf(best, ob));
-        if (ob < best || (ob == best && oj < bidx)) { best = ob; bidx = oj; }
-    };
-    merge(__shfl_xor(best, 32), __shfl_xor(bidx, 32), __shfl_xor(second, 32));
-    if (nc > 1) {
-        if (half == 0) { s_best[wave][col] = best; s_idx[wave][col] = bidx; s_second[wave][col] = second; }
-        __syncthreads();
-        if (wc != 0) return;
-        for (int w = 1; w < nc; ++w) merge(s_best[wave + w][col], s_idx[wave + w][col], s_second[wave + w][col]);
+    if (nc > 1 && may_split ? __syncthreads_or(!split) : !split) {
+        if (!split) {
+            for (int rb = wc; rb < nrb; rb += nc) {
+                load_c(bufB, rb, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].x, x[4 * i], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].y, x[4 * i + 1], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].z, x[4 * i + 2], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufA[i].w, x[4 * i + 3], acc, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                load_c(bufA, min(rb + nc, nrb - 1), 0);     // (past the last row block: a valid one, not used)
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].x, x[4 * (NB + i)], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].y, x[4 * (NB + i) + 1], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].z, x[4 * (NB + i) + 2], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bufB[i].w, x[4 * (NB + i) + 3], acc, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                compare(acc, rb, -2.f, std::false_type{});
+            }
+            merge_halves();
+        }
+        if (nc > 1) __syncthreads();
+        if (!split) merge_waves();
     }
+    if (wc != 0) return;
     // elements 8 q .. 8 q + 7 of the chain of fmaf for centroid j
     auto chain8 = [&](float &dot, int q, int j, const float4 &x0, const float4 &x1) {
         const float4 ev = *reinterpret_cast<const float4 *>(ct + 16 * ((size_t)q * C + j));
@@ -1066,9 +1104,6 @@ __global__ __launch_bounds__(64 * KF_NW, 2) void kmeans_assign_f32_kernel(KmArgs
     // Near-ties of the split products go by the chain of fmaf, as all tokens do without them: a token at a time, KF_CHAINS centroids per
     // lane (one after the other, its loads all requested at once: 6 x 12,000 in 1000 721 instead of 621 us, 1 x 12,000 287 instead of 222).
     if (split) {
-        const float tie = KF_TIE * D * __builtin_amdgcn_sqrtf(x2) * __builtin_amdgcn_sqrtf(__uint_as_float(cn_most)) +
-                          0x1p-22f * (fabsf(best) + fabsf(second));
-        unsigned near = (unsigned)__ballot(n < N && !(second - best > tie));
         for (; near; near &= near - 1) {
             const int c32 = __builtin_ctz(near);
             const float *xr = static_cast<const float *>(S.X) + ((size_t)h * N + n0 + c32) * D;     // (uniform)
@@ -2056,28 +2091,33 @@ int device_cu_count(int *ncu)
 }
 
 // Wavefronts that share a token block of the fp32 assign step: every one of them loads (and splits) the tokens, so a share has at
-// least 16 row blocks where there are 512 token blocks, whatever their number from 4096 on, and as few as one with fewer
+// least 8 row blocks from 512 wavefronts on, and from 4096 wavefronts on none is shared further; as few as one row block with fewer
 // (k-means of five iterations with one, two, four wavefronts, us: 4 x 9601 in 500 288, 275, 290; in 100 192, 203, 201; 6 x 12,000 in
 // 1000 653, 602, 625; 24 x 16,384 in 500 1327, 1489, 1910; 3 x 3000 in 300 131, 106, 118; 1 x 12,000 in 1000 300, 211, 206, all D = 128;
 // 1 x 4096 in 200, D = 64 84, 75, 69).  Without splitting a share has at least four row blocks where the token blocks alone are enough
-// for two wavefronts per SIMD, and as few as one otherwise.  Splitting pays from two row blocks per SIMD on (1 x 4096 in 200, D = 64, with
-// fewer: 75 instead of 69 us).
-// The grid has 64 KF_NW threads per 32 (KF_NW / nc) tokens of a head, 2 nc N, and one grid dimension takes less than 2^32.
-static constexpr bool kmeans_f32_split(int H, int N, int C)
+// for two wavefronts per SIMD, and as few as one otherwise.  Splitting pays from one token block of 128 elements per SIMD
+// on (fp32 instruction / split, D = 128: 4 x 9601 in 100 224 / 195, in 500 406 / 304, 6 x 12,000 in 1000 1021 / 659; below: 1 x 12,000 in 1000 270 / 256
+// and 291 / 397 with one token in twenty equal, 1 x 9601 in 500 185 / 193, 4 x 4000 in 300 147 / 150; D = 64: 6 x 12,000 in 1000 583 / 479, 24 x 16,384
+// in 500 1443 / 870; below: 4 x 9601 in 500 263 / 246 and 268 / 363, 1 x 12,000 in 1000 186 / 251).
+// The grid has 64 KF_NW threads per 32 (KF_NW / nc) tokens of a head, 2 nc N, and one grid dimension takes less than 2^32: 2 N with one
+// wavefront per block, and what is shared is 4096 wavefronts at most.
+static constexpr bool kmeans_f32_split(int H, int N, int C, int d)
 {
-    return C > KF_SPLIT && H * (((long long)N + 31) / 32) * ((C + 31) / 32) >= KF_SPLIT_BLOCKS;
+    return C > KF_SPLIT && H * (((long long)N + 31) / 32) * d >= KF_SPLIT_BLOCKS * 128;
 }
-static constexpr int kmeans_f32_share(int H, int N, int C)
+static constexpr int kmeans_f32_share(int H, int N, int C, int d)
 {
     const int nrb = (C + 31) / 32;
     const long long blocks = H * (((long long)N + 31) / 32);
     int nc = 1;
-    while (nc < KF_NW && 2 * nc <= nrb && 2ll * (2 * nc) * (N + 128ll) < 1ll << 32 &&
-           (!kmeans_f32_split(H, N, C) ? nrb > 4 * nc || blocks * nc < 2048 : blocks * nc < 512 || (nrb >= 16 * nc && blocks * nc < 4096)))
+    while (nc < KF_NW && 2 * nc <= nrb &&
+           (!kmeans_f32_split(H, N, C, d) ? nrb > 4 * nc || blocks * nc < 2048 : blocks * nc < 512 || (nrb >= 16 * nc && blocks * nc < 4096)))
         nc *= 2;
     return nc;
 }
-static_assert(kmeans_f32_share(1, 1000, 4096) == 4 && kmeans_f32_share(1, 1 << 30, 4096) == 1, "the grid of the fp32 assign step stays below 2^32 threads");
+static_assert(kmeans_f32_share(1, 1000, 4096, 64) == 4 && kmeans_f32_share(1, 32767, 4096, 128) == 4 && kmeans_f32_share(1, 32768, 4096, 128) == 4 &&
+              kmeans_f32_share(1, 65537, 4096, 128) == 2 && kmeans_f32_share(1, 131072, 4096, 128) == 1 && kmeans_f32_share(1, 131072, 64, 64) == 1 &&
+              kmeans_f32_share(1, 1 << 30, 4096, 64) == 1, "the grid of the fp32 assign step stays below 2^32 threads");
 
 template <typename T, int D, bool BF16>
 static int kmeans_run(KmArgs a, hipStream_t st)
@@ -2096,8 +2136,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         a.gc[s] = kmeans_update_group(H, a.s[s].C, call);
         ngroups += cdiv(a.s[s].C, a.gc[s]);
         any_few |= !BF16 && kmeans_f32_few(H, N, a.s[s].C);
-        a.split[s] = kmeans_f32_split(H, N, a.s[s].C);
-        a.nc[s] = kmeans_f32_share(H, N, a.s[s].C);
+        a.split[s] = kmeans_f32_split(H, N, a.s[s].C, D);
+        a.nc[s] = kmeans_f32_share(H, N, a.s[s].C, D);
         ncmax = std::max(ncmax, a.nc[s]);
         pmax = std::max(pmax, a.s[s].max_pieces);
         if (a.s[s].objective) {

@@ -284,13 +284,14 @@ def test_kmeans_f32_few_centroids(svg2, oracle, d, H, N, C):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("H,N,C,change", [
     (2, 300, 64, ""), (40, 4000, 65, ""), (1, 97, 97, ""), (13, 2000, 129, ""), (1, 12000, 1000, ""), (6, 6001, 513, ""), (9, 2400, 96, ""),
+    (64, 480, 97, ""), (64, 481, 97, ""), (128, 480, 97, ""), (128, 481, 97, ""),
     # both sides of what sends tokens through the fp32 instruction: ranges, one token or centroid out of range
-    (40, 500, 100, "all+39"), (40, 500, 100, "all+41"), (40, 500, 100, "all-39"), (40, 500, 100, "all-41"), (40, 500, 100, "token+41"),
-    (40, 500, 100, "token-41"), (40, 500, 100, "token0"), (40, 500, 100, "centroid-11"), (40, 500, 100, "centroid-13"), (40, 500, 100, "centroid0"),
-    (40, 500, 100, "inf"), (40, 500, 100, "nan")])
+    (140, 500, 100, "all+39"), (140, 500, 100, "all+41"), (140, 500, 100, "all-39"), (140, 500, 100, "all-41"), (140, 500, 100, "token+41"),
+    (140, 500, 100, "token-41"), (140, 500, 100, "token0"), (140, 500, 100, "centroid-11"), (140, 500, 100, "centroid-13"), (140, 500, 100, "centroid0"),
+    (140, 500, 100, "inf"), (140, 500, 100, "nan")])
 def test_kmeans_f32_split_operands(svg2, d, H, N, C, change):
-    """Labels of one fp32 assign step against float64, operands in two halves and not (40 x 500 in 100 is 2560 row blocks, 2048 is
-    the fewest): a label that differs is a near-tie, its distance larger than the smallest by no more than the roundings of two chains, (2 d + 8) 2^-24 (|x|^2 + |c|^2) and |c| the largest."""
+    """Labels of one fp32 assign step against float64, operands in two halves and not (140 x 500 is 2240 token blocks, 1024 of
+    128 elements are split): a label that differs is a near-tie, its distance larger than the smallest by no more than the roundings of two chains, (2 d + 8) 2^-24 (|x|^2 + |c|^2) and |c| the largest."""
     g = torch.Generator(device="cuda").manual_seed(C + N)
     X = (2.0 * torch.randn((H, C, d), device="cuda", generator=g))[:, torch.randint(C, (N,), device="cuda", generator=g)]
     X = X + torch.randn((H, N, d), device="cuda", generator=g)
@@ -349,7 +350,7 @@ def test_kmeans_f32_split_operands_where_the_chain_errs_most(svg2, d):
     exact = sq(cj) - 2.0 * dot_j - (sq(cb) - 2.0 * dot_b)
     assert exact > 0.8 * off and (sq(cj) - 2.0 * chain_j) - (sq(cb) - 2.0 * chain_b) < -0.05 * off
     g = torch.Generator(device="cuda").manual_seed(d)
-    H, N, C = 70, 500, 100
+    H, N, C = 140, 500, 100
     X = 0.25 * torch.randn((H, N, d), device="cuda", generator=g)
     c0 = 0.25 * torch.randn((H, C, d), device="cuda", generator=g)
     X[:, 70, : d - 1], X[:, 70, d - 1] = 1.0, 0.0
@@ -385,7 +386,7 @@ def test_kmeans_f32_split_operands_leave_near_ties_to_the_fmaf_chain(svg2, d, C,
 
 
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("H,N,C", [(10, 1000, 500), (70, 500, 100)])
+@pytest.mark.parametrize("H,N,C", [(70, 1000, 500), (140, 500, 100)])
 def test_kmeans_f32_objective_of_split_operands(svg2, d, H, N, C):
     """Tokens near their centroids: the heads together, which are split, have the objective that each has alone, too little to split.  The
     same N terms are added in 32s and then in any order, at most 5 + N / 32 roundings of 2^-24 of the sum of their sizes, each at most the squared
@@ -396,11 +397,41 @@ def test_kmeans_f32_objective_of_split_operands(svg2, d, H, N, C):
     X = torch.gather(c0, 1, j[..., None].expand(H, N, d))
     X = (X + 1e-3 * torch.randn((H, N, d), device="cuda", generator=g)).contiguous()
     obj = svg2.svg2_kmeans(X, c0, 1, want_objective=True).objective[:, 0].double()
-    for h in range(H):
+    for h in range(0, H, 7):
         alone = svg2.svg2_kmeans(X[h:h + 1].contiguous(), c0[h:h + 1].contiguous(), 1, want_objective=True).objective[0, 0].double()
         x2, d2 = (X[h].double() ** 2).sum(), ((X[h].double() - c0[h, j[h]].double()) ** 2).sum()
         size = d2 + (2 * d + 8) * 2.0 ** -24 * 2.01 * x2
         assert abs(obj[h] - alone) <= (5 + N / 32) * 2.0 ** -24 * size, ((obj[h] - alone) / x2).item()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N,C", [(40, 1999, 100), (33, 1999, 700), (65, 997, 500), (6, 6001, 1000), (11, 6001, 1000)])
+def test_kmeans_f32_split_operands_with_many_near_ties(svg2, d, H, N, C):
+    """Token blocks with none, a few (settled one by one) and many tokens whose centroid is there twice, and a block of such tokens alone:
+    the heads together, which are split, get the labels that the tokens have in small groups, too little to split; the third iteration, where
+    blocks that had many go straight through the fp32 instruction, those of a first one from the same centroids.  One, two and four wavefronts to
+    a token block, blocks of either kind in one workgroup."""
+    g = torch.Generator(device="cuda").manual_seed(N + C)
+    c0 = 1.5 * torch.randn((H, C, d), device="cuda", generator=g)
+    j = torch.randint(C, (H, N), device="cuda", generator=g)
+    X = torch.gather(c0, 1, j[..., None].expand(H, N, d)) + torch.randn((H, N, d), device="cuda", generator=g)
+    equal = torch.rand((N,), device="cuda", generator=g) < 0.12 * (torch.arange(N, device="cuda") // 32 % 4)
+    equal[64:96] = True
+    X[:, equal] = c0[:, 9:10]
+    c0[:, 77] = c0[:, 9]
+    X = X.contiguous()
+    res = svg2.svg2_kmeans(X, c0, 3)
+    one = svg2.svg2_kmeans(X, c0, 1)
+    assert bool((one.labels[:, equal] == 9).all())
+    n = 256                                             # 32 token blocks at most
+    for h in range(3):
+        for lo in range(0, N - n, n):                   # (C <= N is asked for)
+            part = torch.cat([X[h, lo:lo + n], X[h, :max(C - n, 0)]])[None].contiguous()
+            alone = svg2.svg2_kmeans(part, c0[h:h + 1].contiguous(), 1).labels
+            assert torch.equal(alone[0, :n], one.labels[h, lo:lo + n])
+    prev = svg2.svg2_kmeans(X, c0, 2).centroids
+    again = svg2.svg2_kmeans(X, prev, 1).labels
+    assert torch.equal(again, res.labels)
 
 
 @pytest.mark.parametrize("Cq,Ck", [(1, 70), (70, 1)])
