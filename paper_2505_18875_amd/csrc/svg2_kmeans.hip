@@ -1462,13 +1462,16 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
 //   24 x 30,000, 500: 823 / 762      2 x 30,000, 300: 295 / 250      4 x 20,000, D = 64, 1000: 369 / 283      4 x 9601, fp32, 500: 540 / 488
 // Beyond KU_N tokens the labels cost as much as is gained (8 x 37,800, 500: 523 / 499; 1 x 75,600: 341 / 357; 1 x 118,800, 64: 237 / 439).
 // All tokens are summed this way (mode 1) up to KU_FULL_N: a workgroup then has all rows of its clusters to add, about 100 rows per us, and of
-// a cluster that holds most of a long head the pieces side by side are faster.  Two iterations, sorted in the first / not at all:
-// 4 x 6000, 200 clusters: 82 / 69; 24 x 8000, 100: 112 / 103; all tokens in one cluster: 12 x 8000, 81 / 133, 12 x 12,000, 99 / 187.
-// bf16 heads of more than KU_FULL_N tokens: the assign step lists the tokens that moved (KU_LISTS, kmeans_update_lists).  With four wavefronts in place of eight, so that all workgroups of 24 heads of 16,384 tokens run at once, a late iteration
+// a cluster that holds most of a long head the pieces side by side are faster.  Two iterations, bf16, D = 128, sorted in the first / not at
+// all: 12 heads x 4096 tokens, 100 clusters: 97 / 70 us, all tokens in one cluster 85 / 93; 12 x 5000 88 / 69, in one 81 / 104; 12 x 8000 97 / 82, in one 84 / 135.
+// The same holds for the tokens that move at once between two clusters: a third of them in the second of two iterations, fp32, D = 128,
+// sorted / by labels 1 x 30,000 in 100 172 / 250, 12 x 12,000 in 100 254 / 277, 24 x 16,384 in 500 1406 / 1181.
+// bf16 heads of more than KU_LISTS_N tokens: the assign step lists the tokens that moved (KU_LISTS, kmeans_update_lists).  With four
+// wavefronts in place of eight, so that all workgroups of 24 heads of 16,384 tokens run at once, a late iteration
 // took 21 instead of 26 us and the first of them 97 instead of 60; with 32 clusters to a workgroup and several workgroups for the tokens
 // of few clusters 34 and 88.
 // As few workgroups as give every CU one read the labels (three times as many: 24 x 16,384, 500 clusters: 544; 6 x 11,000, 150: 232).
-static constexpr int KU_N = 32768, KU_FULL_N = 8192;
+static constexpr int KU_N = 32768, KU_FULL_N = 4096, KU_LISTS_N = 8192;
 static constexpr int KU_NW = 8;                 // wavefronts
 static constexpr int KU_G = 16;                 // most clusters of a workgroup
 static constexpr int KU_CAP = 448;              // entries of a wavefront's list (three workgroups fit a CU)
@@ -1700,7 +1703,7 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
 }
 
 // Whether the assign step of bf16 heads lists the tokens that moved.  The update kernel then reads a few per cent of what the labels of two iterations are; the assign step pays for
-// it with a comparison per token, which up to KU_FULL_N tokens is what is gained (24 heads x 6000, 200 clusters, five iterations: 240
+// it with a comparison per token, which up to KU_LISTS_N tokens is what is gained (24 heads x 6000, 200 clusters, five iterations: 240
 // us by the labels, 247 by lists; 24 x 8000, 500: 349 / 351; 40 x 9000, D = 64, 100: 247 / 241).
 //   24 x 16,384, D = 128, 100 / 500 clusters: 339 / 321, 505 / 491      2 x 30,000, 300: 261 / 235      24 x 30,000, 100, Zipf sizes: 520 / 480
 // Beyond KU_N tokens, where the labels are too much for every workgroup to read, it is the sorted order that they replace.  A
@@ -1710,15 +1713,18 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
 static constexpr int KU_LISTS_SIZE = 64;        // tokens per cluster, beyond KU_N tokens
 static bool kmeans_update_lists(int H, int N, int call, int cmin)
 {
-    return !kmeans_update_small(H, N, call) && N > KU_FULL_N && (N <= KU_N || N <= (long long)KU_LISTS_SIZE * cmin);
+    return !kmeans_update_small(H, N, call) && N > KU_LISTS_N && (N <= KU_N || N <= (long long)KU_LISTS_SIZE * cmin);
 }
 
 // Clusters of a workgroup of the update kernel: as many as leave a workgroup per CU over all heads and sides, and no more than a sixteenth
-// of the side's (few large clusters: their tokens are shared out over more CUs).
+// of the side's (few large clusters: their tokens are shared out over more CUs) unless there are four workgroups per CU without that.
+// (With the sixteenth always, many heads of few clusters were a workgroup per cluster, each reading all labels.  Five iterations, sorted / by
+// a sixteenth / now, fp32, D = 64: 1000 x 256 in 20 341 / 677 / 240 us, 5000 x 64 in 8 683 / 1173 / 321, 100 x 3000 in 31 253 / 278 / 229; bf16, D = 128:
+// 1000 x 256 in 40 566 / 918 / 428, 100 x 3000 in 31 275 / 310 / 255, 200 x 4096 in 16 459 / 461 / 408.)
 static int kmeans_update_group(int H, int C, int call)
 {
     int g = KU_G;
-    while (g > 1 && ((long long)call * H < 256ll * g || 16 * g > C)) g >>= 1;
+    while (g > 1 && ((long long)call * H < 256ll * g || (16 * g > C && (long long)H * cdiv(C, g) < 1024))) g >>= 1;
     return g;
 }
 

@@ -503,12 +503,15 @@ def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
 
 
 @pytest.mark.parametrize("dtype,d,H,N,C", [
-    # straight from the labels: all tokens summed that way (up to 8192) or only those that moved (up to 32,768), and one more
+    # straight from the labels: all tokens summed that way (up to 4096) or only those that moved (up to 32,768), and one more
+    ("bf16", 128, 1, 4096, 520), ("bf16", 128, 1, 4097, 520), ("f32", 64, 1, 4096, 520), ("f32", 64, 1, 4097, 520),
     ("bf16", 128, 1, 8192, 520), ("bf16", 128, 1, 8193, 520), ("f32", 64, 1, 32768, 70), ("bf16", 64, 1, 32769, 70),
     # one cluster to a workgroup, whose lists overflow again and again; a last workgroup with one cluster, with all its clusters
     ("bf16", 64, 1, 8192, 2), ("f32", 128, 2, 8129, 3), ("bf16", 64, 12, 4200, 257), ("f32", 128, 12, 4097, 256),
     # a last group of labels with one token, wavefronts without tokens; many heads
-    ("bf16", 128, 40, 2049, 77), ("f32", 64, 700, 65, 20), ("bf16", 128, 2, 20481, 40)])
+    ("bf16", 128, 40, 2049, 77), ("f32", 64, 700, 65, 20), ("bf16", 128, 2, 20481, 40),
+    # few clusters of many heads, more than a sixteenth of them to a workgroup
+    ("f32", 128, 1030, 64, 9), ("bf16", 128, 520, 130, 40), ("bf16", 64, 100, 3000, 31)])
 def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
     r = np.random.default_rng(9900 + N + C)
     centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
