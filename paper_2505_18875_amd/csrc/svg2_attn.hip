@@ -891,7 +891,7 @@ __device__ __forceinline__ void f32_mfma3(const u32x4 (&x)[3], const u32x4 (&y)[
 }
 
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
+__global__ __launch_bounds__(64 * NW, D == 64 && NW == F32_NW ? 4 : 2) void attn_f32_kernel(
     const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, int H, int N, int Cq, int Ck,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ perm_q, const int32_t *__restrict__ perm_k,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ tile_base, const int32_t *__restrict__ order, int max_tiles,
@@ -934,8 +934,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
     // split Q in LDS behind the wavefronts' K blocks: lane's part of step t is elements 16 t + 8 half .. of its row
     u32x4 *s_q = reinterpret_cast<u32x4 *>(s_o + (size_t)NW * 32 * D);
     bool split = false;
-    if constexpr (NW == F32_NW) {
-      if (range) {
+    if (NW == F32_NW && range) {
         float q[D / 2];
 #pragma unroll
         for (int t = 0; t < D / 16; ++t) {
@@ -949,17 +948,18 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void attn_f32_kernel(
 #pragma unroll
         for (int k = 0; k < D / 2; ++k) f32_range(__float_as_uint(q[k]), most, least);
         split = __all(most <= F32_MOST && least <= 0u - F32_LEAST) && scale_log2 <= F32_SCALE;
+        if (split) {
 #pragma unroll
-        for (int t = 0; t < D / 16; ++t)
-            if (t % NW == wave) {               // (wave-uniform; every wavefront holds the same row parts)
-                u32x4 part[3];
+            for (int t = 0; t < D / 16; ++t)
+                if (t % NW == wave) {           // (wave-uniform; every wavefront holds the same row parts)
+                    u32x4 part[3];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) f32_split3(q[8 * t + 2 * e], q[8 * t + 2 * e + 1], part, e);
+                    for (int e = 0; e < 4; ++e) f32_split3(q[8 * t + 2 * e], q[8 * t + 2 * e + 1], part, e);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) s_q[(3 * t + i) * 64 + lane] = part[i];
-            }
-        __syncthreads();
-      }
+                    for (int i = 0; i < 3; ++i) s_q[(3 * t + i) * 64 + lane] = part[i];
+                }
+            __syncthreads();
+        }
     }
     f32x16 oacc[DVB];
 #pragma unroll
@@ -1245,9 +1245,10 @@ static size_t attn_lds_bytes(int d, int Ck)
            (size_t)std::min(Ck + 1, ATT_RUN_LDS) * sizeof(int2);
 }
 
-// The ranges that let a head's operands be split: none for short heads, where looking at K and V costs more than it saves and the
-// LDS that split Q takes leaves a CU fewer work items (1000 heads of 256 tokens, D = 128: 537 instead of 430 us; 5000 of 16, D = 64: 134
-// instead of 55; 200 of 600 340 instead of 457).  Longer heads have eight wavefronts per work item, which share a CU with no other at D = 128.
+// The ranges that let a head's operands be split: none for short heads, where looking at K and V costs more than it saves (with operands in
+// two fp16 halves, which were faster yet: 1000 heads of 256 tokens, D = 128: 537 instead of 430 us; 5000 of 16, D = 64: 134 instead of 55); 200 of 600,
+// fp32 instruction / split, D = 64 221 / 190, D = 128 459 / 431 us, and 247 and 513 where an infinity is found in every head.  Heads
+// with a range have eight wavefronts per work item (attn_f32_nw), which share a CU with no other at D = 128.
 static unsigned *attn_range_of(const AttnWs &a, int N) { return N > F32_SHORT ? a.range : nullptr; }
 
 // (split Q lies behind the K blocks; the padding of the final sum's rows is not there yet)
@@ -1331,6 +1332,7 @@ int attn_main_launch(const void *Qp, const void *Kp, const void *Vp, int dtype, 
         float *o = static_cast<float *>(O);
         static_assert(F32_BM == attn_bm(SVG2_F32), "the plan cuts query clusters into the tiles of this kernel");
         const int nw = attn_f32_nw(H, N);
+        static_assert(F32_SHORT >= 32 * F32_NW / 2, "a head with a range (attn_range_of) has eight wavefronts per work item");
         auto kern = d == 128 ? (nw == 1   ? attn_f32_kernel<128, 1>
                                 : nw == 2 ? attn_f32_kernel<128, 2>
                                 : nw == 4 ? attn_f32_kernel<128, 4>
