@@ -974,12 +974,14 @@ def test_attention_f32_wavefronts_of_a_work_item(svg2, d, H, N):
 
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("N,runs,change", [
-    (1, 1, ""), (31, 3, ""), (33, 2, ""), (65, 60, ""), (257, 256, ""), (700, 650, ""), (1300, 40, ""),
-    # both sides of what sends a head through the fp32 instruction: range of K and V, rows and columns far below the largest
+    (1, 1, ""), (31, 3, ""), (33, 2, ""), (65, 60, ""), (257, 256, ""), (512, 40, ""), (513, 40, ""), (700, 650, ""), (1300, 40, ""),
+    (600, 9, "k+30"), (600, 9, "k-30"), (600, 9, "v+37"), (600, 9, "v-30"), (600, 9, "krow-20"), (600, 9, "vrow-20"), (600, 9, "vcol-20"),
+    (600, 9, "zero"), (600, 9, "vinf"), (600, 9, "flat"),
+    # heads of up to 512 tokens: fp32 instruction
     (300, 9, "k+39"), (300, 9, "k+41"), (300, 9, "k-42"), (300, 9, "v+37"), (300, 9, "v+41"), (300, 9, "v-42"), (300, 9, "krow-11"),
     (300, 9, "krow-20"), (300, 9, "vrow-11"), (300, 9, "vrow-20"), (300, 9, "vcol-20"), (300, 9, "zero"), (300, 9, "vinf"), (300, 9, "flat")])
 def test_attention_f32_split_operands(svg2, oracle, d, N, runs, change):
-    """fp32 attention with operands in two halves, and what it leaves to the fp32 instruction: runs of one key and of none, blocks
+    """fp32 attention with operands in parts, and what it leaves to the fp32 instruction: runs of one key and of none, blocks
     of 32 keys with a remainder.  Bound per element: scores are off by at most d + 8 roundings of 2^-24 of the sum of |q k| (either kind of product),
     which moves a weight by as much, and 64 more for exp2, the sums over keys and the division."""
     r = np.random.default_rng(77 + N + runs)
@@ -1024,6 +1026,69 @@ def test_attention_f32_split_operands(svg2, oracle, d, N, runs, change):
     if change == "vinf":
         assert np.all(np.isinf(O[:, 4]) | np.isnan(O[:, 4])) and fin.sum() == N * (d - 1)
     assert np.all(np.abs(to_np(res.lse[0]) - lse) <= 2 * dS + 4 * eps * np.abs(lse))
+
+
+_UP, _DOWN = float(np.nextafter(np.float32(2.0 ** 40), np.float32(np.inf))), float(np.nextafter(np.float32(2.0 ** -60), np.float32(0)))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("N,where,value,split", [(1001, "", 0.0, True), (512, "", 0.0, False), (513, "", 0.0, True)] + [
+    (N, where, value, split) for N in (600, 1001) for where in "QKV"
+    for value, split in [(0.0, True), (2.0 ** 40, True), (_UP, False), (-(2.0 ** -60), True), (-_DOWN, False), (1e-45, False), (np.inf, False),
+                         (np.nan, False)]] + [(600, "scale", 2.0 ** 39, True), (600, "scale", 2.0 ** 40, False)])
+def test_attention_f32_rule_of_split_operands(svg2, oracle, d, N, where, value, split):
+    """Both sides of every limit of the rule that lets operands be split (of K and V for the head, of Q for a tile of 32 rows), permuted
+    and gather-free.  An infinity in the K row of a cluster that nothing selects sends the head through the fp32 instruction and changes nothing
+    else, so rows whose result stays the same to the bit were not split, and rows that were are not all the same.  Bounds per element as
+    in test_attention_f32_split_operands."""
+    r = np.random.default_rng(N + d)
+    runs = 9
+    Q, K, V = (r.standard_normal((N, d)).astype(np.float32) * np.float32(f) for f in (3, 2, 1))
+    scale = 1.0 / float(np.sqrt(d))
+    if where == "scale":
+        Q, K, scale = np.ldexp(Q, -20), np.ldexp(K, -19), value     # scores of deviation up to 6 sqrt(d)
+    elif where:
+        X = {"Q": Q, "K": K, "V": V}[where]
+        if np.isfinite(value) and abs(value) > 1.0 and where != "V":
+            (K if where == "Q" else Q)[:, 3] *= np.float32(2.0 ** -40)
+        X[5, 3] = value
+    lk = r.integers(0, runs, size=N).astype(np.int32)
+    lk[N - 1] = runs                                                # the cluster that nothing selects
+    lk[5] = 2
+    pk = oracle.permute(lk, runs + 1)
+    one = lambda a: torch.from_numpy(np.asarray(a)[None].astype(np.int32)).cuda()  # noqa: E731
+    lists = (one([0, N]), one(pk.offsets), one([0, runs]), one(np.arange(runs + 1)))
+    up = lambda a: torch.from_numpy(a[None]).cuda()  # noqa: E731
+    got = []
+    for force in (False, True):
+        Kf = K.copy()
+        if force:
+            Kf[N - 1] = np.inf
+        res = svg2.svg2_sparse_attn(up(Q), up(Kf[pk.perm]), up(V[pk.perm]), *lists, scale=scale, want_lse=True)
+        gf = svg2.svg2_sparse_attn_gather_free(up(Q), up(Kf), up(V), *lists, one(np.arange(N)), one(pk.perm), scale=scale, want_lse=True)
+        torch.cuda.synchronize()
+        assert torch.equal(gf.O.view(torch.int32), res.O.view(torch.int32)) and torch.equal(gf.lse.view(torch.int32), res.lse.view(torch.int32))
+        got.append(res)
+    same = (got[0].O[0].view(torch.int32) == got[1].O[0].view(torch.int32)).all(1).cpu().numpy()
+    tile = np.arange(N) < (32 if where == "Q" else N)               # the rows that the value is about
+    assert same[tile].all() if not split else not same[tile].all()
+    if not tile.all():
+        assert not same[~tile].all()
+    q, k, v = (torch.from_numpy(a).cuda().double() for a in (Q, K[:-1], V[:-1]))
+    S = q @ k.T.contiguous() * scale
+    lse = torch.logsumexp(S, 1)
+    P = torch.exp(S - lse[:, None])
+    eps = 2.0 ** -24
+    dS = (d + 8) * eps * (q.abs() @ k.abs().T.contiguous()).max(1).values * scale + 64 * eps
+    O_ref, bound = P @ v, 2.0 * dS[:, None] * (P @ v.abs()) + 1e-300
+    for res in got:
+        fin = torch.isfinite(O_ref) & torch.isfinite(bound)
+        # (an infinite or undefined value is in one row of Q, in all rows by way of K, in one column of V)
+        assert int(fin.sum()) == (N * d if np.isfinite(value) else {"Q": (N - 1) * d, "K": 0, "V": N * (d - 1)}[where])
+        assert bool(((res.O[0].double() - O_ref).abs() <= bound)[fin].all())
+        assert not bool(torch.isfinite(res.O[0])[~fin].any()) or where == "K"
+        ok = torch.isfinite(lse)
+        assert bool(((res.lse[0].double() - lse).abs() <= 2 * dS + 4 * eps * lse.abs())[ok].all())
 
 
 @pytest.mark.parametrize("d", [128, 64])
