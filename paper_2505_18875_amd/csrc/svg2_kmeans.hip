@@ -1464,14 +1464,21 @@ __global__ __launch_bounds__(64 * NW) void kmeans_update_small_kernel(KmArgs a, 
 // All tokens are summed this way (mode 1) up to KU_FULL_N: a workgroup then has all rows of its clusters to add, about 100 rows per us, and of
 // a cluster that holds most of a long head the pieces side by side are faster.  Two iterations, bf16, D = 128, sorted in the first / not at
 // all: 12 heads x 4096 tokens, 100 clusters: 97 / 70 us, all tokens in one cluster 85 / 93; 12 x 5000 88 / 69, in one 81 / 104; 12 x 8000 97 / 82, in one 84 / 135.
-// The same holds for the tokens that move at once between two clusters: a third of them in the second of two iterations, fp32, D = 128,
-// sorted / by labels 1 x 30,000 in 100 172 / 250, 12 x 12,000 in 100 254 / 277, 24 x 16,384 in 500 1406 / 1181.
+// The same holds for the many tokens that move in the second iteration, and with clusters large enough for those of all later ones.  So the
+// second iteration goes by the sorted order from KU_SECOND_SIZE tokens per cluster on (the first one has left its order, beyond KU_FULL_N), every
+// iteration from KU_SIZE on.  D = 128, centroids drawn from the tokens, cluster sizes alike / Zipf; sorted, by the labels, now:
+//   two iterations: bf16 4 x 17,000 in 8 122, 125, 121 / 128, 168, 125; 24 x 32,000 in 16 215, 232, 216 / 223, 302, 224; fp32 1 x 32,000 in 32
+//   120, 153, 120 / 118, 120, 118; 4 x 32,000 in 4 141, 193, 139 / 145, 270, 145
+//   five: bf16 24 x 32,000 in 16 483, 439, 422 / 495, 540, 464; fp32 4 x 32,000 in 16 325, 340, 304 / 349, 419, 339, in 8 308, 396, 307 / 325, 418, 326
+// What remains is tokens that move at once between two of many clusters: a third of them in the second of two iterations, fp32, D = 128,
+// sorted / by labels 12 x 12,000 in 100 254 / 277, 24 x 16,384 in 500 1406 / 1181.
 // bf16 heads of more than KU_LISTS_N tokens: the assign step lists the tokens that moved (KU_LISTS, kmeans_update_lists).  With four
 // wavefronts in place of eight, so that all workgroups of 24 heads of 16,384 tokens run at once, a late iteration
 // took 21 instead of 26 us and the first of them 97 instead of 60; with 32 clusters to a workgroup and several workgroups for the tokens
 // of few clusters 34 and 88.
 // As few workgroups as give every CU one read the labels (three times as many: 24 x 16,384, 500 clusters: 544; 6 x 11,000, 150: 232).
 static constexpr int KU_N = 32768, KU_FULL_N = 4096, KU_LISTS_N = 8192;
+static constexpr int KU_SIZE = 2048, KU_SECOND_SIZE = 256;      // tokens per cluster: most, and most in the second iteration
 static constexpr int KU_NW = 8;                 // wavefronts
 static constexpr int KU_G = 16;                 // most clusters of a workgroup
 static constexpr int KU_CAP = 448;              // entries of a wavefront's list (three workgroups fit a CU)
@@ -1711,9 +1718,13 @@ __global__ __launch_bounds__(64 * KU_NW, 6) void kmeans_update_kernel(KmArgs a, 
 //   8 x 37,800, 1000 / 2000 clusters: 837 / 730, 1392 / 1222 (Zipf sizes 842 / 758, 1436 / 1297)      8 x 75,600, 4000: 3951 / 3648
 //   1 x 118,800, 500, Zipf sizes (not taken): 392 / 513      8 x 37,800, 100 (not taken): 379 / 391
 static constexpr int KU_LISTS_SIZE = 64;        // tokens per cluster, beyond KU_N tokens
+static bool kmeans_update_direct(int H, int N, int call, int cmin)
+{
+    return !kmeans_update_small(H, N, call) && N <= KU_N && N <= (long long)KU_SIZE * cmin;
+}
 static bool kmeans_update_lists(int H, int N, int call, int cmin)
 {
-    return !kmeans_update_small(H, N, call) && N > KU_LISTS_N && (N <= KU_N || N <= (long long)KU_LISTS_SIZE * cmin);
+    return N > KU_LISTS_N && (kmeans_update_direct(H, N, call, cmin) || (N > KU_N && N <= (long long)KU_LISTS_SIZE * cmin));
 }
 
 // Clusters of a workgroup of the update kernel: as many as leave a workgroup per CU over all heads and sides, and no more than a sixteenth
@@ -2161,8 +2172,8 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         }
     }
     const dim3 fin_grid(cdiv(call, KM_FIN_NW), H);
-    const bool small = kmeans_update_small(H, N, call), direct = !small && N <= KU_N;
-    a.lists = BF16 && kmeans_update_lists(H, N, call, cmin);
+    const bool small = kmeans_update_small(H, N, call), direct = kmeans_update_direct(H, N, call, cmin);
+    const bool lists = BF16 && kmeans_update_lists(H, N, call, cmin);
     {
         ProfileSpan sp(SVG2_K_KMEANS_FINALIZE, st);
         hipLaunchKernelGGL((kmeans_finalize_kernel<BF16, D>), fin_grid, dim3(64 * KM_FIN_NW), 0, st, a, KmIter{}, 0);
@@ -2172,6 +2183,11 @@ static int kmeans_run(KmArgs a, hipStream_t st)
         // others only move the tokens whose label changed (a quarter in the second iteration, a few per cent from
         // the third on) between the cluster sums, which reads a fraction of X.
         const bool full = t % KM_FULL_EVERY == 0;
+        // sums and means straight from the labels, or by the label-sorted order (in the second iteration of few large clusters, where
+        // the first one has left its order)
+        const bool by_order = t == 1 && N > KU_FULL_N && N > (long long)KU_SECOND_SIZE * cmin;
+        const bool straight = small || (full ? direct && N <= KU_FULL_N : (direct || lists) && !by_order);
+        a.lists = lists && !by_order;
         KmIter it;
         it.t = t;
         it.set = t & 1;
@@ -2217,7 +2233,6 @@ static int kmeans_run(KmArgs a, hipStream_t st)
             }
         }
         // label-sorted order of the tokens and its pieces, then the segmented sum over it; or sums and means straight from the labels
-        const bool straight = small || (full ? direct && N <= KU_FULL_N : direct || a.lists);
         SortArgs sa = {};
         for (int s = 0; s < ns; ++s) {
             const KmSide &k = a.s[s];

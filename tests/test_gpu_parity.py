@@ -511,8 +511,12 @@ def test_kmeans_update_routes(svg2, oracle, dtype, d, H, N, C):
     # a last group of labels with one token, wavefronts without tokens; many heads
     ("bf16", 128, 40, 2049, 77), ("f32", 64, 700, 65, 20), ("bf16", 128, 2, 20481, 40),
     # few clusters of many heads, more than a sixteenth of them to a workgroup
-    ("f32", 128, 1030, 64, 9), ("bf16", 128, 520, 130, 40), ("bf16", 64, 100, 3000, 31)])
-def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
+    ("f32", 128, 1030, 64, 9), ("bf16", 128, 520, 130, 40), ("bf16", 64, 100, 3000, 31),
+    # tokens per cluster: the second iteration by the sorted order from 257 on (then labels or lists again), every iteration from 2049 on
+    ("bf16", 128, 1, 8448, 33), ("bf16", 128, 1, 8449, 33), ("f32", 64, 1, 16384, 64), ("f32", 64, 1, 16385, 64), ("bf16", 64, 1, 5000, 16),
+    ("f32", 128, 2, 8129, 4), ("bf16", 64, 1, 8192, 4), ("bf16", 64, 1, 8193, 4), ("f32", 128, 1, 6144, 3), ("f32", 128, 1, 6145, 3),
+    ("bf16", 64, 257, 4096, 2), ("f32", 64, 171, 4096, 3)])
+def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C, reach=None):
     r = np.random.default_rng(9900 + N + C)
     centres = 2.0 * r.standard_normal((H, 5, d)).astype(np.float32)
     X = np.stack([centres[h][r.integers(0, 5, size=N)] for h in range(H)]) + r.standard_normal((H, N, d)).astype(np.float32)
@@ -520,6 +524,8 @@ def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
     init = np.stack([X[h][np.sort(r.choice(N, C, replace=False))] for h in range(H)]).astype(np.float32)
     if C > 2:
         init[:, 1] += 60.0                                      # nothing is near it: stays empty
+    if reach:
+        init[:, reach:] += 500.0
     res = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), 4)
     again = svg2.svg2_kmeans(to_dev(X, dtype), to_dev(init), 4)
     torch.cuda.synchronize()
@@ -547,6 +553,14 @@ def test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C):
         dist = c2[None] - 2.0 * X[h].astype(np.float64) @ cen.T
         got = dist[np.arange(N), to_np(step.labels[h])]
         assert np.all(got - dist.min(1) <= 4 * d * 2.0 ** -24 * (x2 + c2.max()))
+
+
+@pytest.mark.parametrize("dtype,d,H,N,C,reach", [
+    ("bf16", 64, 257, 4096, 2, 1), ("f32", 64, 1, 32768, 128, 3), ("bf16", 64, 1, 8192, 32, 3), ("bf16", 128, 1, 32768, 128, 3), ("bf16", 64, 1, 32768, 128, 4)])
+def test_kmeans_update_of_few_clusters_that_hold_all_tokens(svg2, oracle, dtype, d, H, N, C, reach):
+    """The lists of a workgroup's wavefronts overflow again and again: all tokens, and those that move in the second iteration by the labels
+    and by the assign step's lists."""
+    test_kmeans_update_from_labels(svg2, oracle, dtype, d, H, N, C, reach)
 
 
 @pytest.mark.parametrize("d,H,N,C,iters", [
