@@ -9,20 +9,22 @@
 //             Each accumulator gets its position written into its 4 lowest mantissa bits; the largest and the
 //             second largest of these keys are tracked per token (max3 / med3 chains, no compare-and-select
 //             chains), which gives the label and the gap to the runner-up.
-//             fp32 input: MFMA 32x32x2 fp32, the centroids of a token dealt out to several wavefronts; a handful of
-//             centroids: one token per thread.
+//             fp32 input: MFMA 32x32x2 fp32, or with more centroids and tokens 32x32x16 fp16 on operands in two
+//             halves, near-ties by the fp32 chain; the centroids of a token dealt out to several wavefronts; a
+//             handful of centroids: one token per thread.
 //   settle    (bf16) every token whose gap is within the error bound of the fp32 contraction is assigned
 //             again in double precision, over all centroids, lowest index winning an exact tie.  Products of
 //             two bf16 numbers are exact and their sums fit a double, so these labels are THE argmin of the
 //             definition, not an approximation of it; a fraction of a per cent of the tokens take this path.
 //   update    segmented sum over the label-sorted token order (counting sort, shared with the permutation
 //             stage), in double precision: sums of bf16 values are exact in a double, so the cluster sums do
-//             not depend on the order of the additions -- reproducible bit for bit, independent of how skewed
-//             the cluster sizes are, and the delta update below never drifts.  From the second iteration on
-//             only the tokens whose label changed are moved between the cluster sums.
+//             not depend on the order of the additions -- reproducible bit for bit, and the delta update below
+//             never drifts.  The pieces of a cluster are summed side by side, so the time does not depend on how
+//             skewed the cluster sizes are.  From the second iteration on only the tokens whose label changed are
+//             moved between the cluster sums.
 //             Shorter heads: straight from the labels, together with the means (kmeans_update_kernel, with a few clusters of few
-//             heads kmeans_update_small_kernel); the shortest bf16 heads go through all iterations in one workgroup
-//             (kmeans_tiny_bf16_kernel).
+//             heads kmeans_update_small_kernel), where a workgroup adds all rows of its clusters; the shortest bf16 heads go
+//             through all iterations in one workgroup (kmeans_tiny_bf16_kernel).
 //   finalize  mean = sum / count in double (an empty cluster keeps its centroid), the fp32 centroid that is
 //             handed back, the bf16 copy the next assign reads (rounded from the DOUBLE mean, so it is the
 //             correctly rounded bf16 of the mean), and ||c||^2 of that copy.
